@@ -221,7 +221,7 @@ __device__ __forceinline__ void accumulators_to_lds(const BatchAcc<NB> &acc, flo
 // counter adds them in split order for every batch row and writes Y.
 template <int NB, int LPR, int WAVES>
 __device__ __forceinline__ void block_finish_batch(const BatchAcc<NB> &acc, float *red,
-                                                   float *partial, int *counters, float *Y,
+                                                   float *partial, int *counter, float *Y,
                                                    int tile, int col0, int cols, int s, int splits,
                                                    int n, int batch, int cnt,
                                                    const SurvivorReport &report)
@@ -260,7 +260,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc<NB> &acc, floa
     __syncthreads();
     // the ticket wraps to zero with the last arrival: ready for the next call
     if (threadIdx.x == 0)
-        last_flag = atomicInc(reinterpret_cast<unsigned *>(&counters[tile]), (unsigned)splits - 1u) ==
+        last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
     __syncthreads();
     if (!last_flag) return;
@@ -308,7 +308,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc<NB> &acc, floa
 template <int NB, int LPR, int WAVES, int U>
 __device__ __forceinline__ void batch_block(const void *__restrict__ W,
                                             const __half *__restrict__ X, int batch, double bound,
-                                            float *partial, int *counters, float *Y, int m, int n,
+                                            float *partial, int *counter, float *Y, int m, int n,
                                             int ks, int tile, int s, int tile_cols, int splits,
                                             const SurvivorReport &report)
 {
@@ -338,7 +338,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     BatchAcc<NB> acc;
     acc.clear();
     stream_rows_batch<NB, LPR, U>(acc, list_idx, list_x, ks, start, mine, lane_base, row_bytes);
-    block_finish_batch<NB, LPR, WAVES>(acc, red, partial, counters, Y, tile, col0, tile_cols, s,
+    block_finish_batch<NB, LPR, WAVES>(acc, red, partial, counter, Y, tile, col0, tile_cols, s,
                                        splits, n, batch, cnt, report);
 }
 
@@ -348,8 +348,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_batch_kernel(
     float *partial, int *counters, float *Y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
-    batch_block<NB, LPR, WAVES, U>(W, X, batch, bound, partial, counters, Y, m, n, ks,
-                                   blockIdx.x % tiles, blockIdx.x / tiles, tile_cols, splits,
+    const int tile = blockIdx.x % tiles;
+    batch_block<NB, LPR, WAVES, U>(W, X, batch, bound, partial,
+                                   tile_counter(counters, tile, tiles), Y, m, n, ks, tile,
+                                   blockIdx.x / tiles, tile_cols, splits,
                                    survivor_report(counters, 0, splits));
 }
 
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_batch_multi_kernel(
         }
     }
     batch_block<NB, LPR, WAVES, U>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
-                                   counters + ma.tile_begin[k], ma.Y[k], m, ma.n[k], ks,
+                                   tile_counter(counters, gtile, tiles), ma.Y[k], m, ma.n[k], ks,
                                    gtile - ma.tile_begin[k], s, tile_cols, splits,
                                    survivor_report(counters, k, splits));
 }

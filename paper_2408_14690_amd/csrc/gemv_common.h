@@ -141,6 +141,17 @@ __device__ __forceinline__ void report_total(const SurvivorReport &r, int splits
     if (lane == 0) store_coherent(r.total, sum);
 }
 
+// The arrival counter of output tile `tile` of a launch with `tiles` tiles (over all its
+// matrices).  A counter has a 128-byte line of its own wherever the area has room for that
+// (8192 tiles; every shape the library picks has far fewer): atomics on one line are executed
+// one after the other, about 10 ns each, and with 16 counters to a line the 256 arrivals of
+// a launch queued up for 2.6 us (2048 x 2048: last ticket 6.0 us after the first block's
+// start, 3.6 us with a line per counter).
+__device__ __forceinline__ int *tile_counter(int *counters, int tile, int tiles)
+{
+    return counters + (size_t)tile * (tiles <= kMaxSpacedTiles ? kCounterLineInts : 1);
+}
+
 // Where a block's activations come from.  A source loads what it needs for
 // channel i (load) and turns it into an fp32 value that is exactly an fp16 value
 // (value); kHeavy says that value() is worth skipping for segments past the slice.
@@ -604,7 +615,7 @@ __device__ __forceinline__ void store_wave_sums(const float (&acc)[N], float *ds
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <class F, int LPR, int WAVES>
 __device__ __forceinline__ bool block_finish(float *red,
-                                             float *partial, int *counters, float *y, int tile,
+                                             float *partial, int *counter, float *y, int tile,
                                              int col0, int cols, int s, int splits, int n,
                                              const typename F::Args &a, int cnt,
                                              const SurvivorReport &report)
@@ -661,7 +672,7 @@ __device__ __forceinline__ bool block_finish(float *red,
     // acquire invalidates it; measured +1.0 .. +5 us and +0.5 .. +0.9 us per call.  The data
     // this ticket orders never sits in an L2: see store_coherent / load_coherent.)
     if (threadIdx.x == 0)
-        last_flag = atomicInc(reinterpret_cast<unsigned *>(&counters[tile]), (unsigned)splits - 1u) ==
+        last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
     __syncthreads();
     trace_mark(5);
@@ -712,7 +723,7 @@ __device__ __forceinline__ int lane_column(int col0, int cols, int n, int l)
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <class F, int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &x,
-                                           float t, float *partial, int *counters, float *y, int m,
+                                           float t, float *partial, int *counter, float *y, int m,
                                            int n, int ks, int tile, int s, int tile_cols,
                                            int splits, const SurvivorReport &report)
 {
@@ -767,7 +778,7 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
-    return block_finish<F, LPR, WAVES>(red, partial, counters, y, tile, col0, tile_cols, s, splits,
+    return block_finish<F, LPR, WAVES>(red, partial, counter, y, tile, col0, tile_cols, s, splits,
                                        n, a, cnt, report);
 }
 
@@ -782,8 +793,9 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_kernel(
     float *y, int m, int n, int ks, int tiles, int tile_cols, int splits)
 {
     trace_mark(0);
-    gemv_block<F, LPR, WAVES, U>(a, HalfSource{x}, t, partial, counters, y, m, n, ks,
-                                 blockIdx.x % tiles, blockIdx.x / tiles, tile_cols, splits,
+    const int tile = blockIdx.x % tiles;
+    gemv_block<F, LPR, WAVES, U>(a, HalfSource{x}, t, partial, tile_counter(counters, tile, tiles),
+                                 y, m, n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
                                  survivor_report(counters, 0, splits));
     trace_mark(6);
 }
@@ -797,8 +809,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_swiglu_kernel(
     float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
-    gemv_block<F, LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial, counters, y, m, n, ks,
-                                 blockIdx.x % tiles, blockIdx.x / tiles, tile_cols, splits,
+    const int tile = blockIdx.x % tiles;
+    gemv_block<F, LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
+                                 tile_counter(counters, tile, tiles), y, m, n, ks, tile,
+                                 blockIdx.x / tiles, tile_cols, splits,
                                  survivor_report(counters, 0, splits));
 }
 
@@ -837,7 +851,7 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
         }
     }
     gemv_block<F, LPR, WAVES, U>(ma.a[k], x, ma.t[k], partial + partial_off,
-                                 counters + ma.tile_begin[k], ma.y[k], m, ma.n[k], ks,
+                                 tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
                                  gtile - ma.tile_begin[k], s, tile_cols, splits,
                                  survivor_report(counters, k, splits));
 }

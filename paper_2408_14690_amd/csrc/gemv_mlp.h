@@ -77,11 +77,11 @@ struct GemvBody {
     typedef F Format;
     template <int LPR, class XS>
     static __device__ __forceinline__ bool run(const typename F::Args &a, const XS &x, float t,
-                                               float *partial, int *counters, float *y, int m,
+                                               float *partial, int *counter, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)
     {
-        return gemv_block<F, LPR, 8, 4>(a, x, t, partial, counters, y, m, n, ks, tile, s,
+        return gemv_block<F, LPR, 8, 4>(a, x, t, partial, counter, y, m, n, ks, tile, s,
                                         tile_cols, splits, report);
     }
 };
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
         const int k = blk.kind;
         const bool wrote = Body::template run<LPR_GU>(
             A.a_gu[k], HalfSource{A.x}, A.t_gu[k], A.partial_gu + (size_t)k * g.splits_gu * g.f,
-            A.counters_gu + k * g.tiles_gu, A.y_gu[k], A.m, g.f, A.ks_gu, blk.tile, blk.split,
+            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu), A.y_gu[k], A.m, g.f, A.ks_gu, blk.tile, blk.split,
             g.tile_cols_gu, g.splits_gu, survivor_report(A.counters_gu, k, g.splits_gu));
         trace_mark(6);
         if (!wrote) return;
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
     if (!inputs_ready) return;
 
     const bool wrote = Body::template run<LPR_D>(
-        A.a_d, SwigluReadySource{A.y_gu[0], A.y_gu[1]}, A.t_d, A.partial_d, A.counters_d, A.y_d,
-        g.f, A.n_d, g.ks_d, blk.tile, blk.split, A.tile_cols_d, g.splits_d,
+        A.a_d, SwigluReadySource{A.y_gu[0], A.y_gu[1]}, A.t_d, A.partial_d,
+        tile_counter(A.counters_d, blk.tile, g.tiles_d), A.y_d, g.f, A.n_d, g.ks_d, blk.tile, blk.split, A.tile_cols_d, g.splits_d,
         survivor_report(A.counters_d, 0, g.splits_d));
     trace_mark(6);
     (void)wrote;

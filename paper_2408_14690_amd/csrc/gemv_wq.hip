@@ -115,7 +115,7 @@ struct W4Batch {
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
-                                         float t, float *partial, int *counters, float *y, int m,
+                                         float t, float *partial, int *counter, float *y, int m,
                                          int n, int ks, int tile, int s, int tile_cols, int splits,
                                          const SurvivorReport &report)
 {
@@ -247,7 +247,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
-    return block_finish<F, LPR, WAVES>(red, partial, counters, y, tile, col0, tile_cols, s, splits,
+    return block_finish<F, LPR, WAVES>(red, partial, counter, y, tile, col0, tile_cols, s, splits,
                                        n, a, cnt, report);
 }
 
@@ -257,8 +257,9 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_kernel(
     int m, int n, int ks, int tiles, int tile_cols, int splits)
 {
     trace_mark(0);
-    w4_block<LPR, WAVES, U>(a, HalfSource{x}, t, partial, counters, y, m, n, ks,
-                            blockIdx.x % tiles, blockIdx.x / tiles, tile_cols, splits,
+    const int tile = blockIdx.x % tiles;
+    w4_block<LPR, WAVES, U>(a, HalfSource{x}, t, partial, tile_counter(counters, tile, tiles), y,
+                            m, n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
                             survivor_report(counters, 0, splits));
     trace_mark(6);
 }
@@ -271,8 +272,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_swiglu_kernel(
     float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
-    w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial, counters, y, m, n, ks,
-                            blockIdx.x % tiles, blockIdx.x / tiles, tile_cols, splits,
+    const int tile = blockIdx.x % tiles;
+    w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
+                            tile_counter(counters, tile, tiles), y, m, n, ks, tile,
+                            blockIdx.x / tiles, tile_cols, splits,
                             survivor_report(counters, 0, splits));
 }
 
@@ -296,7 +299,7 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
         }
     }
     w4_block<LPR, WAVES, U>(ma.a[k], x, ma.t[k], partial + partial_off,
-                            counters + ma.tile_begin[k], ma.y[k], m, ma.n[k], ks,
+                            tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
                             gtile - ma.tile_begin[k], s, tile_cols, splits,
                             survivor_report(counters, k, splits));
 }
@@ -596,12 +599,12 @@ struct W4Body {
     typedef FmtW4 Format;
     template <int LPR, class XS>
     static __device__ __forceinline__ bool run(const FmtW4::Args &a, const XS &x, float t,
-                                               float *partial, int *counters, float *y, int m,
+                                               float *partial, int *counter, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)
     {
         static_assert(LPR == 16 || LPR == 32, "a lane covers 32 int4 columns");
-        return w4_block<LPR, kW4Waves, kW4Unroll>(a, x, t, partial, counters, y, m, n, ks, tile,
+        return w4_block<LPR, kW4Waves, kW4Unroll>(a, x, t, partial, counter, y, m, n, ks, tile,
                                                   s, tile_cols, splits, report);
     }
 };
