@@ -2,8 +2,19 @@
 // channels is dropped for the whole batch, chosen by the magnitude averaged
 // over the batch dimension, and every row of the batch is multiplied with the
 // surviving rows of the input-channel-major weights.  The weight stream is the
-// same as for one vector (each surviving row is read once); a block keeps one
-// accumulator set per batch row.
+// same as for one vector (each surviving row is read once).
+//
+// The products run on the matrix cores.  With fp32 FMAs a 16-byte load costs 64 FMAs and 8
+// conversions per lane at 8 batch rows, which is more issue than the stream leaves (8 rows
+// took 1.5 times the time of one vector).  v_mfma_f32_16x16x32_bf16 takes 16 columns x 32
+// input channels of weights and 32 channels x 16 columns of activations: bf16 weights go in
+// as they are, and an fp16 activation is the exact sum of two bf16 numbers (8 + 3
+// significand bits), so 8 batch rows x (high, low) fill its 16 columns and the products
+// are exact.  What a 16-byte load costs then is 4 byte permutes (a lane's 8 weights of 8
+// rows become 8 rows of 8 columns) and one matrix instruction, whatever the batch size.
+// Llama-3-8B-shaped block at 50 %, 8 rows: 81.0 us with FMAs, 58.9 us this way (220 MB: 3.7 TB/s;
+// one vector 52 us).  The row stream is bound by HBM; what remains above it is the compaction of 8
+// activation vectors by every block (1.4 us at 512 channels, 3.4 us at 4096) and the combine.
 #include "gemv_common.h"
 
 namespace teal {
@@ -15,48 +26,123 @@ namespace {
 // up to kMaxBatch fp16 magnitudes is exact in fp64 and so is batch * t, so the
 // decision involves no rounding and does not depend on the order of the batch.
 // A NaN makes the sum NaN, which compares false (the channel is dropped).
+// The activations of a channel are kept as fp16 pairs (batch rows 2k and 2k + 1); `batch` of the
+// NB values count.
 template <int NB>
-__device__ __forceinline__ bool survives_batch(const float (&xv)[NB], double bound)
+__device__ __forceinline__ bool survives_batch(const unsigned (&pair)[NB / 2], int batch, double bound)
 {
     double s = 0.0;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) s += (double)fabsf(xv[b]);
+    for (int b = 0; b < NB; ++b) {
+        const unsigned short h = (unsigned short)(pair[b / 2] >> (16 * (b & 1)));
+        s += b < batch ? (double)fabsf(__half2float(__ushort_as_half(h))) : 0.0;
+    }
     return s > bound;
 }
 
-// compact_slice for a batch: list_idx[] receives the surviving channels of
-// [k0, k1) in ascending order and list_x[] their NB activations each (rows at
-// or past `batch` are zero).  Same scheme: ballots and popcounts per
-// 64-channel segment, segment counts through LDS, every wavefront scans them.
-template <int NB, int WAVES>
+// The same decision for a wavefront's 64 channels, as a ballot, from an fp32 sum (weight[b] = 1
+// for batch rows that count, else 0).  The sum is within 2^-21 of the exact one, and bound
+// rounded to fp32 within 2^-24, so where the two lie further apart than 2^-20 of each the fp32
+// comparison is the exact one; only if that leaves a lane open (a sum next to the bound, an
+// infinity, a NaN, zeros against t = 0) the wavefront evaluates the fp64 form.
+template <int NB>
+__device__ __forceinline__ unsigned long long ballot_batch(const unsigned (&pair)[NB / 2],
+                                                           const float (&weight)[NB], int batch,
+                                                           double bound)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < NB / 2; ++k) {
+        const __half2 h = __builtin_bit_cast(__half2, pair[k]);
+        s = fmaf(fabsf(__low2float(h)), weight[2 * k], s);
+        s = fmaf(fabsf(__high2float(h)), weight[2 * k + 1], s);
+    }
+    const float bf = (float)bound;
+    const float margin = 9.5367431640625e-7f * (s + bf);      // 2^-20
+    const float d = s - bf;
+    const bool keep = d > margin;
+    if (__ballot(!keep && !(d < -margin)) == 0) return __ballot(keep);
+    return __ballot(survives_batch<NB>(pair, batch, bound));
+}
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Rows one matrix instruction takes (K), and the output columns of a block: 16 lanes share a
+// weight row, 8 columns each; the four groups of 16 lanes hold different rows.
+constexpr int kChunkRows = 32;
+constexpr int kBatchTile = 128;
+// Activations of one surviving channel in LDS: 8 fp16 values (batch rows past NB are never written
+// and feed matrix columns that are never read).  They are split into their high and low parts
+// when a chunk is multiplied, where vector instructions are to be had under the row stream, and
+// not in the compaction, where every block waits for them (4.4 -> 3.4 us at 4096 channels
+// and 8 rows).
+constexpr int kActBytes = 16;
+
+// Rows of one wavefront: equal contiguous shares, in multiples of the 4 rows that one
+// wavefront load covers.
+template <int WAVES>
+__device__ __forceinline__ int batch_share_rows(int cnt)
+{
+    return 4 * ((cnt + 4 * WAVES - 1) / (4 * WAVES));
+}
+
+// compact_slice for a batch: list_idx[] receives the surviving channels of [k0, k1) in
+// ascending order and act[] their activations.  Same scheme: ballots and popcounts, counts
+// through LDS, every wavefront scans them.  A lane looks at VEC (1, 2, 4) consecutive channels with
+// one load per batch row (2 * VEC bytes aligned), PASSES times: the slice has at most
+// 64 * VEC * PASSES * WAVES channels, a multiple of VEC.  What this takes is vector instructions (8
+// cycles each with two wavefronts to a SIMD), so a channel's values stay packed.
+template <int NB, int WAVES, int VEC, int PASSES>
 __device__ __forceinline__ int compact_slice_batch(const __half *__restrict__ X, int batch, int m,
                                                    double bound, int k0, int k1, int *list_idx,
-                                                   float *list_x, int *seg_cnt)
+                                                   unsigned char *act, int *seg_cnt)
 {
-    constexpr int PER_WAVE = kMaxSliceBatch / 64 / WAVES;
+    constexpr int WORDS = (VEC + 1) / 2;
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
-    const int nseg = (k1 - k0 + 63) >> 6;
+    const int nseg = (k1 - k0 + 64 * VEC - 1) / (64 * VEC);
 
-    float xv[PER_WAVE][NB];
-    unsigned long long bal[PER_WAVE];
-    // Unconditional loads from clamped positions (k1 > k0, batch >= 1), zeroed afterwards
-    // where out of range, so that all loads are in flight together.
+    // Unconditional loads from clamped positions (k1 > k0), so that all loads are in flight
+    // together.  Batch rows past the last repeat it and have no weight in the sums.
+    unsigned raw[PASSES][NB][WORDS];
 #pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int i = k0 + (w + j * WAVES) * 64 + lane;
-        const int ic = min(i, k1 - 1);
+    for (int j = 0; j < PASSES; ++j) {
+        const int ic = min(k0 + ((w + j * WAVES) * 64 + lane) * VEC, k1 - VEC);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const float v = __half2float(X[(size_t)min(b, batch - 1) * m + ic]);
-            xv[j][b] = (i < k1 && b < batch) ? v : 0.f;
+            const __half *p = X + (size_t)min(b, batch - 1) * m + ic;
+            if constexpr (VEC == 1) {
+                raw[j][b][0] = *reinterpret_cast<const unsigned short *>(p);
+            } else if constexpr (VEC == 2) {
+                raw[j][b][0] = *reinterpret_cast<const unsigned *>(p);
+            } else {
+                const uint2 u = *reinterpret_cast<const uint2 *>(p);
+                raw[j][b][0] = u.x;
+                raw[j][b][WORDS - 1] = u.y;
+            }
         }
     }
+    float weight[NB];
 #pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
+    for (int b = 0; b < NB; ++b) weight[b] = b < batch ? 1.f : 0.f;
+    unsigned pair[PASSES][VEC][NB / 2];
+    unsigned long long bal[PASSES][VEC];
+#pragma unroll
+    for (int j = 0; j < PASSES; ++j) {
         const int seg = w + j * WAVES;
-        bal[j] = __ballot(survives_batch<NB>(xv[j], bound));
-        if (lane == 0 && seg < nseg) seg_cnt[seg] = __popcll(bal[j]);
+        const unsigned long long inside = __ballot(k0 + (seg * 64 + lane) * VEC < k1);
+        int kept = 0;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+#pragma unroll
+            for (int k = 0; k < NB / 2; ++k)
+                pair[j][e][k] = __builtin_amdgcn_perm(raw[j][2 * k + 1][e / 2], raw[j][2 * k][e / 2],
+                                                      (e & 1) ? 0x07060302u : 0x05040100u);
+            bal[j][e] = ballot_batch<NB>(pair[j][e], weight, batch, bound) & inside;
+            kept += __popcll(bal[j][e]);
+        }
+        if (lane == 0 && seg < nseg) seg_cnt[seg] = kept;
     }
     __syncthreads();
     const int c = lane < nseg ? seg_cnt[lane] : 0;
@@ -64,15 +150,20 @@ __device__ __forceinline__ int compact_slice_batch(const __half *__restrict__ X,
     const int seg_excl = incl - c;
     const int total = __builtin_amdgcn_readlane(incl, 63);
 #pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
+    for (int j = 0; j < PASSES; ++j) {
         const int seg = w + j * WAVES;
-        if (seg < nseg) {                              // wavefront-uniform
-            const int base = __builtin_amdgcn_readlane(seg_excl, seg);
-            if ((bal[j] >> lane) & 1ull) {
-                const int slot = base + lanes_below(bal[j]);
-                list_idx[slot] = k0 + seg * 64 + lane;
+        if (seg >= nseg) continue;                     // wavefront-uniform
+        int rank = __builtin_amdgcn_readlane(seg_excl, seg);
 #pragma unroll
-                for (int b = 0; b < NB; ++b) list_x[slot * NB + b] = xv[j][b];
+        for (int e = 0; e < VEC; ++e) rank += lanes_below(bal[j][e]);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            if ((bal[j][e] >> lane) & 1ull) {
+                list_idx[rank] = k0 + (seg * 64 + lane) * VEC + e;
+                unsigned *dst = reinterpret_cast<unsigned *>(act + rank * kActBytes);
+#pragma unroll
+                for (int k = 0; k < NB / 2; ++k) dst[k] = pair[j][e][k];
+                ++rank;
             }
         }
     }
@@ -80,232 +171,248 @@ __device__ __forceinline__ int compact_slice_batch(const __half *__restrict__ X,
     return total;
 }
 
-// The accumulators of one lane: a[bb][e] belongs to batch row bb and to column e
-// of the lane's 8 columns.  Plain fp32 FMAs; products are exact in fp32 (8 + 11
-// significand bits) and each accumulator sees its rows in list order.  (An
-// outer-product formulation on the matrix cores, v_mfma_f32_4x4x1_16b_f32 with
-// the weights as A and the batch's activations as B, computes the same sums
-// but measured slower than the FMAs at 4 and 8 rows.)
-template <int NB>
+// The accumulators of one lane: v[c][r] belongs to activation column lane % 16 and to output
+// column 8 * (4 * (lane / 16) + r) + c of the tile.
 struct BatchAcc {
-    float a[NB][8];
-    __device__ __forceinline__ void clear()
-    {
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a[bb][e] = 0.f;
-    }
+    f32x4 v[8];
 };
 
-// The NB activations of one surviving row.
-template <int NB>
-struct RowX {
-    float v[NB];
-};
-
-template <int NB>
-__device__ __forceinline__ RowX<NB> load_row_x(const float *entry)
+// Multiplies a chunk in: rows[u] holds this lane's 8 weights of row 4 u + lane / 16, `x` the
+// activations.  Two rows' weights of one column are joined by one byte permute.
+__device__ __forceinline__ void multiply_chunk(BatchAcc &acc, const u32x4 (&rows)[8], bf16x8 x)
 {
-    RowX<NB> r;
-    if constexpr (NB == 2) {
-        const float2 f = *reinterpret_cast<const float2 *>(entry);
-        r.v[0] = f.x; r.v[1] = f.y;
-    } else {
 #pragma unroll
-        for (int q = 0; q < NB / 4; ++q) {
-            const float4 f = *reinterpret_cast<const float4 *>(entry + 4 * q);
-            r.v[4 * q] = f.x; r.v[4 * q + 1] = f.y; r.v[4 * q + 2] = f.z; r.v[4 * q + 3] = f.w;
-        }
+    for (int c = 0; c < 8; ++c) {
+        u32x4 a;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            a[k] = __builtin_amdgcn_perm(rows[2 * k + 1][c / 2], rows[2 * k][c / 2],
+                                         (c & 1) ? 0x07060302u : 0x05040100u);
+        acc.v[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), x,
+                                                           acc.v[c], 0, 0, 0);
     }
-    return r;
 }
 
-template <int NB>
-__device__ __forceinline__ void multiply_row(BatchAcc<NB> &acc, u32x4 w, const RowX<NB> &x)
+// The activations of one chunk for this lane: rows 4 u + lane / 16, u = 0..7, of batch row
+// lane % 8, the high part in lanes with lane % 16 < 8, else the low part.  A transposing LDS read
+// gives each of 16 lanes one column of a 4 x 16 block of 16-bit values, of which every lane
+// addresses four neighbouring columns of one row (columns 8..15 are 0..7 again): `act` is what
+// this lane addresses in the first block, the second lies 16 rows further.  High part: the upper
+// 16 bits of the value in fp32; the rest has at most 3 significant bits (an infinity leaves a
+// NaN, see the sums in block_finish_batch).  Rows from `rows_left` on belong to another wavefront
+// (or to nobody) and count as zeros.
+__device__ __forceinline__ bf16x8 chunk_activations(const unsigned char *act, int rows_left,
+                                                     int lane)
 {
-    float wv[8];                       // bf16 -> fp32 is a 16-bit shift
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)act);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(act + 16 * kActBytes));
+    const uint2 wa = __builtin_bit_cast(uint2, a), wb = __builtin_bit_cast(uint2, b);
+    u32x4 x = {wa.x, wa.y, wb.x, wb.y};
+    if (rows_left < kChunkRows) {                     // wavefront-uniform
+        const int live = rows_left - (lane >> 4);     // rows 4 u < live are ours
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        wv[2 * q] = __uint_as_float(w[q] << 16);
-        wv[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
+        for (int k = 0; k < 4; ++k)
+            x[k] &= (8 * k < live ? 0x0000FFFFu : 0u) | (8 * k + 4 < live ? 0xFFFF0000u : 0u);
     }
+    const unsigned take = (lane & 8) ? 0xFFFF0000u : 0u;         // what the low part leaves out
 #pragma unroll
-    for (int bb = 0; bb < NB; ++bb)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc.a[bb][e] = fmaf(x.v[bb], wv[e], acc.a[bb][e]);
+    for (int k = 0; k < 4; ++k) {
+        const __half2 h = __builtin_bit_cast(__half2, (unsigned)x[k]);
+        const float f0 = __low2float(h), f1 = __high2float(h);
+        const float v0 = f0 - __uint_as_float(__float_as_uint(f0) & take);
+        const float v1 = f1 - __uint_as_float(__float_as_uint(f1) & take);
+        x[k] = __builtin_amdgcn_perm(__float_as_uint(v1), __float_as_uint(v0), 0x07060302u);
+    }
+    return __builtin_bit_cast(bf16x8, x);
 }
 
-// stream_rows for a batch: per surviving row one 16-byte load per lane.  Slots
-// past the end of the wavefront's share point at an all-zero entry (zero_slot).
-template <int NB, int LPR, int U>
-__device__ __forceinline__ void stream_rows_batch(BatchAcc<NB> &acc, const int *list_idx,
-                                                  const float *list_x, int zero_slot, int start,
-                                                  int mine,
+// stream_rows for a batch: the `mine` rows of a wavefront's share in chunks of 32, 8 loads of 16
+// bytes per lane each, two chunks in flight.  Slots behind the end of the share load its last
+// row again (no new traffic) and count as zeros.
+__device__ __forceinline__ void stream_rows_batch(BatchAcc &acc, const int *list_idx, int start,
+                                                  int mine, const unsigned char *act,
                                                   const unsigned char *__restrict__ lane_base,
                                                   unsigned row_bytes)
 {
-    constexpr int R = 64 / LPR;
     if (mine <= 0) return;
-    const int g = (threadIdx.x & 63) / LPR;
+    // the lane from its own instruction: one register across the loop (128 are all there are)
+    const int lane = lanes_below(~0ull);
     const int last = mine - 1;
-    const int batches = (mine + U * R - 1) / (U * R);
+    const int chunks = (mine + kChunkRows - 1) / kChunkRows;
+    const int *share = list_idx + start;
+    const unsigned char *act_lane =
+        act + (start + 4 * ((lane & 15) >> 2) + (lane >> 4)) * kActBytes + (lane & 1) * 8;
 
-    struct Batch {
-        u32x4 v[U];
-        RowX<NB> x[U];
-    };
-    // The activations are fetched from LDS when the row load is issued, so that they
-    // are in registers long before the weights arrive.
-    auto issue = [&](Batch &b, int batch_no) {
+    auto issue = [&](u32x4 (&rows)[8], int chunk) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = (batch_no * U + u) * R + g;
-            const int row = list_idx[start + min(e, last)];
-            b.v[u] = load_stream16(lane_base + (size_t)(unsigned)row * row_bytes);
-            b.x[u] = load_row_x<NB>(list_x + (e <= last ? start + e : zero_slot) * NB);
+        for (int u = 0; u < 8; ++u) {
+            const int row = share[min(chunk * kChunkRows + 4 * u + (lane >> 4), last)];
+            rows[u] = load_stream16(lane_base + (size_t)(unsigned)row * row_bytes);
         }
     };
-    auto consume = [&](const Batch &b) {
+    auto consume = [&](const u32x4 (&rows)[8], int chunk) {
+        multiply_chunk(acc, rows, chunk_activations(act_lane + chunk * kChunkRows * kActBytes,
+                                                    kChunkRows, lane));
+    };
+    auto consume_last = [&](u32x4 (&rows)[8]) {
+        const int rows_left = mine - (chunks - 1) * kChunkRows;
+        // 0 times an infinite weight is a NaN: the weights of the slots behind the share go, too
 #pragma unroll
-        for (int u = 0; u < U; ++u) multiply_row<NB>(acc, b.v[u], b.x[u]);
+        for (int u = 0; u < 8; ++u)
+            if (4 * u + (lane >> 4) >= rows_left) rows[u] = u32x4{0u, 0u, 0u, 0u};
+        multiply_chunk(acc, rows,
+                       chunk_activations(act_lane + (chunks - 1) * kChunkRows * kActBytes, rows_left,
+                                         lane));
     };
 
-    // Scheduling fences keep the two batches apart: without them the compiler issues both
-    // batches back to back and drains the queue before the next pair.
-    Batch b0, b1;
+    // Scheduling fences keep the two chunks apart: without them the compiler issues both
+    // back to back and drains the queue before the next pair.
+    u32x4 b0[8], b1[8];
     issue(b0, 0);
     int it = 0;
-    for (; it + 2 < batches; it += 2) {
+    for (; it + 2 < chunks; it += 2) {
         issue(b1, it + 1);
         __builtin_amdgcn_sched_barrier(0);
-        consume(b0);
+        consume(b0, it);
         __builtin_amdgcn_sched_barrier(0);
         issue(b0, it + 2);
         __builtin_amdgcn_sched_barrier(0);
-        consume(b1);
+        consume(b1, it + 1);
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (it + 1 < batches) {
+    if (it + 1 < chunks) {
         issue(b1, it + 1);
         __builtin_amdgcn_sched_barrier(0);
-        consume(b0);
-        consume(b1);
+        consume(b0, it);
+        __builtin_amdgcn_sched_barrier(0);
+        consume_last(b1);
     } else {
-        consume(b0);
+        consume_last(b0);
     }
 }
 
-// Leaves every lane's accumulators in red[], laid out [wavefront x row group]
-// [batch row][tile column].
-template <int NB, int LPR>
-__device__ __forceinline__ void accumulators_to_lds(const BatchAcc<NB> &acc, float *red)
+// One activation column of the combine buffer, padded so that the 16 columns a row of lanes
+// holds are written to different LDS banks.
+constexpr int kBatchRedRow = kBatchTile + 8;
+constexpr int kBatchRedWave = 16 * kBatchRedRow;       // floats per wavefront
+
+// Leaves this wavefront's accumulators in red[], laid out [wavefront][activation column][tile
+// column]: high part of batch row b in activation column b, low part in column b + 8.
+__device__ __forceinline__ void batch_sums_to_lds(const BatchAcc &acc, float *red, int w)
 {
-    constexpr int TN = LPR * 8;
-    constexpr int R = 64 / LPR;
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int g = lane / LPR, l = lane % LPR;
-    float *mine = red + (size_t)((w * R + g) * NB) * TN;
+    const int lane = lanes_below(~0ull);
+    float *dst = red + w * kBatchRedWave + (lane & 15) * kBatchRedRow +
+                 32 * (lane >> 4);
 #pragma unroll
-    for (int bb = 0; bb < NB; ++bb) {
-        float4 *dst = reinterpret_cast<float4 *>(mine + bb * TN + l * 8);
-        dst[0] = make_float4(acc.a[bb][0], acc.a[bb][1], acc.a[bb][2], acc.a[bb][3]);
-        dst[1] = make_float4(acc.a[bb][4], acc.a[bb][5], acc.a[bb][6], acc.a[bb][7]);
-    }
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<float4 *>(dst + 8 * r + 4 * q) =
+                make_float4(acc.v[4 * q][r], acc.v[4 * q + 1][r], acc.v[4 * q + 2][r],
+                            acc.v[4 * q + 3][r]);
 }
 
-// block_finish for a batch.  red[] (WAVES x 64 lanes x NB x 8 floats) lies over the list,
-// which is dead once every wavefront has left the row stream.  Partial rows are
-// laid out [split][batch row][n]; the block that arrives last at the tile's
-// counter adds them in split order for every batch row and writes Y.
-template <int NB, int LPR, int WAVES>
-__device__ __forceinline__ void block_finish_batch(const BatchAcc<NB> &acc, float *red,
+__device__ __forceinline__ void store_coherent2(float *p, float2 v)      // 8-byte aligned
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p),
+                       __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_coherent2(const float *p)        // 8-byte aligned
+{
+    return __builtin_bit_cast(
+        float2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// block_finish for a batch.  red[] (WAVES x kBatchRedWave floats) lies over the list,
+// which is dead once every wavefront has left the row stream.  A thread owns two neighbouring
+// columns of one batch row.  Partial rows are laid out [split][batch row][n]; the block that
+// arrives last at the tile's counter adds them in split order and writes Y.
+template <int NB, int WAVES>
+__device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *red,
                                                    float *partial, int *counter, float *Y,
                                                    int tile, int col0, int cols, int s, int splits,
-                                                   int n, int batch, int cnt,
+                                                   int n, int batch, int cnt, int w,
                                                    const SurvivorReport &report)
 {
-    constexpr int TN = LPR * 8;
-    constexpr int THREADS = WAVES * 64;
-    constexpr int R = 64 / LPR;
+    static_assert(NB * kBatchTile / 2 <= WAVES * 64, "one pair of columns per thread");
     __shared__ int last_flag;
+    const int thread = w * 64 + lanes_below(~0ull);
     if (cols > n - col0) cols = n - col0;
     __syncthreads();                   // every wavefront is done with the list
-    // Every lane leaves its accumulators in LDS: WAVES x R row groups per output.  (Folding
-    // the R row groups of a wavefront with lane shuffles first costs more than the extra
-    // LDS reads below once there are several accumulator sets.)
-    accumulators_to_lds<NB, LPR>(acc, red);
+    batch_sums_to_lds(acc, red, w);
     __syncthreads();
-    const int total = batch * cols;
-    auto wave_sum = [&](int bb, int c) {
-        float sum = 0.f;
+    trace_mark(7);
+    const int bb = thread / (kBatchTile / 2);
+    const int c = 2 * (thread % (kBatchTile / 2));
+    const bool owner = bb < batch && c < cols;          // cols is a multiple of 8
+    float2 sum = make_float2(0.f, 0.f);
+    if (owner) {
+        // The high parts of all wavefronts, then the low ones.  Where the high sum is not
+        // finite it is the result: an infinite weight or activation makes it infinite or a NaN,
+        // as the product is, and the low part a NaN.
+        const float *hi = red + bb * kBatchRedRow + c, *lo = hi + 8 * kBatchRedRow;
+        float2 h = make_float2(0.f, 0.f), l = h;
 #pragma unroll
-        for (int q = 0; q < WAVES * R; ++q) sum += red[(q * NB + bb) * TN + c];
-        return sum;
-    };
-    if (tile == 0 && threadIdx.x == 0) report_slice(report, s, splits, cnt);
+        for (int q = 0; q < WAVES; ++q) {
+            const float2 a = *reinterpret_cast<const float2 *>(hi + q * kBatchRedWave);
+            const float2 b = *reinterpret_cast<const float2 *>(lo + q * kBatchRedWave);
+            h.x += a.x; h.y += a.y;
+            l.x += b.x; l.y += b.y;
+        }
+        sum.x = fabsf(h.x) < INFINITY ? h.x + l.x : h.x;
+        sum.y = fabsf(h.y) < INFINITY ? h.y + l.y : h.y;
+    }
+    if (tile == 0 && thread == 0) report_slice(report, s, splits, cnt);
+    float *y = Y + (size_t)bb * n + col0 + c;
     if (splits == 1) {
-        for (int k = threadIdx.x; k < total; k += THREADS) {
-            const int bb = k / cols, c = k - bb * cols;
-            store_coherent(Y + (size_t)bb * n + col0 + c, wave_sum(bb, c));
+        if (owner) {
+            store_coherent(y, sum.x);
+            store_coherent(y + 1, sum.y);
         }
         return;
     }
-    for (int k = threadIdx.x; k < total; k += THREADS) {
-        const int bb = k / cols, c = k - bb * cols;
-        store_coherent(partial + ((size_t)s * batch + bb) * n + col0 + c, wave_sum(bb, c));
-    }
+    const size_t split_stride = (size_t)batch * n;
+    float *p = partial + (size_t)bb * n + col0 + c;
+    if (owner) store_coherent2(p + s * split_stride, sum);
     wait_vector_memory();
     __syncthreads();
+    trace_mark(4);
     // the ticket wraps to zero with the last arrival: ready for the next call
-    if (threadIdx.x == 0)
+    if (thread == 0)
         last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
     __syncthreads();
+    trace_mark(5);
     if (!last_flag) return;
-    if (tile == 0 && threadIdx.x < 64) report_total(report, splits);
+    if (tile == 0 && w == 0) report_total(report, splits);
 
-    // Second pass.  A thread owns up to OUT outputs (batch row, column) and keeps the
-    // loads of MAXLD splits of all of them in flight at once; each output is summed in
-    // split order, so the result does not depend on which block is last.
-    constexpr int OUT = (NB * TN + THREADS - 1) / THREADS;
+    // Second pass, up to 16 loads in flight; every output is summed in split order, so the
+    // result does not depend on which block is last.
+    if (!owner) return;
     constexpr int MAXLD = 16;
-    const size_t split_stride = (size_t)batch * n;
-    const float *p[OUT];
-    float sum[OUT];
+    sum = make_float2(0.f, 0.f);
+    for (int j = 0; j < splits; j += MAXLD) {
+        float2 v[MAXLD];
 #pragma unroll
-    for (int o = 0; o < OUT; ++o) {
-        const int k = (int)threadIdx.x + o * THREADS;
-        const int bb = k < total ? k / cols : 0, c = k < total ? k - bb * cols : 0;
-        p[o] = partial + (size_t)bb * n + col0 + c;
-        sum[o] = 0.f;
-    }
-    for (int k0 = 0; k0 < splits; k0 += MAXLD) {
-        float v[OUT][MAXLD];
+        for (int u = 0; u < MAXLD; ++u)
+            v[u] = j + u < splits ? load_coherent2(p + (size_t)(j + u) * split_stride)
+                                  : make_float2(0.f, 0.f);
 #pragma unroll
-        for (int o = 0; o < OUT; ++o)
-#pragma unroll
-            for (int u = 0; u < MAXLD; ++u)
-                v[o][u] = ((int)threadIdx.x + o * THREADS < total && k0 + u < splits)
-                              ? load_coherent(p[o] + (size_t)(k0 + u) * split_stride) : 0.f;
-#pragma unroll
-        for (int o = 0; o < OUT; ++o)
-#pragma unroll
-            for (int u = 0; u < MAXLD; ++u) sum[o] += v[o][u];
-    }
-#pragma unroll
-    for (int o = 0; o < OUT; ++o) {
-        const int k = (int)threadIdx.x + o * THREADS;
-        if (k < total) {
-            const int bb = k / cols, c = k - bb * cols;
-            store_coherent(Y + (size_t)bb * n + col0 + c, sum[o]);
+        for (int u = 0; u < MAXLD; ++u) {
+            sum.x += v[u].x;
+            sum.y += v[u].y;
         }
     }
+    store_coherent(y, sum.x);
+    store_coherent(y + 1, sum.y);
 }
 
 // Work of one block: output tile `tile` x K-slice `s` of one matrix, all batch rows.
-template <int NB, int LPR, int WAVES, int U>
+template <int NB, int WAVES>
 __device__ __forceinline__ void batch_block(const void *__restrict__ W,
                                             const __half *__restrict__ X, int batch, double bound,
                                             float *partial, int *counter, float *Y, int m, int n,
@@ -313,46 +420,63 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
                                             const SurvivorReport &report)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    // [list_x: (ks + 1) x NB floats][list_idx: ks ints]; red[] reuses the front.
-    float *list_x = reinterpret_cast<float *>(smem);
-    int *list_idx = reinterpret_cast<int *>(smem + (size_t)(ks + 1) * NB * sizeof(float));
+    // [activations: ks rows, and a chunk that may be read past the last][list_idx: ks ints];
+    // red[] reuses the front.
+    int *list_idx = reinterpret_cast<int *>(smem + (size_t)(ks + kChunkRows) * kActBytes);
     float *red = reinterpret_cast<float *>(smem);
-    __shared__ int seg_cnt[kMaxSliceBatch / 64];
+    __shared__ int seg_cnt[kMaxSegs];
 
+    trace_mark(0);
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
-    if (threadIdx.x < NB) list_x[ks * NB + threadIdx.x] = 0.f;    // the all-zero entry
-    const int cnt = compact_slice_batch<NB, WAVES>(X, batch, m, bound, k0, k1, list_idx, list_x,
-                                                   seg_cnt);
+    // Channels per lane by the length of the slice, so that short slices occupy every wavefront;
+    // one by one where the rows of X do not lie on 8-byte boundaries.
+    constexpr int kLanes = 64 * WAVES;
+    const int len = k1 - k0;                           // block-uniform
+    const bool vec = (m & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 7) == 0;
+#define TEAL_COMPACT(VEC, PASSES)                                                                \
+    compact_slice_batch<NB, WAVES, VEC, PASSES>(X, batch, m, bound, k0, k1, list_idx, smem, seg_cnt)
+    const int cnt = len <= kLanes               ? TEAL_COMPACT(1, 1)
+                    : !vec                      ? TEAL_COMPACT(1, kMaxLongSliceBatch / kLanes)
+                    : len <= 2 * kLanes         ? TEAL_COMPACT(2, 1)
+                    : len <= 4 * kLanes         ? TEAL_COMPACT(4, 1)
+                                                : TEAL_COMPACT(4, kMaxLongSliceBatch / (4 * kLanes));
+#undef TEAL_COMPACT
 
-    const int lane = threadIdx.x & 63;
+    trace_mark(2);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int start, mine;
-    wave_share(cnt, w, WAVES, start, mine);
+    const int share = batch_share_rows<WAVES>(cnt);
+    const int start = w * share;
+    const int mine = min(max(cnt - start, 0), share);
 
     const int col0 = tile * tile_cols;
-    const int col = lane_column<8>(col0, tile_cols, n, lane % LPR);
+    const int col = lane_column<8>(col0, tile_cols, n, threadIdx.x & 15);
     const unsigned row_bytes = (unsigned)n * 2u;
     const unsigned char *lane_base = static_cast<const unsigned char *>(W) + (size_t)col * 2;
 
-    BatchAcc<NB> acc;
-    acc.clear();
-    stream_rows_batch<NB, LPR, U>(acc, list_idx, list_x, ks, start, mine, lane_base, row_bytes);
-    block_finish_batch<NB, LPR, WAVES>(acc, red, partial, counter, Y, tile, col0, tile_cols, s,
-                                       splits, n, batch, cnt, report);
+    BatchAcc acc;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc.v[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    stream_rows_batch(acc, list_idx, start, mine, smem, lane_base, row_bytes);
+    trace_mark(3);
+    trace_mark_thread(1, (WAVES - 1) * 64);
+    block_finish_batch<NB, WAVES>(acc, red, partial, counter, Y, tile, col0, tile_cols, s, splits,
+                                  n, batch, cnt, w, report);
+    trace_mark(6);
 }
 
-template <int NB, int LPR, int WAVES, int U>
-__global__ __launch_bounds__(WAVES * 64) void sparse_gemv_batch_kernel(
+// 4 wavefronts per SIMD (at most 128 registers): two blocks share a unit, so that one's compaction
+// and combine lie under the other's row stream where there are more blocks than units.
+template <int NB, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_kernel(
     const void *__restrict__ W, const __half *__restrict__ X, int batch, double bound,
     float *partial, int *counters, float *Y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
     const int tile = blockIdx.x % tiles;
-    batch_block<NB, LPR, WAVES, U>(W, X, batch, bound, partial,
-                                   tile_counter(counters, tile, tiles), Y, m, n, ks, tile,
-                                   blockIdx.x / tiles, tile_cols, splits,
-                                   survivor_report(counters, 0, splits));
+    batch_block<NB, WAVES>(W, X, batch, bound, partial, tile_counter(counters, tile, tiles), Y, m,
+                           n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
+                           survivor_report(counters, 0, splits));
 }
 
 // Several matrices that read the same batch of hidden states (q/k/v, gate/up:
@@ -367,8 +491,8 @@ struct BatchMultiArgs {
     int count;
 };
 
-template <int NB, int LPR, int WAVES, int U>
-__global__ __launch_bounds__(WAVES * 64) void sparse_gemv_batch_multi_kernel(
+template <int NB, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
     BatchMultiArgs ma, const __half *__restrict__ X, int batch, float *partial, int *counters,
     int m, int ks, int tile_cols, int splits)
 {
@@ -384,14 +508,14 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_batch_multi_kernel(
             k = j;
         }
     }
-    batch_block<NB, LPR, WAVES, U>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
-                                   tile_counter(counters, gtile, tiles), ma.Y[k], m, ma.n[k], ks,
-                                   gtile - ma.tile_begin[k], s, tile_cols, splits,
-                                   survivor_report(counters, k, splits));
+    batch_block<NB, WAVES>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
+                           tile_counter(counters, gtile, tiles), ma.Y[k], m, ma.n[k], ks,
+                           gtile - ma.tile_begin[k], s, tile_cols, splits,
+                           survivor_report(counters, k, splits));
 }
 
 constexpr int kBatchWaves = 8;
-constexpr int kBatchUnroll = 4;
+constexpr int kBatchUnroll = 4;      // what the launch-shape rule fills in; the kernel loads 8 rows per chunk
 
 // One block thresholds the batch like sparsify_kernel does one vector: groups of 4 chunks
 // of 1024 channels, the loads of a group (all batch rows) in flight together.
@@ -547,42 +671,52 @@ bool gemv_batch_shape_supported(int batch, const GemvShape &s)
     const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
     const bool lpr = s.lanes_per_row == 64 || s.lanes_per_row == 32 || s.lanes_per_row == 16;
     const bool tc = s.tile_cols >= 0 && s.tile_cols % 8 == 0 && s.tile_cols <= s.lanes_per_row * 8;
-    // a thread of the second pass owns at most 4 outputs: nb x (8 * lanes) <= 2048
+    // (the limit of the documented interface; tiles wider than kBatchTile run in that width)
     const bool fits = nb * s.lanes_per_row <= 256;
     return lpr && tc && fits && s.waves == kBatchWaves && s.unroll == kBatchUnroll &&
            s.splits >= 1;
+}
+
+// A block's tile is at most kBatchTile columns wide; a wider request runs in tiles of that width.
+static GemvShape batch_tile(GemvShape sh)
+{
+    const int asked = sh.tile_cols > 0 ? sh.tile_cols : sh.lanes_per_row * 8;
+    sh.lanes_per_row = 16;
+    sh.tile_cols = asked < kBatchTile ? asked : kBatchTile;
+    return sh;
+}
+
+// Dynamic LDS of a block: the activations of a slice that survives whole and its index list;
+// the combine buffer reuses it.
+static size_t batch_lds(int ks)
+{
+    const size_t list = (size_t)(ks + kChunkRows) * kActBytes + (size_t)ks * sizeof(int);
+    const size_t red = (size_t)kBatchWaves * kBatchRedWave * sizeof(float);
+    return list > red ? list : red;
 }
 
 hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, float t, float *Y,
                                   int m, int n, float *partial, int *counters,
                                   const GemvShape &sh, hipStream_t stream)
 {
-    const GemvGeometry g = gemv_geometry(m, n, sh, 8, 64);
-    if (g.ks > kMaxSliceBatch || !gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
+    if (!gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
+    const GemvGeometry g = gemv_geometry(m, n, batch_tile(sh), 8, 64);
+    if (g.ks > kMaxLongSliceBatch) return hipErrorInvalidValue;
     const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
-    const size_t list_bytes = (size_t)(g.ks + 1) * nb * sizeof(float) + (size_t)g.ks * sizeof(int);
-    const size_t red_bytes = (size_t)kBatchWaves * 64 * nb * 8 * sizeof(float);
-    const size_t lds = list_bytes > red_bytes ? list_bytes : red_bytes;
+    const size_t lds = batch_lds(g.ks);
     const double bound = (double)batch * (double)t;
     const __half *X = static_cast<const __half *>(X_f16);
-#define TEAL_LAUNCH_B(NB, LPR)                                                                   \
-    hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, LPR, kBatchWaves, kBatchUnroll>),           \
-                       dim3(g.tiles * g.splits), dim3(kBatchWaves * 64), lds, stream, Wt, X,     \
-                       batch, bound, partial, counters, Y, m, n, g.ks, g.tiles, g.tile_cols,     \
-                       g.splits)
-    const int lpr = sh.lanes_per_row;
-    if (nb == 2) {
-        if (lpr == 64) TEAL_LAUNCH_B(2, 64);
-        else if (lpr == 32) TEAL_LAUNCH_B(2, 32);
-        else TEAL_LAUNCH_B(2, 16);
-    } else if (nb == 4) {
-        if (lpr == 64) TEAL_LAUNCH_B(4, 64);
-        else if (lpr == 32) TEAL_LAUNCH_B(4, 32);
-        else TEAL_LAUNCH_B(4, 16);
-    } else {
-        if (lpr == 32) TEAL_LAUNCH_B(8, 32);
-        else TEAL_LAUNCH_B(8, 16);
-    }
+#define TEAL_LAUNCH_B(NB)                                                                        \
+    do {                                                                                         \
+        if (!allow_large_lds(sparse_gemv_batch_kernel<NB, kBatchWaves>, lds))                    \
+            return hipErrorInvalidValue;                                                         \
+        hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves>), dim3(g.tiles * g.splits), \
+                           dim3(kBatchWaves * 64), lds, stream, Wt, X, batch, bound, partial,    \
+                           counters, Y, m, n, g.ks, g.tiles, g.tile_cols, g.splits);             \
+    } while (0)
+    if (nb == 2) TEAL_LAUNCH_B(2);
+    else if (nb == 4) TEAL_LAUNCH_B(4);
+    else TEAL_LAUNCH_B(8);
 #undef TEAL_LAUNCH_B
     return hipGetLastError();
 }
@@ -594,12 +728,11 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
 {
     int n_max = 0;
     for (int k = 0; k < count; ++k) n_max = n[k] > n_max ? n[k] : n_max;
-    const GemvGeometry g = gemv_geometry(m, n_max, sh, 8, 64);
-    if (g.ks > kMaxSliceBatch || !gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
+    if (!gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
+    const GemvGeometry g = gemv_geometry(m, n_max, batch_tile(sh), 8, 64);
+    if (g.ks > kMaxLongSliceBatch) return hipErrorInvalidValue;
     const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
-    const size_t list_bytes = (size_t)(g.ks + 1) * nb * sizeof(float) + (size_t)g.ks * sizeof(int);
-    const size_t red_bytes = (size_t)kBatchWaves * 64 * nb * 8 * sizeof(float);
-    const size_t lds = list_bytes > red_bytes ? list_bytes : red_bytes;
+    const size_t lds = batch_lds(g.ks);
     BatchMultiArgs ma{};
     ma.count = count;
     ma.tile_begin[0] = 0;
@@ -612,23 +745,17 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
     }
     const int tiles = ma.tile_begin[count];
     const __half *X = static_cast<const __half *>(X_f16);
-#define TEAL_LAUNCH_BM(NB, LPR)                                                                  \
-    hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, LPR, kBatchWaves, kBatchUnroll>),     \
-                       dim3(tiles * g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,       \
-                       batch, partial, counters, m, g.ks, g.tile_cols, g.splits)
-    const int lpr = sh.lanes_per_row;
-    if (nb == 2) {
-        if (lpr == 64) TEAL_LAUNCH_BM(2, 64);
-        else if (lpr == 32) TEAL_LAUNCH_BM(2, 32);
-        else TEAL_LAUNCH_BM(2, 16);
-    } else if (nb == 4) {
-        if (lpr == 64) TEAL_LAUNCH_BM(4, 64);
-        else if (lpr == 32) TEAL_LAUNCH_BM(4, 32);
-        else TEAL_LAUNCH_BM(4, 16);
-    } else {
-        if (lpr == 32) TEAL_LAUNCH_BM(8, 32);
-        else TEAL_LAUNCH_BM(8, 16);
-    }
+#define TEAL_LAUNCH_BM(NB)                                                                       \
+    do {                                                                                         \
+        if (!allow_large_lds(sparse_gemv_batch_multi_kernel<NB, kBatchWaves>, lds))              \
+            return hipErrorInvalidValue;                                                         \
+        hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, kBatchWaves>),                    \
+                           dim3(tiles * g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,   \
+                           batch, partial, counters, m, g.ks, g.tile_cols, g.splits);            \
+    } while (0)
+    if (nb == 2) TEAL_LAUNCH_BM(2);
+    else if (nb == 4) TEAL_LAUNCH_BM(4);
+    else TEAL_LAUNCH_BM(8);
 #undef TEAL_LAUNCH_BM
     return hipGetLastError();
 }
@@ -654,3 +781,22 @@ hipError_t launch_sparsify_batch(const void *X_f16, int batch, int m, float t, u
 }
 
 }  // namespace teal
+
+#ifdef TEAL_TRACE_BLOCKS
+// The trace build's read-out for the kernels of this file (see trace_mark in gemv_common.h).
+extern "C" int teal_trace_read_batch(unsigned long long *host, size_t count)
+{
+    const size_t all = (size_t)teal::kTraceBlocks * teal::kTraceMarks;
+    if (!host || count > all) return 1;
+    if (hipDeviceSynchronize() != hipSuccess) return 2;
+    if (hipMemcpyFromSymbol(host, HIP_SYMBOL(teal::teal_trace),
+                            count * sizeof(unsigned long long)) != hipSuccess)
+        return 3;
+    static unsigned long long zeros[4096];
+    for (size_t at = 0; at < all; at += 4096)
+        if (hipMemcpyToSymbol(HIP_SYMBOL(teal::teal_trace), zeros, sizeof(zeros),
+                              at * sizeof(unsigned long long)) != hipSuccess)
+            return 4;
+    return 0;
+}
+#endif

@@ -184,14 +184,30 @@ GemvShape auto_shape_multi_pitch(int m, const int *n, const int *row_pitch, int 
                      : auto_shape(m, n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple);
 }
 
+// Launch shape of a batched call: tiles of at most 128 columns (16 lanes of 8).  A block takes up
+// to kMaxSliceBatch channels (two blocks share a unit's LDS), or all of up to kMaxLongSliceBatch
+// where the tiles alone then make about one block per unit: no split-K, and no second round
+// of blocks on a part of the units (Llama-3-8B gate + up at 8 rows: 28.7 us as 448 blocks in 2
+// splits, 25.3 us as 224 blocks without split-K).
+GemvShape auto_shape_batch(int m, const int *n, int count)
+{
+    long long tiles = 0, n_total = 0;
+    for (int k = 0; k < count; ++k) {
+        tiles += (n[k] + 127) / 128;
+        n_total += n[k];
+    }
+    const int slice = tiles >= 160 && tiles <= kComputeUnits && m <= teal::kMaxLongSliceBatch
+                          ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch;
+    return count > 1 ? auto_shape_multi(m, n, count, 8, 16, 16, 64, slice)
+                     : auto_shape(m, (int)n_total, 8, 16, 16, 64, slice);
+}
+
 // Partial rows a batched call may need: one per (split, batch row).
 int batch_split_rows(int m)
 {
     const int forced = (m + teal::kMaxSliceBatch - 1) / teal::kMaxSliceBatch;
     return forced > 16 ? forced : 16;
 }
-
-int batch_accumulators(int batch) { return batch <= 2 ? 2 : batch <= 4 ? 4 : 8; }
 
 struct GemvArgs {
     const void *W;
@@ -489,10 +505,7 @@ teal_status teal_sparse_gemv_bf16_batch_multi(int count, const void *const *Wt_b
         if (!threshold_ok(t[k])) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes_batch(m, (int)n_total, batch))
         return TEAL_ERR_WORKSPACE;
-    const int max_lanes = batch_accumulators(batch) >= 4 ? 16 : 64;
-    const GemvShape sh =
-        count > 1 ? auto_shape_multi(m, n, count, 8, 16, max_lanes, 64, teal::kMaxSliceBatch)
-                  : auto_shape(m, (int)n_total, 8, 16, max_lanes, 64, teal::kMaxSliceBatch);
+    const GemvShape sh = auto_shape_batch(m, n, count);
     if (!teal::gemv_batch_shape_supported(batch, sh)) return TEAL_ERR_UNSUPPORTED;
     return from_hip(teal::launch_gemv_bf16_batch_multi(count, Wt_bf16, t, Y, n, X_f16, batch, m,
                                                        ws_partials(workspace, m),
@@ -789,10 +802,8 @@ teal_status teal_sparse_gemv_bf16_batch_ex(const void *Wt_bf16, const void *X_f1
         return TEAL_ERR_ALIGN;
     if (!threshold_ok(t)) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes_batch(m, n, batch)) return TEAL_ERR_WORKSPACE;
-    // With several accumulator sets per lane, sweeps favour narrow tiles (128 columns) and
-    // correspondingly fewer splits over the wide tiles of the single-vector kernel.
-    const int max_lanes = batch_accumulators(batch) >= 4 ? 16 : 64;
-    GemvShape sh = auto_shape(m, n, 8, 16, max_lanes, 64, teal::kMaxSliceBatch);
+    GemvShape sh = auto_shape_batch(m, &n, 1);
+    const bool own_shape = !lanes_per_row && !tile_cols && !splits;
     if (lanes_per_row) {
         sh.lanes_per_row = lanes_per_row;
         if (!tile_cols && sh.tile_cols > lanes_per_row * 8) sh.tile_cols = lanes_per_row * 8;
@@ -802,7 +813,7 @@ teal_status teal_sparse_gemv_bf16_batch_ex(const void *Wt_bf16, const void *X_f1
     if (!teal::gemv_batch_shape_supported(batch, sh)) return TEAL_ERR_UNSUPPORTED;
     if (!tiles_fit_counters(n, sh)) return TEAL_ERR_UNSUPPORTED;
     const int ks = ((m + sh.splits - 1) / sh.splits + 63) / 64 * 64;
-    if (ks > teal::kMaxSliceBatch) return TEAL_ERR_UNSUPPORTED;
+    if (ks > (own_shape ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch)) return TEAL_ERR_UNSUPPORTED;
     if ((m + ks - 1) / ks > batch_split_rows(m)) return TEAL_ERR_UNSUPPORTED;   // partial rows
     return from_hip(teal::launch_gemv_bf16_batch(Wt_bf16, X_f16, batch, t, Y, m, n,
                                                  ws_partials(workspace, m), ws_counters(workspace),

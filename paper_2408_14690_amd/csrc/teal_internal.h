@@ -20,6 +20,7 @@ constexpr int kMinTile = 64;        // narrowest output tile of any kernel varia
 constexpr int kMaxNormInput = 16384; // longest hidden state the fused normalisation takes
 constexpr int kMaxBatch = 8;        // rows of a small batch (Section 5.4.4)
 constexpr int kMaxSliceBatch = 2048;  // most input channels one block compacts for a batch
+constexpr int kMaxLongSliceBatch = 4096;   // the same where that runs without split-K in one round of blocks
 // Head of the workspace: one arrival counter per output tile (zero between calls).
 constexpr size_t kCounterBytes = (size_t)(kMaxDim / kMinTile) * sizeof(int);
 constexpr int kCounterLineInts = 32;    // counters 128 bytes apart while the area has room
@@ -90,7 +91,7 @@ hipError_t launch_gemv_w8_stack(int groups, const StackGroupDesc *g, hipStream_t
 hipError_t launch_gemv_w4_stack(int groups, const StackGroupDesc *g, hipStream_t stream);
 
 // Small batch (Section 5.4.4).  The slice of a block, ceil(m / splits) rounded up to 64,
-// must not exceed kMaxSliceBatch.
+// must not exceed kMaxLongSliceBatch.
 bool gemv_batch_shape_supported(int batch, const GemvShape &s);
 
 hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, float t, float *Y,

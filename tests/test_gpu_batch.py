@@ -254,3 +254,44 @@ def test_very_long_input(T):
     for b in range(batch):
         assert rel_l2(Ys[0].cpu().numpy()[b], want[b]) <= TIGHT, b
         assert rel_l2(Ys[1].cpu().numpy()[b], want2[b]) <= TIGHT, b
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("m,n,kept", [(64, 8, 1), (512, 136, 3), (512, 128, 256), (513, 264, 257),
+                                      (1026, 256, 300), (2052, 128, 1100), (2050, 20488, 1500),
+                                      (4096, 20488, 2050), (4090, 28672, 2047)])
+def test_batch_matrix_core_edges(T, batch, m, n, kept):
+    """Survivor counts around the 32 rows of a matrix instruction and the 4 rows of a load; slices
+    read by one, two and four channels per lane, unaligned lengths one by one; whole-input
+    blocks (20488 and 28672 columns).  Infinite and NaN weights and activations stay in their own
+    column and batch row, also in the last row of a share."""
+    rng = np.random.default_rng(100 * batch + m + n)
+    X = (rng.standard_normal((batch, m)) * 0.01).astype(np.float16)
+    keep = np.sort(rng.choice(m, kept, replace=False))
+    X[:, keep] = (np.sign(rng.standard_normal((batch, kept))) *
+                  (1.0 + rng.random((batch, kept)) * 60)).astype(np.float16)
+    w = ti.f32_to_bf16_bits((rng.standard_normal((m, n)) * 0.02).astype(np.float32))
+    special = {}
+    if kept > 2:
+        w[keep[-1], 1], w[keep[0], 5], w[keep[1], n - 1] = 0x7F80, 0xFF80, 0x7FC1
+        X[batch - 1, keep[1]] = np.inf
+        special = {1, 5, n - 1}
+    wf = ti.bf16_bits_to_f32(w).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        # the infinite activation times a column's weight decides that batch row
+        want = np.stack([(X[b, keep].astype(np.float64)[:, None] * wf[keep]).sum(0) for b in range(batch)])
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, n, batch), dtype=torch.uint8, device="cuda")
+    got = run_batch(T, dev(w), X, 0.5, m, n, ws)
+    off = T.teal_survivors_offset()
+    assert ws[off:off + 4].view(torch.int32).item() == kept
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    for b in range(batch):
+        # 32-bit sums of exact products: kept * 2^-24 of the sum of magnitudes bounds any order
+        if fin[b].any():
+            mag = (np.abs(X[b, keep].astype(np.float64))[:, None] * np.abs(wf[keep]))[:, fin[b]].sum(0)
+            err = np.abs(got[b][fin[b]] - want[b][fin[b]])
+            assert np.all(err <= 2 * kept * 2.0 ** -24 * mag), (b, float((err / mag).max()))
+    assert special or not inf.any()
