@@ -100,3 +100,47 @@ def test_calibrated_threshold_gives_the_requested_sparsity(T):
     kept = int(count.item())
     assert kept == orc.sparsify(x, t50)[3]
     assert abs(1 - kept / 4096 - 0.5) < 0.03       # a fresh draw: binomial spread ~0.008
+
+
+@pytest.mark.parametrize("count,off", [(1, 0), (7, 1), (8191, 3), (8192 * 256, 0), (8192 * 256 + 9, 5),
+                                       (8192 * 700 + 4095, 0)])
+def test_histogram_shares_zeros_and_nans(T, count, off):
+    """Contiguous shares of the blocks (one value, less than a unit, a unit per block, ragged),
+    many zeros (counted lane by lane), NaNs (left out) and every sign."""
+    rng = np.random.default_rng(count)
+    x = rng.standard_normal(count).astype(np.float16)
+    x[rng.random(count) < 0.4] = np.float16(0.0)
+    x[rng.random(count) < 0.1] = np.float16(-0.0)
+    x[rng.random(count) < 0.01] = np.float16(np.nan)
+    x[rng.random(count) < 0.01] = np.float16(-np.inf)
+    buf = torch.zeros(count + 8, dtype=torch.int16, device="cuda")
+    buf[off:off + count] = torch.from_numpy(x.view(np.int16)).cuda()
+    hist = torch.zeros(T.TEAL_HIST_BINS, dtype=torch.int64, device="cuda")
+    for _ in range(2):
+        T.check(T.teal_abs_histogram(buf[off:off + count], count, hist))
+    torch.cuda.synchronize()
+    mag = x.view(np.uint16).astype(np.int64) & 0x7FFF
+    want = 2 * np.bincount(mag[mag <= 0x7C00], minlength=T.TEAL_HIST_BINS)
+    assert np.array_equal(hist.cpu().numpy(), want)
+
+
+def test_thresholds_at_every_row_and_wavefront_edge(T):
+    """Ranks whose bin is the first or last of a lane's pair, of a row of 128 bins and of a
+    wavefront's 2048 bins, counts beyond 32 bits, and levels 0 and 1."""
+    bins = [0, 1, 2, 127, 128, 2047, 2048, 2175, 2176, 4095, 4096, 20000, 30719, 30720, 31743, 31744]
+    hist = np.zeros(T.TEAL_HIST_BINS, np.int64)
+    hist[bins] = [3, 1, 5, 2, 2, 7, 1, 1, 4, 9, (1 << 33) + 1, 2, 6, 1, 1, 2]
+    total = int(hist.sum())
+    cum = np.cumsum(hist)
+    ranks = sorted({int(r) for b in bins for r in (cum[b], cum[b] - hist[b] + 1)})
+    hd = torch.from_numpy(hist).cuda()
+    levels = [0.0, 1.0] + [r / total for r in ranks]
+    for i in range(0, len(levels), 16):
+        part = levels[i:i + 16]
+        t = torch.full((len(part),), -1.0, dtype=torch.float32, device="cuda")
+        T.check(T.teal_histogram_thresholds(hd, part, t))
+        torch.cuda.synchronize()
+        for p, got in zip(part, t.cpu().numpy()):
+            k = min(total, max(0, int(np.ceil(p * float(total) - 1e-9))))
+            want = 0.0 if k == 0 else float(np.uint16(np.searchsorted(cum, k)).view(np.float16))
+            assert got == want, (p, k)
