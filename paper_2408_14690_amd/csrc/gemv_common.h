@@ -350,8 +350,27 @@ struct RmsnormSource {                // hidden state and norm weights, fp32 in 
 // Definition 1 on one element: fp16 -> fp32 is exact, the compare is fp32.
 __device__ __forceinline__ bool survives(float xv, float t) { return fabsf(xv) > t; }
 
+// What a list entry holds beside its channel.  PlainBits: x as fp32 bits.  (FixedDigits, for the
+// int4 kernel, needs the largest survivor of the slice before it can encode one: kScaled.)
+struct PlainBits {
+    static constexpr bool kScaled = false;
+    static __device__ __forceinline__ int encode(float x, unsigned) { return __float_as_int(x); }
+};
+
+// Largest value over the 64 lanes (inclusive scan; lanes shifted in from outside hold zero).
+__device__ __forceinline__ unsigned wave_max(unsigned v)
+{
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Compacts the survivors of channels [k0, k1) into list[] as (channel, x as
-// fp32 bits), ascending.  Each wavefront ballots its 64-channel segments and
+// fp32 bits or as Enc encodes it), ascending.  Each wavefront ballots its 64-channel segments and
 // leaves their popcounts in seg_cnt[] (LDS, kMaxSegs ints); after one barrier
 // every wavefront computes the exclusive prefix over the segment counts
 // itself (lane j holds the prefix of segment j in `seg_excl`; lanes past the
@@ -362,12 +381,15 @@ __device__ __forceinline__ bool survives(float xv, float t) { return fabsf(xv) >
 // with a barrier after which list[] is complete.  `prepared`, when given, carries
 // what the source prepares once per block (the scale of the normalisation) from
 // one piece of a long slice to the next: computed when `have_prepared` is false
-// (block-uniform), reused otherwise.
-template <int WAVES, class XS>
+// (block-uniform), reused otherwise.  `largest`, with an encoding that needs it: the fp32 bits
+// of the largest surviving |x| (infinities and all; 0 when nothing survives), the same in all
+// threads; seg_cnt[] then has WAVES ints more.
+template <int WAVES, class XS, class Enc = PlainBits>
 __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
                                              int k1, int2 *list, int *seg_cnt, int &seg_excl,
                                              float *prepared_io = nullptr,
-                                             bool have_prepared = false)
+                                             bool have_prepared = false,
+                                             unsigned *largest = nullptr)
 {
     constexpr int PER_WAVE = kMaxSegs / WAVES;
     const int lane = threadIdx.x & 63;
@@ -401,11 +423,25 @@ __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
         bal[j] = __ballot(survives(xv[j], t));
         if (lane == 0 && seg < nseg) seg_cnt[seg] = __popcll(bal[j]);
     }
+    unsigned top = 0;
+    if constexpr (Enc::kScaled) {
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j)
+            top = max(top, survives(xv[j], t) ? __float_as_uint(fabsf(xv[j])) : 0u);
+        top = wave_max(top);
+        if (lane == 0) seg_cnt[kMaxSegs + w] = (int)top;
+    }
     __syncthreads();
     const int c = lane < nseg ? seg_cnt[lane] : 0;
     const int incl = wave_inclusive_scan(c);
     seg_excl = incl - c;
     const int total = __builtin_amdgcn_readlane(incl, 63);
+    if constexpr (Enc::kScaled) {
+        top = 0;
+#pragma unroll
+        for (int ww = 0; ww < WAVES; ++ww) top = max(top, (unsigned)seg_cnt[kMaxSegs + ww]);
+        *largest = top = __builtin_amdgcn_readfirstlane(top);
+    }
 #pragma unroll
     for (int j = 0; j < PER_WAVE; ++j) {
         const int seg = w + j * WAVES;
@@ -413,7 +449,7 @@ __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
             const int base = __builtin_amdgcn_readlane(seg_excl, seg);
             if (survives(xv[j], t))
                 list[base + lanes_below(bal[j])] =
-                    make_int2(k0 + seg * 64 + lane, __float_as_int(xv[j]));
+                    make_int2(k0 + seg * 64 + lane, Enc::encode(xv[j], top));
         }
     }
     __syncthreads();
@@ -433,12 +469,14 @@ __device__ __forceinline__ void wave_share(int cnt, int w, int waves, int &start
 // lane, the same number compact_slice issues), so it knows every count and writes exactly
 // those entries of list[] that fall into its own share [start, start + mine) -- the entries
 // it alone will read.  The result (list contents, total, seg_excl) is that of compact_slice.
-template <int P, int WAVES>
+// The wavefront's share is `share` of `shares`; wavefronts with the same share write the same
+// entries.
+template <int P, class Enc = PlainBits>
 __device__ __forceinline__ int compact_slice_private(const __half *__restrict__ x, float t, int k0,
-                                                     int k1, int2 *list, int &seg_excl)
+                                                     int k1, int share, int shares, int2 *list,
+                                                     int &seg_excl, unsigned *largest = nullptr)
 {
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     __half raw[P];
 #pragma unroll
     for (int j = 0; j < P; ++j) raw[j] = x[min(k0 + j * 64 + lane, k1 - 1)];
@@ -457,15 +495,22 @@ __device__ __forceinline__ int compact_slice_private(const __half *__restrict__ 
     seg_excl = total;                                         // lane j: prefix of segment j
 #pragma unroll
     for (int j = 0; j < P; ++j) seg_excl = lane == j ? base[j] : seg_excl;
+    unsigned top = 0;
+    if constexpr (Enc::kScaled) {
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+            top = max(top, survives(xv[j], t) ? __float_as_uint(fabsf(xv[j])) : 0u);
+        *largest = top = wave_max(top);
+    }
     int start, mine;
-    wave_share(total, w, WAVES, start, mine);
+    wave_share(total, share, shares, start, mine);
     const int end = start + mine;
 #pragma unroll
     for (int j = 0; j < P; ++j) {
         if (base[j] < end && base[j + 1] > start) {           // wavefront-uniform
             const int rank = base[j] + lanes_below(bal[j]);
             if (survives(xv[j], t) && rank >= start && rank < end)
-                list[rank] = make_int2(k0 + j * 64 + lane, __float_as_int(xv[j]));
+                list[rank] = make_int2(k0 + j * 64 + lane, Enc::encode(xv[j], top));
         }
     }
     return total;
@@ -536,13 +581,14 @@ __device__ __forceinline__ void stream_rows(float (&acc)[F::kElemsPerLane], cons
 // Where column c of a tile lies in a wavefront's row of the LDS combine buffer.  Lanes
 // write their sums one float at a time (see store_wave_sums), EPL columns apart from their
 // neighbours; one float of padding per EPL columns keeps those writes off a common bank.
+// (The int4 kernel, EPL = 32, writes pairs of neighbouring columns.)
 template <int EPL, int LPR>
 __device__ __forceinline__ int combine_index(int c)
 {
-    return LPR == 64 ? c : c + c / EPL;
+    return LPR == 64 || EPL == 32 ? c : c + c / EPL;
 }
 template <int EPL, int LPR>
-constexpr int combine_row = LPR == 64 ? LPR * EPL : LPR * EPL + LPR;
+constexpr int combine_row = LPR == 64 || EPL == 32 ? LPR * EPL : LPR * EPL + LPR;
 
 // Two accumulators a and b of a lane are exchanged with the partner lane 16 (or 32) lanes
 // away such that one addition leaves a's pair sum in the even rows of 16 lanes (lower 32
@@ -613,7 +659,9 @@ __device__ __forceinline__ void store_wave_sums(const float (&acc)[N], float *ds
 // y.  The split-K combine of Section 4.4, without atomics on y and without a
 // second launch.  The tile is columns [col0, col0 + cols) of y, cols <= TN.
 // Returns (block-uniform) whether this block wrote the tile's outputs.
-template <class F, int LPR, int WAVES>
+// The combine buffer has SUMS rows of combine_row floats, a row per wavefront unless a format
+// says otherwise.
+template <class F, int LPR, int WAVES, int SUMS = WAVES>
 __device__ __forceinline__ bool block_finish(float *red,
                                              float *partial, int *counter, float *y, int tile,
                                              int col0, int cols, int s, int splits, int n,
@@ -644,7 +692,7 @@ __device__ __forceinline__ bool block_finish(float *red,
             if (c < cols) {
                 float sum = 0.f;
 #pragma unroll
-                for (int ww = 0; ww < WAVES; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
+                for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
                 store_coherent(y + col0 + c, F::finish(sum, scale[k]));
             }
         }
@@ -660,7 +708,7 @@ __device__ __forceinline__ bool block_finish(float *red,
     for (int c = threadIdx.x; c < cols; c += THREADS) {
         float sum = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < WAVES; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
+        for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
         store_coherent(row + c, sum);
     }
     wait_vector_memory();   // this thread's write-through stores have completed
@@ -736,12 +784,13 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
     int cnt;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (XS::kPlainHalf) {
         // short slices: each wavefront compacts its own share, no barrier before the stream
         const int nseg = (k1 - k0 + 63) >> 6;                 // block-uniform
         int seg_excl;
         if (nseg <= 8) {
-            cnt = compact_slice_private<8, WAVES>(x.x, t, k0, k1, list, seg_excl);
+            cnt = compact_slice_private<8>(x.x, t, k0, k1, wave, WAVES, list, seg_excl);
         } else {
             // a slice longer than kMaxSlice is compacted in pieces of that length, one
             // behind the other in the list (block-uniform trip count)
@@ -838,6 +887,7 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
                                             int *counters, int m, int ks, int tile_cols, int splits,
                                             int block)
 {
+    trace_mark(0);
     const int tiles = ma.tile_begin[ma.count];
     const int gtile = block % tiles;
     const int s = block / tiles;
@@ -854,6 +904,7 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
                                  tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
                                  gtile - ma.tile_begin[k], s, tile_cols, splits,
                                  survivor_report(counters, k, splits));
+    trace_mark(6);
 }
 
 template <class F, int LPR, int WAVES, int U>

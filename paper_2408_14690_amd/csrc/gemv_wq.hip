@@ -47,37 +47,6 @@ struct FmtW4 {
         const void *W;
         const __half *scale;
     };
-    // Converting a nibble to fp32 the plain way costs two instructions per element.
-    // Instead: q + 8 (the nibble with its top bit flipped) is left where it lies and read
-    // as an fp16 subnormal: a nibble in bits 0..3 of a 16-bit half is the value
-    // (q + 8) 2^-24, in bits 4..7 it is (q + 8) 2^-20 (no implicit one, so no offset
-    // that would cost accumulator precision).  One AND isolates two nibbles (one per
-    // half), one shift by 8 serves the upper two nibbles of each half, and the FMA reads
-    // the fp16 halves directly: 14 vector instructions per 8 weights.  The scaling by
-    // 2^24 / 2^20 and the offset 8 are undone once per group from sum x*v and sum x
-    // (exact products, fp32 sums).  Relies on fp16 subnormals being honoured by the
-    // mixed-precision FMA (they are in the default floating-point mode).  (Pairing two
-    // rows per fp16 dot-product instruction saves another 1 % of the step time, but that
-    // instruction's sum is less accurate: 5e-5 relative on a dense 14336-channel input.)
-    static constexpr float kScaleEven = 16777216.f;   // 2^24: columns 0, 2 of each group of 4
-    static constexpr float kScaleOdd = 1048576.f;     // 2^20: columns 1, 3
-    static constexpr float kOffset = 8.f;             // q = scale * v - kOffset
-    static __device__ __forceinline__ void fma(float (&acc)[32], u32x4 v, float xv)
-    {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t d = v[q] ^ 0x88888888u;
-            const uint32_t d8 = d >> 8;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                // nibble k in the low half, nibble k + 4 in the high half
-                const uint32_t pair = (k < 2 ? d : d8) & ((k & 1) ? 0x00F000F0u : 0x000F000Fu);
-                const __half2 h = *reinterpret_cast<const __half2 *>(&pair);
-                acc[8 * q + k] = fmaf(__low2float(h), xv, acc[8 * q + k]);
-                acc[8 * q + k + 4] = fmaf(__high2float(h), xv, acc[8 * q + k + 4]);
-            }
-        }
-    }
     struct ColumnScale {};
     static __device__ __forceinline__ ColumnScale column_scale(const Args &, int) { return {}; }
     static __device__ __forceinline__ float finish(float sum, ColumnScale) { return sum; }
@@ -87,31 +56,90 @@ constexpr int kGroup = 128;
 constexpr int kW4Waves = 8;
 constexpr int kW4Unroll = 4;
 
-// One batch of row loads of the int4 kernel: up to U wavefront loads, all from
-// one 128-channel group, and, if the batch is the wavefront's last of that
-// group, the group's scales for this lane's 32 columns.
+// The int4 products run on the matrix cores, in integers.  With fp32 FMAs every weight costs its FMA
+// and 0.75 instructions to extract it, 71 vector instructions per 16-byte load with the
+// addressing: the row stream was bound by instruction issue (two wavefronts per SIMD), not by HBM
+// (dense 28672 x 8192: 21 us of rows for 14.7 us of bytes at the peak).
+//
+// v_mfma_i32_16x16x32_i8: a lane's 8 bytes of one weight row are 8 of the 32 values of K, its
+// lane % 16 the row of A, lane / 16 the quarter of K, so with 16 lanes to a weight row the weights go
+// in as they were loaded.  B separates the bytes again: it is zero except where the byte's place
+// in the lane equals the column's, B[8 g + j][j] = the activation of lane group g's row, so the
+// product of chunk m (16 bytes, 32 output columns) with column j is the sum over the rows of activation
+// times byte j, and the four rows of a load are added by the instruction.  A byte is two
+// nibbles: with the low one offset by 8 it is the signed number 16 hi + (lo + 8), and masked it is
+// lo + 8, so hi and lo follow from the two sums by integer arithmetic: 8 instructions per 16-byte
+// load in place of 56.
+//
+// Activations enter as integers too: X = x 2^s, with s such that the largest survivor of the
+// slice has 30 bits, in four signed base-256 digits; columns j and j + 8 of B take two digits, two
+// instructions the four.  X is exact for every x that is a multiple of 2^-s (all of fp16 where the
+// largest is below 64, else all but values more than 2^19 times smaller than it), the sums are exact,
+// and are rounded to fp32 once per 128-channel group, where the group's scale is applied:
+// no larger error than the fp32 sums had.  An infinite activation makes every column NaN, as it
+// did when the nibbles were offset by 8 and the correction was infinite, too.
+struct FixedDigits {
+    static constexpr bool kScaled = true;
+    static constexpr int kBits = 29;                // 2^kBits <= largest |X| < 2^(kBits + 1)
+    // s from the fp32 bits of the largest |x| (0: nothing survives)
+    static __device__ __forceinline__ int shift(unsigned largest)
+    {
+        return kBits - ((int)(largest >> 23) - 127);
+    }
+    static __device__ __forceinline__ float power_of_two(int e)
+    {
+        return __int_as_float((e + 127) << 23);
+    }
+    static __device__ __forceinline__ int encode(float x, unsigned largest)
+    {
+        // digit d of X is byte d: adding 128 to each of the lower three digits makes the bytes
+        // of X unsigned digits without a borrow, and the flip of their top bits takes it off again
+        const int X = __float2int_rn(x * power_of_two(shift(largest)));
+        return (int)(((unsigned)X + 0x00808080u) ^ 0x00808080u);
+    }
+};
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ i32x4 mfma_i8(unsigned a0, unsigned a1, unsigned b0, unsigned b1, i32x4 c)
+{
+    return __builtin_amdgcn_mfma_i32_16x16x32_i8((long)(((unsigned long)a1 << 32) | a0),
+                                                 (long)(((unsigned long)b1 << 32) | b0), c, 0, 0, 0);
+}
+
+// One batch of row loads of the int4 kernel: U wavefront loads of 4 rows, all from one 128-channel
+// group, and the group's scales for the columns this lane holds sums of.
 template <int U>
 struct W4Batch {
     u32x4 v[U];
-    float xv[U];
-    uint4 sc[4];      // 32 fp16 scales (loaded only when ends_run)
+    int x[U];         // digits of the activations
+    unsigned sc[8];   // fp16 pairs: chunk 4 * (lane / 16) + r, bytes lane % 8 + 8 h, at [4 h + r]
     int rows;         // live rows in this batch (wavefront-uniform); 0 = the share is exhausted
     bool ends_run;    // wavefront-uniform
+};
+
+// Integer sums over the rows of one run (a wavefront's rows of one group): lane (n = lane % 16,
+// g = lane / 16) holds, in register r, chunk 4 g + r, byte n % 8 of half h, digit n / 8 + 2 p.
+struct W4Sums {
+    i32x4 v[2][2][2];      // [nibble][h][p] sum of digit * 16 * nibble
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k >> 2][(k >> 1) & 1][k & 1] = i32x4{0, 0, 0, 0};
+    }
 };
 
 // Work of one block for int4 weights with group scales: output tile `tile`
 // (tile_cols columns) x K-slice `s` (ks channels, a multiple of 128).
 //
-// The wavefronts take equal contiguous shares of the compacted list, as for
+// A wavefront covers 512 columns (16 lanes of 32, four rows per load).  With LPR = 32 (tiles of up to
+// 1024 columns) the even wavefronts take the left half of the tile and the odd ones the right, and a
+// pair shares its rows.  The wavefronts take equal contiguous shares of the compacted list, as for
 // the other formats.  The list is ascending, so each 128-channel group is a
 // run of it, delimited by the segment prefixes (two 64-channel segments per
-// group), and a wavefront's share crosses few group boundaries.  Within a group
-// a wavefront accumulates sum_i x_i v[i][j] unscaled (v = the offset nibble
-// read as a tiny fp16, see FmtW4); at the end of its rows of that group it undoes the
-// affine map and folds the sums into the running sums with the group's scales:
-// once per (wavefront, group it touches), not once per row.  Batches never
-// straddle a group, and two batches are in flight per wavefront across group
-// boundaries.
+// group), and a wavefront's share crosses few group boundaries: the scales are applied once per
+// (wavefront, group it touches).  Batches never straddle a group, and two batches are in flight
+// per wavefront across group boundaries.
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
@@ -121,42 +149,72 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
 {
     using F = FmtW4;
     constexpr int EPL = F::kElemsPerLane;
-    constexpr int R = 64 / LPR;
+    constexpr int R = 4;                          // rows per wavefront load
+    constexpr int PARTS = LPR / 16;               // wavefronts side by side over the tile's columns
+    constexpr int SHARES = WAVES / PARTS;
+    constexpr int PART_COLS = 16 * EPL;
+    static_assert(LPR == 16 || LPR == 32, "tiles of up to 512 or 1024 columns");
     extern __shared__ __align__(16) unsigned char smem[];
     int2 *list = reinterpret_cast<int2 *>(smem);
     float *red = reinterpret_cast<float *>(smem + (size_t)ks * sizeof(int2));
-    __shared__ int seg_cnt[kMaxSegs];
+    __shared__ int seg_cnt[kMaxSegs + WAVES];
 
     const int k0 = s * ks;                       // multiple of 128
     const int k1 = min(m, k0 + ks);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = w % PARTS, share = w / PARTS;
     int seg_excl;
     int cnt;
+    unsigned largest;
     if constexpr (XS::kPlainHalf) {
         if (k1 - k0 <= 8 * 64)         // block-uniform: short slices need no barrier
-            cnt = compact_slice_private<8, WAVES>(x.x, t, k0, k1, list, seg_excl);
+            cnt = compact_slice_private<8, FixedDigits>(x.x, t, k0, k1, share, SHARES, list, seg_excl,
+                                                        &largest);
         else
-            cnt = compact_slice<WAVES>(x, t, k0, k1, list, seg_cnt, seg_excl);
+            cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl,
+                                                        nullptr, false, &largest);
     } else {
-        cnt = compact_slice<WAVES>(x, t, k0, k1, list, seg_cnt, seg_excl);
+        cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl, nullptr,
+                                                    false, &largest);
     }
 
     trace_mark(2);
     const int lane = threadIdx.x & 63;
-    const int g = lane / LPR;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = lane & 15, g = lane >> 4;
     const int col0 = tile * tile_cols;
-    const int col = lane_column<EPL>(col0, tile_cols, n, lane % LPR);
+    const int part0 = col0 + part * PART_COLS;
+    const int part_cols = tile_cols - part * PART_COLS;
     const unsigned row_bytes = (unsigned)(n / 2);
-    const unsigned char *lane_base = static_cast<const unsigned char *>(a.W) + col / 2;
-    const __half *scale_base = a.scale + (size_t)(k0 / kGroup) * n + col;
-
-    float acc[EPL], gacc[EPL];
+    const unsigned char *lane_base =
+        static_cast<const unsigned char *>(a.W) + lane_column<EPL>(part0, part_cols, n, l) / 2;
+    // columns of this lane's sums: chunk 4 g + r, byte l % 8 of the first half
+    const __half *scale_base = a.scale + (size_t)(k0 / kGroup) * n + 2 * (l & 7);
+    int scale_col[4];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = gacc[e] = 0.f;
-    float xsum = 0.f;                             // sum of x over this lane's rows of the current run
+    for (int r = 0; r < 4; ++r) scale_col[r] = lane_column<EPL>(part0, part_cols, n, 4 * g + r);
+    // B: this lane's column takes byte l % 8 of a lane, from digit l / 8 + 2 p of the row
+    unsigned pick[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const unsigned at = 8 * (l & 3), digit = 2 * p + (l >> 3);
+            pick[p][q] = ((l >> 2) & 1) == q ? (0x0C0C0C0Cu & ~(0xFFu << at)) | (digit << at)
+                                             : 0x0C0C0C0Cu;
+        }
+
+    float acc[2][2][4];                           // [h][nibble][r], lane layout of W4Sums
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[h][q][r] = 0.f;
+    W4Sums sums;
+    sums.clear();
 
     int start, mine;
-    wave_share(cnt, w, WAVES, start, mine);
+    wave_share(cnt, share, SHARES, start, mine);
     // Walk state (all wavefront-uniform): next list position, end of the share, current
     // group of the slice and the end of this wavefront's rows in it.
     // list offset at which group j of the slice begins: the prefix of segment 2j (lanes past
@@ -168,7 +226,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const int end = start + mine;
     int gi = 0, gend = min(end, group_begin(1));
 
-    // Every call issues exactly U row loads and the four scale loads of the batch's group,
+    // Every call issues exactly U row loads and the eight scale loads of the batch's group,
     // whether or not rows are left: the compiler then knows how many loads are outstanding at
     // every wait and waits for a batch's own loads only.  (With a conditional scale load and an
     // early return for an exhausted share it waited for older loads between the loads of a
@@ -188,47 +246,58 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
         for (int u = 0; u < U; ++u) {
             const int e = cur + u * R + g;
             const int2 ent = list[min(e, last)];
-            b.xv[u] = (live && e <= last) ? __int_as_float(ent.y) : 0.f;
+            b.x[u] = (live && e <= last) ? ent.y : 0;
             b.v[u] = load_stream16(lane_base + (size_t)(unsigned)ent.x * row_bytes);
         }
         b.rows = nb;
         b.ends_run = live && cur + nb == gend;
-        const uint4 *sp = reinterpret_cast<const uint4 *>(scale_base + (size_t)gi * n);
+        const __half *sp = scale_base + (size_t)gi * n;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) b.sc[q] = sp[q];
+        for (int r = 0; r < 4; ++r) {
+            b.sc[r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r]);
+            b.sc[4 + r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r] + 16);
+        }
         cur += nb;
     };
     auto consume = [&](const W4Batch<U> &b) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {             // slots past the end of a run multiply by zero
-            F::fma(gacc, b.v[u], b.xv[u]);
-            xsum += b.xv[u];
-        }
-        if (!b.ends_run) return;
-        // sum x*q = scale * sum x*v - 8 sum x; then times the group's scale
-        const float corr = -F::kOffset * xsum;
+            unsigned nib[2][4], B[2][2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const unsigned sw[4] = {b.sc[q].x, b.sc[q].y, b.sc[q].z, b.sc[q].w};
+            for (int q = 0; q < 4; ++q) {
+                nib[0][q] = (b.v[u][q] << 4) & 0xF0F0F0F0u;
+                nib[1][q] = b.v[u][q] & 0xF0F0F0F0u;
+            }
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                const __half2 sh = *reinterpret_cast<const __half2 *>(&sw[h]);
-                const float q0 = fmaf(gacc[8 * q + 2 * h], F::kScaleEven, corr);
-                const float q1 = fmaf(gacc[8 * q + 2 * h + 1], F::kScaleOdd, corr);
-                acc[8 * q + 2 * h] = fmaf(__low2float(sh), q0, acc[8 * q + 2 * h]);
-                acc[8 * q + 2 * h + 1] = fmaf(__high2float(sh), q1, acc[8 * q + 2 * h + 1]);
-                gacc[8 * q + 2 * h] = 0.f;
-                gacc[8 * q + 2 * h + 1] = 0.f;
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    B[p][q] = __builtin_amdgcn_perm((unsigned)b.x[u], (unsigned)b.x[u], pick[p][q]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int q = k >> 2, h = (k >> 1) & 1, p = k & 1;
+                sums.v[q][h][p] = mfma_i8(nib[q][2 * h], nib[q][2 * h + 1], B[p][0], B[p][1],
+                                          sums.v[q][h][p]);
             }
         }
-        xsum = 0.f;
+        if (!b.ends_run) return;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const __half2 sc = __builtin_bit_cast(__half2, b.sc[4 * h + r]);
+                // the digits of p = 1 weigh 2^16 more
+                const float lo = fmaf((float)sums.v[0][h][1][r], 65536.f, (float)sums.v[0][h][0][r]);
+                const float hi = fmaf((float)sums.v[1][h][1][r], 65536.f, (float)sums.v[1][h][0][r]);
+                acc[h][0][r] = fmaf(__low2float(sc), lo, acc[h][0][r]);
+                acc[h][1][r] = fmaf(__high2float(sc), hi, acc[h][1][r]);
+            }
+        sums.clear();
     };
 
     // Two batches in flight.  The fences keep the compiler from sinking a batch's loads into
-    // the consumption of the batch before it.  (A third batch in flight was measured slower:
-    // the row stream of this format is held back by its vector instructions, about 2.2 per
-    // weight with the addressing, issued by two wavefronts per SIMD -- the older of the two
-    // finishes its share 4-5 us before the younger -- not by the loads in flight.)
+    // the consumption of the batch before it.  (A third batch in flight was measured 2 to 6 %
+    // slower.)
     if (mine > 0) {                               // wavefront-uniform
         W4Batch<U> b0, b1;
         issue(b0);
@@ -246,9 +315,30 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     }
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
-    store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
-    return block_finish<F, LPR, WAVES>(red, partial, counter, y, tile, col0, tile_cols, s, splits,
-                                       n, a, cnt, report);
+    // The digits of a column sit 8 lanes apart; both lanes form the sum, and the lanes with
+    // l < 8 write the first half of a chunk, the others the second.
+    const bool finite = largest < 0x7F800000u;
+    const float unit = !finite ? __uint_as_float(0x7FC00000u)
+                       : largest ? FixedDigits::power_of_two(-FixedDigits::shift(largest)) : 0.f;
+    const float mine_unit = 0.0625f * (l < 8 ? unit : 256.f * unit);
+    float *row = red + share * combine_row<EPL, LPR> + part * PART_COLS;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float v[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float own = acc[h][q][r] * mine_unit;
+                v[h][q] = own + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(
+                                    0, (int)__float_as_uint(own), 0x128 /* row_ror:8 */, 0xF, 0xF,
+                                    false));
+            }
+        *reinterpret_cast<float2 *>(row + EPL * (4 * g + r) + (l < 8 ? 0 : 16) + 2 * (l & 7)) =
+            l < 8 ? make_float2(v[0][0], v[0][1]) : make_float2(v[1][0], v[1][1]);
+    }
+    return block_finish<F, LPR, WAVES, SHARES>(red, partial, counter, y, tile, col0, tile_cols, s,
+                                               splits, n, a, cnt, report);
 }
 
 template <int LPR, int WAVES, int U>
@@ -272,6 +362,7 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_swiglu_kernel(
     float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
+    trace_mark(0);
     const int tile = blockIdx.x % tiles;
     w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
                             tile_counter(counters, tile, tiles), y, m, n, ks, tile,
@@ -286,6 +377,7 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
                                                float *partial, int *counters, int m, int ks,
                                                int tile_cols, int splits, int block)
 {
+    trace_mark(0);
     const int tiles = ma.tile_begin[ma.count];
     const int gtile = block % tiles;
     const int s = block / tiles;
@@ -302,6 +394,7 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
                             tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
                             gtile - ma.tile_begin[k], s, tile_cols, splits,
                             survivor_report(counters, k, splits));
+    trace_mark(6);
 }
 
 template <int LPR, int WAVES, int U>

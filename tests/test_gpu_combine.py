@@ -32,3 +32,64 @@ def test_counters_with_a_line_each_and_packed(T, tiles):   # noqa: F811
         assert rel_l2(y, want) <= TIGHT and survivors(T, ws) == [kept]
         y = run_bf16(T, wt2, x2, t2, 2048, 1032, ws)
         assert rel_l2(y, want2) <= TIGHT and survivors(T, ws) == [kept2]
+
+
+def w4_case(n, m, seed):
+    q, scale = ti.quantize_w4(ti.weights_bf16(n, m, seed))
+    b = q.view(np.int8)
+    lo, hi = (b << 4).astype(np.int8) >> 4, b >> 4
+    w = np.stack([lo, hi], axis=2).reshape(m, n).astype(np.float64)
+    w *= np.repeat(scale.astype(np.float64), 128, axis=0)
+    return dev(q), dev(scale), w
+
+
+@pytest.mark.parametrize("kind", ["mixed range", "subnormal", "one", "equal", "large", "ends"])
+@pytest.mark.parametrize("m,n", [(128, 32), (512, 544), (1152, 1056), (4096, 1024), (2048, 28672)])
+def test_w4_integer_activations(T, kind, m, n):   # noqa: F811
+    """The int4 kernel's activations are integers in units of the slice's largest: values over all
+    of fp16's range, subnormals alone, a single survivor, equal values, and survivors only at the
+    ends of the 128-channel groups; slices of one and of several passes, both tile widths."""
+    rng = np.random.default_rng(m + n)
+    q, scale, w = w4_case(n, m, 9900 + m + n)
+    x = rng.standard_normal(m)
+    t = 0.5
+    if kind == "mixed range":
+        x, t = np.sign(x) * 2.0 ** rng.uniform(-24, 15.9, m), 0.0
+    elif kind == "subnormal":
+        x, t = x * 2.0 ** -18, 2.0 ** -18
+    elif kind == "one":
+        x = np.zeros(m)
+        x[m - 1] = -3.0
+    elif kind == "equal":
+        x = np.full(m, 0.50048828125)
+    elif kind == "large":
+        x, t = x * 20000, 9000.0
+        x = np.clip(x, -65504, 65504)
+    else:
+        x = np.zeros(m)
+        x[0::128], x[127::128] = 1.5, -2.5
+    x = x.astype(np.float16)
+    kept = np.abs(x.astype(np.float32)) > np.float32(t)
+    xk = np.where(kept, x, 0).astype(np.float64)
+    y = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    T.check(T.teal_sparse_gemv_w4(q, scale, 128, dev(x), t, y, m, n, ws))
+    torch.cuda.synchronize()
+    assert survivors(T, ws) == [int(kept.sum())]
+    # the integers are within 2^-31 of the largest activation's power of two, and the group sums
+    # are added in fp32
+    bound = (2.0 ** -30 * np.abs(xk).max() * np.abs(w[kept]).sum(0) +
+             (2 + m / 128) * 2.0 ** -24 * (np.abs(xk)[:, None] * np.abs(w)).sum(0))
+    assert np.all(np.abs(y.cpu().numpy() - xk @ w) <= bound)
+
+
+def test_w4_infinite_activation_gives_nan(T):   # noqa: F811
+    m, n = 1024, 512
+    q, scale, _ = w4_case(n, m, 9950)
+    x = np.ones(m, np.float16)
+    x[700] = -np.inf
+    y = torch.zeros(n, dtype=torch.float32, device="cuda")
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    T.check(T.teal_sparse_gemv_w4(q, scale, 128, dev(x), 0.5, y, m, n, ws))
+    torch.cuda.synchronize()
+    assert torch.isnan(y).all()
