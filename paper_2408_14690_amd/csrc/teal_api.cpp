@@ -28,6 +28,26 @@ int max_splits_for(int m)
     return forced > teal::kMaxSplits ? forced : teal::kMaxSplits;
 }
 
+// Rows whose length is no multiple of 128 bytes (`unit` elements) do not begin on cache lines, and
+// every tile fetches the two lines at its ends with its neighbours.  Tiles of at least 512 bytes
+// of a row, with up to 16 splits, then cost less than the 256 bytes x 8 splits of aligned rows,
+// provided that they still fill the chip: at least 12 such tiles and inputs long enough for the
+// splits (bf16, us per call: 5000 -> 3416 at 25 % 10.1 -> 9.2, 6000 -> 5000 10.8 -> 10.0, q + k + v of
+// a 4664-wide block 13.7 -> 12.5; below the line 2104 -> 1800 would take 6.1 instead of 5.6 and
+// 8000 -> 600 7.9 instead of 6.8).  Not for int4, whose narrowest tile has 512 columns (5120 -> 3200
+// 10.1 instead of 8.1).
+bool wide_tiles(int m, const int *n, const int *row_pitch, int count, int elems_per_lane)
+{
+    const int unit = 8 * elems_per_lane;
+    long long tiles = 0;
+    bool off_lines = false;
+    for (int k = 0; k < count; ++k) {
+        off_lines |= (row_pitch ? row_pitch[k] : n[k]) % unit != 0;
+        tiles += (n[k] + 4 * unit - 1) / (4 * unit);
+    }
+    return off_lines && elems_per_lane < 32 && m >= 2560 && tiles >= 12;
+}
+
 // Launch shape for one GEMV, from sweeps on MI355X.  A call costs a fixed latency
 // chain (load x, compact, first weight rows), the row stream, and with split-K
 // (Section 4.4) the publish / ticket / second-pass chain, which grows with the
@@ -37,13 +57,14 @@ int max_splits_for(int m)
 // (c) a block's row segment is 256 B .. 1 KiB and starts on a 128-byte boundary
 // (or neighbouring blocks would each fetch the cache line they share).
 GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_lanes,
-                     int ks_multiple, int max_slice = teal::kMaxSlice)
+                     int ks_multiple, int max_slice = teal::kMaxSlice, const int *row_pitch = nullptr)
 {
     const int tc_min = min_lanes * elems_per_lane, tc_max = max_lanes * elems_per_lane;
     const int unit = 8 * elems_per_lane;                       // 128 bytes of a row
     int tc = (n + 31) / 32;                                    // 32 tiles x 8 splits = 256 blocks
     tc = (tc + unit - 1) / unit * unit;
     if (tc < tc_min) tc = tc_min;
+    if (tc < 4 * unit && wide_tiles(m, &n, row_pitch, 1, elems_per_lane)) tc = 4 * unit;
     if (tc > tc_max) tc = tc_max;
     const int tiles = (n + tc - 1) / tc;
     int splits = 8;
@@ -79,12 +100,16 @@ GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_la
 // and a slight preference for wider row segments.  For one matrix this reproduces the
 // choices of auto_shape above.
 GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
-                           int max_lanes, int ks_multiple, int max_slice = teal::kMaxSlice)
+                           int max_lanes, int ks_multiple, int max_slice = teal::kMaxSlice,
+                           const int *row_pitch = nullptr)
 {
     long long n_total = 0;
     for (int k = 0; k < count; ++k) n_total += n[k];
-    const int tc_min = min_lanes * elems_per_lane, tc_max = max_lanes * elems_per_lane;
     const int unit = 8 * elems_per_lane;
+    const bool wide = wide_tiles(m, n, row_pitch, count, elems_per_lane);
+    const int tc_max = max_lanes * elems_per_lane;
+    int tc_min = min_lanes * elems_per_lane;
+    if (wide && tc_min < 4 * unit) tc_min = tc_max < 4 * unit ? tc_max : 4 * unit;
     double best = -1.0;
     int best_tc = tc_min, best_splits = 1;
     for (int tc = tc_min; tc <= tc_max; tc += unit) {
@@ -98,7 +123,7 @@ GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, i
             const int s = (m + ks - 1) / ks;
             if (tiles * s > kComputeUnits) continue;
             double score = (double)n_total * m / ((double)kComputeUnits * tc * ks);
-            for (int e = 8; e < s; ++e) score *= 0.97;
+            for (int e = wide ? 16 : 8; e < s; ++e) score *= 0.97;
             score *= 1.0 + 0.00002 * tc;
             if (score > best) {
                 best = score;
@@ -180,8 +205,10 @@ GemvShape auto_shape_multi_pitch(int m, const int *n, const int *row_pitch, int 
     }
     int n_total = 0;
     for (int k = 0; k < count; ++k) n_total += n[k];
-    return count > 1 ? auto_shape_multi(m, n, count, elems_per_lane, min_lanes, max_lanes, ks_multiple)
-                     : auto_shape(m, n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple);
+    return count > 1 ? auto_shape_multi(m, n, count, elems_per_lane, min_lanes, max_lanes, ks_multiple,
+                                        teal::kMaxSlice, row_pitch)
+                     : auto_shape(m, n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple,
+                                  teal::kMaxSlice, row_pitch);
 }
 
 // Launch shape of a batched call: tiles of at most 128 columns (16 lanes of 8).  A block takes up

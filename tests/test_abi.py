@@ -816,3 +816,23 @@ def test_a_recording_does_not_swallow_other_threads_calls():
     th.join()
     assert seen == [T.TEAL_ERR_THRESHOLD]                 # executed, not recorded
     assert run() == T.TEAL_ERR_THRESHOLD                  # only the recording thread's call
+
+
+def test_plans_widen_tiles_where_rows_lie_off_cache_lines():
+    """Rows that are no multiple of 128 bytes get tiles of at least 512 bytes with up to 16 splits
+    where those fill the chip (12 tiles, 2560 input channels), also in groups; aligned rows,
+    aligned pitches, int4 and the sizes below the line keep the narrow tiles."""
+    for bits, e in ((16, 8), (8, 16)):
+        off, on = 3000 * 16 // bits // e * e, 3072 * 16 // bits
+        st, p = T.teal_gemv_plan(bits, 3000, off)
+        assert st == 0 and p["tile_cols"] * bits // 8 >= 512 and 8 < p["splits"] <= 16
+        st, p = T.teal_gemv_plan(bits, 3000, on)
+        assert st == 0 and p["tile_cols"] * bits // 8 < 512
+        assert T.teal_gemv_plan(bits, 2504, off)[1]["tile_cols"] * bits // 8 < 512
+        st, p = T.teal_gemv_plan_multi(bits, 4656, [4656, 1152, 1168])
+        assert st == 0 and p["tile_cols"] * bits // 8 >= 512
+    assert T.teal_gemv_plan(16, 8000, 600)[1]["tile_cols"] == 128
+    assert T.teal_gemv_plan(4, 5120, 3200)[1]["tile_cols"] == 512
+    narrow = T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3008 + 64])[1]
+    assert narrow["tile_cols"] == 128 and T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3008])[1] == narrow
+    assert T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3016])[1] == T.teal_gemv_plan(16, 3000, 3000)[1]
