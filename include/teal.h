@@ -609,8 +609,8 @@ teal_status teal_histogram_thresholds(const uint64_t *hist, const double *p, int
  * teal_sparse_gemv_bf16_batch_ex: the same with a caller-chosen launch shape
  * (0 = library's choice): lanes_per_row 64, 32 or 16 with
  * lanes_per_row * B <= 256, B = batch rounded up to 2, 4 or 8; tile_cols a
- * multiple of 8, at most 8 * lanes_per_row (tiles wider than 128 columns are
- * run as tiles of 128); splits such that a block's slice,
+ * multiple of 8, at most 8 * lanes_per_row (from three rows on, tiles wider
+ * than 128 columns are run as tiles of 128); splits such that a block's slice,
  * ceil(m / splits) rounded up to 64, is at most 2048 channels.
  *
  * teal_sparse_gemv_bf16_batch_multi: count (1..4) matrices that read the same

@@ -15,6 +15,12 @@
 // Llama-3-8B-shaped block at 50 %, 8 rows: 81.0 us with FMAs, 58.9 us this way (220 MB: 3.7 TB/s;
 // one vector 52 us).  The row stream is bound by HBM; what remains above it is the compaction of 8
 // activation vectors by every block (1.4 us at 512 channels, 3.4 us at 4096) and the combine.
+//
+// At one and two rows up to 4 wavefronts lie side by side over a tile of up to 512 columns (PARTS):
+// with the narrow tile alone 2 rows of large matrices were slower than with FMAs in wide tiles
+// (us per block, FMAs / narrow / now: 70B shape 156 / 167 / 153, 13B 76 / 82 / 72, ragged 4664-wide
+// 71 / 81 / 67; 4096 -> 50264 40.1 / 55.0 / 41.7, whose unaligned rows cost more in pieces of 256
+// bytes).  From three rows on the narrow tile is ahead of the FMAs at every size.
 #include "gemv_common.h"
 
 namespace teal {
@@ -68,7 +74,7 @@ __device__ __forceinline__ unsigned long long ballot_batch(const unsigned (&pair
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Rows one matrix instruction takes (K), and the output columns of a block: 16 lanes share a
+// Rows one matrix instruction takes (K), and the output columns of a wavefront: 16 lanes share a
 // weight row, 8 columns each; the four groups of 16 lanes hold different rows.
 constexpr int kChunkRows = 32;
 constexpr int kBatchTile = 128;
@@ -81,10 +87,10 @@ constexpr int kActBytes = 16;
 
 // Rows of one wavefront: equal contiguous shares, in multiples of the 4 rows that one
 // wavefront load covers.
-template <int WAVES>
+template <int SHARES>
 __device__ __forceinline__ int batch_share_rows(int cnt)
 {
-    return 4 * ((cnt + 4 * WAVES - 1) / (4 * WAVES));
+    return 4 * ((cnt + 4 * SHARES - 1) / (4 * SHARES));
 }
 
 // compact_slice for a batch: list_idx[] receives the surviving channels of [k0, k1) in
@@ -328,17 +334,18 @@ __device__ __forceinline__ float2 load_coherent2(const float *p)        // 8-byt
 }
 
 // block_finish for a batch.  red[] (WAVES x kBatchRedWave floats) lies over the list,
-// which is dead once every wavefront has left the row stream.  A thread owns two neighbouring
-// columns of one batch row.  Partial rows are laid out [split][batch row][n]; the block that
+// which is dead once every wavefront has left the row stream.  Wavefront w holds sums of part
+// w % PARTS of the tile's columns.  A thread owns two neighbouring columns of one batch row.  Partial rows are laid out [split][batch row][n]; the block that
 // arrives last at the tile's counter adds them in split order and writes Y.
-template <int NB, int WAVES>
+template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *red,
                                                    float *partial, int *counter, float *Y,
                                                    int tile, int col0, int cols, int s, int splits,
                                                    int n, int batch, int cnt, int w,
                                                    const SurvivorReport &report)
 {
-    static_assert(NB * kBatchTile / 2 <= WAVES * 64, "one pair of columns per thread");
+    constexpr int PAIRS = PARTS * kBatchTile / 2;
+    static_assert(NB * PAIRS <= WAVES * 64, "one pair of columns per thread");
     __shared__ int last_flag;
     const int thread = w * 64 + lanes_below(~0ull);
     if (cols > n - col0) cols = n - col0;
@@ -346,18 +353,19 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     batch_sums_to_lds(acc, red, w);
     __syncthreads();
     trace_mark(7);
-    const int bb = thread / (kBatchTile / 2);
-    const int c = 2 * (thread % (kBatchTile / 2));
+    const int bb = thread / PAIRS;
+    const int c = 2 * (thread % PAIRS);
     const bool owner = bb < batch && c < cols;          // cols is a multiple of 8
     float2 sum = make_float2(0.f, 0.f);
     if (owner) {
         // The high parts of all wavefronts, then the low ones.  Where the high sum is not
         // finite it is the result: an infinite weight or activation makes it infinite or a NaN,
         // as the product is, and the low part a NaN.
-        const float *hi = red + bb * kBatchRedRow + c, *lo = hi + 8 * kBatchRedRow;
+        const float *hi = red + c / kBatchTile * kBatchRedWave + bb * kBatchRedRow + c % kBatchTile;
+        const float *lo = hi + 8 * kBatchRedRow;
         float2 h = make_float2(0.f, 0.f), l = h;
 #pragma unroll
-        for (int q = 0; q < WAVES; ++q) {
+        for (int q = 0; q < WAVES; q += PARTS) {
             const float2 a = *reinterpret_cast<const float2 *>(hi + q * kBatchRedWave);
             const float2 b = *reinterpret_cast<const float2 *>(lo + q * kBatchRedWave);
             h.x += a.x; h.y += a.y;
@@ -411,8 +419,9 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     store_coherent(y + 1, sum.y);
 }
 
-// Work of one block: output tile `tile` x K-slice `s` of one matrix, all batch rows.
-template <int NB, int WAVES>
+// Work of one block: output tile `tile` x K-slice `s` of one matrix, all batch rows.  The tile has
+// up to PARTS x kBatchTile columns; PARTS wavefronts side by side share their rows.
+template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void batch_block(const void *__restrict__ W,
                                             const __half *__restrict__ X, int batch, double bound,
                                             float *partial, int *counter, float *Y, int m, int n,
@@ -445,12 +454,13 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
 
     trace_mark(2);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int share = batch_share_rows<WAVES>(cnt);
-    const int start = w * share;
+    const int share = batch_share_rows<WAVES / PARTS>(cnt);
+    const int start = w / PARTS * share;
     const int mine = min(max(cnt - start, 0), share);
 
     const int col0 = tile * tile_cols;
-    const int col = lane_column<8>(col0, tile_cols, n, threadIdx.x & 15);
+    const int part0 = w % PARTS * kBatchTile;      // lanes past the tile's edge re-read its last columns
+    const int col = lane_column<8>(col0 + part0, min(tile_cols - part0, kBatchTile), n, threadIdx.x & 15);
     const unsigned row_bytes = (unsigned)n * 2u;
     const unsigned char *lane_base = static_cast<const unsigned char *>(W) + (size_t)col * 2;
 
@@ -460,21 +470,21 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     stream_rows_batch(acc, list_idx, start, mine, smem, lane_base, row_bytes);
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
-    block_finish_batch<NB, WAVES>(acc, red, partial, counter, Y, tile, col0, tile_cols, s, splits,
+    block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, counter, Y, tile, col0, tile_cols, s, splits,
                                   n, batch, cnt, w, report);
     trace_mark(6);
 }
 
 // 4 wavefronts per SIMD (at most 128 registers): two blocks share a unit, so that one's compaction
 // and combine lie under the other's row stream where there are more blocks than units.
-template <int NB, int WAVES>
+template <int NB, int WAVES, int PARTS>
 __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_kernel(
     const void *__restrict__ W, const __half *__restrict__ X, int batch, double bound,
     float *partial, int *counters, float *Y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
     const int tile = blockIdx.x % tiles;
-    batch_block<NB, WAVES>(W, X, batch, bound, partial, tile_counter(counters, tile, tiles), Y, m,
+    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial, tile_counter(counters, tile, tiles), Y, m,
                            n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
                            survivor_report(counters, 0, splits));
 }
@@ -491,7 +501,7 @@ struct BatchMultiArgs {
     int count;
 };
 
-template <int NB, int WAVES>
+template <int NB, int WAVES, int PARTS>
 __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
     BatchMultiArgs ma, const __half *__restrict__ X, int batch, float *partial, int *counters,
     int m, int ks, int tile_cols, int splits)
@@ -508,7 +518,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
             k = j;
         }
     }
-    batch_block<NB, WAVES>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
+    batch_block<NB, WAVES, PARTS>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
                            tile_counter(counters, gtile, tiles), ma.Y[k], m, ma.n[k], ks,
                            gtile - ma.tile_begin[k], s, tile_cols, splits,
                            survivor_report(counters, k, splits));
@@ -671,18 +681,20 @@ bool gemv_batch_shape_supported(int batch, const GemvShape &s)
     const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
     const bool lpr = s.lanes_per_row == 64 || s.lanes_per_row == 32 || s.lanes_per_row == 16;
     const bool tc = s.tile_cols >= 0 && s.tile_cols % 8 == 0 && s.tile_cols <= s.lanes_per_row * 8;
-    // (the limit of the documented interface; tiles wider than kBatchTile run in that width)
+    // (the limit of the documented interface; see batch_tile for the width a launch runs in)
     const bool fits = nb * s.lanes_per_row <= 256;
     return lpr && tc && fits && s.waves == kBatchWaves && s.unroll == kBatchUnroll &&
            s.splits >= 1;
 }
 
-// A block's tile is at most kBatchTile columns wide; a wider request runs in tiles of that width.
-static GemvShape batch_tile(GemvShape sh)
+// At one or two rows a block takes tiles of up to 512 columns, else of at most kBatchTile; a wider
+// request runs in tiles of that width.
+static GemvShape batch_tile(int batch, GemvShape sh)
 {
-    const int asked = sh.tile_cols > 0 ? sh.tile_cols : sh.lanes_per_row * 8;
+    if (sh.tile_cols <= 0) sh.tile_cols = sh.lanes_per_row * 8;
+    if (batch <= 2) return sh;
     sh.lanes_per_row = 16;
-    sh.tile_cols = asked < kBatchTile ? asked : kBatchTile;
+    if (sh.tile_cols > kBatchTile) sh.tile_cols = kBatchTile;
     return sh;
 }
 
@@ -700,23 +712,25 @@ hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, 
                                   const GemvShape &sh, hipStream_t stream)
 {
     if (!gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
-    const GemvGeometry g = gemv_geometry(m, n, batch_tile(sh), 8, 64);
+    const GemvGeometry g = gemv_geometry(m, n, batch_tile(batch, sh), 8, 64);
     if (g.ks > kMaxLongSliceBatch) return hipErrorInvalidValue;
-    const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
+    const int lanes = batch_tile(batch, sh).lanes_per_row;
     const size_t lds = batch_lds(g.ks);
     const double bound = (double)batch * (double)t;
     const __half *X = static_cast<const __half *>(X_f16);
-#define TEAL_LAUNCH_B(NB)                                                                        \
+#define TEAL_LAUNCH_B(NB, PARTS)                                                                        \
     do {                                                                                         \
-        if (!allow_large_lds(sparse_gemv_batch_kernel<NB, kBatchWaves>, lds))                    \
+        if (!allow_large_lds(sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>, lds))                    \
             return hipErrorInvalidValue;                                                         \
-        hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves>), dim3(g.tiles * g.splits), \
+        hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>), dim3(g.tiles * g.splits), \
                            dim3(kBatchWaves * 64), lds, stream, Wt, X, batch, bound, partial,    \
                            counters, Y, m, n, g.ks, g.tiles, g.tile_cols, g.splits);             \
     } while (0)
-    if (nb == 2) TEAL_LAUNCH_B(2);
-    else if (nb == 4) TEAL_LAUNCH_B(4);
-    else TEAL_LAUNCH_B(8);
+    if (batch > 4) TEAL_LAUNCH_B(8, 1);
+    else if (batch > 2) TEAL_LAUNCH_B(4, 1);
+    else if (lanes == 64) TEAL_LAUNCH_B(2, 4);
+    else if (lanes == 32) TEAL_LAUNCH_B(2, 2);
+    else TEAL_LAUNCH_B(2, 1);
 #undef TEAL_LAUNCH_B
     return hipGetLastError();
 }
@@ -729,9 +743,9 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
     int n_max = 0;
     for (int k = 0; k < count; ++k) n_max = n[k] > n_max ? n[k] : n_max;
     if (!gemv_batch_shape_supported(batch, sh)) return hipErrorInvalidValue;
-    const GemvGeometry g = gemv_geometry(m, n_max, batch_tile(sh), 8, 64);
+    const GemvGeometry g = gemv_geometry(m, n_max, batch_tile(batch, sh), 8, 64);
     if (g.ks > kMaxLongSliceBatch) return hipErrorInvalidValue;
-    const int nb = batch <= 2 ? 2 : batch <= 4 ? 4 : 8;
+    const int lanes = batch_tile(batch, sh).lanes_per_row;
     const size_t lds = batch_lds(g.ks);
     BatchMultiArgs ma{};
     ma.count = count;
@@ -745,17 +759,19 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
     }
     const int tiles = ma.tile_begin[count];
     const __half *X = static_cast<const __half *>(X_f16);
-#define TEAL_LAUNCH_BM(NB)                                                                       \
+#define TEAL_LAUNCH_BM(NB, PARTS)                                                                       \
     do {                                                                                         \
-        if (!allow_large_lds(sparse_gemv_batch_multi_kernel<NB, kBatchWaves>, lds))              \
+        if (!allow_large_lds(sparse_gemv_batch_multi_kernel<NB, kBatchWaves, PARTS>, lds))              \
             return hipErrorInvalidValue;                                                         \
-        hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, kBatchWaves>),                    \
+        hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, kBatchWaves, PARTS>),                    \
                            dim3(tiles * g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,   \
                            batch, partial, counters, m, g.ks, g.tile_cols, g.splits);            \
     } while (0)
-    if (nb == 2) TEAL_LAUNCH_BM(2);
-    else if (nb == 4) TEAL_LAUNCH_BM(4);
-    else TEAL_LAUNCH_BM(8);
+    if (batch > 4) TEAL_LAUNCH_BM(8, 1);
+    else if (batch > 2) TEAL_LAUNCH_BM(4, 1);
+    else if (lanes == 64) TEAL_LAUNCH_BM(2, 4);
+    else if (lanes == 32) TEAL_LAUNCH_BM(2, 2);
+    else TEAL_LAUNCH_BM(2, 1);
 #undef TEAL_LAUNCH_BM
     return hipGetLastError();
 }

@@ -211,22 +211,52 @@ GemvShape auto_shape_multi_pitch(int m, const int *n, const int *row_pitch, int 
                                   teal::kMaxSlice, row_pitch);
 }
 
+// What a batched call in this shape is expected to take, in weights a compute unit streams (27
+// thousand a microsecond at 50 %): the unit's average share and a quarter of what the fullest unit has
+// beyond it, 1/16 more for 256-byte pieces of a row, 0.1 us per split and 1 us for having any.
+double batch_cost(const GemvShape &sh, int m, const int *n, int count)
+{
+    int ks = (m + sh.splits - 1) / sh.splits;
+    ks = (ks + 63) / 64 * 64;
+    long long blocks = 0;
+    double weights = 0.0;
+    for (int k = 0; k < count; ++k) {
+        blocks += (long long)((n[k] + sh.tile_cols - 1) / sh.tile_cols) * sh.splits;
+        weights += (double)n[k] * m;
+    }
+    const double rounds = (double)((blocks + kComputeUnits - 1) / kComputeUnits);
+    const double mean = weights / kComputeUnits, most = rounds * ks * sh.tile_cols;
+    double cost = 0.75 * mean + 0.25 * most;
+    if (sh.tile_cols <= 128) cost *= 17.0 / 16.0;
+    return cost + 2700.0 * sh.splits + (sh.splits > 1 ? 27000.0 : 0.0);
+}
+
 // Launch shape of a batched call: tiles of at most 128 columns (16 lanes of 8).  A block takes up
 // to kMaxSliceBatch channels (two blocks share a unit's LDS), or all of up to kMaxLongSliceBatch
 // where the tiles alone then make about one block per unit: no split-K, and no second round
 // of blocks on a part of the units (Llama-3-8B gate + up at 8 rows: 28.7 us as 448 blocks in 2
-// splits, 25.3 us as 224 blocks without split-K).
-GemvShape auto_shape_batch(int m, const int *n, int count)
+// splits, 25.3 us as 224 blocks without split-K; between 160 and 256 tiles and 2112 and 4096
+// channels 6 to 14 % faster, with more tiles up to 17 % slower).
+// One or two rows may also have tiles of up to 512 columns: a block compacts a slice once for more of
+// a matrix and reads longer pieces of a row.  2 rows, 128 columns or 512: 8192 -> 2 x 28672 81.6 or
+// 77.3 us, 4096 -> 51200 44.1 or 36.8, but 2048 -> 2 x 8192 10.8 or 12.4 (2 splits instead of 8)
+// and 6656 -> 2 x 17920 46.3 or 52.0 (280 blocks).  The cheaper of the two.
+GemvShape auto_shape_batch(int m, const int *n, int count, int batch)
 {
     long long tiles = 0, n_total = 0;
     for (int k = 0; k < count; ++k) {
         tiles += (n[k] + 127) / 128;
         n_total += n[k];
     }
-    const int slice = tiles >= 160 && tiles <= kComputeUnits && m <= teal::kMaxLongSliceBatch
-                          ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch;
-    return count > 1 ? auto_shape_multi(m, n, count, 8, 16, 16, 64, slice)
-                     : auto_shape(m, (int)n_total, 8, 16, 16, 64, slice);
+    const auto shape = [&](int max_lanes, int max_slice) {
+        return count > 1 ? auto_shape_multi(m, n, count, 8, 16, max_lanes, 64, max_slice)
+                         : auto_shape(m, (int)n_total, 8, 16, max_lanes, 64, max_slice);
+    };
+    const bool whole = tiles >= 160 && tiles <= kComputeUnits && m <= teal::kMaxLongSliceBatch;
+    const GemvShape narrow = shape(16, whole ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch);
+    if (batch > 2) return narrow;
+    const GemvShape wide = shape(64, teal::kMaxSliceBatch);
+    return batch_cost(narrow, m, n, count) < batch_cost(wide, m, n, count) ? narrow : wide;
 }
 
 // Partial rows a batched call may need: one per (split, batch row).
@@ -532,7 +562,7 @@ teal_status teal_sparse_gemv_bf16_batch_multi(int count, const void *const *Wt_b
         if (!threshold_ok(t[k])) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes_batch(m, (int)n_total, batch))
         return TEAL_ERR_WORKSPACE;
-    const GemvShape sh = auto_shape_batch(m, n, count);
+    const GemvShape sh = auto_shape_batch(m, n, count, batch);
     if (!teal::gemv_batch_shape_supported(batch, sh)) return TEAL_ERR_UNSUPPORTED;
     return from_hip(teal::launch_gemv_bf16_batch_multi(count, Wt_bf16, t, Y, n, X_f16, batch, m,
                                                        ws_partials(workspace, m),
@@ -829,7 +859,7 @@ teal_status teal_sparse_gemv_bf16_batch_ex(const void *Wt_bf16, const void *X_f1
         return TEAL_ERR_ALIGN;
     if (!threshold_ok(t)) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes_batch(m, n, batch)) return TEAL_ERR_WORKSPACE;
-    GemvShape sh = auto_shape_batch(m, &n, 1);
+    GemvShape sh = auto_shape_batch(m, &n, 1, batch);
     const bool own_shape = !lanes_per_row && !tile_cols && !splits;
     if (lanes_per_row) {
         sh.lanes_per_row = lanes_per_row;

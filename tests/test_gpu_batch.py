@@ -295,3 +295,53 @@ def test_batch_matrix_core_edges(T, batch, m, n, kept):
             err = np.abs(got[b][fin[b]] - want[b][fin[b]])
             assert np.all(err <= 2 * kept * 2.0 ** -24 * mag), (b, float((err / mag).max()))
     assert special or not inf.any()
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("m,n,kept,lanes,tile_cols", [
+    (64, 8, 1, 64, 0), (130, 264, 9, 32, 136), (512, 520, 33, 64, 0), (513, 1040, 257, 64, 392),
+    (1028, 1288, 700, 32, 0), (2052, 1032, 1100, 64, 512), (4097, 2056, 2050, 32, 248)])
+def test_batch_wide_tiles(T, batch, m, n, kept, lanes, tile_cols):
+    """One and two rows in tiles of up to 256 and 512 columns: 2 or 4 wavefronts side by side, a share
+    of the rows for each group of them; tiles that end inside a wavefront's columns, wavefronts past
+    the edge, a single survivor; infinite weights and activations stay in their column and row."""
+    rng = np.random.default_rng(1000 * batch + m + n)
+    X = (rng.standard_normal((batch, m)) * 0.01).astype(np.float16)
+    keep = np.sort(rng.choice(m, kept, replace=False))
+    X[:, keep] = (np.sign(rng.standard_normal((batch, kept))) *
+                  (1.0 + rng.random((batch, kept)) * 60)).astype(np.float16)
+    w = ti.f32_to_bf16_bits((rng.standard_normal((m, n)) * 0.02).astype(np.float32))
+    if kept > 2:
+        w[keep[-1], 1], w[keep[0], n - 2] = 0x7F80, 0xFF80
+    wf = ti.bf16_bits_to_f32(w).astype(np.float64)
+    want = np.stack([(X[b, keep].astype(np.float64)[:, None] * wf[keep]).sum(0) for b in range(batch)])
+    mag = np.stack([(np.abs(X[b, keep].astype(np.float64))[:, None] * np.abs(wf[keep])).sum(0)
+                    for b in range(batch)])
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, n, batch), dtype=torch.uint8, device="cuda")
+    off = T.teal_survivors_offset()
+    for splits in (3, 16):
+        got = run_batch(T, dev(w), X, 0.5, m, n, ws, lanes_per_row=lanes, tile_cols=tile_cols, splits=splits)
+        assert ws[off:off + 4].view(torch.int32).item() == kept
+        fin = np.isfinite(want)
+        assert np.array_equal(got[~fin], want[~fin])
+        # 32-bit sums of exact products: kept * 2^-24 of the sum of magnitudes bounds any order
+        assert np.all(np.abs(got[fin] - want[fin]) <= 2 * kept * 2.0 ** -24 * mag[fin])
+
+
+@pytest.mark.parametrize("batch,m,ns", [(2, 2048, [40960]), (1, 1100, [66048]), (2, 2504, [20488, 20488]),
+                                        (2, 700, [8200, 16392])])
+def test_batch_planned_shapes_of_wide_outputs(T, batch, m, ns):
+    """Sizes at which one and two rows are planned in tiles of up to 512 columns, singly and in a
+    group, in the default launch against the oracle."""
+    X = ti.make_X(batch, m, 40 + m, "gaussian")
+    t = ti.batch_quantile_threshold(X, 0.5)
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, sum(ns), 8), dtype=torch.uint8, device="cuda")
+    ws_host = [ti.weights_bf16(n, m, 60 + n) for n in ns]
+    wts = [dev(ti.to_input_channel_major(w)) for w in ws_host]
+    Ys = [torch.full((batch, n), float("nan"), dtype=torch.float32, device="cuda") for n in ns]
+    T.check(T.teal_sparse_gemv_bf16_batch_multi(wts, [t] * len(ns), Ys, ns, dev(X), batch, m, ws))
+    torch.cuda.synchronize()
+    for k, n in enumerate(ns):
+        want = orc.sparse_gemv_bf16_batch(ws_host[k], X, t)
+        for b in range(batch):
+            assert rel_l2(Ys[k].cpu().numpy()[b], want[b]) <= TIGHT, (k, b)
