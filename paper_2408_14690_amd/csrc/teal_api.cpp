@@ -56,15 +56,15 @@ bool wide_tiles(int m, const int *n, const int *row_pitch, int count, int elems_
 // nearly empty second round, (b) the split-K depth is about 8, at most 16, and
 // (c) a block's row segment is 256 B .. 1 KiB and starts on a 128-byte boundary
 // (or neighbouring blocks would each fetch the cache line they share).
-GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_lanes,
-                     int ks_multiple, int max_slice = teal::kMaxSlice, const int *row_pitch = nullptr)
+GemvShape shape_for(int m, int n, int elems_per_lane, int min_lanes, int max_lanes,
+                    int ks_multiple, int max_slice, bool wide)
 {
     const int tc_min = min_lanes * elems_per_lane, tc_max = max_lanes * elems_per_lane;
     const int unit = 8 * elems_per_lane;                       // 128 bytes of a row
     int tc = (n + 31) / 32;                                    // 32 tiles x 8 splits = 256 blocks
     tc = (tc + unit - 1) / unit * unit;
     if (tc < tc_min) tc = tc_min;
-    if (tc < 4 * unit && wide_tiles(m, &n, row_pitch, 1, elems_per_lane)) tc = 4 * unit;
+    if (wide && tc < 4 * unit) tc = 4 * unit;
     if (tc > tc_max) tc = tc_max;
     const int tiles = (n + tc - 1) / tc;
     int splits = 8;
@@ -98,15 +98,13 @@ GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_la
 // per compute unit is scored by how evenly it spreads the work: total work over 256 times
 // the largest block's work, with a small penalty per split beyond 8 (longer combine chain)
 // and a slight preference for wider row segments.  For one matrix this reproduces the
-// choices of auto_shape above.
-GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
-                           int max_lanes, int ks_multiple, int max_slice = teal::kMaxSlice,
-                           const int *row_pitch = nullptr)
+// choices of shape_for above.
+GemvShape shape_for_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
+                          int max_lanes, int ks_multiple, int max_slice, bool wide)
 {
     long long n_total = 0;
     for (int k = 0; k < count; ++k) n_total += n[k];
     const int unit = 8 * elems_per_lane;
-    const bool wide = wide_tiles(m, n, row_pitch, count, elems_per_lane);
     const int tc_max = max_lanes * elems_per_lane;
     int tc_min = min_lanes * elems_per_lane;
     if (wide && tc_min < 4 * unit) tc_min = tc_max < 4 * unit ? tc_max : 4 * unit;
@@ -133,8 +131,8 @@ GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, i
         }
     }
     if (best < 0.0)                    // more tiles than compute units at every width
-        return auto_shape(m, (int)n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple,
-                          max_slice);
+        return shape_for(m, (int)n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple,
+                         max_slice, wide);
     GemvShape sh;
     sh.splits = best_splits;
     sh.tile_cols = best_tc;
@@ -144,6 +142,22 @@ GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, i
     sh.waves = 8;
     sh.unroll = 4;
     return sh;
+}
+
+// The shape of a call on rows `row_pitch` elements apart (NULL: packed rows).
+GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_lanes,
+                     int ks_multiple, const int *row_pitch = nullptr)
+{
+    return shape_for(m, n, elems_per_lane, min_lanes, max_lanes, ks_multiple, teal::kMaxSlice,
+                     wide_tiles(m, &n, row_pitch, 1, elems_per_lane));
+}
+GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
+                           int max_lanes, int ks_multiple, const int *row_pitch = nullptr)
+{
+    if (count == 1)
+        return auto_shape(m, n[0], elems_per_lane, min_lanes, max_lanes, ks_multiple, row_pitch);
+    return shape_for_multi(m, n, count, elems_per_lane, min_lanes, max_lanes, ks_multiple,
+                           teal::kMaxSlice, wide_tiles(m, n, row_pitch, count, elems_per_lane));
 }
 
 // A grouped call on matrices with padded rows.  When every matrix's rows lie an odd multiple
@@ -203,12 +217,7 @@ GemvShape auto_shape_multi_pitch(int m, const int *n, const int *row_pitch, int 
             }
         }
     }
-    int n_total = 0;
-    for (int k = 0; k < count; ++k) n_total += n[k];
-    return count > 1 ? auto_shape_multi(m, n, count, elems_per_lane, min_lanes, max_lanes, ks_multiple,
-                                        teal::kMaxSlice, row_pitch)
-                     : auto_shape(m, n_total, elems_per_lane, min_lanes, max_lanes, ks_multiple,
-                                  teal::kMaxSlice, row_pitch);
+    return auto_shape_multi(m, n, count, elems_per_lane, min_lanes, max_lanes, ks_multiple, row_pitch);
 }
 
 // What a batched call in this shape is expected to take, in weights a compute unit streams (27
@@ -240,7 +249,9 @@ double batch_cost(const GemvShape &sh, int m, const int *n, int count)
 // One or two rows may also have tiles of up to 512 columns: a block compacts a slice once for more of
 // a matrix and reads longer pieces of a row.  2 rows, 128 columns or 512: 8192 -> 2 x 28672 81.6 or
 // 77.3 us, 4096 -> 51200 44.1 or 36.8, but 2048 -> 2 x 8192 10.8 or 12.4 (2 splits instead of 8)
-// and 6656 -> 2 x 17920 46.3 or 52.0 (280 blocks).  The cheaper of the two.
+// and 6656 -> 2 x 17920 46.3 or 52.0 (280 blocks).  The cheaper of the two.  (Rows off cache lines
+// widen the wide shape as for one vector, a 4664-wide block 69.0 -> 67.7 us; the narrow one has nothing
+// to widen, and more splits alone change nothing.)
 GemvShape auto_shape_batch(int m, const int *n, int count, int batch)
 {
     long long tiles = 0, n_total = 0;
@@ -248,14 +259,15 @@ GemvShape auto_shape_batch(int m, const int *n, int count, int batch)
         tiles += (n[k] + 127) / 128;
         n_total += n[k];
     }
-    const auto shape = [&](int max_lanes, int max_slice) {
-        return count > 1 ? auto_shape_multi(m, n, count, 8, 16, max_lanes, 64, max_slice)
-                         : auto_shape(m, (int)n_total, 8, 16, max_lanes, 64, max_slice);
+    const auto shape = [&](int max_lanes, int max_slice, bool off_lines) {
+        return count > 1 ? shape_for_multi(m, n, count, 8, 16, max_lanes, 64, max_slice, off_lines)
+                         : shape_for(m, (int)n_total, 8, 16, max_lanes, 64, max_slice, off_lines);
     };
     const bool whole = tiles >= 160 && tiles <= kComputeUnits && m <= teal::kMaxLongSliceBatch;
-    const GemvShape narrow = shape(16, whole ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch);
+    const GemvShape narrow =
+        shape(16, whole ? teal::kMaxLongSliceBatch : teal::kMaxSliceBatch, false);
     if (batch > 2) return narrow;
-    const GemvShape wide = shape(64, teal::kMaxSliceBatch);
+    const GemvShape wide = shape(64, teal::kMaxSliceBatch, wide_tiles(m, n, nullptr, count, 8));
     return batch_cost(narrow, m, n, count) < batch_cost(wide, m, n, count) ? narrow : wide;
 }
 
@@ -792,10 +804,9 @@ static teal_status gemv_bf16_rmsnorm_multi(int count, const void *const *Wt_bf16
     if (!norm_eps_ok(eps)) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes(m, (int)n_total)) return TEAL_ERR_WORKSPACE;
     // The launch shape of teal_sparse_gemv_bf16_multi (_pitch): same sums, bit for bit.  This
-    // kernel has no instance with 8 lanes per row: there the shape of the packed call.
+    // kernel has no instance with 8 lanes per row: there the shape of rows that do not rotate.
     GemvShape sh = auto_shape_multi_pitch(m, n, row_pitch, count, 16, 8, 16, 64, 64);
-    if (sh.lanes_per_row < 16)
-        sh = auto_shape_multi_pitch(m, n, nullptr, count, 16, 8, 16, 64, 64);
+    if (sh.lanes_per_row < 16) sh = auto_shape_multi(m, n, count, 8, 16, 64, 64, row_pitch);
     return from_hip(teal::launch_gemv_bf16_rmsnorm_multi(
         count, Wt_bf16, row_pitch, t, y, n, h, gamma, eps, m, ws_partials(workspace, m),
         ws_counters(workspace), sh, static_cast<hipStream_t>(stream)));
@@ -1202,12 +1213,12 @@ GemvShape to_shape(int lanes, int tile_cols, int splits)
 // tiles without split-K also for slices of up to 8192 channels and in tiles of 512 or 128
 // bytes (int8 at Llama-3-8B sizes: 26.8 -> 23.7 us; bf16 at 70B sizes: 113.5 -> 109.5 us).
 void mlp_default_shape(const MlpFormat &fm, int m, int f, int d, int gu_row_pitch,
-                       teal_mlp_shape *out)
+                       int down_row_pitch, teal_mlp_shape *out)
 {
     const int n2[2] = {f, f};
     const int pitch2[2] = {gu_row_pitch, gu_row_pitch};
-    GemvShape gu =
-        auto_shape_multi(m, n2, 2, fm.elems_per_lane, fm.min_lanes, fm.max_lanes, fm.ks_multiple);
+    GemvShape gu = auto_shape_multi(m, n2, 2, fm.elems_per_lane, fm.min_lanes, fm.max_lanes,
+                                    fm.ks_multiple, gu_row_pitch > 0 ? pitch2 : nullptr);
     const int narrow = 256 * 8 / fm.bits;                     // columns in 256 bytes of a row
     const long long narrow_blocks = 2LL * ((f + narrow - 1) / narrow);
     GemvShape rotating = gu;
@@ -1219,7 +1230,8 @@ void mlp_default_shape(const MlpFormat &fm, int m, int f, int d, int gu_row_pitc
     else if (m <= teal::kMaxSlice && narrow_blocks >= 160 && narrow_blocks <= 384 &&
              narrow / fm.elems_per_lane >= fm.min_lanes)
         gu = to_shape(narrow / fm.elems_per_lane, narrow, 1);
-    const GemvShape dn = auto_shape(f, d, fm.elems_per_lane, fm.min_lanes, fm.max_lanes, fm.ks_multiple);
+    const GemvShape dn = auto_shape(f, d, fm.elems_per_lane, fm.min_lanes, fm.max_lanes,
+                                    fm.ks_multiple, down_row_pitch > 0 ? &down_row_pitch : nullptr);
     out->gu_lanes_per_row = gu.lanes_per_row;
     out->gu_tile_cols = gu.tile_cols;
     out->gu_splits = gu.splits;
@@ -1299,7 +1311,7 @@ teal_status mlp_call(int weight_bits, const MlpCall &c, int group, const teal_ml
     if (c.workspace_bytes < teal_workspace_bytes_mlp(c.m, c.f, c.d)) return TEAL_ERR_WORKSPACE;
     teal_mlp_shape chosen;
     if (!shape) {
-        mlp_default_shape(fm, c.m, c.f, c.d, 0, &chosen);
+        mlp_default_shape(fm, c.m, c.f, c.d, 0, 0, &chosen);
         chosen.gu_row_pitch = 0;
         chosen.down_row_pitch = 0;
         shape = &chosen;
@@ -1360,7 +1372,7 @@ teal_status teal_mlp_plan(int weight_bits, int m, int f, int d, teal_mlp_shape *
     };
     if (!pitch_ok(shape->gu_row_pitch, f) || !pitch_ok(shape->down_row_pitch, d))
         return TEAL_ERR_UNSUPPORTED;
-    mlp_default_shape(fm, m, f, d, shape->gu_row_pitch, shape);
+    mlp_default_shape(fm, m, f, d, shape->gu_row_pitch, shape->down_row_pitch, shape);
     return TEAL_OK;
 }
 

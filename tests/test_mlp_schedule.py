@@ -282,3 +282,29 @@ def test_every_plan_for_padded_rows_is_a_shape_the_launch_accepts():
                             assert m <= 8192
                         st, _ = T.teal_mlp_block_info(bits, m, f, d, sh, 0)
                         assert st == T.TEAL_OK, (bits, m, f, d, extra, sh.as_dict())
+
+
+@pytest.mark.parametrize("bits", [16, 8])
+def test_plan_judges_cache_lines_by_the_pitch_and_not_by_the_width(bits):
+    """Wider tiles are for rows that begin off cache lines.  Padded to a line, W_down and gate / up
+    get the tiles of an aligned width, and padded off a line those of an unaligned one."""
+    m, f, d = 4096, 11008, 4096 * 16 // bits               # widths on lines, 12 tiles of 512 bytes and more
+    unit = 16                                              # a step off a line that both formats accept
+    line = 128 * 8 // bits
+
+    def plan(mm, ff, dd, *pitches):
+        st, sh = T.teal_mlp_plan(bits, mm, ff, dd, *pitches)
+        assert st == T.TEAL_OK
+        return ((sh.gu_lanes_per_row, sh.gu_tile_cols, sh.gu_splits),
+                (sh.down_lanes_per_row, sh.down_tile_cols, sh.down_splits))
+
+    narrow, wide = plan(m, f, d)[1], plan(m, f, d + unit)[1]
+    assert narrow[1] * bits // 8 < 512 <= wide[1] * bits // 8
+    assert plan(m, f, d + unit, 0, d + 5 * line)[1] == plan(m, f, d + line)[1]
+    assert plan(m, f, d, 0, d + unit)[1][1] == wide[1]
+    # gate / up where no tile without split-K fits: m beyond one slice, few columns
+    m, f = 5120, 3584 * 16 // bits
+    narrow, wide = plan(m, f, d)[0], plan(m, f + unit, d)[0]
+    assert narrow[1] * bits // 8 < wide[1] * bits // 8
+    assert plan(m, f + unit, d, f + 4 * line)[0] == plan(m, f + line, d)[0]
+    assert plan(m, f, d, f + unit)[0][1] > narrow[1]
