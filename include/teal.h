@@ -611,7 +611,8 @@ teal_status teal_histogram_thresholds(const uint64_t *hist, const double *p, int
  * lanes_per_row * B <= 256, B = batch rounded up to 2, 4 or 8; tile_cols a
  * multiple of 8, at most 8 * lanes_per_row (from three rows on, tiles wider
  * than 128 columns are run as tiles of 128); splits such that a block's slice,
- * ceil(m / splits) rounded up to 64, is at most 2048 channels.
+ * ceil(m / splits) rounded up to 64, is at most 2048 channels (the library's
+ * own choice, with all three 0, may take up to 4096).
  *
  * teal_sparse_gemv_bf16_batch_multi: count (1..4) matrices that read the same
  * batch, one kernel launch, each matrix with its own threshold; Wt_bf16, t, Y, n

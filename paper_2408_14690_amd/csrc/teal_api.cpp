@@ -870,14 +870,19 @@ teal_status teal_sparse_gemv_bf16_batch_ex(const void *Wt_bf16, const void *X_f1
         return TEAL_ERR_ALIGN;
     if (!threshold_ok(t)) return TEAL_ERR_THRESHOLD;
     if (workspace_bytes < teal_workspace_bytes_batch(m, n, batch)) return TEAL_ERR_WORKSPACE;
-    GemvShape sh = auto_shape_batch(m, &n, 1, batch);
     const bool own_shape = !lanes_per_row && !tile_cols && !splits;
-    if (lanes_per_row) {
-        sh.lanes_per_row = lanes_per_row;
-        if (!tile_cols && sh.tile_cols > lanes_per_row * 8) sh.tile_cols = lanes_per_row * 8;
+    GemvShape sh = auto_shape_batch(m, &n, 1, batch);
+    if (!own_shape) {
+        // What the caller left open: lanes for the widest tile that may be asked for at this n
+        // and batch, the library's width as far as it fits, and as many splits as keep a
+        // slice within kMaxSliceBatch.
+        const GemvShape wide =
+            shape_for(m, n, 8, 16, batch <= 2 ? 64 : 16, 64, teal::kMaxSliceBatch, false);
+        sh.lanes_per_row = lanes_per_row ? lanes_per_row : wide.lanes_per_row;
+        if (tile_cols) sh.tile_cols = tile_cols;
+        else if (sh.tile_cols > sh.lanes_per_row * 8) sh.tile_cols = sh.lanes_per_row * 8;
+        sh.splits = splits ? splits : wide.splits;
     }
-    if (splits) sh.splits = splits;
-    if (tile_cols) sh.tile_cols = tile_cols;
     if (!teal::gemv_batch_shape_supported(batch, sh)) return TEAL_ERR_UNSUPPORTED;
     if (!tiles_fit_counters(n, sh)) return TEAL_ERR_UNSUPPORTED;
     const int ks = ((m + sh.splits - 1) / sh.splits + 63) / 64 * 64;

@@ -836,3 +836,31 @@ def test_plans_widen_tiles_where_rows_lie_off_cache_lines():
     narrow = T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3008 + 64])[1]
     assert narrow["tile_cols"] == 128 and T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3008])[1] == narrow
     assert T.teal_gemv_plan_multi_pitch(16, 3000, [3000], [3016])[1] == T.teal_gemv_plan(16, 3000, 3000)[1]
+
+
+def test_batch_ex_accepts_every_partly_filled_shape():
+    """teal_sparse_gemv_bf16_batch_ex with any of its shape arguments 0 ("the library's choice"):
+    what a caller may give by teal.h's rules is accepted whatever the library would have chosen
+    itself, over sizes at which its own choice takes whole inputs or wide tiles.  An accepted call
+    goes on to launch, so this runs only where there is no device to launch on."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("an accepted call would launch on these addresses")
+    for batch in (1, 2, 3, 8):
+        nb = 2 if batch <= 2 else 4 if batch <= 4 else 8
+        for m in (64, 2049, 3000, 4096, 5000):
+            for n in (8, 3416, 4096, 8192, 16384, 20488, 28672, 32768, 50264):
+                tc = max(128, ((n + 31) // 32 + 63) // 64 * 64)      # 32 tiles, in steps of 64 columns
+                lanes_left_open = 16 if nb > 2 or tc <= 128 else 32 if tc <= 256 else 64
+                for lanes in (0, 16, 32, 64):
+                    for tile in (0, 64, 128, 256, 512):
+                        for splits in (0, 1, 2, 16, 17):
+                            has = lanes or lanes_left_open
+                            ok = nb * has <= 256 and tile <= 8 * has
+                            if splits:
+                                ks = ((m + splits - 1) // splits + 63) // 64 * 64
+                                ok = ok and ks <= 2048 and (m + ks - 1) // ks <= 16
+                            got = T.teal_sparse_gemv_bf16_batch_ex(W, X, batch, 0.5, Y, m, n, WS, BIG, 0,
+                                                                   lanes_per_row=lanes, tile_cols=tile, splits=splits)
+                            want = T.TEAL_ERR_HIP if ok else T.TEAL_ERR_UNSUPPORTED
+                            assert got == want, (batch, m, n, lanes, tile, splits)

@@ -345,3 +345,19 @@ def test_batch_planned_shapes_of_wide_outputs(T, batch, m, ns):
         want = orc.sparse_gemv_bf16_batch(ws_host[k], X, t)
         for b in range(batch):
             assert rel_l2(Ys[k].cpu().numpy()[b], want[b]) <= TIGHT, (k, b)
+
+
+@pytest.mark.parametrize("batch,m,n,shape", [
+    (8, 4096, 20488, dict(lanes_per_row=16)), (3, 3000, 20488, dict(tile_cols=128)),
+    (2, 2050, 28672, dict(tile_cols=64)), (2, 2050, 28672, dict(lanes_per_row=32)),
+    (1, 1000, 16384, dict(tile_cols=512)), (2, 700, 8200, dict(tile_cols=256)),
+    (4, 1000, 4096, dict(lanes_per_row=64, splits=3)), (2, 4096, 20488, dict(splits=2))])
+def test_batch_partly_filled_shapes(T, batch, m, n, shape):
+    """Shapes of which the caller gives a part, at sizes where the library's own choice is another."""
+    w = ti.weights_bf16(n, m, 70 + m)
+    X = ti.make_X(batch, m, 71 + n, "gaussian")
+    t = ti.batch_quantile_threshold(X, 0.8)
+    want = orc.sparse_gemv_bf16_batch(w, X, t)
+    got = run_batch(T, dev(ti.to_input_channel_major(w)), X, t, m, n, **shape)
+    for b in range(batch):
+        assert rel_l2(got[b], want[b]) <= TIGHT
