@@ -439,13 +439,16 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
     // Channels per lane by the length of the slice, so that short slices occupy every wavefront;
-    // one by one where the rows of X do not lie on 8-byte boundaries.
+    // one by one where the rows of X do not lie on 8-byte boundaries, in as many passes as the
+    // slice needs (8 rows 4097 -> 4096: 14.6 us with always 8 passes, 12.4 us).
     constexpr int kLanes = 64 * WAVES;
     const int len = k1 - k0;                           // block-uniform
     const bool vec = (m & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 7) == 0;
 #define TEAL_COMPACT(VEC, PASSES)                                                                \
     compact_slice_batch<NB, WAVES, VEC, PASSES>(X, batch, m, bound, k0, k1, list_idx, smem, seg_cnt)
     const int cnt = len <= kLanes               ? TEAL_COMPACT(1, 1)
+                    : !vec && len <= 2 * kLanes ? TEAL_COMPACT(1, 2)
+                    : !vec && len <= 4 * kLanes ? TEAL_COMPACT(1, 4)
                     : !vec                      ? TEAL_COMPACT(1, kMaxLongSliceBatch / kLanes)
                     : len <= 2 * kLanes         ? TEAL_COMPACT(2, 1)
                     : len <= 4 * kLanes         ? TEAL_COMPACT(4, 1)

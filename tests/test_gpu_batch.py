@@ -361,3 +361,27 @@ def test_batch_partly_filled_shapes(T, batch, m, n, shape):
     got = run_batch(T, dev(ti.to_input_channel_major(w)), X, t, m, n, **shape)
     for b in range(batch):
         assert rel_l2(got[b], want[b]) <= TIGHT
+
+
+@pytest.mark.parametrize("batch", [1, 3, 8])
+@pytest.mark.parametrize("m,x_off", [(511, 0), (513, 0), (1022, 0), (1024, 2), (1025, 0), (2047, 0), (2048, 1)])
+def test_batch_slices_read_one_by_one(T, batch, m, x_off):
+    """Activations that do not lie on 8-byte boundaries are read channel by channel in as many passes
+    as the slice needs: lengths around each number of passes, all in one slice."""
+    n = 136
+    w = ti.weights_bf16(n, m, 80 + m)
+    X = ti.make_X(batch, m, 81 + m, "laplace")
+    t = ti.batch_quantile_threshold(X, 0.4)
+    buf = torch.zeros(batch * m + 8, dtype=torch.int16, device="cuda")
+    Xd = buf[x_off:x_off + batch * m]
+    Xd.copy_(torch.from_numpy(X.view(np.int16).reshape(-1)))
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, n, batch), dtype=torch.uint8, device="cuda")
+    Y = torch.full((batch, n), float("nan"), dtype=torch.float32, device="cuda")
+    T.check(T.teal_sparse_gemv_bf16_batch_ex(dev(ti.to_input_channel_major(w)), Xd, batch, t, Y, m, n, ws,
+                                             lanes_per_row=16, tile_cols=128, splits=1))
+    torch.cuda.synchronize()
+    off = T.teal_survivors_offset()
+    assert ws[off:off + 4].view(torch.int32).item() == orc.sparsify_batch(X, t)[3]
+    want = orc.sparse_gemv_bf16_batch(w, X, t)
+    for b in range(batch):
+        assert rel_l2(Y.cpu().numpy()[b], want[b]) <= TIGHT
