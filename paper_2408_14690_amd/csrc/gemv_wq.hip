@@ -113,7 +113,7 @@ template <int U>
 struct W4Batch {
     u32x4 v[U];
     int x[U];         // digits of the activations
-    unsigned sc[8];   // fp16 pairs: chunk 4 * (lane / 16) + r, bytes lane % 8 + 8 h, at [4 h + r]
+    unsigned sc[4];   // fp16 pairs: chunk 4 * (lane / 16) + r, byte lane % 16, at [r]
     int rows;         // live rows in this batch (wavefront-uniform); 0 = the share is exhausted
     bool ends_run;    // wavefront-uniform
 };
@@ -187,8 +187,8 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const unsigned row_bytes = (unsigned)(n / 2);
     const unsigned char *lane_base =
         static_cast<const unsigned char *>(a.W) + lane_column<EPL>(part0, part_cols, n, l) / 2;
-    // columns of this lane's sums: chunk 4 g + r, byte l % 8 of the first half
-    const __half *scale_base = a.scale + (size_t)(k0 / kGroup) * n + 2 * (l & 7);
+    // columns this lane adds up: chunk 4 g + r, byte l
+    const __half *scale_base = a.scale + (size_t)(k0 / kGroup) * n + 2 * l;
     int scale_col[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) scale_col[r] = lane_column<EPL>(part0, part_cols, n, 4 * g + r);
@@ -203,13 +203,13 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
                                              : 0x0C0C0C0Cu;
         }
 
-    float acc[2][2][4];                           // [h][nibble][r], lane layout of W4Sums
+    float acc[2][4];                              // [nibble][r]: chunk 4 g + r, byte l
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[h][q][r] = 0.f;
+        for (int r = 0; r < 4; ++r) acc[q][r] = 0.f;
+    // where a digit's sum lies when the two lanes that hold a pair of digits join them
+    const int own_shift = l < 8 ? 0 : 8, other_shift = 8 - own_shift;
     W4Sums sums;
     sums.clear();
 
@@ -226,7 +226,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const int end = start + mine;
     int gi = 0, gend = min(end, group_begin(1));
 
-    // Every call issues exactly U row loads and the eight scale loads of the batch's group,
+    // Every call issues exactly U row loads and the four scale loads of the batch's group,
     // whether or not rows are left: the compiler then knows how many loads are outstanding at
     // every wait and waits for a batch's own loads only.  (With a conditional scale load and an
     // early return for an exhausted share it waited for older loads between the loads of a
@@ -253,10 +253,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
         b.ends_run = live && cur + nb == gend;
         const __half *sp = scale_base + (size_t)gi * n;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            b.sc[r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r]);
-            b.sc[4 + r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r] + 16);
-        }
+        for (int r = 0; r < 4; ++r) b.sc[r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r]);
         cur += nb;
     };
     auto consume = [&](const W4Batch<U> &b) {
@@ -281,16 +278,26 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
             }
         }
         if (!b.ends_run) return;
+        // The lanes l < 8 take the first half of a chunk and give the second to the lane 8 further,
+        // which holds the other digit of a pair.  A column's sum is complete before the group's
+        // scale multiplies it: an infinite scale then gives what it gives the whole sum.
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const __half2 sc = __builtin_bit_cast(__half2, b.sc[4 * h + r]);
+                int pair[2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int first = sums.v[q][0][p][r], second = sums.v[q][1][p][r];
+                    const int own = l < 8 ? first : second, give = l < 8 ? second : first;
+                    const int got = __builtin_amdgcn_update_dpp(0, give, 0x128 /* row_ror:8 */, 0xF,
+                                                                0xF, false);
+                    pair[p] = (int)(((unsigned)own << own_shift) + ((unsigned)got << other_shift));
+                }
                 // the digits of p = 1 weigh 2^16 more
-                const float lo = fmaf((float)sums.v[0][h][1][r], 65536.f, (float)sums.v[0][h][0][r]);
-                const float hi = fmaf((float)sums.v[1][h][1][r], 65536.f, (float)sums.v[1][h][0][r]);
-                acc[h][0][r] = fmaf(__low2float(sc), lo, acc[h][0][r]);
-                acc[h][1][r] = fmaf(__high2float(sc), hi, acc[h][1][r]);
+                const float sum = fmaf((float)pair[1], 65536.f, (float)pair[0]);
+                const __half2 sc = __builtin_bit_cast(__half2, b.sc[r]);
+                acc[q][r] = fmaf(q ? __high2float(sc) : __low2float(sc), sum, acc[q][r]);
             }
         sums.clear();
     };
@@ -315,28 +322,14 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     }
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
-    // The digits of a column sit 8 lanes apart; both lanes form the sum, and the lanes with
-    // l < 8 write the first half of a chunk, the others the second.
     const bool finite = largest < 0x7F800000u;
-    const float unit = !finite ? __uint_as_float(0x7FC00000u)
-                       : largest ? FixedDigits::power_of_two(-FixedDigits::shift(largest)) : 0.f;
-    const float mine_unit = 0.0625f * (l < 8 ? unit : 256.f * unit);
-    float *row = red + share * combine_row<EPL, LPR> + part * PART_COLS;
+    const float unit = 0.0625f * (!finite ? __uint_as_float(0x7FC00000u)
+                                  : largest ? FixedDigits::power_of_two(-FixedDigits::shift(largest)) : 0.f);
+    float *row = red + share * combine_row<EPL, LPR> + part * PART_COLS + 2 * l;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        float v[2][2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float own = acc[h][q][r] * mine_unit;
-                v[h][q] = own + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(
-                                    0, (int)__float_as_uint(own), 0x128 /* row_ror:8 */, 0xF, 0xF,
-                                    false));
-            }
-        *reinterpret_cast<float2 *>(row + EPL * (4 * g + r) + (l < 8 ? 0 : 16) + 2 * (l & 7)) =
-            l < 8 ? make_float2(v[0][0], v[0][1]) : make_float2(v[1][0], v[1][1]);
-    }
+    for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<float2 *>(row + EPL * (4 * g + r)) =
+            make_float2(acc[0][r] * unit, acc[1][r] * unit);
     return block_finish<F, LPR, WAVES, SHARES>(red, partial, counter, y, tile, col0, tile_cols, s,
                                                splits, n, a, cnt, report);
 }

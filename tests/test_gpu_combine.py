@@ -93,3 +93,24 @@ def test_w4_infinite_activation_gives_nan(T):   # noqa: F811
     T.check(T.teal_sparse_gemv_w4(q, scale, 128, dev(x), 0.5, y, m, n, ws))
     torch.cuda.synchronize()
     assert torch.isnan(y).all()
+
+
+@pytest.mark.parametrize("m,n", [(1024, 544), (4096, 1056), (2048, 28672)])
+def test_w4_infinite_scale_gives_the_sign_of_its_sum(T, m, n):   # noqa: F811
+    """A group whose scale is infinite in some columns: products of one sign give an infinity of that
+    sign there, whatever digits the activations have, and leave the other columns alone."""
+    rng = np.random.default_rng(m)
+    q = rng.integers(1, 8, (m, n)) * np.where(np.arange(n) % 2, -1, 1)
+    packed = ((q[:, 0::2] & 15) | ((q[:, 1::2] & 15) << 4)).astype(np.uint8)
+    scale = np.full((m // 128, n), 0.01, np.float16)
+    scale[3, ::3] = np.inf
+    x = (2.0 ** rng.integers(-6, 7, m)).astype(np.float16)
+    x[::5] *= np.float16(1.2001953125)
+    y = torch.zeros(n, dtype=torch.float32, device="cuda")
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    T.check(T.teal_sparse_gemv_w4(dev(packed), dev(scale), 128, dev(x), 0.0, y, m, n, ws))
+    torch.cuda.synchronize()
+    got, hit = y.cpu().numpy(), np.arange(n) % 3 == 0
+    assert np.array_equal(got[hit], np.where(np.arange(n) % 2, -np.inf, np.inf)[hit].astype(np.float32))
+    want = x.astype(np.float64) @ (q * np.repeat(scale.astype(np.float64), 128, 0))[:, ~hit]
+    assert rel_l2(got[~hit], want) <= TIGHT
