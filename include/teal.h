@@ -26,8 +26,10 @@
  *     compares false (dropped); +-Inf is kept.  t = 0 is the dense product
  *     (only entries equal to zero are skipped).
  *   - y is fp32, fully overwritten (all zeros when nothing survives).
- *     Products are formed and summed in fp32, in a fixed order: results are
- *     bitwise reproducible from run to run for a given shape.
+ *     Products are formed and summed in fp32, or exactly and rounded to fp32
+ *     once (int4: a 128-channel group's integer sums, before its scale), in a
+ *     fixed order: results are bitwise reproducible from run to run for a
+ *     given shape.
  *   - All argument checks happen on the host before any GPU work and return
  *     a status; nothing aborts, throws or prints.
  *   - `workspace` is caller-provided device scratch of at least

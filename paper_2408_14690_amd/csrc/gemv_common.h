@@ -350,24 +350,24 @@ struct RmsnormSource {                // hidden state and norm weights, fp32 in 
 // Definition 1 on one element: fp16 -> fp32 is exact, the compare is fp32.
 __device__ __forceinline__ bool survives(float xv, float t) { return fabsf(xv) > t; }
 
-// What a list entry holds beside its channel.  PlainBits: x as fp32 bits.  (FixedDigits, for the
-// int4 kernel, needs the largest survivor of the slice before it can encode one: kScaled.)
-struct PlainBits {
-    static constexpr bool kScaled = false;
-    static __device__ __forceinline__ int encode(float x, unsigned) { return __float_as_int(x); }
-};
-
-// Largest value over the 64 lanes (inclusive scan; lanes shifted in from outside hold zero).
-__device__ __forceinline__ unsigned wave_max(unsigned v)
+// How large the survivors of a slice are, for a list whose entries depend on it: nothing beyond
+// kModestLimit, something beyond it, an infinity.
+enum Magnitude { kModest = 0, kLarge = 1, kInfinite = 2 };
+constexpr float kModestLimit = 127.f;
+__device__ __forceinline__ int magnitude_of(unsigned long long large, unsigned long long infinite)
 {
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true));
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+    return infinite ? kInfinite : large ? kLarge : kModest;
 }
+
+// A list entry for channel k0 + offset.  PlainBits: the channel and x as fp32 bits.  (FixedDigits, for
+// the int4 kernel, whose kernel also needs to know how large the survivors are.)
+struct PlainBits {
+    static constexpr bool kMagnitude = false;
+    static __device__ __forceinline__ int2 entry(int k0, int offset, float x)
+    {
+        return make_int2(k0 + offset, __float_as_int(x));
+    }
+};
 
 // Compacts the survivors of channels [k0, k1) into list[] as (channel, x as
 // fp32 bits or as Enc encodes it), ascending.  Each wavefront ballots its 64-channel segments and
@@ -381,15 +381,14 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
 // with a barrier after which list[] is complete.  `prepared`, when given, carries
 // what the source prepares once per block (the scale of the normalisation) from
 // one piece of a long slice to the next: computed when `have_prepared` is false
-// (block-uniform), reused otherwise.  `largest`, with an encoding that needs it: the fp32 bits
-// of the largest surviving |x| (infinities and all; 0 when nothing survives), the same in all
-// threads; seg_cnt[] then has WAVES ints more.
+// (block-uniform), reused otherwise.  `magnitude`, with an encoding that needs it: how large the
+// survivors are, the same in all threads; seg_cnt[] then has WAVES ints more.
 template <int WAVES, class XS, class Enc = PlainBits>
 __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
                                              int k1, int2 *list, int *seg_cnt, int &seg_excl,
                                              float *prepared_io = nullptr,
                                              bool have_prepared = false,
-                                             unsigned *largest = nullptr)
+                                             int *magnitude = nullptr)
 {
     constexpr int PER_WAVE = kMaxSegs / WAVES;
     const int lane = threadIdx.x & 63;
@@ -423,24 +422,26 @@ __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
         bal[j] = __ballot(survives(xv[j], t));
         if (lane == 0 && seg < nseg) seg_cnt[seg] = __popcll(bal[j]);
     }
-    unsigned top = 0;
-    if constexpr (Enc::kScaled) {
+    if constexpr (Enc::kMagnitude) {
+        unsigned long long large = 0, infinite = 0;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j)
-            top = max(top, survives(xv[j], t) ? __float_as_uint(fabsf(xv[j])) : 0u);
-        top = wave_max(top);
-        if (lane == 0) seg_cnt[kMaxSegs + w] = (int)top;
+        for (int j = 0; j < PER_WAVE; ++j) large |= bal[j] & __ballot(fabsf(xv[j]) > kModestLimit);
+        if (large) {
+#pragma unroll
+            for (int j = 0; j < PER_WAVE; ++j) infinite |= bal[j] & __ballot(isinf(xv[j]));
+        }
+        if (lane == 0) seg_cnt[kMaxSegs + w] = magnitude_of(large, infinite);
     }
     __syncthreads();
     const int c = lane < nseg ? seg_cnt[lane] : 0;
     const int incl = wave_inclusive_scan(c);
     seg_excl = incl - c;
     const int total = __builtin_amdgcn_readlane(incl, 63);
-    if constexpr (Enc::kScaled) {
-        top = 0;
+    if constexpr (Enc::kMagnitude) {
+        int top = kModest;
 #pragma unroll
-        for (int ww = 0; ww < WAVES; ++ww) top = max(top, (unsigned)seg_cnt[kMaxSegs + ww]);
-        *largest = top = __builtin_amdgcn_readfirstlane(top);
+        for (int ww = 0; ww < WAVES; ++ww) top = max(top, seg_cnt[kMaxSegs + ww]);
+        *magnitude = __builtin_amdgcn_readfirstlane(top);
     }
 #pragma unroll
     for (int j = 0; j < PER_WAVE; ++j) {
@@ -449,7 +450,7 @@ __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0,
             const int base = __builtin_amdgcn_readlane(seg_excl, seg);
             if (survives(xv[j], t))
                 list[base + lanes_below(bal[j])] =
-                    make_int2(k0 + seg * 64 + lane, Enc::encode(xv[j], top));
+                    Enc::entry(k0, seg * 64 + lane, xv[j]);
         }
     }
     __syncthreads();
@@ -474,7 +475,7 @@ __device__ __forceinline__ void wave_share(int cnt, int w, int waves, int &start
 template <int P, class Enc = PlainBits>
 __device__ __forceinline__ int compact_slice_private(const __half *__restrict__ x, float t, int k0,
                                                      int k1, int share, int shares, int2 *list,
-                                                     int &seg_excl, unsigned *largest = nullptr)
+                                                     int &seg_excl, int *magnitude = nullptr)
 {
     const int lane = threadIdx.x & 63;
     __half raw[P];
@@ -495,12 +496,15 @@ __device__ __forceinline__ int compact_slice_private(const __half *__restrict__ 
     seg_excl = total;                                         // lane j: prefix of segment j
 #pragma unroll
     for (int j = 0; j < P; ++j) seg_excl = lane == j ? base[j] : seg_excl;
-    unsigned top = 0;
-    if constexpr (Enc::kScaled) {
+    if constexpr (Enc::kMagnitude) {
+        unsigned long long large = 0, infinite = 0;
 #pragma unroll
-        for (int j = 0; j < P; ++j)
-            top = max(top, survives(xv[j], t) ? __float_as_uint(fabsf(xv[j])) : 0u);
-        *largest = top = wave_max(top);
+        for (int j = 0; j < P; ++j) large |= bal[j] & __ballot(fabsf(xv[j]) > kModestLimit);
+        if (large) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) infinite |= bal[j] & __ballot(isinf(xv[j]));
+        }
+        *magnitude = magnitude_of(large, infinite);
     }
     int start, mine;
     wave_share(total, share, shares, start, mine);
@@ -510,7 +514,7 @@ __device__ __forceinline__ int compact_slice_private(const __half *__restrict__ 
         if (base[j] < end && base[j + 1] > start) {           // wavefront-uniform
             const int rank = base[j] + lanes_below(bal[j]);
             if (survives(xv[j], t) && rank >= start && rank < end)
-                list[rank] = make_int2(k0 + j * 64 + lane, Enc::encode(xv[j], top));
+                list[rank] = Enc::entry(k0, j * 64 + lane, xv[j]);
         }
     }
     return total;

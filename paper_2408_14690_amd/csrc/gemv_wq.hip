@@ -3,6 +3,8 @@
 //   int8: W[j][i] = q[i][j] * scale[j]            (channel-wise)
 //   int4: W[j][i] = nibble(i, j) * scale[i/128][j] (groups of 128 input channels)
 // Dequantisation happens in registers; only surviving rows are read.
+#include <type_traits>
+
 #include "gemv_common.h"
 #include "gemv_dispatch.h"
 #include "gemv_mlp.h"
@@ -61,71 +63,75 @@ constexpr int kW4Unroll = 4;
 // addressing: the row stream was bound by instruction issue (two wavefronts per SIMD), not by HBM
 // (dense 28672 x 8192: 21 us of rows for 14.7 us of bytes at the peak).
 //
-// v_mfma_i32_16x16x32_i8: a lane's 8 bytes of one weight row are 8 of the 32 values of K, its
-// lane % 16 the row of A, lane / 16 the quarter of K, so with 16 lanes to a weight row the weights go
-// in as they were loaded.  B separates the bytes again: it is zero except where the byte's place
-// in the lane equals the column's, B[8 g + j][j] = the activation of lane group g's row, so the
-// product of chunk m (16 bytes, 32 output columns) with column j is the sum over the rows of activation
-// times byte j, and the four rows of a load are added by the instruction.  A byte is two
-// nibbles: with the low one offset by 8 it is the signed number 16 hi + (lo + 8), and masked it is
-// lo + 8, so hi and lo follow from the two sums by integer arithmetic: 8 instructions per 16-byte
-// load in place of 56.
+// v_mfma_i32_16x16x64_i8: a lane's 16 bytes are 16 of the 64 values of K, its lane % 16 the row of A,
+// lane / 16 the quarter of K, so with 16 lanes to a weight row the weights go in as they were
+// loaded, 8 bytes of one row and 8 of the same columns of another.  B separates the bytes again: it
+// is zero except where the byte's place in its row equals the column's, B[16 g + 8 i + j][j] =
+// the activation of the i-th of lane group g's rows, so the product of half a chunk (a chunk: 16
+// bytes, 32 output columns) with column j is the sum over the rows of activation times byte j, and
+// the eight rows of two loads are added by the instruction.  A byte is two nibbles: each, masked into
+// the upper half of a byte of its own, is 16 times its signed value, so extraction is an AND and
+// a shift-and-AND per 4 bytes, 12 instructions per 16-byte load.
 //
-// Activations enter as integers too: X = x 2^s, with s such that the largest survivor of the
-// slice has 30 bits, in four signed base-256 digits; columns j and j + 8 of B take two digits, two
-// instructions the four.  X is exact for every x that is a multiple of 2^-s (all of fp16 where the
-// largest is below 64, else all but values more than 2^19 times smaller than it), the sums are exact,
-// and are rounded to fp32 once per 128-channel group, where the group's scale is applied:
-// no larger error than the fp32 sums had.  An infinite activation makes every column NaN, as it
-// did when the nibbles were offset by 8 and the correction was infinite, too.
+// Activations enter as integers too: an fp16 value is a whole multiple of 2^-24, X = x 2^24, below
+// 2^40, in signed base-256 digits; columns j and j + 8 of B take two digits, so two
+// instructions take four digits (|x| <= 127) and three take six (all of fp16).  How many is
+// decided per slice by its survivors.  The products of a wavefront's rows of a 128-channel
+// group and their sums are exact; a group's sum is rounded when it is put together from its digits,
+// and its scale is applied in fp32.  An infinite activation makes every column NaN.
+// (us at 50 %, FMAs / four digits / six: 4096 -> 4096 8.1 / 7.2 / 7.8, 14336 -> 4096 11.4 / 10.1 / 10.8,
+// 8192 -> 2 x 28672 29.8 / 26.6 / 27.3.  Activations scaled by the slice's largest to 30 bits
+// took four digits everywhere, but with 2000 beside values around 0.001 a column whose weight
+// of the 2000 is zero was 2e-4 off; with six digits it is 8e-8.)
 struct FixedDigits {
-    static constexpr bool kScaled = true;
-    static constexpr int kBits = 29;                // 2^kBits <= largest |X| < 2^(kBits + 1)
-    // s from the fp32 bits of the largest |x| (0: nothing survives)
-    static __device__ __forceinline__ int shift(unsigned largest)
+    static constexpr bool kMagnitude = true;
+    static constexpr float kUnit = 5.9604644775390625e-8f;       // 2^-24
+    // Four digits reach to 127 (2^24 + 2^16 + 2^8 + 1).
+    static_assert(kModestLimit <= 127.f, "slices of modest survivors need four digits");
+    // Digits 0 to 3 in the second word, 4 and 5 in the lower half of the first, below the channel
+    // counted from the slice's first.  Digit d of X is byte d: adding 128 to each digit that a higher
+    // one follows makes the bytes of X unsigned digits without a borrow, and the flip of their
+    // top bits takes it off again.  X is put together from the nearest whole number and what is left.
+    static_assert(kMaxSlice <= 1 << 15, "a channel of a slice fits the upper half of a word");
+    static __device__ __forceinline__ int2 entry(int, int offset, float x)
     {
-        return kBits - ((int)(largest >> 23) - 127);
-    }
-    static __device__ __forceinline__ float power_of_two(int e)
-    {
-        return __int_as_float((e + 127) << 23);
-    }
-    static __device__ __forceinline__ int encode(float x, unsigned largest)
-    {
-        // digit d of X is byte d: adding 128 to each of the lower three digits makes the bytes
-        // of X unsigned digits without a borrow, and the flip of their top bits takes it off again
-        const int X = __float2int_rn(x * power_of_two(shift(largest)));
-        return (int)(((unsigned)X + 0x00808080u) ^ 0x00808080u);
+        const float whole = rintf(x);
+        const unsigned rest = (unsigned)(int)((x - whole) * 16777216.f) + 0x00808080u;   // below 2^25
+        const unsigned upper = (unsigned)(int)whole + 0x8080u + (rest >> 24);            // digits 3, 4, 5
+        const unsigned low = __builtin_amdgcn_perm(upper, rest, 0x04020100u) ^ 0x80808080u;
+        const unsigned high = __builtin_amdgcn_perm((unsigned)offset, upper ^ 0x8000u, 0x05040201u);
+        return make_int2((int)high, (int)low);
     }
 };
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ i32x4 mfma_i8(unsigned a0, unsigned a1, unsigned b0, unsigned b1, i32x4 c)
-{
-    return __builtin_amdgcn_mfma_i32_16x16x32_i8((long)(((unsigned long)a1 << 32) | a0),
-                                                 (long)(((unsigned long)b1 << 32) | b0), c, 0, 0, 0);
-}
 
 // One batch of row loads of the int4 kernel: U wavefront loads of 4 rows, all from one 128-channel
 // group, and the group's scales for the columns this lane holds sums of.
-template <int U>
+template <int U, int P>
 struct W4Batch {
     u32x4 v[U];
-    int x[U];         // digits of the activations
+    int x[U][P - 1];  // digits of the activations: 0..3, and 4, 5
     unsigned sc[4];   // fp16 pairs: chunk 4 * (lane / 16) + r, byte lane % 16, at [r]
     int rows;         // live rows in this batch (wavefront-uniform); 0 = the share is exhausted
     bool ends_run;    // wavefront-uniform
 };
 
-// Integer sums over the rows of one run (a wavefront's rows of one group): lane (n = lane % 16,
-// g = lane / 16) holds, in register r, chunk 4 g + r, byte n % 8 of half h, digit n / 8 + 2 p.
+// Integer sums over the rows of one run (a wavefront's rows of one group), P pairs of digits: lane
+// (n = lane % 16, g = lane / 16) holds, in register r, chunk 4 g + r, byte n % 8 of half h, digit
+// n / 8 + 2 p.  At most 128 rows of |digit| <= 128 and |16 nibble| <= 128: 2^21, a pair 2^29.
+template <int P>
 struct W4Sums {
-    i32x4 v[2][2][2];      // [nibble][h][p] sum of digit * 16 * nibble
+    i32x4 v[2][2][P];      // [nibble][h][p] sum of digit * 16 * nibble
     __device__ __forceinline__ void clear()
     {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k >> 2][(k >> 1) & 1][k & 1] = i32x4{0, 0, 0, 0};
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int p = 0; p < P; ++p) v[k][h][p] = i32x4{0, 0, 0, 0};
     }
 };
 
@@ -165,17 +171,17 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const int part = w % PARTS, share = w / PARTS;
     int seg_excl;
     int cnt;
-    unsigned largest;
+    int magnitude;
     if constexpr (XS::kPlainHalf) {
         if (k1 - k0 <= 8 * 64)         // block-uniform: short slices need no barrier
             cnt = compact_slice_private<8, FixedDigits>(x.x, t, k0, k1, share, SHARES, list, seg_excl,
-                                                        &largest);
+                                                        &magnitude);
         else
             cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl,
-                                                        nullptr, false, &largest);
+                                                        nullptr, false, &magnitude);
     } else {
         cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl, nullptr,
-                                                    false, &largest);
+                                                    false, &magnitude);
     }
 
     trace_mark(2);
@@ -186,13 +192,15 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const int part_cols = tile_cols - part * PART_COLS;
     const unsigned row_bytes = (unsigned)(n / 2);
     const unsigned char *lane_base =
-        static_cast<const unsigned char *>(a.W) + lane_column<EPL>(part0, part_cols, n, l) / 2;
+        static_cast<const unsigned char *>(a.W) + (size_t)k0 * row_bytes +
+        lane_column<EPL>(part0, part_cols, n, l) / 2;
     // columns this lane adds up: chunk 4 g + r, byte l
     const __half *scale_base = a.scale + (size_t)(k0 / kGroup) * n + 2 * l;
     int scale_col[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) scale_col[r] = lane_column<EPL>(part0, part_cols, n, 4 * g + r);
-    // B: this lane's column takes byte l % 8 of a lane, from digit l / 8 + 2 p of the row
+    // B: this lane's column takes byte l % 8 of a lane, from digit l / 8 + 2 p of the row (of digits
+    // 4 and 5, digit l / 8 of the channel's word)
     unsigned pick[2][2];
 #pragma unroll
     for (int p = 0; p < 2; ++p)
@@ -210,9 +218,6 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
         for (int r = 0; r < 4; ++r) acc[q][r] = 0.f;
     // where a digit's sum lies when the two lanes that hold a pair of digits join them
     const int own_shift = l < 8 ? 0 : 8, other_shift = 8 - own_shift;
-    W4Sums sums;
-    sums.clear();
-
     int start, mine;
     wave_share(cnt, share, SHARES, start, mine);
     // Walk state (all wavefront-uniform): next list position, end of the share, current
@@ -226,105 +231,120 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     const int end = start + mine;
     int gi = 0, gend = min(end, group_begin(1));
 
-    // Every call issues exactly U row loads and the four scale loads of the batch's group,
-    // whether or not rows are left: the compiler then knows how many loads are outstanding at
-    // every wait and waits for a batch's own loads only.  (With a conditional scale load and an
-    // early return for an exhausted share it waited for older loads between the loads of a
-    // batch, and little more than one batch was ever in flight.)  A batch past the end of the
-    // share re-reads the share's last row with zero multipliers.
-    auto issue = [&](W4Batch<U> &b) {
-        const bool live = cur < end;                  // wavefront-uniform
-        if (live) {
-            while (cur >= gend) {                     // next group with rows in this share
-                ++gi;
-                gend = min(end, group_begin(gi + 1));
-            }
-        }
-        const int nb = live ? min(U * R, gend - cur) : 0;
-        const int last = live ? cur + nb - 1 : end - 1;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = cur + u * R + g;
-            const int2 ent = list[min(e, last)];
-            b.x[u] = (live && e <= last) ? ent.y : 0;
-            b.v[u] = load_stream16(lane_base + (size_t)(unsigned)ent.x * row_bytes);
-        }
-        b.rows = nb;
-        b.ends_run = live && cur + nb == gend;
-        const __half *sp = scale_base + (size_t)gi * n;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) b.sc[r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r]);
-        cur += nb;
-    };
-    auto consume = [&](const W4Batch<U> &b) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {             // slots past the end of a run multiply by zero
-            unsigned nib[2][4], B[2][2];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                nib[0][q] = (b.v[u][q] << 4) & 0xF0F0F0F0u;
-                nib[1][q] = b.v[u][q] & 0xF0F0F0F0u;
-            }
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    B[p][q] = __builtin_amdgcn_perm((unsigned)b.x[u], (unsigned)b.x[u], pick[p][q]);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int q = k >> 2, h = (k >> 1) & 1, p = k & 1;
-                sums.v[q][h][p] = mfma_i8(nib[q][2 * h], nib[q][2 * h + 1], B[p][0], B[p][1],
-                                          sums.v[q][h][p]);
-            }
-        }
-        if (!b.ends_run) return;
-        // The lanes l < 8 take the first half of a chunk and give the second to the lane 8 further,
-        // which holds the other digit of a pair.  A column's sum is complete before the group's
-        // scale multiplies it: an infinite scale then gives what it gives the whole sum.
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int pair[2];
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const int first = sums.v[q][0][p][r], second = sums.v[q][1][p][r];
-                    const int own = l < 8 ? first : second, give = l < 8 ? second : first;
-                    const int got = __builtin_amdgcn_update_dpp(0, give, 0x128 /* row_ror:8 */, 0xF,
-                                                                0xF, false);
-                    pair[p] = (int)(((unsigned)own << own_shift) + ((unsigned)got << other_shift));
-                }
-                // the digits of p = 1 weigh 2^16 more
-                const float sum = fmaf((float)pair[1], 65536.f, (float)pair[0]);
-                const __half2 sc = __builtin_bit_cast(__half2, b.sc[r]);
-                acc[q][r] = fmaf(q ? __high2float(sc) : __low2float(sc), sum, acc[q][r]);
-            }
+    auto stream = [&](auto pairs) {
+        constexpr int P = pairs.value;
+        W4Sums<P> sums;
         sums.clear();
-    };
+        // Every call issues exactly U row loads and the four scale loads of the batch's group,
+        // whether or not rows are left: the compiler then knows how many loads are outstanding at
+        // every wait and waits for a batch's own loads only.  (With a conditional scale load and an
+        // early return for an exhausted share it waited for older loads between the loads of a
+        // batch, and little more than one batch was ever in flight.)  A batch past the end of the
+        // share re-reads the share's last row with zero multipliers.
+        auto issue = [&](W4Batch<U, P> &b) {
+            const bool live = cur < end;                  // wavefront-uniform
+            if (live) {
+                while (cur >= gend) {                     // next group with rows in this share
+                    ++gi;
+                    gend = min(end, group_begin(gi + 1));
+                }
+            }
+            const int nb = live ? min(U * R, gend - cur) : 0;
+            const int last = live ? cur + nb - 1 : end - 1;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = cur + u * R + g;
+                const int2 ent = list[min(e, last)];
+                const bool ours = live && e <= last;
+                b.x[u][0] = ours ? ent.y : 0;
+                if constexpr (P == 3) b.x[u][1] = ours ? ent.x : 0;
+                b.v[u] = load_stream16(lane_base + (size_t)((unsigned)ent.x >> 16) * row_bytes);
+            }
+            b.rows = nb;
+            b.ends_run = live && cur + nb == gend;
+            const __half *sp = scale_base + (size_t)gi * n;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b.sc[r] = *reinterpret_cast<const unsigned *>(sp + scale_col[r]);
+            cur += nb;
+        };
+        auto consume = [&](const W4Batch<U, P> &b) {
+#pragma unroll
+            for (int u = 0; u < U; u += 2) {          // slots past the end of a run multiply by zero
+                i32x4 half[2][2], B[P];               // [nibble][h] of two rows
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const unsigned v = b.v[u + i][q];
+                        half[0][q / 2][2 * i + q % 2] = (int)((v << 4) & 0xF0F0F0F0u);
+                        half[1][q / 2][2 * i + q % 2] = (int)(v & 0xF0F0F0F0u);
+                    }
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            const unsigned digits = (unsigned)b.x[u + i][p / 2];
+                            B[p][2 * i + q] = (int)__builtin_amdgcn_perm(digits, digits, pick[p % 2][q]);
+                        }
+#pragma unroll
+                for (int k = 0; k < 4 * P; ++k) {
+                    const int q = k / (2 * P), h = k / P % 2, p = k % P;
+                    sums.v[q][h][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(half[q][h], B[p],
+                                                                            sums.v[q][h][p], 0, 0, 0);
+                }
+            }
+            if (!b.ends_run) return;
+            // The lanes l < 8 take the first half of a chunk and give the second to the lane 8 further,
+            // which holds the other digit of a pair.  A column's sum is complete before the group's
+            // scale multiplies it: an infinite scale then gives what it gives the whole sum.
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    int pair[P];
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const int first = sums.v[q][0][p][r], second = sums.v[q][1][p][r];
+                        const int own = l < 8 ? first : second, give = l < 8 ? second : first;
+                        const int got = __builtin_amdgcn_update_dpp(0, give, 0x128 /* row_ror:8 */, 0xF,
+                                                                    0xF, false);
+                        pair[p] = (int)(((unsigned)own << own_shift) + ((unsigned)got << other_shift));
+                    }
+                    float sum = (float)pair[P - 1];       // each pair weighs 2^16 more than the one before
+#pragma unroll
+                    for (int p = P - 2; p >= 0; --p) sum = fmaf(sum, 65536.f, (float)pair[p]);
+                    const __half2 sc = __builtin_bit_cast(__half2, b.sc[r]);
+                    acc[q][r] = fmaf(q ? __high2float(sc) : __low2float(sc), sum, acc[q][r]);
+                }
+            sums.clear();
+        };
 
-    // Two batches in flight.  The fences keep the compiler from sinking a batch's loads into
-    // the consumption of the batch before it.  (A third batch in flight was measured 2 to 6 %
-    // slower.)
-    if (mine > 0) {                               // wavefront-uniform
-        W4Batch<U> b0, b1;
-        issue(b0);
-        while (b0.rows > 0) {
-            issue(b1);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(b0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (b1.rows <= 0) break;
+        // Two batches in flight.  The fences keep the compiler from sinking a batch's loads into
+        // the consumption of the batch before it.  (A third batch in flight was measured 2 to 6 %
+        // slower.)
+        if (mine > 0) {                               // wavefront-uniform
+            W4Batch<U, P> b0, b1;
             issue(b0);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(b1);
-            __builtin_amdgcn_sched_barrier(0);
+            while (b0.rows > 0) {
+                issue(b1);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(b0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (b1.rows <= 0) break;
+                issue(b0);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(b1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    }
+    };
+    if (magnitude != kModest) stream(std::integral_constant<int, 3>{});
+    else stream(std::integral_constant<int, 2>{});
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
-    const bool finite = largest < 0x7F800000u;
-    const float unit = 0.0625f * (!finite ? __uint_as_float(0x7FC00000u)
-                                  : largest ? FixedDigits::power_of_two(-FixedDigits::shift(largest)) : 0.f);
+    const float unit = magnitude == kInfinite ? __uint_as_float(0x7FC00000u) : 0.0625f * FixedDigits::kUnit;
     float *row = red + share * combine_row<EPL, LPR> + part * PART_COLS + 2 * l;
 #pragma unroll
     for (int r = 0; r < 4; ++r)

@@ -43,12 +43,20 @@ def w4_case(n, m, seed):
     return dev(q), dev(scale), w
 
 
+def w4_bound(m, xk, w):
+    """Exact integer sums per run (a wavefront's rows of a group), put together from three pairs of
+    digits with at most 8 roundings of a term each (the pairs' magnitudes add up to at most 3.02 of
+    the value's: 3.02 for the conversions, 3.02 and 1 for the two sums), then fp32 sums over at most
+    m / 128 runs, 8 wavefronts and 16 splits."""
+    return (8 + m / 128 + 8 + 16) * 2.0 ** -24 * (np.abs(xk)[:, None] * np.abs(w)).sum(0)
+
+
 @pytest.mark.parametrize("kind", ["mixed range", "subnormal", "one", "equal", "large", "ends"])
 @pytest.mark.parametrize("m,n", [(128, 32), (512, 544), (1152, 1056), (4096, 1024), (2048, 28672)])
 def test_w4_integer_activations(T, kind, m, n):   # noqa: F811
-    """The int4 kernel's activations are integers in units of the slice's largest: values over all
-    of fp16's range, subnormals alone, a single survivor, equal values, and survivors only at the
-    ends of the 128-channel groups; slices of one and of several passes, both tile widths."""
+    """The int4 kernel's activations are integers in units of 2^-24: values over all of fp16's range,
+    subnormals alone, a single survivor, equal values, and survivors only at the ends of the
+    128-channel groups; slices of one and of several passes, both tile widths."""
     rng = np.random.default_rng(m + n)
     q, scale, w = w4_case(n, m, 9900 + m + n)
     x = rng.standard_normal(m)
@@ -76,11 +84,7 @@ def test_w4_integer_activations(T, kind, m, n):   # noqa: F811
     T.check(T.teal_sparse_gemv_w4(q, scale, 128, dev(x), t, y, m, n, ws))
     torch.cuda.synchronize()
     assert survivors(T, ws) == [int(kept.sum())]
-    # the integers are within 2^-31 of the largest activation's power of two, and the group sums
-    # are added in fp32
-    bound = (2.0 ** -30 * np.abs(xk).max() * np.abs(w[kept]).sum(0) +
-             (2 + m / 128) * 2.0 ** -24 * (np.abs(xk)[:, None] * np.abs(w)).sum(0))
-    assert np.all(np.abs(y.cpu().numpy() - xk @ w) <= bound)
+    assert np.all(np.abs(y.cpu().numpy() - xk @ w) <= w4_bound(m, xk, w))
 
 
 def test_w4_infinite_activation_gives_nan(T):   # noqa: F811
@@ -114,3 +118,67 @@ def test_w4_infinite_scale_gives_the_sign_of_its_sum(T, m, n):   # noqa: F811
     assert np.array_equal(got[hit], np.where(np.arange(n) % 2, -np.inf, np.inf)[hit].astype(np.float32))
     want = x.astype(np.float64) @ (q * np.repeat(scale.astype(np.float64), 128, 0))[:, ~hit]
     assert rel_l2(got[~hit], want) <= TIGHT
+
+
+@pytest.mark.parametrize("large", [127.0, -127.0625, 128.0, -2000.0, 65504.0])
+@pytest.mark.parametrize("m,n", [(128, 32), (640, 544), (4096, 1056), (2048, 28672)])
+def test_w4_small_activations_beside_a_large_one(T, large, m, n):   # noqa: F811
+    """Four digits up to 127, six beyond: one large activation whose weights are zero in some columns,
+    or whose group's scale is, must leave the other activations' products in those columns as
+    exact as they are without it (a bound per column, from that column's own terms)."""
+    rng = np.random.default_rng(n + int(abs(large)))
+    q, scale = ti.quantize_w4(ti.weights_bf16(n, m, 9960 + m))
+    q, scale = q.copy(), scale.copy()
+    at = m - 77
+    q[at, : n // 4] = 0                                 # columns 0 .. n / 2
+    scale[at // 128, n // 2 + 5:: 3] = 0
+    b = q.view(np.int8)
+    w = np.stack([(b << 4).astype(np.int8) >> 4, b >> 4], axis=2).reshape(m, n).astype(np.float64)
+    w *= np.repeat(scale.astype(np.float64), 128, axis=0)
+    for spread in (0.01, 2.0 ** -22):
+        x = (rng.standard_normal(m) * spread).astype(np.float16)
+        x[at] = large
+        y = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+        T.check(T.teal_sparse_gemv_w4(dev(q), dev(scale), 128, dev(x), 0.0, y, m, n, ws))
+        torch.cuda.synchronize()
+        assert survivors(T, ws) == [int(np.count_nonzero(x))]
+        xd = x.astype(np.float64)
+        assert np.all(np.abs(y.cpu().numpy() - xd @ w) <= w4_bound(m, xd, w)), spread
+
+
+@pytest.mark.parametrize("m", [512, 4096])
+def test_w4_fused_calls_with_large_activations_are_the_plain_calls(T, m):   # noqa: F811
+    """Six digits where the input is formed in the kernel: bitwise the producer kernel followed by
+    the plain call, with a few activations far beyond 127."""
+    rng = np.random.default_rng(m)
+    ns = [1056, 544]
+    mats = [ti.quantize_w4(ti.weights_bf16(n, m, 9970 + n), 128) for n in ns]
+    qd, sd = [dev(q) for q, _ in mats], [dev(s) for _, s in mats]
+    h = rng.standard_normal(m).astype(np.float32)
+    h[::97] *= 40
+    gamma = np.full(m, 60.0, np.float32)
+    up = (rng.standard_normal(m) * 30).astype(np.float32)
+    gate = (rng.standard_normal(m) * 4).astype(np.float32)
+    up[::101] = 900.0
+    gate[::101] = 9.0
+    hd, gd, ud, ad = dev(h), dev(gamma), dev(up), dev(gate)
+    ws = torch.zeros(T.teal_workspace_bytes(m, sum(ns)), dtype=torch.uint8, device="cuda")
+    xd = torch.empty(m, dtype=torch.int16, device="cuda")
+    ys = [[torch.empty(n, dtype=torch.float32, device="cuda") for n in ns] for _ in range(2)]
+    T.check(T.teal_rmsnorm_f16(hd, gd, 1e-5, xd, m))
+    T.check(T.teal_sparse_gemv_w4_multi(qd, sd, 128, [5.0, 0.0], ys[0], ns, xd, m, ws))
+    T.check(T.teal_sparse_gemv_w4_rmsnorm_multi(qd, sd, 128, [5.0, 0.0], ys[1], ns, hd, gd, 1e-5, m, ws))
+    torch.cuda.synchronize()
+    x = xd.cpu().numpy().view(np.float16)
+    assert np.abs(x).max() > 200
+    for k, n in enumerate(ns):
+        assert torch.equal(ys[0][k], ys[1][k])
+        want = orc.sparse_gemv_w4(mats[k][0], mats[k][1], 128, x, [5.0, 0.0][k])
+        assert rel_l2(ys[0][k].cpu().numpy(), want) <= TIGHT
+    T.check(T.teal_swiglu_f16(ad, ud, xd, m))
+    T.check(T.teal_sparse_gemv_w4(qd[0], sd[0], 128, xd, 1.0, ys[0][0], m, ns[0], ws))
+    T.check(T.teal_sparse_gemv_w4_swiglu(qd[0], sd[0], 128, ad, ud, 1.0, ys[1][0], m, ns[0], ws))
+    torch.cuda.synchronize()
+    assert xd.view(torch.float16).abs().max().item() > 2000
+    assert torch.equal(ys[0][0], ys[1][0])
