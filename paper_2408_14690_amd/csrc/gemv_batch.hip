@@ -446,13 +446,16 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     const bool vec = (m & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 7) == 0;
 #define TEAL_COMPACT(VEC, PASSES)                                                                \
     compact_slice_batch<NB, WAVES, VEC, PASSES>(X, batch, m, bound, k0, k1, list_idx, smem, seg_cnt)
-    const int cnt = len <= kLanes               ? TEAL_COMPACT(1, 1)
-                    : !vec && len <= 2 * kLanes ? TEAL_COMPACT(1, 2)
-                    : !vec && len <= 4 * kLanes ? TEAL_COMPACT(1, 4)
-                    : !vec                      ? TEAL_COMPACT(1, kMaxLongSliceBatch / kLanes)
-                    : len <= 2 * kLanes         ? TEAL_COMPACT(2, 1)
-                    : len <= 4 * kLanes         ? TEAL_COMPACT(4, 1)
-                                                : TEAL_COMPACT(4, kMaxLongSliceBatch / (4 * kLanes));
+    int cnt;
+    if (len <= kLanes) cnt = TEAL_COMPACT(1, 1);
+    else if (vec)
+        cnt = len <= 2 * kLanes   ? TEAL_COMPACT(2, 1)
+              : len <= 4 * kLanes ? TEAL_COMPACT(4, 1)
+                                  : TEAL_COMPACT(4, kMaxLongSliceBatch / (4 * kLanes));
+    else
+        cnt = len <= 2 * kLanes   ? TEAL_COMPACT(1, 2)
+              : len <= 4 * kLanes ? TEAL_COMPACT(1, 4)
+                                  : TEAL_COMPACT(1, kMaxLongSliceBatch / kLanes);
 #undef TEAL_COMPACT
 
     trace_mark(2);
