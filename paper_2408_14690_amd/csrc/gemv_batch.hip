@@ -531,7 +531,6 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
 }
 
 constexpr int kBatchWaves = 8;
-constexpr int kBatchUnroll = 4;      // what the launch-shape rule fills in; the kernel loads 8 rows per chunk
 
 // One block thresholds the batch like sparsify_kernel does one vector: groups of 4 chunks
 // of 1024 channels, the loads of a group (all batch rows) in flight together.
@@ -689,8 +688,7 @@ bool gemv_batch_shape_supported(int batch, const GemvShape &s)
     const bool tc = s.tile_cols >= 0 && s.tile_cols % 8 == 0 && s.tile_cols <= s.lanes_per_row * 8;
     // (the limit of the documented interface; see batch_tile for the width a launch runs in)
     const bool fits = nb * s.lanes_per_row <= 256;
-    return lpr && tc && fits && s.waves == kBatchWaves && s.unroll == kBatchUnroll &&
-           s.splits >= 1;
+    return lpr && tc && fits && s.waves == kBatchWaves && s.splits >= 1;
 }
 
 // At one or two rows a block takes tiles of up to 512 columns, else of at most kBatchTile; a wider
@@ -805,20 +803,5 @@ hipError_t launch_sparsify_batch(const void *X_f16, int batch, int m, float t, u
 }  // namespace teal
 
 #ifdef TEAL_TRACE_BLOCKS
-// The trace build's read-out for the kernels of this file (see trace_mark in gemv_common.h).
-extern "C" int teal_trace_read_batch(unsigned long long *host, size_t count)
-{
-    const size_t all = (size_t)teal::kTraceBlocks * teal::kTraceMarks;
-    if (!host || count > all) return 1;
-    if (hipDeviceSynchronize() != hipSuccess) return 2;
-    if (hipMemcpyFromSymbol(host, HIP_SYMBOL(teal::teal_trace),
-                            count * sizeof(unsigned long long)) != hipSuccess)
-        return 3;
-    static unsigned long long zeros[4096];
-    for (size_t at = 0; at < all; at += 4096)
-        if (hipMemcpyToSymbol(HIP_SYMBOL(teal::teal_trace), zeros, sizeof(zeros),
-                              at * sizeof(unsigned long long)) != hipSuccess)
-            return 4;
-    return 0;
-}
+extern "C" int teal_trace_read_batch(unsigned long long *host, size_t count) { return teal::read_trace(host, count); }
 #endif

@@ -27,7 +27,7 @@ constexpr int kMaxSegs = kMaxSlice / 64;   // 64-channel segments per slice
 // Measurement aid, compiled in only with -DTEAL_TRACE_BLOCKS (a separate build of the library
 // used to look at where the time of a launch goes; the library proper contains none of it):
 // thread 0 of a block leaves the 100 MHz device clock at up to 8 marks in a device array (one
-// per source file; teal_trace_read copies out that of the bf16 kernels).
+// per source file, read out by teal_trace_read, teal_trace_read_wq, teal_trace_read_batch).
 #ifdef TEAL_TRACE_BLOCKS
 constexpr int kTraceBlocks = 8192, kTraceMarks = 8;
 static __device__ unsigned long long teal_trace[kTraceBlocks * kTraceMarks];
@@ -40,6 +40,23 @@ __device__ __forceinline__ void trace_mark_thread(int slot, int thread)
 {
     if ((int)threadIdx.x == thread && blockIdx.x < kTraceBlocks)
         teal_trace[blockIdx.x * kTraceMarks + slot] = wall_clock64();
+}
+// Copies the marks of the including file's kernels to HOST memory after synchronising the
+// device, and clears them.
+[[maybe_unused]] static int read_trace(unsigned long long *host, size_t count)
+{
+    const size_t all = (size_t)kTraceBlocks * kTraceMarks;
+    if (!host || count > all) return 1;
+    if (hipDeviceSynchronize() != hipSuccess) return 2;
+    if (hipMemcpyFromSymbol(host, HIP_SYMBOL(teal_trace), count * sizeof(unsigned long long)) !=
+        hipSuccess)
+        return 3;
+    static unsigned long long zeros[4096];
+    for (size_t at = 0; at < all; at += 4096)
+        if (hipMemcpyToSymbol(HIP_SYMBOL(teal_trace), zeros, sizeof(zeros),
+                              at * sizeof(unsigned long long)) != hipSuccess)
+            return 4;
+    return 0;
 }
 #else
 __device__ __forceinline__ void trace_mark(int) {}

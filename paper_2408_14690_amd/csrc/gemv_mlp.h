@@ -105,8 +105,9 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
         const int k = blk.kind;
         const bool wrote = Body::template run<LPR_GU>(
             A.a_gu[k], HalfSource{A.x}, A.t_gu[k], A.partial_gu + (size_t)k * g.splits_gu * g.f,
-            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu), A.y_gu[k], A.m, g.f, A.ks_gu, blk.tile, blk.split,
-            g.tile_cols_gu, g.splits_gu, survivor_report(A.counters_gu, k, g.splits_gu));
+            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu), A.y_gu[k], A.m,
+            g.f, A.ks_gu, blk.tile, blk.split, g.tile_cols_gu, g.splits_gu,
+            survivor_report(A.counters_gu, k, g.splits_gu));
         trace_mark(6);
         if (!wrote) return;
         // The tile's columns of gate / up are written (write-through stores): once every
@@ -152,8 +153,8 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
 
     const bool wrote = Body::template run<LPR_D>(
         A.a_d, SwigluReadySource{A.y_gu[0], A.y_gu[1]}, A.t_d, A.partial_d,
-        tile_counter(A.counters_d, blk.tile, g.tiles_d), A.y_d, g.f, A.n_d, g.ks_d, blk.tile, blk.split, A.tile_cols_d, g.splits_d,
-        survivor_report(A.counters_d, 0, g.splits_d));
+        tile_counter(A.counters_d, blk.tile, g.tiles_d), A.y_d, g.f, A.n_d, g.ks_d, blk.tile,
+        blk.split, A.tile_cols_d, g.splits_d, survivor_report(A.counters_d, 0, g.splits_d));
     trace_mark(6);
     (void)wrote;
 }
