@@ -49,10 +49,16 @@ def run_calibration(T, torch, args) -> int:
              ("mlp_in", d, "gaussian"), ("mlp_mid", d_ff, "laplace")]
     samples, hists, ts = [], [], []
     for k, (_, width, dist) in enumerate(sites):
-        # one seeded row block of 64 tokens, tiled: the kernel's work does not depend on repeats
-        base = ti.make_x(64 * width, 7000 + k, dist)
-        xd = torch.from_numpy(base.view(np.int16)).cuda().repeat(tokens // 64)
-        samples.append(xd)
+        # every value drawn: a sample tiled from a short one gives a block few distinct values, and
+        # the flush of its counters is a third of the kernel's time
+        g = torch.Generator(device="cuda")
+        g.manual_seed(7000 + k)
+        if dist == "gaussian":
+            x = torch.randn(tokens * width, generator=g, device="cuda")
+        else:
+            u = torch.rand(tokens * width, generator=g, device="cuda") - 0.4999999
+            x = -torch.sign(u) * torch.log1p(-2 * u.abs())
+        samples.append(x.half().view(torch.int16))
         hists.append(torch.zeros(T.TEAL_HIST_BINS, dtype=torch.int64, device="cuda"))
         ts.append(torch.zeros(len(CALIBRATION_LEVELS), dtype=torch.float32, device="cuda"))
     counts = [x.numel() for x in samples]
