@@ -47,7 +47,7 @@ hipError_t launch_gemv_bf16(const void *Wt, const void *x_f16, float t, float *y
     do {                                                                                       \
         if (!allow_large_lds(sparse_gemv_kernel<F, LPR, WAVES, U>, g.lds))                     \
             return hipErrorInvalidValue;                                                       \
-        hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles * g.splits),   \
+        hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits),   \
                            dim3(WAVES * 64), g.lds, stream, a, x, t, partial, counters, y, m,  \
                            n, g.ks, g.tiles, g.tile_cols, g.splits);                           \
     } while (0)
@@ -63,7 +63,7 @@ hipError_t launch_gemv_bf16_swiglu(const void *Wt, const float *gate, const floa
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtBF16::kElemsPerLane, 64);
     FmtBF16::Args a{Wt};
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
-    hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<F, LPR, WAVES, U>), dim3(g.tiles * g.splits), \
+    hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits), \
                        dim3(WAVES * 64), g.lds, stream, a, gate, up, t, partial, counters, y,  \
                        m, n, g.ks, g.tiles, g.tile_cols, g.splits)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtBF16, sh);
@@ -99,7 +99,7 @@ hipError_t launch_gemv_bf16_multi(int count, const void *const *Wt, const int *r
         if (!allow_large_lds(sparse_gemv_multi_kernel<F, LPR, WAVES, U>, g.lds))               \
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_multi_kernel<F, LPR, WAVES, U>),                       \
-                           dim3(tiles * g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
+                           dim3(tiles, g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
                            partial, counters, m, g.ks, g.tile_cols, g.splits);                 \
     } while (0)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtBF16, sh);
@@ -150,7 +150,7 @@ hipError_t launch_gemv_bf16_rmsnorm_multi(int count, const void *const *Wt, cons
         if (!allow_large_lds(sparse_gemv_rmsnorm_multi_kernel<FmtBF16, LPR, 4>, g.lds))        \
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtBF16, LPR, 4>),                \
-                           dim3(tiles * g.splits), dim3(kNormWaves * 64), g.lds, stream, ma,   \
+                           dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma,   \
                            h, gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits);  \
     } while (0)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);

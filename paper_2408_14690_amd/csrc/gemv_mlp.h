@@ -43,6 +43,12 @@ struct SwigluReadySource {
     {
         return make_float2(load_coherent(gate + i), load_coherent(up + i));
     }
+    __device__ __forceinline__ bool run_aligned() const { return true; }
+    template <int E>
+    __device__ __forceinline__ void load_run(Raw (&raw)[E], int k0, int len, int at) const
+    {
+        pairs_of_slice<E, 16>(raw, gate, up, k0, len, at);
+    }
     __device__ __forceinline__ float prepare() const { return 0.f; }
     __device__ __forceinline__ float value(Raw r, float) const { return swiglu_value(r.x, r.y); }
 };

@@ -163,26 +163,27 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     extern __shared__ __align__(16) unsigned char smem[];
     int2 *list = reinterpret_cast<int2 *>(smem);
     float *red = reinterpret_cast<float *>(smem + (size_t)ks * sizeof(int2));
-    __shared__ int seg_cnt[kMaxSegs + WAVES];
+    __shared__ int counts[kCompactInts];
 
+    asm volatile("" ::"s"(a.W), "s"(a.scale), "s"(partial), "s"(counter), "s"(y));   // as in gemv_block
     const int k0 = s * ks;                       // multiple of 128
     const int k1 = min(m, k0 + ks);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = w % PARTS, share = w / PARTS;
-    int seg_excl;
-    int cnt;
-    int magnitude;
+    int group_excl;                    // lane j: where group j of the slice begins in the list
+    int cnt = 0;
+    int magnitude = kModest;
+    bool compacted = false;
     if constexpr (XS::kPlainHalf) {
-        if (k1 - k0 <= 8 * 64)         // block-uniform: short slices need no barrier
-            cnt = compact_slice_private<8, FixedDigits>(x.x, t, k0, k1, share, SHARES, list, seg_excl,
-                                                        &magnitude);
-        else
-            cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl,
-                                                        nullptr, false, &magnitude);
-    } else {
-        cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, seg_cnt, seg_excl, nullptr,
-                                                    false, &magnitude);
+        if (k1 - k0 <= kPrivateSlice) {         // block-uniform: short slices need no barrier
+            cnt = compact_slice_private<FixedDigits>(x.x, t, k0, k1, share, SHARES, list, group_excl,
+                                                     &magnitude);
+            compacted = true;
+        }
     }
+    if (!compacted)
+        cnt = compact_slice<WAVES, XS, FixedDigits>(x, t, k0, k1, list, counts, group_excl, nullptr, false,
+                                                    &magnitude);
 
     trace_mark(2);
     const int lane = threadIdx.x & 63;
@@ -222,11 +223,8 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     wave_share(cnt, share, SHARES, start, mine);
     // Walk state (all wavefront-uniform): next list position, end of the share, current
     // group of the slice and the end of this wavefront's rows in it.
-    // list offset at which group j of the slice begins: the prefix of segment 2j (lanes past
-    // the last segment hold the total)
-    auto group_begin = [&](int j) {
-        return 2 * j < 64 ? __builtin_amdgcn_readlane(seg_excl, 2 * j) : cnt;
-    };
+    // list offset at which group j of the slice begins (past the last group: the total)
+    auto group_begin = [&](int j) { return __builtin_amdgcn_readlane(group_excl, j); };
     int cur = start;
     const int end = start + mine;
     int gi = 0, gend = min(end, group_begin(1));
@@ -360,9 +358,9 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_kernel(
     int m, int n, int ks, int tiles, int tile_cols, int splits)
 {
     trace_mark(0);
-    const int tile = blockIdx.x % tiles;
+    const int tile = blockIdx.x;
     w4_block<LPR, WAVES, U>(a, HalfSource{x}, t, partial, tile_counter(counters, tile, tiles), y,
-                            m, n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
+                            m, n, ks, tile, blockIdx.y, tile_cols, splits,
                             survivor_report(counters, 0, splits));
     trace_mark(6);
 }
@@ -376,10 +374,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_swiglu_kernel(
     int splits)
 {
     trace_mark(0);
-    const int tile = blockIdx.x % tiles;
+    const int tile = blockIdx.x;
     w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
                             tile_counter(counters, tile, tiles), y, m, n, ks, tile,
-                            blockIdx.x / tiles, tile_cols, splits,
+                            blockIdx.y, tile_cols, splits,
                             survivor_report(counters, 0, splits));
 }
 
@@ -388,12 +386,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_swiglu_kernel(
 template <int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const XS &x,
                                                float *partial, int *counters, int m, int ks,
-                                               int tile_cols, int splits, int block)
+                                               int tile_cols, int splits, int gtile, int s)
 {
     trace_mark(0);
     const int tiles = ma.tile_begin[ma.count];
-    const int gtile = block % tiles;
-    const int s = block / tiles;
     int k = 0;
     size_t partial_off = 0;
 #pragma unroll
@@ -416,7 +412,7 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_multi_kernel(
     int ks, int tile_cols, int splits)
 {
     w4_multi_block<LPR, WAVES, U>(ma, HalfSource{x}, partial, counters, m, ks, tile_cols, splits,
-                                  (int)blockIdx.x);
+                                  (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // The grouped int4 launch with its shared input formed from the hidden state before the
@@ -428,7 +424,7 @@ __global__ __launch_bounds__(kNormWaves * 64) void sparse_gemv_w4_rmsnorm_multi_
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
     w4_multi_block<LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, eps, wave_sums}, partial,
-                                       counters, m, ks, tile_cols, splits, (int)blockIdx.x);
+                                       counters, m, ks, tile_cols, splits, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // Independent int4 groups in one launch (see sparse_gemv_stack_kernel).
@@ -437,12 +433,13 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_stack_kernel(StackA
 {
     int block;
     const StackGroup<FmtW4> &sg = sa.g[stack_group_of_block(sa, block)];
+    const int tiles = sg.ma.tile_begin[sg.ma.count], gtile = block % tiles, s = block / tiles;
     if (sg.lanes_per_row == 32)
         w4_multi_block<32, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.counters, sg.m, sg.ks,
-                                     sg.tile_cols, sg.splits, block);
+                                     sg.tile_cols, sg.splits, gtile, s);
     else
         w4_multi_block<16, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.counters, sg.m, sg.ks,
-                                     sg.tile_cols, sg.splits, block);
+                                     sg.tile_cols, sg.splits, gtile, s);
 }
 
 hipError_t launch_gemv_w8_stack(int groups, const StackGroupDesc *d, hipStream_t stream)
@@ -483,7 +480,7 @@ hipError_t launch_gemv_w8(const int8_t *Wq, const void *scale_f16, const void *x
     FmtW8::Args a{Wq, static_cast<const __half *>(scale_f16)};
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
-    hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles * g.splits), \
+    hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits), \
                        dim3(WAVES * 64), g.lds, stream, a, x, t, partial, counters, y, m, n,   \
                        g.ks, g.tiles, g.tile_cols, g.splits)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtW8, sh);
@@ -519,7 +516,7 @@ hipError_t launch_gemv_w8_multi(int count, const int8_t *const *Wq, const int *r
         if (!allow_large_lds(sparse_gemv_multi_kernel<F, LPR, WAVES, U>, g.lds))               \
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_multi_kernel<F, LPR, WAVES, U>),                       \
-                           dim3(tiles * g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
+                           dim3(tiles, g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
                            partial, counters, m, g.ks, g.tile_cols, g.splits);                 \
     } while (0)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtW8, sh);
@@ -545,7 +542,7 @@ hipError_t launch_gemv_w8_swiglu(const int8_t *Wq, const void *scale_f16, const 
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtW8::kElemsPerLane, 64);
     FmtW8::Args a{Wq, static_cast<const __half *>(scale_f16)};
 #define TEAL_LAUNCH_S(LPR)                                                                     \
-    hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<FmtW8, LPR, 8, 4>), dim3(g.tiles * g.splits), \
+    hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<FmtW8, LPR, 8, 4>), dim3(g.tiles, g.splits), \
                        dim3(8 * 64), g.lds, stream, a, gate, up, t, partial, counters, y, m, n, \
                        g.ks, g.tiles, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_S(64);
@@ -583,7 +580,7 @@ hipError_t launch_gemv_w8_rmsnorm_multi(int count, const int8_t *const *Wq, cons
     const int tiles = ma.tile_begin[count];
 #define TEAL_LAUNCH_N(LPR)                                                                     \
     hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtW8, LPR, 4>),                      \
-                       dim3(tiles * g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
+                       dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
                        gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_N(32);
@@ -604,7 +601,7 @@ hipError_t launch_gemv_w4(const uint8_t *Wq, const void *scale_f16, const void *
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH_W4(LPR)                                                                    \
     hipLaunchKernelGGL((sparse_gemv_w4_kernel<LPR, kW4Waves, kW4Unroll>),                      \
-                       dim3(g.tiles * g.splits), dim3(kW4Waves * 64), g.lds, stream, a, x, t,  \
+                       dim3(g.tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, a, x, t,  \
                        partial, counters, y, m, n, g.ks, g.tiles, g.tile_cols, g.splits)
     // A lane covers 32 columns: 16 lanes per row (tiles up to 512 columns) or 32 lanes
     // per row (up to 1024 columns).
@@ -624,7 +621,7 @@ hipError_t launch_gemv_w4_swiglu(const uint8_t *Wq, const void *scale_f16, const
     FmtW4::Args a{Wq, static_cast<const __half *>(scale_f16)};
 #define TEAL_LAUNCH_W4S(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_swiglu_kernel<LPR, kW4Waves, kW4Unroll>),               \
-                       dim3(g.tiles * g.splits), dim3(kW4Waves * 64), g.lds, stream, a, gate,  \
+                       dim3(g.tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, a, gate,  \
                        up, t, partial, counters, y, m, n, g.ks, g.tiles, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4S(32);
     else TEAL_LAUNCH_W4S(16);
@@ -659,7 +656,7 @@ hipError_t launch_gemv_w4_rmsnorm_multi(int count, const uint8_t *const *Wq,
     const int tiles = ma.tile_begin[count];
 #define TEAL_LAUNCH_W4N(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_rmsnorm_multi_kernel<LPR, kW4Unroll>),                  \
-                       dim3(tiles * g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
+                       dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
                        gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4N(32);
     else TEAL_LAUNCH_W4N(16);
@@ -692,7 +689,7 @@ hipError_t launch_gemv_w4_multi(int count, const uint8_t *const *Wq, const void 
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH_W4M(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_multi_kernel<LPR, kW4Waves, kW4Unroll>),                \
-                       dim3(tiles * g.splits), dim3(kW4Waves * 64), g.lds, stream, ma, x,      \
+                       dim3(tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, ma, x,      \
                        partial, counters, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4M(32);
     else TEAL_LAUNCH_W4M(16);
