@@ -138,14 +138,14 @@ __device__ __forceinline__ SurvivorReport survivor_report(int *counters_base, in
     return SurvivorReport{area + matrix, area + kReportHeaderInts + matrix * splits};
 }
 
-// Called by thread 0 of a block of tile 0 before the block's arrival (or instead of it
+// Called by one thread of a block of tile 0 before the block's arrival (or instead of it
 // when there is one split).
 __device__ __forceinline__ void report_slice(const SurvivorReport &r, int s, int splits, int cnt)
 {
     store_coherent(splits == 1 ? r.total : r.per_split + s, cnt);
 }
 
-// Called by the first wavefront of the block that arrived last at tile 0.
+// Called by one wavefront of the block that arrived last at tile 0.
 __device__ __forceinline__ void report_total(const SurvivorReport &r, int splits)
 {
     const int lane = threadIdx.x & 63;
@@ -871,8 +871,7 @@ template <class F, int LPR, int WAVES, int SUMS = WAVES>
 __device__ __forceinline__ bool block_finish(float *red,
                                              float *partial, int *counter, float *y, int tile,
                                              int col0, int cols, int s, int splits, int n,
-                                             const typename F::Args &a, int cnt,
-                                             const SurvivorReport &report)
+                                             const typename F::Args &a, const SurvivorReport &report)
 {
     constexpr int EPL = F::kElemsPerLane;
     constexpr int TN = LPR * EPL;
@@ -890,7 +889,6 @@ __device__ __forceinline__ bool block_finish(float *red,
     __syncthreads();                   // every wavefront has left its sums in red[]
     trace_mark(7);
     constexpr int ROW = combine_row<EPL, LPR>;
-    if (tile == 0 && threadIdx.x == 0) report_slice(report, s, splits, cnt);
     if (splits == 1) {
 #pragma unroll
         for (int k = 0; k < OWN; ++k) {
@@ -931,7 +929,9 @@ __device__ __forceinline__ bool block_finish(float *red,
     __syncthreads();
     trace_mark(5);
     if (!last_flag) return false;
-    if (tile == 0 && w == 0) report_total(report, splits);
+    // (by a wavefront that has no columns where there is one: ahead of the first wavefront's partial rows
+    // its loads made tile 0 the last to end, 1.0 us after its ticket against 0.76 for the others)
+    if (tile == 0 && w == WAVES - 1) report_total(report, splits);
 
     // Second pass.  A thread owns a column and adds its partial rows in split order (a fixed
     // order, whichever block happens to be last), up to 16 loads in flight at once.  (Spreading
@@ -1013,6 +1013,7 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     }
 
     trace_mark(2);
+    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int start, mine;
@@ -1032,7 +1033,7 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     trace_mark_thread(1, (WAVES - 1) * 64);
     store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
     return block_finish<F, LPR, WAVES>(red, partial, counter, y, tile, col0, tile_cols, s, splits,
-                                       n, a, cnt, report);
+                                       n, a, report);
 }
 
 // One matrix per launch.  Grid: tiles x splits blocks (two dimensions: a division of the block index

@@ -186,6 +186,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
                                                     &magnitude);
 
     trace_mark(2);
+    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int lane = threadIdx.x & 63;
     const int l = lane & 15, g = lane >> 4;
     const int col0 = tile * tile_cols;
@@ -349,7 +350,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
         *reinterpret_cast<float2 *>(row + EPL * (4 * g + r)) =
             make_float2(acc[0][r] * unit, acc[1][r] * unit);
     return block_finish<F, LPR, WAVES, SHARES>(red, partial, counter, y, tile, col0, tile_cols, s,
-                                               splits, n, a, cnt, report);
+                                               splits, n, a, report);
 }
 
 template <int LPR, int WAVES, int U>

@@ -49,7 +49,7 @@ def test_thresholds_between_and_beyond_fp16_values(T, m):   # noqa: F811
     bits[:12] = [0, 0x8000, 1, 0x8001, 2, 0x3FF, 0x400, 0x7BFF, 0xFBFF, 0x7C00, 0xFC00, 0x7E00]
     x = bits.view(np.float16)
     for t in (0.0, 2.0 ** -30, 2.0 ** -24, 1.5 * 2.0 ** -24, 2.0 ** -14, 1.0, 1.00048828125, float(np.float32(1.0004)),
-              65504.0, 65519.0, 65536.0, 1e30):
+              65504.0, 65519.0, 65536.0, 2.0 ** 100):
         run_bf16(T, wt, dev(x), t, m, n, ws, splits=1)
         assert survivors(T, ws) == [orc.sparsify(x, t)[3]], t
 
