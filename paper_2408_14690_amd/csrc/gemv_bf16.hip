@@ -12,6 +12,15 @@ struct FmtBF16 {
         const void *W;
         int ld = 0;             // elements from one row of W to the next; 0 = n
     };
+    static __device__ __forceinline__ void read_now(const Args (&a)[4])
+    {
+        asm volatile("" ::"s"(a[0].ld), "s"(a[1].ld), "s"(a[2].ld), "s"(a[3].ld));
+    }
+    static __device__ __forceinline__ void select(Args &a, const Args &b, bool take)
+    {
+        a.W = take ? b.W : a.W;
+        a.ld = take ? b.ld : a.ld;
+    }
     // bf16 -> fp32 is a 16-bit shift; bf16 * fp16 is exact in fp32 (8 + 11 significand bits).
     static __device__ __forceinline__ void fma(float (&acc)[8], u32x4 v, float xv)
     {
@@ -151,7 +160,7 @@ hipError_t launch_gemv_bf16_rmsnorm_multi(int count, const void *const *Wt, cons
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtBF16, LPR, 4>),                \
                            dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma,   \
-                           h, gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits);  \
+                           h, gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits);  \
     } while (0)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_N(32);

@@ -173,64 +173,50 @@ __device__ __forceinline__ Buffer buffer_of(const void *first, unsigned bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(first), 0, (int)bytes, 0x00027000);
 }
-// WORDS consecutive 32-bit words `offset` bytes into the buffer (offset and its address multiples of
-// 4).  CACHE: cache policy bits of the load, 16 = past the local L2 (agent scope).
-template <int WORDS, int CACHE = 0>
-__device__ __forceinline__ void buffer_words(unsigned (&w)[WORDS], Buffer b, int offset)
-{
-    if constexpr (WORDS == 1) {
-        w[0] = __builtin_amdgcn_raw_buffer_load_b32(b, offset, 0, CACHE);
-    } else if constexpr (WORDS == 2) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(b, offset, 0, CACHE);
-        w[0] = v[0];
-        w[1] = v[1];
-    } else {
-#pragma unroll
-        for (int q = 0; q < WORDS / 4; ++q) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(b, offset + 16 * q, 0, CACHE);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) w[4 * q + k] = v[k];
-        }
-    }
-}
-// E consecutive pairs (a[i], b[i]) of fp32 vectors, from channel `at` of a slice of `len` that begins
-// at channel k0; zeros past its end.
+// E pairs (a[i], b[i]) of fp32 vectors 64 channels apart, from channel `at` of a slice of `len` that begins at
+// channel k0; zeros past its end.  CACHE: cache policy bits of the loads, 16 = past the local L2 (agent scope).
 template <int E, int CACHE = 0>
 __device__ __forceinline__ void pairs_of_slice(float2 (&raw)[E], const float *a, const float *b, int k0,
                                                int len, int at)
 {
-    unsigned va[E], vb[E];
-    buffer_words<E, CACHE>(va, buffer_of(a + k0, 4u * len), 4 * at);
-    buffer_words<E, CACHE>(vb, buffer_of(b + k0, 4u * len), 4 * at);
+    const Buffer va = buffer_of(a + k0, 4u * len), vb = buffer_of(b + k0, 4u * len);
 #pragma unroll
-    for (int e = 0; e < E; ++e) raw[e] = make_float2(__uint_as_float(va[e]), __uint_as_float(vb[e]));
+    for (int j = 0; j < E; ++j) {
+        raw[j].x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(va, 4 * at + 256 * j, 0, CACHE));
+        raw[j].y = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vb, 4 * at + 256 * j, 0, CACHE));
+    }
 }
 
-// Where a block's activations come from.  A source loads what it needs for
-// channel i (load) or for E consecutive channels of a slice (load_run, where run_aligned() says that
-// its vectors allow that) and turns it into an fp32 value that is exactly an fp16 value
-// (value); kHeavy says that value() is worth skipping for segments past the slice.
+// Where a block's activations come from.  A source loads what it needs for E channels of a
+// slice that lie 64 apart (load; zeros past the slice's end) and turns it into an fp32 value that is
+// exactly an fp16 value (value; zero for zeros); kHeavy says that value() is worth skipping for segments past the slice.
 // Between the loads and the first value() every thread of the block calls prepare()
 // once: block-wide work whose result value() needs (it may contain barriers) runs
 // there, with the slice's own loads already in flight.
+// The largest fp16 value that is not above t (t >= 0): an fp16 magnitude is above t exactly if it is
+// above this, so an fp16 state is compared as it is.
+__device__ __forceinline__ _Float16 half_threshold(float t)
+{
+    return __builtin_bit_cast(_Float16, __builtin_amdgcn_cvt_pkrtz(fminf(t, 65504.f), 0.f)[0]);
+}
+
 struct HalfSource {                   // the hidden state itself, fp16 in memory
     static constexpr bool kHeavy = false;
     static constexpr bool kPlainHalf = true;
-    typedef __half Raw;
+    typedef _Float16 Raw;
+    typedef _Float16 Compared;
+    static __device__ __forceinline__ _Float16 threshold(float t) { return half_threshold(t); }
     const __half *x;
-    __device__ __forceinline__ Raw load(int i) const { return x[i]; }
-    __device__ __forceinline__ bool run_aligned() const { return (reinterpret_cast<uintptr_t>(x) & 3) == 0; }
     template <int E>
-    __device__ __forceinline__ void load_run(Raw (&raw)[E], int k0, int len, int at) const
+    __device__ __forceinline__ void load(Raw (&raw)[E], int k0, int len, int at) const
     {
-        unsigned w[E / 2];
-        buffer_words<E / 2>(w, buffer_of(x + k0, 2u * len), 2 * at);
+        const Buffer v = buffer_of(x + k0, 2u * len);
 #pragma unroll
-        for (int e = 0; e < E; ++e)
-            raw[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e & 1))));
+        for (int j = 0; j < E; ++j)
+            raw[j] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(v, 2 * at + 128 * j, 0, 0));
     }
     __device__ __forceinline__ float prepare() const { return 0.f; }
-    __device__ __forceinline__ float value(Raw r, float) const { return __half2float(r); }
+    __device__ __forceinline__ float value(Raw r, float) const { return (float)r; }
 };
 
 // SiLU(g) * u rounded to fp16 (Appendix A.3: the input of W_down), in stated
@@ -242,9 +228,7 @@ struct HalfSource {                   // the hidden state itself, fp16 in memory
 __device__ __forceinline__ float swiglu_value(float g, float u)
 {
 #pragma clang fp contract(off)
-    float z = -g;
-    z = z > 80.0f ? 80.0f : z;
-    z = z < -80.0f ? -80.0f : z;
+    const float z = __builtin_amdgcn_fmed3f(-g, -80.0f, 80.0f);      // (of a NaN: any number, see below)
     const float k = rintf(z * 1.44269502f);
     float r = fmaf(k, -0.693145752f, z);
     r = fmaf(k, -1.42860677e-06f, r);
@@ -271,12 +255,12 @@ struct SwigluSource {                 // gate = x W_gate^T and up = x W_up^T, fp
     static constexpr bool kHeavy = true;
     static constexpr bool kPlainHalf = false;
     typedef float2 Raw;
+    typedef float Compared;
+    static __device__ __forceinline__ float threshold(float t) { return t; }
     const float *gate;
     const float *up;
-    __device__ __forceinline__ Raw load(int i) const { return make_float2(gate[i], up[i]); }
-    __device__ __forceinline__ bool run_aligned() const { return true; }
     template <int E>
-    __device__ __forceinline__ void load_run(Raw (&raw)[E], int k0, int len, int at) const
+    __device__ __forceinline__ void load(Raw (&raw)[E], int k0, int len, int at) const
     {
         pairs_of_slice<E>(raw, gate, up, k0, len, at);
     }
@@ -366,10 +350,10 @@ __device__ __forceinline__ void chunk_wave_sums(const float *__restrict__ h, int
     }
 }
 
-// r = binary32(1 / sqrt(mean(h^2) + eps)) as stated above.  All kNormWaves * 64 threads of
+// r = binary32(1 / sqrt(mean(h^2) + eps)) as stated above; inv_m = binary64(1 / m).  All kNormWaves * 64 threads of
 // the block call it; wave_sums is LDS for kMaxNormChunks * kNormWaves doubles.  Needs
 // 8 <= m <= kMaxNormDim, m % 8 == 0, h 16-byte aligned.  Contains one barrier.
-__device__ __forceinline__ float rms_scale(const float *__restrict__ h, int m, float eps,
+__device__ __forceinline__ float rms_scale(const float *__restrict__ h, int m, double inv_m, float eps,
                                            double *wave_sums)
 {
 #pragma clang fp contract(off)
@@ -387,8 +371,22 @@ __device__ __forceinline__ float rms_scale(const float *__restrict__ h, int m, f
                     : 0.0;
     }
     const double ss = (cs[0] + cs[1]) + (cs[2] + cs[3]);
-    const double var = ss / (double)m + (double)eps;
-    return (float)(1.0 / sqrt(var));
+    // ss / m, correctly rounded: with the correctly rounded reciprocal of m a quotient is one remainder away from
+    // its rounded value (Markstein).  An infinite sum has no remainder.
+    const double q = ss * inv_m;
+    const double mean = fma(fma(-q, (double)m, ss), inv_m, q);
+    const double var = (ss < __builtin_inf() ? mean : ss) + (double)eps;
+    // 1 / sqrt(var) by Newton's iteration from the hardware's estimate, within 2^-50 of the stated value (a
+    // square root and a quotient, each rounded to binary64).  Both round to the same binary32 unless
+    // a boundary between two lies in between; where one is near, and out of the ordinary range, the stated
+    // operations themselves decide.
+    double r = __builtin_amdgcn_rsq(var);
+    const double hv = 0.5 * var;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) r = fma(r, fma(-hv * r, r, 0.5), r);
+    const int near_tie = (__double2loint(r) & 0x1FFFFFFF) - 0x10000000;
+    if (!(r > 0x1p-100 && r < 0x1p100) || abs(near_tie) <= 64) r = 1.0 / sqrt(var);
+    return (float)r;
 }
 
 __device__ __forceinline__ float rmsnorm_value(float h, float gamma, float r)
@@ -405,27 +403,25 @@ struct RmsnormSource {                // hidden state and norm weights, fp32 in 
     static constexpr bool kHeavy = false;
     static constexpr bool kPlainHalf = false;
     typedef float2 Raw;
+    typedef float Compared;
+    static __device__ __forceinline__ float threshold(float t) { return t; }
     const float *h;
     const float *gamma;
     int m;
+    double inv_m;
     float eps;
     double *wave_sums;                // LDS, kMaxNormChunks * kNormWaves doubles
-    __device__ __forceinline__ Raw load(int i) const { return make_float2(h[i], gamma[i]); }
-    __device__ __forceinline__ bool run_aligned() const { return true; }
     template <int E>
-    __device__ __forceinline__ void load_run(Raw (&raw)[E], int k0, int len, int at) const
+    __device__ __forceinline__ void load(Raw (&raw)[E], int k0, int len, int at) const
     {
         pairs_of_slice<E>(raw, h, gamma, k0, len, at);
     }
-    __device__ __forceinline__ float prepare() const { return rms_scale(h, m, eps, wave_sums); }
+    __device__ __forceinline__ float prepare() const { return rms_scale(h, m, inv_m, eps, wave_sums); }
     __device__ __forceinline__ float value(Raw raw, float r) const
     {
         return rmsnorm_value(raw.x, raw.y, r);
     }
 };
-
-// Definition 1 on one element: fp16 -> fp32 is exact, the compare is fp32.
-__device__ __forceinline__ bool survives(float xv, float t) { return fabsf(xv) > t; }
 
 // How large the survivors of a slice are, for a list whose entries depend on it: nothing beyond
 // kModestLimit, something beyond it, an infinity.
@@ -446,139 +442,62 @@ struct PlainBits {
     }
 };
 
-// Compacts the survivors of channels [k0, k1) into list[] as (channel, x as
-// fp32 bits or as Enc encodes it), ascending, for slices of any length and alignment (compact_slice
-// takes the faster forms where it can).  Each wavefront ballots its 64-channel segments and
-// leaves their popcounts in seg_cnt[] (LDS, kMaxSegs ints); after one barrier
-// every wavefront computes the exclusive prefix over the segment counts
-// itself (lane j holds the prefix of segment j in `seg_excl`; lanes past the
-// last segment hold the total) and scatters its survivors.  The x values and
-// ballots stay in registers between the two steps, and all of a wavefront's
-// loads of x are issued together.  Returns the total (same in all threads).
-// Needs k1 - k0 <= kMaxSlice.  All threads of the block must call it; ends
-// with a barrier after which list[] is complete.  `prepared`, when given, carries
+// Compacts the survivors of the `len` channels from k0 on into list[] as (channel, x as fp32 bits or as
+// Enc encodes it), ascending.  Wavefront w takes the E segments of 64 channels from w * E on, balloted into
+// scalar registers, and leaves its count in LDS; after one barrier every wavefront adds up the counts ahead
+// of its own and scatters its survivors.  All of a wavefront's loads are issued together.  Returns
+// the total (same in all threads).  Needs len <= WAVES * E * 64.  All threads of the block must call it;
+// ends with a barrier after which list[] is complete.  `prepared`, when given, carries
 // what the source prepares once per block (the scale of the normalisation) from
 // one piece of a long slice to the next: computed when `have_prepared` is false
-// (block-uniform), reused otherwise.  `magnitude`, with an encoding that needs it: how large the
-// survivors are, the same in all threads; seg_cnt[] then has WAVES ints more.
-template <int WAVES, class XS, class Enc = PlainBits>
-__device__ __forceinline__ int compact_segments(const XS &x, float t, int k0,
-                                                int k1, int2 *list, int *seg_cnt, int &group_excl,
-                                                float *prepared_io, bool have_prepared,
-                                                int *magnitude)
-{
-    constexpr int PER_WAVE = kMaxSegs / WAVES;
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int nseg = (k1 - k0 + 63) >> 6;
-
-    float xv[PER_WAVE];
-    unsigned long long bal[PER_WAVE];
-    // Unconditional loads from a clamped position (k1 > k0), the out-of-range lanes zeroed
-    // afterwards: a load inside a branch is waited for before the next one is issued.
-    typename XS::Raw raw[PER_WAVE];
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j)
-        raw[j] = x.load(min(k0 + (w + j * WAVES) * 64 + lane, k1 - 1));
-    float prepared;
-    if (prepared_io && have_prepared) prepared = *prepared_io;
-    else prepared = x.prepare();
-    if (prepared_io) *prepared_io = prepared;
-    const int w_uniform = __builtin_amdgcn_readfirstlane(w);
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int i = k0 + (w + j * WAVES) * 64 + lane;
-        float v = 0.f;
-        if (!XS::kHeavy || w_uniform + j * WAVES < nseg)          // wavefront-uniform
-            v = x.value(raw[j], prepared);
-        xv[j] = i < k1 ? v : 0.f;                     // x = 0 never survives (t >= 0)
-    }
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int seg = w + j * WAVES;
-        bal[j] = __ballot(survives(xv[j], t));
-        if (lane == 0 && seg < nseg) seg_cnt[seg] = __popcll(bal[j]);
-    }
-    if constexpr (Enc::kMagnitude) {
-        unsigned long long large = 0, infinite = 0;
-#pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) large |= bal[j] & __ballot(fabsf(xv[j]) > kModestLimit);
-        if (large) {
-#pragma unroll
-            for (int j = 0; j < PER_WAVE; ++j) infinite |= bal[j] & __ballot(isinf(xv[j]));
-        }
-        if (lane == 0) seg_cnt[kMaxSegs + w] = magnitude_of(large, infinite);
-    }
-    __syncthreads();
-    const int c = lane < nseg ? seg_cnt[lane] : 0;
-    const int incl = wave_inclusive_scan(c);
-    const int seg_excl = incl - c;
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    if constexpr (Enc::kMagnitude) {                    // the callers that walk groups of 128
-        const int first = __shfl(seg_excl, (2 * lane) & 63);
-        group_excl = lane < 32 ? first : total;         // past the last segment: the total
-    }
-    if constexpr (Enc::kMagnitude) {
-        int top = kModest;
-#pragma unroll
-        for (int ww = 0; ww < WAVES; ++ww) top = max(top, seg_cnt[kMaxSegs + ww]);
-        *magnitude = __builtin_amdgcn_readfirstlane(top);
-    }
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int seg = w + j * WAVES;
-        if (seg < nseg) {                              // wavefront-uniform
-            const int base = __builtin_amdgcn_readlane(seg_excl, seg);
-            if (survives(xv[j], t))
-                list[base + lanes_below(bal[j])] =
-                    Enc::entry(k0, seg * 64 + lane, xv[j]);
-        }
-    }
-    __syncthreads();
-    return total;
-}
-
-// compact_slice for a slice whose length is a multiple of 8 and at most WAVES * 64 * E: a lane takes E
-// consecutive channels in one load per vector, counts its survivors, and one scan over the lanes of a
-// wavefront and one over the wavefronts place them.  The time before a block's first weight row is
-// instructions, not the latency of x (by the core clock 1060 of 2450 cycles from x in registers to the
-// list, 145 for x itself), and this takes less than half of those of compact_segments, which pays a
-// ballot, a count in LDS, a prefix look-up and a position's clamp and test per 64 channels.  (us per call at
-// 50 %, compact_segments / this: Llama-3-8B q + k + v with the normalisation 9.74 / 9.40, W_down with
-// SiLU(gate) * up 14.8 / 14.2, gate + up 20.7 / 20.4.)
+// (block-uniform), reused otherwise.  With an encoding that needs them: how large the survivors are
+// (`magnitude`), and where group j of 128 channels begins in the list (`group_excl` in lane j; lanes past the
+// last group: the total).
+// The time before a block's first weight row is instructions, not the latency of x, so positions come from
+// scalar counts and mbcnt, lanes past the slice read zeros instead of being clamped and tested, and a plain
+// state is compared as fp16.  (Compacted after the block's start, us, per-segment counts in LDS and vector
+// compares for what is uniform / consecutive channels in a lane, eight conditional LDS writes one behind
+// the other / this: 4096 channels of a plain state 2.1 / 1.7 / 1.2, 1792 of SiLU(gate) * up - / 1.5 / 1.3.)
 template <int E, int WAVES, class XS, class Enc>
-__device__ __forceinline__ int compact_runs(const XS &x, float t, int k0, int len, int2 *list, int *counts,
-                                            int &group_excl, float *prepared_io, bool have_prepared,
-                                            int *magnitude)
+__device__ __forceinline__ int compact_strips(const XS &x, float t, int k0, int len, int2 *list, int *counts,
+                                              int &group_excl, float *prepared_io, bool have_prepared,
+                                              int *magnitude)
 {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int at = (w * 64 + lane) * E;
+    const int at = w * E * 64 + lane;
     typename XS::Raw raw[E];
-    x.template load_run<E>(raw, k0, len, at);
+    x.load(raw, k0, len, at);
     float prepared;
     if (prepared_io && have_prepared) prepared = *prepared_io;
     else prepared = x.prepare();
     if (prepared_io) *prepared_io = prepared;
-    float xv[E];
-    int mine = 0;
+
+    // v[j]: x of channel at + 64 j as it is compared and, later, listed
+    typename XS::Compared v[E];
+    const auto bound = XS::threshold(t);
+    unsigned long long bal[E];
+    int base[E + 1];
+    base[0] = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) xv[e] = 0.f;              // x = 0 never survives (t >= 0)
-    if (!XS::kHeavy || w * 64 * E < len) {                // wavefront-uniform
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            xv[e] = x.value(raw[e], prepared);
-            mine += survives(xv[e], t) ? 1 : 0;
-        }
+    for (int j = 0; j < E; ++j) {
+        v[j] = 0;                                         // x = 0 never survives (t >= 0)
+        if (!XS::kHeavy || (w * E + j) * 64 < len)        // wavefront-uniform
+            v[j] = (typename XS::Compared)x.value(raw[j], prepared);
+        bal[j] = __ballot(__builtin_elementwise_abs(v[j]) > bound);
+        base[j + 1] = base[j] + __popcll(bal[j]);
     }
-    const int incl = wave_inclusive_scan(mine);
-    int sum = __builtin_amdgcn_readlane(incl, 63);
+    int sum = base[E];                                    // at most 64 E
     if constexpr (Enc::kMagnitude) {
-        float top = 0.f;
+        unsigned long long large = 0, infinite = 0;
 #pragma unroll
-        for (int e = 0; e < E; ++e) top = fmaxf(top, survives(xv[e], t) ? fabsf(xv[e]) : 0.f);
-        const unsigned long long large = __ballot(top > kModestLimit), infinite = __ballot(isinf(top));
-        sum |= magnitude_of(large, infinite) << 16;       // at most 64 * E survivors
+        for (int j = 0; j < E; ++j)
+            large |= bal[j] & __ballot(__builtin_elementwise_abs(v[j]) > (typename XS::Compared)kModestLimit);
+        if (large) {
+#pragma unroll
+            for (int j = 0; j < E; ++j) infinite |= bal[j] & __ballot(isinf((float)v[j]));
+        }
+        sum |= magnitude_of(large, infinite) << 16;
     }
     if (lane == 0) counts[w] = sum;
     __syncthreads();
@@ -597,41 +516,44 @@ __device__ __forceinline__ int compact_runs(const XS &x, float t, int k0, int le
     if constexpr (WAVES > 8) upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, true);
     const int total = __builtin_amdgcn_readlane(upto, WAVES - 1);
     const int before = __builtin_amdgcn_readlane(upto - c, w);
-    int pos = before + incl - mine;
-    if constexpr (Enc::kMagnitude) {                      // the callers that walk groups of 128
-        if ((at & 127) == 0) counts[WAVES + (at >> 7)] = pos;
-    }
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (survives(xv[e], t)) list[pos++] = Enc::entry(k0, at + e, xv[e]);
+    for (int j = 0; j < E; ++j) {
+        const int pos = before + base[j] + lanes_below(bal[j]);
+        if (__builtin_elementwise_abs(v[j]) > bound)
+            list[pos] = Enc::entry(k0, at + 64 * j, (float)v[j]);
+    }
+    if constexpr (Enc::kMagnitude) {
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < E; j += 2) counts[WAVES + (w * E + j) / 2] = before + base[j];
+        }
+    }
     __syncthreads();
     if constexpr (Enc::kMagnitude)
         group_excl = lane * 128 < len ? counts[WAVES + min(lane, WAVES * E / 2 - 1)] : total;
     return total;
 }
 
-// compact_segments or, where the slice allows it, compact_runs: the shortest runs that cover the slice,
-// so that all wavefronts share in it.  `counts` is LDS for kCompactInts ints.
-constexpr int kCompactInts = kMaxSegs + 16;
+// compact_strips for channels [k0, k1) with the shortest strips that cover them, so that all wavefronts
+// share in the work.  k1 - k0 <= kMaxSlice.  `counts` is LDS for kCompactInts ints.
+constexpr int kCompactInts = 16 + kMaxSegs;
 template <int WAVES, class XS, class Enc = PlainBits>
 __device__ __forceinline__ int compact_slice(const XS &x, float t, int k0, int k1, int2 *list, int *counts,
                                              int &group_excl, float *prepared_io = nullptr,
                                              bool have_prepared = false, int *magnitude = nullptr)
 {
     const int len = k1 - k0;                              // block-uniform, as all below
-    if (len % 8 == 0 && x.run_aligned()) {
-        if (len <= WAVES * 128)
-            return compact_runs<2, WAVES, XS, Enc>(x, t, k0, len, list, counts, group_excl, prepared_io,
-                                                   have_prepared, magnitude);
-        if (len <= WAVES * 256)
-            return compact_runs<4, WAVES, XS, Enc>(x, t, k0, len, list, counts, group_excl, prepared_io,
-                                                   have_prepared, magnitude);
-        if (len <= WAVES * 512)
-            return compact_runs<8, WAVES, XS, Enc>(x, t, k0, len, list, counts, group_excl, prepared_io,
-                                                   have_prepared, magnitude);
-    }
-    return compact_segments<WAVES, XS, Enc>(x, t, k0, k1, list, counts, group_excl, prepared_io,
-                                            have_prepared, magnitude);
+#define TEAL_STRIPS(E)                                                                         \
+    return compact_strips<E, WAVES, XS, Enc>(x, t, k0, len, list, counts, group_excl,          \
+                                             prepared_io, have_prepared, magnitude)
+    constexpr int MOST = kMaxSegs / WAVES;
+    if (len <= WAVES * 128) TEAL_STRIPS(2);
+    if constexpr (MOST > 4)
+        if (len <= WAVES * 256) TEAL_STRIPS(4);
+    if constexpr (MOST > 8)
+        if (len <= WAVES * 512) TEAL_STRIPS(8);
+    TEAL_STRIPS(MOST);
+#undef TEAL_STRIPS
 }
 
 // Wavefront-uniform contiguous share of `cnt` items for wavefront w of WAVES.
@@ -640,13 +562,6 @@ __device__ __forceinline__ void wave_share(int cnt, int w, int waves, int &start
     const int per = cnt / waves, rem = cnt - per * waves;
     start = w * per + min(w, rem);
     mine = per + (w < rem ? 1 : 0);
-}
-
-// The largest fp16 value that is not above t (t >= 0): an fp16 magnitude is above t exactly if it is
-// above this, so an fp16 state is compared as it is.
-__device__ __forceinline__ _Float16 half_threshold(float t)
-{
-    return __builtin_bit_cast(_Float16, __builtin_amdgcn_cvt_pkrtz(fminf(t, 65504.f), 0.f)[0]);
 }
 
 // compact_slice for short slices (at most P segments of 64 channels) of an fp16 state,
@@ -1063,11 +978,13 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_swiglu_kernel(
     float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
+    trace_mark(0);
     const int tile = blockIdx.x;
     gemv_block<F, LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
                                  tile_counter(counters, tile, tiles), y, m, n, ks, tile,
                                  blockIdx.y, tile_cols, splits,
                                  survivor_report(counters, 0, splits));
+    trace_mark(6);
 }
 
 // Several matrices that read the same hidden state (q/k/v, or gate/up:
@@ -1093,19 +1010,32 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
                                             int gtile, int s)
 {
     trace_mark(0);
-    const int tiles = ma.tile_begin[ma.count];
-    int k = 0;
+    // All matrices' arguments are read at once and one is selected: looked up by the index found, they
+    // would be a second scalar load behind the first, 0.4 us of every grouped call.
+    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];
     size_t partial_off = 0;            // each matrix owns splits * n floats of partial rows
+    typename F::Args a = ma.a[0];
+    float *y = ma.y[0];
+    float t = ma.t[0];
+    asm volatile("" ::"s"(ma.y[0]), "s"(ma.y[1]), "s"(ma.y[2]), "s"(ma.y[3]), "s"(ma.n[0]), "s"(ma.n[1]),
+                 "s"(ma.n[2]), "s"(ma.n[3]), "s"(ma.t[0]), "s"(ma.t[1]), "s"(ma.t[2]), "s"(ma.t[3]),
+                 "s"(ma.a[0].W), "s"(ma.a[1].W), "s"(ma.a[2].W), "s"(ma.a[3].W), "s"(ma.tile_begin[4]),
+                 "s"(partial), "s"(counters), "s"(splits), "s"(ks), "s"(tile_cols), "s"(m));
+    F::read_now(ma.a);
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count && gtile >= ma.tile_begin[j]) {
-            partial_off += (size_t)splits * ma.n[j - 1];
-            k = j;
-        }
+        if (j < ma.count) tiles = ma.tile_begin[j + 1];
+        const bool here = j < ma.count && gtile >= ma.tile_begin[j];
+        partial_off += here ? (size_t)splits * ma.n[j - 1] : 0;
+        k = here ? j : k;
+        first = here ? ma.tile_begin[j] : first;
+        n = here ? ma.n[j] : n;
+        y = here ? ma.y[j] : y;
+        t = here ? ma.t[j] : t;
+        F::select(a, ma.a[j], here);
     }
-    gemv_block<F, LPR, WAVES, U>(ma.a[k], x, ma.t[k], partial + partial_off,
-                                 tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
-                                 gtile - ma.tile_begin[k], s, tile_cols, splits,
+    gemv_block<F, LPR, WAVES, U>(a, x, t, partial + partial_off, tile_counter(counters, gtile, tiles), y, m,
+                                 n, ks, gtile - first, s, tile_cols, splits,
                                  survivor_report(counters, k, splits));
     trace_mark(6);
 }
@@ -1115,6 +1045,7 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_multi_kernel(
     MultiArgs<F> ma, const __half *__restrict__ x, float *partial, int *counters, int m, int ks,
     int tile_cols, int splits)
 {
+    asm volatile("" ::"s"(x));                 // as in multi_block
     multi_block<F, LPR, WAVES, U>(ma, HalfSource{x}, partial, counters, m, ks, tile_cols, splits,
                                   (int)blockIdx.x, (int)blockIdx.y);
 }
@@ -1127,10 +1058,11 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_multi_kernel(
 template <class F, int LPR, int U>
 __global__ __launch_bounds__(kNormWaves * 64) void sparse_gemv_rmsnorm_multi_kernel(
     MultiArgs<F> ma, const float *__restrict__ h, const float *__restrict__ gamma, float eps,
-    float *partial, int *counters, int m, int ks, int tile_cols, int splits)
+    double inv_m, float *partial, int *counters, int m, int ks, int tile_cols, int splits)
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
-    multi_block<F, LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, eps, wave_sums}, partial,
+    asm volatile("" ::"s"(h), "s"(gamma), "s"(eps), "s"(inv_m));      // as in multi_block
+    multi_block<F, LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, inv_m, eps, wave_sums}, partial,
                                        counters, m, ks, tile_cols, splits, (int)blockIdx.x,
                                        (int)blockIdx.y);
 }

@@ -37,15 +37,12 @@ struct SwigluReadySource {
     static constexpr bool kHeavy = true;
     static constexpr bool kPlainHalf = false;
     typedef float2 Raw;
+    typedef float Compared;
+    static __device__ __forceinline__ float threshold(float t) { return t; }
     const float *gate;
     const float *up;
-    __device__ __forceinline__ Raw load(int i) const
-    {
-        return make_float2(load_coherent(gate + i), load_coherent(up + i));
-    }
-    __device__ __forceinline__ bool run_aligned() const { return true; }
     template <int E>
-    __device__ __forceinline__ void load_run(Raw (&raw)[E], int k0, int len, int at) const
+    __device__ __forceinline__ void load(Raw (&raw)[E], int k0, int len, int at) const
     {
         pairs_of_slice<E, 16>(raw, gate, up, k0, len, at);
     }

@@ -19,6 +19,17 @@ struct FmtW8 {
         const __half *scale;
         int ld = 0;             // elements from one row of W to the next; 0 = n
     };
+    static __device__ __forceinline__ void read_now(const Args (&a)[4])
+    {
+        asm volatile("" ::"s"(a[0].ld), "s"(a[1].ld), "s"(a[2].ld), "s"(a[3].ld), "s"(a[0].scale),
+                     "s"(a[1].scale), "s"(a[2].scale), "s"(a[3].scale));
+    }
+    static __device__ __forceinline__ void select(Args &a, const Args &b, bool take)
+    {
+        a.W = take ? b.W : a.W;
+        a.scale = take ? b.scale : a.scale;
+        a.ld = take ? b.ld : a.ld;
+    }
     static __device__ __forceinline__ void fma(float (&acc)[16], u32x4 v, float xv)
     {
 #pragma unroll
@@ -390,20 +401,31 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
                                                int tile_cols, int splits, int gtile, int s)
 {
     trace_mark(0);
-    const int tiles = ma.tile_begin[ma.count];
-    int k = 0;
+    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];      // as in multi_block
     size_t partial_off = 0;
+    FmtW4::Args a = ma.a[0];
+    float *y = ma.y[0];
+    float t = ma.t[0];
+    asm volatile("" ::"s"(ma.y[0]), "s"(ma.y[1]), "s"(ma.y[2]), "s"(ma.y[3]), "s"(ma.n[0]), "s"(ma.n[1]),
+                 "s"(ma.n[2]), "s"(ma.n[3]), "s"(ma.t[0]), "s"(ma.t[1]), "s"(ma.t[2]), "s"(ma.t[3]),
+                 "s"(ma.a[0].W), "s"(ma.a[1].W), "s"(ma.a[2].W), "s"(ma.a[3].W), "s"(ma.tile_begin[4]),
+                 "s"(partial), "s"(counters), "s"(splits), "s"(ma.a[0].scale), "s"(ma.a[1].scale), "s"(ma.a[2].scale),
+                 "s"(ma.a[3].scale));
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count && gtile >= ma.tile_begin[j]) {
-            partial_off += (size_t)splits * ma.n[j - 1];
-            k = j;
-        }
+        if (j < ma.count) tiles = ma.tile_begin[j + 1];
+        const bool here = j < ma.count && gtile >= ma.tile_begin[j];
+        partial_off += here ? (size_t)splits * ma.n[j - 1] : 0;
+        k = here ? j : k;
+        first = here ? ma.tile_begin[j] : first;
+        n = here ? ma.n[j] : n;
+        y = here ? ma.y[j] : y;
+        t = here ? ma.t[j] : t;
+        a.W = here ? ma.a[j].W : a.W;
+        a.scale = here ? ma.a[j].scale : a.scale;
     }
-    w4_block<LPR, WAVES, U>(ma.a[k], x, ma.t[k], partial + partial_off,
-                            tile_counter(counters, gtile, tiles), ma.y[k], m, ma.n[k], ks,
-                            gtile - ma.tile_begin[k], s, tile_cols, splits,
-                            survivor_report(counters, k, splits));
+    w4_block<LPR, WAVES, U>(a, x, t, partial + partial_off, tile_counter(counters, gtile, tiles), y, m, n, ks,
+                            gtile - first, s, tile_cols, splits, survivor_report(counters, k, splits));
     trace_mark(6);
 }
 
@@ -412,6 +434,7 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_multi_kernel(
     MultiArgs<FmtW4> ma, const __half *__restrict__ x, float *partial, int *counters, int m,
     int ks, int tile_cols, int splits)
 {
+    asm volatile("" ::"s"(x));                 // as in multi_block
     w4_multi_block<LPR, WAVES, U>(ma, HalfSource{x}, partial, counters, m, ks, tile_cols, splits,
                                   (int)blockIdx.x, (int)blockIdx.y);
 }
@@ -421,10 +444,11 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_multi_kernel(
 template <int LPR, int U>
 __global__ __launch_bounds__(kNormWaves * 64) void sparse_gemv_w4_rmsnorm_multi_kernel(
     MultiArgs<FmtW4> ma, const float *__restrict__ h, const float *__restrict__ gamma, float eps,
-    float *partial, int *counters, int m, int ks, int tile_cols, int splits)
+    double inv_m, float *partial, int *counters, int m, int ks, int tile_cols, int splits)
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
-    w4_multi_block<LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, eps, wave_sums}, partial,
+    asm volatile("" ::"s"(h), "s"(gamma), "s"(eps), "s"(inv_m));      // as in multi_block
+    w4_multi_block<LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, inv_m, eps, wave_sums}, partial,
                                        counters, m, ks, tile_cols, splits, (int)blockIdx.x, (int)blockIdx.y);
 }
 
@@ -582,7 +606,7 @@ hipError_t launch_gemv_w8_rmsnorm_multi(int count, const int8_t *const *Wq, cons
 #define TEAL_LAUNCH_N(LPR)                                                                     \
     hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtW8, LPR, 4>),                      \
                        dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
-                       gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits)
+                       gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_N(32);
     else if (sh.lanes_per_row == 16) TEAL_LAUNCH_N(16);
@@ -658,7 +682,7 @@ hipError_t launch_gemv_w4_rmsnorm_multi(int count, const uint8_t *const *Wq,
 #define TEAL_LAUNCH_W4N(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_rmsnorm_multi_kernel<LPR, kW4Unroll>),                  \
                        dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
-                       gamma, eps, partial, counters, m, g.ks, g.tile_cols, g.splits)
+                       gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4N(32);
     else TEAL_LAUNCH_W4N(16);
 #undef TEAL_LAUNCH_W4N

@@ -172,11 +172,11 @@ __global__ __launch_bounds__(256) void swiglu_f16_kernel(const float *__restrict
 // W_q/W_k/W_v and W_gate/W_up on its own, in the arithmetic the fused kernel uses.
 // Every block computes the scale from all of h and writes its 512 entries.
 __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_f16_kernel(
-    const float *__restrict__ h, const float *__restrict__ gamma, float eps,
+    const float *__restrict__ h, const float *__restrict__ gamma, float eps, double inv_m,
     __half *__restrict__ x, int m)
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
-    const float r = rms_scale(h, m, eps, wave_sums);
+    const float r = rms_scale(h, m, inv_m, eps, wave_sums);
     const int i = (int)(blockIdx.x * (kNormWaves * 64) + threadIdx.x);
     if (i < m) x[i] = __float2half_rn(rmsnorm_value(h[i], gamma[i], r));
 }
@@ -250,7 +250,8 @@ hipError_t launch_rmsnorm_f16(const float *h, const float *gamma, float eps, voi
     if (m < 8 || m > kMaxNormDim || m % 8 != 0) return hipErrorInvalidValue;
     const int threads = kNormWaves * 64;
     hipLaunchKernelGGL(rmsnorm_f16_kernel, dim3((unsigned)((m + threads - 1) / threads)),
-                       dim3(threads), 0, stream, h, gamma, eps, static_cast<__half *>(x_f16), m);
+                       dim3(threads), 0, stream, h, gamma, eps, 1.0 / m, static_cast<__half *>(x_f16),
+                       m);
     return hipGetLastError();
 }
 

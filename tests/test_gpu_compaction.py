@@ -1,6 +1,6 @@
 """The compaction of a slice at the edges of its forms, against the CPU oracle through the C ABI: short
-slices (2, 4 or 8 segments of 64 channels), runs of 2, 4 or 8 channels per lane, and the form for
-lengths and addresses that fit neither.  Survivor counts are exact; a channel that is missing, doubled or
+slices (2, 4 or 8 segments of 64 channels, every wavefront for itself), longer ones (2, 4, 8 or 16 segments
+per wavefront) and pieces of 4096, on any address.  Survivor counts are exact; a channel that is missing, doubled or
 misplaced moves y by far more than the tolerance."""
 import numpy as np
 import pytest
@@ -55,8 +55,8 @@ def test_thresholds_between_and_beyond_fp16_values(T, m):   # noqa: F811
 
 
 @pytest.mark.parametrize("m", [1000, 1001, 1024, 1032, 2048, 2056, 4096])
-def test_formed_inputs_in_runs(T, m):   # noqa: F811
-    """SiLU(gate) * up formed in runs: bitwise the producer kernel and the plain call, in one slice (a
+def test_formed_inputs(T, m):   # noqa: F811
+    """SiLU(gate) * up: bitwise the producer kernel and the plain call, in one slice (a
     matrix wide enough to go without split-K) and in short ones."""
     for n in (264, 33000):
         g = torch.Generator(device="cuda").manual_seed(m + n)
@@ -89,3 +89,19 @@ def test_w4_groups_of_long_slices(T, m):   # noqa: F811
     kept = x.float().abs() > t
     want = (torch.where(kept, x.double(), 0.0)[:, None] * w).sum(0).cpu().numpy()
     assert rel_l2(y[cols].cpu().numpy(), want) <= TIGHT and survivors(T, ws) == [int(kept.sum())]
+
+
+@pytest.mark.parametrize("m", [8, 4096, 5000, 16384])
+@pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e-12, 1.0, 1e12, 1e30])
+def test_scale_of_the_normalisation_over_its_range(T, m, scale):   # noqa: F811
+    """The iteration for 1 / sqrt and, where its result is out of the ordinary range, the operations it stands
+    for: bit for bit the oracle's state."""
+    h, gamma = ti.norm_inputs(m, 7 * m)
+    h = (h * np.float32(scale)).astype(np.float32)
+    x = torch.empty(m, dtype=torch.int16, device="cuda")
+    for eps in (0.0, 2.0 ** -20):
+        T.check(T.teal_rmsnorm_f16(dev(h), dev(gamma), eps, x, m))
+        got, want = x.cpu().numpy().view(np.float16), orc.rmsnorm_f16(h, gamma, eps)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), eps
+        keep = ~np.isnan(want)
+        assert np.array_equal(got.view(np.uint16)[keep], want.view(np.uint16)[keep]), eps
