@@ -106,26 +106,28 @@ __device__ __forceinline__ int compact_slice_batch(const __half *__restrict__ X,
 {
     constexpr int WORDS = (VEC + 1) / 2;
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nseg = (k1 - k0 + 64 * VEC - 1) / (64 * VEC);
 
-    // Unconditional loads from clamped positions (k1 > k0), so that all loads are in flight
-    // together.  Batch rows past the last repeat it and have no weight in the sums.
+    // All loads are in flight together, from one position per pass and a scalar offset per batch row.  Past
+    // the end of X they read zeros; what lies past the slice's is left out below.  Batch rows past the
+    // last repeat it and have no weight in the sums.
+    const Buffer states = buffer_of(X, 2u * (unsigned)batch * (unsigned)m);
     unsigned raw[PASSES][NB][WORDS];
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
-        const int ic = min(k0 + ((w + j * WAVES) * 64 + lane) * VEC, k1 - VEC);
+        const int at = 2 * (k0 + ((w + j * WAVES) * 64 + lane) * VEC);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const __half *p = X + (size_t)min(b, batch - 1) * m + ic;
+            const int row = 2 * min(b, batch - 1) * m;
             if constexpr (VEC == 1) {
-                raw[j][b][0] = *reinterpret_cast<const unsigned short *>(p);
+                raw[j][b][0] = __builtin_amdgcn_raw_buffer_load_b16(states, at, row, 0);
             } else if constexpr (VEC == 2) {
-                raw[j][b][0] = *reinterpret_cast<const unsigned *>(p);
+                raw[j][b][0] = __builtin_amdgcn_raw_buffer_load_b32(states, at, row, 0);
             } else {
-                const uint2 u = *reinterpret_cast<const uint2 *>(p);
-                raw[j][b][0] = u.x;
-                raw[j][b][WORDS - 1] = u.y;
+                const auto u = __builtin_amdgcn_raw_buffer_load_b64(states, at, row, 0);
+                raw[j][b][0] = u[0];
+                raw[j][b][WORDS - 1] = u[1];
             }
         }
     }
@@ -341,7 +343,7 @@ template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *red,
                                                    float *partial, int *counter, float *Y,
                                                    int tile, int col0, int cols, int s, int splits,
-                                                   int n, int batch, int cnt, int w,
+                                                   int n, int batch, int w,
                                                    const SurvivorReport &report)
 {
     constexpr int PAIRS = PARTS * kBatchTile / 2;
@@ -374,7 +376,6 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
         sum.x = fabsf(h.x) < INFINITY ? h.x + l.x : h.x;
         sum.y = fabsf(h.y) < INFINITY ? h.y + l.y : h.y;
     }
-    if (tile == 0 && thread == 0) report_slice(report, s, splits, cnt);
     float *y = Y + (size_t)bb * n + col0 + c;
     if (splits == 1) {
         if (owner) {
@@ -396,7 +397,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     __syncthreads();
     trace_mark(5);
     if (!last_flag) return;
-    if (tile == 0 && w == 0) report_total(report, splits);
+    if (tile == 0 && w == WAVES - 1) report_total(report, splits);
 
     // Second pass, up to 16 loads in flight; every output is summed in split order, so the
     // result does not depend on which block is last.
@@ -436,6 +437,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     __shared__ int seg_cnt[kMaxSegs];
 
     trace_mark(0);
+    asm volatile("" ::"s"(W), "s"(partial), "s"(counter), "s"(Y));      // as in gemv_block
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
     // Channels per lane by the length of the slice, so that short slices occupy every wavefront;
@@ -459,6 +461,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
 #undef TEAL_COMPACT
 
     trace_mark(2);
+    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int share = batch_share_rows<WAVES / PARTS>(cnt);
     const int start = w / PARTS * share;
@@ -477,7 +480,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, counter, Y, tile, col0, tile_cols, s, splits,
-                                  n, batch, cnt, w, report);
+                                  n, batch, w, report);
     trace_mark(6);
 }
 
@@ -489,9 +492,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_kernel(
     float *partial, int *counters, float *Y, int m, int n, int ks, int tiles, int tile_cols,
     int splits)
 {
-    const int tile = blockIdx.x % tiles;
+    const int tile = blockIdx.x;
     batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial, tile_counter(counters, tile, tiles), Y, m,
-                           n, ks, tile, blockIdx.x / tiles, tile_cols, splits,
+                           n, ks, tile, blockIdx.y, tile_cols, splits,
                            survivor_report(counters, 0, splits));
 }
 
@@ -512,22 +515,32 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
     BatchMultiArgs ma, const __half *__restrict__ X, int batch, float *partial, int *counters,
     int m, int ks, int tile_cols, int splits)
 {
-    const int tiles = ma.tile_begin[ma.count];
-    const int gtile = blockIdx.x % tiles;
-    const int s = blockIdx.x / tiles;
-    int k = 0;
+    const int gtile = blockIdx.x, s = blockIdx.y;
+    // all matrices' arguments at once, as in multi_block
+    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];
     size_t partial_off = 0;            // each matrix owns splits * batch * n floats of partial rows
+    const void *W = ma.W[0];
+    float *Y = ma.Y[0];
+    double bound = ma.bound[0];
+    asm volatile("" ::"s"(ma.W[0]), "s"(ma.W[1]), "s"(ma.W[2]), "s"(ma.W[3]), "s"(ma.Y[0]), "s"(ma.Y[1]),
+                 "s"(ma.Y[2]), "s"(ma.Y[3]), "s"(ma.bound[0]), "s"(ma.bound[1]), "s"(ma.bound[2]),
+                 "s"(ma.bound[3]), "s"(ma.n[0]), "s"(ma.n[1]), "s"(ma.n[2]), "s"(ma.n[3]),
+                 "s"(ma.tile_begin[4]), "s"(partial), "s"(counters), "s"(X), "s"(batch), "s"(m), "s"(splits));
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count && gtile >= ma.tile_begin[j]) {
-            partial_off += (size_t)splits * batch * ma.n[j - 1];
-            k = j;
-        }
+        if (j < ma.count) tiles = ma.tile_begin[j + 1];
+        const bool here = j < ma.count && gtile >= ma.tile_begin[j];
+        partial_off += here ? (size_t)splits * batch * ma.n[j - 1] : 0;
+        k = here ? j : k;
+        first = here ? ma.tile_begin[j] : first;
+        n = here ? ma.n[j] : n;
+        W = here ? ma.W[j] : W;
+        Y = here ? ma.Y[j] : Y;
+        bound = here ? ma.bound[j] : bound;
     }
-    batch_block<NB, WAVES, PARTS>(ma.W[k], X, batch, ma.bound[k], partial + partial_off,
-                           tile_counter(counters, gtile, tiles), ma.Y[k], m, ma.n[k], ks,
-                           gtile - ma.tile_begin[k], s, tile_cols, splits,
-                           survivor_report(counters, k, splits));
+    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial + partial_off,
+                                  tile_counter(counters, gtile, tiles), Y, m, n, ks, gtile - first, s,
+                                  tile_cols, splits, survivor_report(counters, k, splits));
 }
 
 constexpr int kBatchWaves = 8;
@@ -726,7 +739,7 @@ hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, 
     do {                                                                                         \
         if (!allow_large_lds(sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>, lds))                    \
             return hipErrorInvalidValue;                                                         \
-        hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>), dim3(g.tiles * g.splits), \
+        hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>), dim3(g.tiles, g.splits), \
                            dim3(kBatchWaves * 64), lds, stream, Wt, X, batch, bound, partial,    \
                            counters, Y, m, n, g.ks, g.tiles, g.tile_cols, g.splits);             \
     } while (0)
@@ -768,7 +781,7 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
         if (!allow_large_lds(sparse_gemv_batch_multi_kernel<NB, kBatchWaves, PARTS>, lds))              \
             return hipErrorInvalidValue;                                                         \
         hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, kBatchWaves, PARTS>),                    \
-                           dim3(tiles * g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,   \
+                           dim3(tiles, g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,   \
                            batch, partial, counters, m, g.ks, g.tile_cols, g.splits);            \
     } while (0)
     if (batch > 4) TEAL_LAUNCH_BM(8, 1);
