@@ -232,6 +232,10 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     // where a digit's sum lies when the two lanes that hold a pair of digits join them
     const int own_shift = l < 8 ? 0 : 8, other_shift = 8 - own_shift;
     int start, mine;
+    // Told to be uniform: without this the walk over the groups is compiled with masks and vector compares, 30
+    // registers and a loop of its own more per batch.
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+    magnitude = __builtin_amdgcn_readfirstlane(magnitude);
     wave_share(cnt, share, SHARES, start, mine);
     // Walk state (all wavefront-uniform): next list position, end of the share, current
     // group of the slice and the end of this wavefront's rows in it.
