@@ -95,6 +95,10 @@ template <class Body, int LPR_GU, int LPR_D>
 __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Body::Format> A)
 {
     const MlpGrid &g = A.grid;
+    // gate's and up's arguments at once, as in multi_block
+    asm volatile("" ::"s"(A.a_gu[0].W), "s"(A.a_gu[1].W), "s"(A.y_gu[0]), "s"(A.y_gu[1]), "s"(A.t_gu[0]),
+                 "s"(A.t_gu[1]), "s"(A.x), "s"(A.m), "s"(A.ks_gu), "s"(A.partial_gu), "s"(A.counters_gu),
+                 "s"(g.f), "s"(g.tiles_gu), "s"(g.tile_cols_gu), "s"(g.splits_gu), "s"(g.phase_tiles));
     const MlpBlock blk = mlp_block(g, (int)blockIdx.x);
     trace_mark(0);
 #ifdef TEAL_TRACE_BLOCKS
@@ -106,10 +110,13 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
 #endif
     if (blk.kind != kMlpDown) {
         const int k = blk.kind;
+        typename Body::Format::Args a = A.a_gu[0];
+        Body::Format::select(a, A.a_gu[1], k != 0);
         const bool wrote = Body::template run<LPR_GU>(
-            A.a_gu[k], HalfSource{A.x}, A.t_gu[k], A.partial_gu + (size_t)k * g.splits_gu * g.f,
-            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu), A.y_gu[k], A.m,
-            g.f, A.ks_gu, blk.tile, blk.split, g.tile_cols_gu, g.splits_gu,
+            a, HalfSource{A.x}, k ? A.t_gu[1] : A.t_gu[0],
+            A.partial_gu + (k ? (size_t)g.splits_gu * g.f : 0),
+            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu),
+            k ? A.y_gu[1] : A.y_gu[0], A.m, g.f, A.ks_gu, blk.tile, blk.split, g.tile_cols_gu, g.splits_gu,
             survivor_report(A.counters_gu, k, g.splits_gu));
         trace_mark(6);
         if (!wrote) return;

@@ -60,6 +60,11 @@ struct FmtW4 {
         const void *W;
         const __half *scale;
     };
+    static __device__ __forceinline__ void select(Args &a, const Args &b, bool take)
+    {
+        a.W = take ? b.W : a.W;
+        a.scale = take ? b.scale : a.scale;
+    }
     struct ColumnScale {};
     static __device__ __forceinline__ ColumnScale column_scale(const Args &, int) { return {}; }
     static __device__ __forceinline__ float finish(float sum, ColumnScale) { return sum; }
@@ -425,8 +430,7 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
         n = here ? ma.n[j] : n;
         y = here ? ma.y[j] : y;
         t = here ? ma.t[j] : t;
-        a.W = here ? ma.a[j].W : a.W;
-        a.scale = here ? ma.a[j].scale : a.scale;
+        FmtW4::select(a, ma.a[j], here);
     }
     w4_block<LPR, WAVES, U>(a, x, t, partial + partial_off, tile_counter(counters, gtile, tiles), y, m, n, ks,
                             gtile - first, s, tile_cols, splits, survivor_report(counters, k, splits));

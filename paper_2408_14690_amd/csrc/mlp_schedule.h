@@ -54,12 +54,13 @@ TEAL_HD inline MlpBlock mlp_block(const MlpGrid &g, int b)
     MlpBlock out;
     const int gu = mlp_blocks_gu(g);
     if (b < gu) {
+        // no division where there is one phase or one split: it is on the way to the first load
         const int per_phase = 2 * g.phase_tiles * g.splits_gu;
-        const int p = b / per_phase;
+        const int p = g.phase_tiles == g.tiles_gu ? 0 : b / per_phase;
         const int r = b - p * per_phase;
         const int left = g.tiles_gu - p * g.phase_tiles;          // tiles of this and later phases
         const int here = left < g.phase_tiles ? left : g.phase_tiles;
-        out.split = r / (2 * here);
+        out.split = g.splits_gu == 1 ? 0 : r / (2 * here);
         const int j = r - out.split * 2 * here;
         out.kind = j & 1;
         out.tile = p * g.phase_tiles + (j >> 1);
