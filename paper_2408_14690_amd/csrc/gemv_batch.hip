@@ -109,14 +109,14 @@ __device__ __forceinline__ int compact_slice_batch(const __half *__restrict__ X,
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nseg = (k1 - k0 + 64 * VEC - 1) / (64 * VEC);
 
-    // All loads are in flight together, from one position per pass and a scalar offset per batch row.  Past
-    // the end of X they read zeros; what lies past the slice's is left out below.  Batch rows past the
-    // last repeat it and have no weight in the sums.
+    // All loads are in flight together, from one position per pass (clamped to the slice; what lies past it is
+    // left out below) and a scalar offset per batch row.  Batch rows past the last repeat it and have no
+    // weight in the sums.
     const Buffer states = buffer_of(X, 2u * (unsigned)batch * (unsigned)m);
     unsigned raw[PASSES][NB][WORDS];
 #pragma unroll
     for (int j = 0; j < PASSES; ++j) {
-        const int at = 2 * (k0 + ((w + j * WAVES) * 64 + lane) * VEC);
+        const int at = 2 * min(k0 + ((w + j * WAVES) * 64 + lane) * VEC, k1 - VEC);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int row = 2 * min(b, batch - 1) * m;
