@@ -44,7 +44,7 @@ struct SwigluReadySource {
     template <int E>
     __device__ __forceinline__ void load(Raw (&raw)[E], int k0, int len, int at) const
     {
-        pairs_of_slice<E, 16>(raw, gate, up, k0, len, at);
+        pairs_of_slice<E, kAgentScope>(raw, gate, up, k0, len, at);
     }
     __device__ __forceinline__ float prepare() const { return 0.f; }
     __device__ __forceinline__ float value(Raw r, float) const { return swiglu_value(r.x, r.y); }
