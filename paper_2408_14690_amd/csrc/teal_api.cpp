@@ -144,46 +144,12 @@ GemvShape shape_for_multi(int m, const int *n, int count, int elems_per_lane, in
     return sh;
 }
 
-// The share of the chip's time that a shape's blocks work, taking them all for as long as the largest, and 3 %
-// less per split beyond 8 (as shape_for_multi scores).
-double shape_efficiency(int m, int n, const GemvShape &sh, int ks_multiple)
-{
-    const int ks = ((m + sh.splits - 1) / sh.splits + ks_multiple - 1) / ks_multiple * ks_multiple;
-    double score = (double)n * m / ((double)kComputeUnits * sh.tile_cols * ks);
-    for (int e = 8; e < sh.splits; ++e) score *= 0.97;
-    return score;
-}
-
 // The shape of a call on rows `row_pitch` elements apart (NULL: packed rows).
-// bf16 matrices of 4097 to 8192 columns and up to 8192 input channels on cache lines: shape_for takes 192 or
-// 256 columns and 8 splits.  Tiles of 128 with about half the splits are better where they spread the work as
-// well: 192 columns leave 8 of 32 lanes idle, which counts for 5 %, and for short inputs the shorter
-// combine beats the longer pieces of a row.  us per call at 50 %, before / now: 1024 -> 4352 5.23 / 4.75,
-// 1024 -> 5120 5.36 / 4.73, 4096 -> 4352 7.42 / 6.87, 2048 -> 8192 6.75 / 6.43 (dense 10.6 / 8.7), 3072 -> 5120 7.11 / 6.38, 4096 -> 5120
-// 7.58 / 7.29 (80 % 5.73 / 5.86), 6144 -> 5120 9.26 / 8.81.  The lines: 4096 -> 6144 would take 8.1 instead of 7.7
-// (192 columns in 8 splits are exactly 256 blocks), 4096 -> 8192 dense 14.1 instead of 13.3, and between
-// 1536 and 2560 channels 192 and 128 columns are even (2048 -> 4608 5.28 / 5.45, 2048 -> 5120 5.15 / 5.06).
 GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_lanes,
                      int ks_multiple, const int *row_pitch = nullptr)
 {
-    const bool wide = wide_tiles(m, &n, row_pitch, 1, elems_per_lane);
-    const GemvShape sh =
-        shape_for(m, n, elems_per_lane, min_lanes, max_lanes, ks_multiple, teal::kMaxSlice, wide);
-    const bool idle = sh.tile_cols == 192 && (m <= 1536 || m >= 2560) && m <= 8192;
-    const bool shorter = sh.tile_cols == 256 && m <= 2048;
-    if (wide || elems_per_lane != 8 || !(idle || shorter)) return sh;
-    GemvShape narrow = sh;
-    narrow.lanes_per_row = 16;
-    narrow.tile_cols = 128;
-    narrow.splits = kComputeUnits / ((n + 127) / 128);
-    if (narrow.splits < 2 || narrow.splits > sh.splits) return sh;
-    const int ks = ((m + narrow.splits - 1) / narrow.splits + ks_multiple - 1) / ks_multiple * ks_multiple;
-    if (ks > teal::kMaxSlice) return sh;
-    narrow.splits = (m + ks - 1) / ks;
-    const double lanes = idle ? 0.95 : 1.0;
-    return shape_efficiency(m, n, narrow, ks_multiple) >= lanes * shape_efficiency(m, n, sh, ks_multiple)
-               ? narrow
-               : sh;
+    return shape_for(m, n, elems_per_lane, min_lanes, max_lanes, ks_multiple, teal::kMaxSlice,
+                     wide_tiles(m, &n, row_pitch, 1, elems_per_lane));
 }
 GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
                            int max_lanes, int ks_multiple, const int *row_pitch = nullptr)

@@ -864,3 +864,27 @@ def test_batch_ex_accepts_every_partly_filled_shape():
                                                                    lanes_per_row=lanes, tile_cols=tile, splits=splits)
                             want = T.TEAL_ERR_HIP if ok else T.TEAL_ERR_UNSUPPORTED
                             assert got == want, (batch, m, n, lanes, tile, splits)
+
+
+def test_ex_accepts_every_partly_filled_shape():
+    """teal_sparse_gemv_bf16_ex with any of its shape arguments 0: the lanes left open are those of tiles
+    that make 32 of the columns (at least 512 bytes wide where long rows lie off cache lines), so a tile of
+    up to that width is accepted without naming them, at every size.  Runs where no call can launch."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("an accepted call would launch on these addresses")
+    for m in (64, 1024, 2048, 2560, 4096, 8192, 9000):
+        for n in (8, 4096, 4104, 4352, 5120, 6144, 7168, 8192, 8256, 14336):
+            tc = min(512, max(128, ((n + 31) // 32 + 63) // 64 * 64))
+            if n % 64 and m >= 2560 and -(-n // 256) >= 12:
+                tc = max(tc, 256)
+            open_lanes = 16 if tc <= 128 else 32 if tc <= 256 else 64
+            for lanes in (0, 16, 32, 64):
+                for tile in (0, 64, 136, 192, 256, 512):
+                    for splits in (0, 1, 16, 128, 129):
+                        for waves in (0, 16):
+                            ok = tile <= 8 * (lanes or open_lanes) and splits <= 128
+                            got = T.teal_sparse_gemv_bf16_ex(W, X, 0.5, Y, m, n, WS, BIG, 0, lanes_per_row=lanes,
+                                                             tile_cols=tile, splits=splits, waves=waves)
+                            assert got == (T.TEAL_ERR_HIP if ok else T.TEAL_ERR_UNSUPPORTED), \
+                                (m, n, lanes, tile, splits, waves)

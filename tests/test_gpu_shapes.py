@@ -1,5 +1,5 @@
-"""Launch shapes on both sides of the rule for 4097 to 8192 columns: against the CPU oracle, and the calls
-that stand for one another bit for bit."""
+"""Launch shapes of matrices with 1024 to 8256 input channels and 4097 to 8192 columns: against the CPU oracle, and
+the calls that stand for one another bit for bit."""
 import numpy as np
 import pytest
 
@@ -11,11 +11,11 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n,tile,splits", [(1024, 4352, 128, 6), (1536, 5120, 128, 6), (1600, 5120, 192, 7),
-                                             (2048, 8192, 128, 4), (2112, 8192, 256, 7), (2560, 5120, 128, 6),
-                                             (4096, 4352, 128, 7), (4096, 6144, 192, 8), (8192, 5120, 128, 6),
+@pytest.mark.parametrize("m,n,tile,splits", [(1024, 4352, 192, 8), (1536, 5120, 192, 8), (1600, 5120, 192, 7),
+                                             (2048, 8192, 256, 8), (2112, 8192, 256, 7), (2560, 5120, 192, 8),
+                                             (4096, 4352, 192, 11), (4096, 6144, 192, 8), (8192, 5120, 192, 8),
                                              (8256, 5120, 192, 8)])
-def test_narrow_tiles_for_4097_to_8192_columns(T, m, n, tile, splits):   # noqa: F811
+def test_planned_shapes_of_4097_to_8192_columns(T, m, n, tile, splits):   # noqa: F811
     status, plan = T.teal_gemv_plan(16, m, n)
     assert status == 0 and (plan["tile_cols"], plan["splits"]) == (tile, splits)
     w = ti.weights_bf16(n, m, seed=m + n)
