@@ -19,6 +19,8 @@ samples from C4 / WikiText runs, Section 4.1 and Section 5):
 from __future__ import annotations
 
 import math
+import random
+from fractions import Fraction
 
 import numpy as np
 
@@ -133,6 +135,40 @@ def norm_inputs(m: int, seed: int):
     h = np.where(big, h * 40.0, h).astype(np.float32)
     gamma = (0.5 + 0.1 * rng.standard_normal(m)).astype(np.float32)
     return h, gamma
+
+
+def norm_inputs_near_tie(m: int, eps: float, off: int, seed: int):
+    """(h, gamma) whose scale 1 / sqrt(mean(h^2) + eps), computed in binary64, lies `off` units in the last
+    place of binary64 (give or take 2) from the midpoint of two neighbouring binary32 numbers, in
+    [1/4, 1/2); 8 <= m <= 16384, eps a binary32 number.  Three entries, each the binary32 below the root of what is still missing, bring
+    the sum of squares to within 2^-72 of the wanted one; entry 3 is 2^-20, and its gamma is chosen so that the
+    two binary32 scales next to the midpoint give different x_3.  The other entries are zero.  Returns
+    (h, gamma, x_3 with the lower scale, x_3 with the upper one)."""
+    rng = random.Random(1000003 * seed + 8191 * m + off)
+    f32 = np.float32
+    while True:
+        low = (1 << 23) + rng.randrange((1 << 23) - 1)          # the lower binary32, in units of 2^-25
+        want = 1 / (Fraction(2 * low + 1, 1 << 26) + Fraction(off, 1 << 54)) ** 2 - Fraction(eps)
+        h, gamma = np.zeros(m, f32), np.ones(m, f32)
+        h[3] = f32(2.0 ** -20)
+        rest = m * want - Fraction(1, 1 << 40)
+        for k in range(3):
+            root = Fraction(math.isqrt(rest.numerator * (1 << 400) // rest.denominator), 1 << 200)
+            c = f32(float(root))
+            if Fraction(float(c)) ** 2 > rest:
+                c = np.nextafter(c, f32(0))
+            h[k] = c
+            rest -= Fraction(float(c)) ** 2
+        scales = np.array([low, low + 1], np.float64).astype(f32) * f32(2.0 ** -25)
+        a = h[3] * scales
+        for tie in 1.0 + (2 * np.arange(8) + 1) / 2048.0:        # midpoints of binary16
+            g = f32(tie / float(a[1]))
+            for _ in range(4):
+                x = (a * g).astype(np.float16)
+                if x[0] != x[1]:
+                    gamma[3] = g
+                    return h, gamma, x[0], x[1]
+                g = np.nextafter(g, f32(np.inf))
 
 
 def make_X(batch: int, m: int, seed: int, dist: str) -> np.ndarray:

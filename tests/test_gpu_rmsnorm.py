@@ -276,3 +276,28 @@ def test_fused_grouped_product_int4_weights(T, name, ns, m, ps):
     torch.cuda.synchronize()
     for a, b in zip(ys, ys2):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("m", [8, 4096, 5000, 16384])
+def test_scale_near_a_rounding_boundary(T, m):
+    """Where 1 / sqrt lies next to the midpoint of two binary32 numbers the kernel computes the stated operations
+    instead of its iteration: the state is the oracle's on both sides of the midpoint, at it, and where the
+    kernel goes from one to the other (64 units).  The iteration alone, from estimates within 2^-23, gives the
+    wrong neighbour for one in 7 to 20 of the states within one unit (emulated with fma)."""
+    n = 64
+    wt = dev(ti.to_input_channel_major(ti.weights_bf16(n, m, seed=m)))
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    for eps in (0.0, EPS):
+        for off, count in ((-66, 4), (-64, 4), (-62, 4), (-2, 10), (-1, 30), (0, 30), (1, 30), (2, 10), (62, 4),
+                           (64, 4), (66, 4)):
+            for seed in range(count):
+                h, gamma, lo, hi = ti.norm_inputs_near_tie(m, eps, off, seed)
+                want = orc.rmsnorm_f16(h, gamma, eps).view(np.uint16)
+                assert np.array_equal(gpu_x(T, h, gamma, eps), want), (eps, off, seed)
+                if seed:
+                    continue
+                ys = [torch.empty(n, device="cuda") for _ in range(2)]
+                T.check(T.teal_sparse_gemv_bf16_rmsnorm_multi([wt], [0.0], ys[:1], [n], dev(h), dev(gamma), eps,
+                                                              m, ws))
+                T.check(T.teal_sparse_gemv_bf16(wt, dev(want.view(np.float16)), 0.0, ys[1], m, n, ws))
+                assert torch.equal(ys[0], ys[1]), (eps, off)

@@ -164,3 +164,19 @@ def test_product_is_the_composition_with_definition_1(n, m):
     want = ti.bf16_bits_to_f32(w).astype(np.float64) @ xs
     got = orc.sparse_gemv_bf16_rmsnorm(w, h, gamma, EPS, t)
     assert np.allclose(got, want, rtol=1e-12, atol=1e-14)
+
+
+@pytest.mark.parametrize("m", [8, 4096, 5000, 16384])
+def test_states_near_a_rounding_boundary_of_the_scale(m):
+    """teal_inputs.norm_inputs_near_tie: x_3 is what the lower or the upper of two neighbouring binary32 scales
+    gives, the lower below the midpoint and the upper above it, and both occur within one unit of it."""
+    for eps in (0.0, EPS):
+        upper = {}
+        for off in (-64, -1, 0, 1, 64):
+            for seed in range(12):
+                h, gamma, lo, hi = ti.norm_inputs_near_tie(m, eps, off, seed)
+                x = orc.rmsnorm_f16(h, gamma, eps)[3]
+                assert lo < hi and x in (lo, hi)
+                upper.setdefault(off, []).append(x == hi)
+        assert not any(upper[-64]) and all(upper[64])
+        assert 0 < sum(upper[-1] + upper[0] + upper[1]) < 36
