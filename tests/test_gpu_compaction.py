@@ -91,6 +91,55 @@ def test_w4_groups_of_long_slices(T, m):   # noqa: F811
     assert rel_l2(y[cols].cpu().numpy(), want) <= TIGHT and survivors(T, ws) == [int(kept.sum())]
 
 
+@pytest.mark.parametrize("m", [2048, 4096, 8192])
+def test_w4_one_large_or_infinite_survivor_of_a_long_slice(T, m):   # noqa: F811
+    """Two splits of 1024 to 4096 channels: how large the survivors are comes from the strips of 8 wavefronts,
+    and one survivor beyond 127, or one infinity, in any of them is enough."""
+    n = 131072
+    assert T.teal_gemv_plan(4, m, n)[1]["splits"] == 2
+    g = torch.Generator(device="cuda").manual_seed(m + 1)
+    q = torch.randint(0, 256, (m, n // 2), generator=g, device="cuda", dtype=torch.uint8)
+    scale = (0.01 + 0.01 * torch.rand(m // 128, n, generator=g, device="cuda")).half()
+    x = torch.randn(m, generator=g, device="cuda").half()
+    ws, y = workspace(T, m, n), torch.empty(n, device="cuda")
+    cols = torch.arange(0, n, 509, device="cuda")
+    b = q[:, cols // 2].view(torch.int8)
+    w = torch.where(cols % 2 == 0, (b << 4) >> 4, b >> 4).double() * scale[:, cols].double().repeat_interleave(128, 0)
+    strip = m // 16
+    for place in (0, 3 * strip + 77, 7 * strip, m // 2 - 1, m // 2, m // 2 + 4 * strip + 1, m - 1):
+        xl = x.clone()
+        xl[place] = 2000.0
+        T.check(T.teal_sparse_gemv_w4(q, scale, 128, xl, 0.5, y, m, n, ws))
+        want = (torch.where(xl.abs() > 0.5, xl.double(), 0.0)[:, None] * w).sum(0).cpu().numpy()
+        assert rel_l2(y[cols].cpu().numpy(), want) <= TIGHT, place
+        for inf in (float("inf"), -float("inf")):
+            xl[place] = inf
+            T.check(T.teal_sparse_gemv_w4(q, scale, 128, xl, 0.5, y, m, n, ws))
+            assert bool(y.isnan().all()), (place, inf)
+
+
+@pytest.mark.parametrize("m,n", [(1024, 512), (4096, 4096), (4096, 131072)])
+def test_w4_formed_input_that_overflows(T, m, n):   # noqa: F811
+    """SiLU(gate) * up beyond 65504 is an infinity of the state that W_down reads, as in the separate calls."""
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    q = torch.randint(0, 256, (m, n // 2), generator=g, device="cuda", dtype=torch.uint8)
+    scale = (0.01 + 0.01 * torch.rand(m // 128, n, generator=g, device="cuda")).half()
+    gate, up = torch.randn(m, generator=g, device="cuda"), torch.randn(m, generator=g, device="cuda")
+    ws, y, h = workspace(T, m, n), torch.empty(n, device="cuda"), torch.empty(m, dtype=torch.float16, device="cuda")
+    for place in (0, m // 2 - 1, m - 1):
+        for high, nan in ((250.0, False), (300.0, True)):      # 62500 and 90000
+            gl, ul = gate.clone(), up.clone()
+            gl[place], ul[place] = high, high
+            T.check(T.teal_swiglu_f16(gl, ul, h, m))
+            assert bool(h[place].isinf()) == nan
+            T.check(T.teal_sparse_gemv_w4_swiglu(q, scale, 128, gl, ul, 0.25, y, m, n, ws))
+            assert bool(y.isnan().all()) == nan and bool(y.isnan().any()) == nan, (place, high)
+            if not nan:
+                plain = torch.empty(n, device="cuda")
+                T.check(T.teal_sparse_gemv_w4(q, scale, 128, h, 0.25, plain, m, n, ws))
+                assert torch.equal(y, plain), place
+
+
 @pytest.mark.parametrize("m", [8, 4096, 5000, 16384])
 @pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e-12, 1.0, 1e12, 1e30])
 def test_scale_of_the_normalisation_over_its_range(T, m, scale):   # noqa: F811
