@@ -76,10 +76,6 @@ __device__ __forceinline__ void store_coherent(float *p, float v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float load_coherent(const float *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void store_coherent(int *p, int v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -173,7 +169,11 @@ __device__ __forceinline__ Buffer buffer_of(const void *first, unsigned bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(first), 0, (int)bytes, 0x00027000);
 }
-constexpr int kAgentScope = 16;       // cache policy of a buffer access: past the local L2 (load_coherent)
+// Cache policy (sc1) of a buffer access to data that crosses XCDs within a launch: write-through, and loads not
+// served from the local L2, as in store_coherent / load_coherent.  Unlike those the accesses are no atomics: what
+// keeps a store before the ticket or signal is wait_vector_memory(), and a load behind the ticket or the
+// readiness poll the fences of the __syncthreads() in between.  Never one without the other.
+constexpr int kAgentScope = 16;
 
 // E pairs (a[i], b[i]) of fp32 vectors 64 channels apart, from channel `at` of a slice of `len` that begins at
 // channel k0; zeros past its end.  CACHE: cache policy of the loads.
@@ -189,19 +189,19 @@ __device__ __forceinline__ void pairs_of_slice(float2 (&raw)[E], const float *a,
     }
 }
 
-// Where a block's activations come from.  A source loads what it needs for E channels of a
-// slice that lie 64 apart (load; zeros past the slice's end) and turns it into an fp32 value that is
-// exactly an fp16 value (value; zero for zeros); kHeavy says that value() is worth skipping for segments past the slice.
-// Between the loads and the first value() every thread of the block calls prepare()
-// once: block-wide work whose result value() needs (it may contain barriers) runs
-// there, with the slice's own loads already in flight.
-// The largest fp16 value that is not above t (t >= 0): an fp16 magnitude is above t exactly if it is
-// above this, so an fp16 state is compared as it is.
+// The largest fp16 value that is not above t (finite and >= 0: the entry points accept no other).  An fp16
+// magnitude is above t exactly if it is above this, so an fp16 state is compared as it is.
 __device__ __forceinline__ _Float16 half_threshold(float t)
 {
     return __builtin_bit_cast(_Float16, __builtin_amdgcn_cvt_pkrtz(fminf(t, 65504.f), 0.f)[0]);
 }
 
+// Where a block's activations come from.  A source loads what it needs for E channels of a slice that lie 64
+// apart (load; zeros past the slice's end) and turns it into an fp32 value that is exactly an fp16 value
+// (value; zero for zeros); kHeavy says that value() is worth skipping for segments past the slice.
+// Between the loads and the first value() every thread of the block calls prepare()
+// once: block-wide work whose result value() needs (it may contain barriers) runs
+// there, with the slice's own loads already in flight.
 struct HalfSource {                   // the hidden state itself, fp16 in memory
     static constexpr bool kHeavy = false;
     static constexpr bool kPlainHalf = true;
@@ -843,7 +843,7 @@ __device__ __forceinline__ bool block_finish(float *red,
     // same atomic, so the counter is ready for the next call without a second access.
     // (Relaxed: an agent-scope release here makes the compiler write the whole L2 back, an
     // acquire invalidates it; measured +1.0 .. +5 us and +0.5 .. +0.9 us per call.  The data
-    // this ticket orders never sits in an L2: see store_coherent / load_coherent.)
+    // this ticket orders never sits in an L2: see kAgentScope.)
     if (threadIdx.x == 0)
         last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
@@ -1122,6 +1122,10 @@ __device__ __forceinline__ int stack_group_of_block(const StackArgs<F> &sa, int 
     return k;
 }
 
+// The group is found by an index, so its matrices' arguments lie behind another load; reading all of them at once
+// (multi_block) is still the better form although it spills 8 to 18 scalar registers here: looked up one by one,
+// without spills, int8 stacks took 1.00 to 1.06 times as long, bf16 0.99 to 1.02, int4 0.99 (12 decoder
+// blocks of 2048 to 5120 channels, dense to 95 %).
 // LANES8: the format's launch shapes include 8 lanes per row (int8 weights).
 template <class F, int WAVES, int U, bool LANES8>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_stack_kernel(StackArgs<F> sa)
