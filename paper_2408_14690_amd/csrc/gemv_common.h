@@ -1124,8 +1124,8 @@ __device__ __forceinline__ int stack_group_of_block(const StackArgs<F> &sa, int 
 
 // The group is found by an index, so its matrices' arguments lie behind another load; reading all of them at once
 // (multi_block) is still the better form although it spills 8 to 18 scalar registers here: looked up one by one,
-// without spills, int8 stacks took 1.00 to 1.06 times as long, bf16 0.99 to 1.02, int4 0.99 (12 decoder
-// blocks of 2048 to 5120 channels, dense to 95 %).
+// without spills, int8 stacks took 0.99 to 1.06 times as long, bf16 0.99 to 1.02, int4 0.99 to 1.00 (decoder
+// blocks of four sizes from 2048 to 5120 channels, dense to 95 %).
 // LANES8: the format's launch shapes include 8 lanes per row (int8 weights).
 template <class F, int WAVES, int U, bool LANES8>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_stack_kernel(StackArgs<F> sa)
