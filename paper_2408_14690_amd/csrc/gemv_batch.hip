@@ -343,7 +343,7 @@ __device__ __forceinline__ float2 load_coherent2(const float *p)        // 8-byt
 // arrives last at the tile's counter adds them in split order and writes Y.
 template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *red,
-                                                   float *partial, int *counter, float *Y,
+                                                   float *partial, const Meeting &meet, int gtile, float *Y,
                                                    int tile, int col0, int cols, int s, int splits,
                                                    int n, int batch, int w,
                                                    const SurvivorReport &report)
@@ -394,7 +394,8 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     trace_mark(4);
     // the ticket wraps to zero with the last arrival: ready for the next call
     if (thread == 0)
-        last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
+        last_flag = atomicInc(reinterpret_cast<unsigned *>(meet.counters + (size_t)gtile * meet.counter_step),
+                              (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
     __syncthreads();
     trace_mark(5);
@@ -427,7 +428,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
 template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void batch_block(const void *__restrict__ W,
                                             const __half *__restrict__ X, int batch, double bound,
-                                            float *partial, int *counter, float *Y, int m, int n,
+                                            float *partial, const Meeting &meet, int gtile, float *Y, int m, int n,
                                             int ks, int tile, int s, int tile_cols, int splits,
                                             const SurvivorReport &report)
 {
@@ -439,7 +440,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     __shared__ int seg_cnt[kMaxSegs];
 
     trace_mark(0);
-    asm volatile("" ::"s"(W), "s"(partial), "s"(counter), "s"(Y));      // as in gemv_block
+    asm volatile("" ::"s"(W), "s"(partial), "s"(meet.counters), "s"(Y));      // as in gemv_block
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
     // Channels per lane by the length of the slice, so that short slices occupy every wavefront;
@@ -481,7 +482,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     stream_rows_batch(acc, list_idx, start, mine, smem, lane_base, row_bytes);
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
-    block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, counter, Y, tile, col0, tile_cols, s, splits,
+    block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, meet, gtile, Y, tile, col0, tile_cols, s, splits,
                                   n, batch, w, report);
     trace_mark(6);
 }
@@ -491,13 +492,11 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
 template <int NB, int WAVES, int PARTS>
 __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_kernel(
     const void *__restrict__ W, const __half *__restrict__ X, int batch, double bound,
-    float *partial, int *counters, float *Y, int m, int n, int ks, int tiles, int tile_cols,
-    int splits)
+    float *partial, Meeting meet, float *Y, int m, int n, int ks, int tile_cols, int splits)
 {
     const int tile = blockIdx.x;
-    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial, tile_counter(counters, tile, tiles), Y, m,
-                           n, ks, tile, blockIdx.y, tile_cols, splits,
-                           survivor_report(counters, 0, splits));
+    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial, meet, tile, Y, m, n, ks, tile, blockIdx.y,
+                                  tile_cols, splits, survivor_report(meet.counters, 0, splits));
 }
 
 // Several matrices that read the same batch of hidden states (q/k/v, gate/up:
@@ -514,12 +513,12 @@ struct BatchMultiArgs {
 
 template <int NB, int WAVES, int PARTS>
 __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
-    BatchMultiArgs ma, const __half *__restrict__ X, int batch, float *partial, int *counters,
+    BatchMultiArgs ma, const __half *__restrict__ X, int batch, float *partial, Meeting meet,
     int m, int ks, int tile_cols, int splits)
 {
     const int gtile = blockIdx.x, s = blockIdx.y;
     // all matrices' arguments at once, as in multi_block
-    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];
+    int k = 0, first = 0, n = ma.n[0];
     size_t partial_off = 0;            // each matrix owns splits * batch * n floats of partial rows
     const void *W = ma.W[0];
     float *Y = ma.Y[0];
@@ -527,10 +526,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
     asm volatile("" ::"s"(ma.W[0]), "s"(ma.W[1]), "s"(ma.W[2]), "s"(ma.W[3]), "s"(ma.Y[0]), "s"(ma.Y[1]),
                  "s"(ma.Y[2]), "s"(ma.Y[3]), "s"(ma.bound[0]), "s"(ma.bound[1]), "s"(ma.bound[2]),
                  "s"(ma.bound[3]), "s"(ma.n[0]), "s"(ma.n[1]), "s"(ma.n[2]), "s"(ma.n[3]),
-                 "s"(ma.tile_begin[4]), "s"(partial), "s"(counters), "s"(X), "s"(batch), "s"(m), "s"(splits));
+                 "s"(ma.tile_begin[4]), "s"(partial), "s"(meet.counters), "s"(X), "s"(batch), "s"(m), "s"(splits));
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count) tiles = ma.tile_begin[j + 1];
         const bool here = j < ma.count && gtile >= ma.tile_begin[j];
         partial_off += here ? (size_t)splits * batch * ma.n[j - 1] : 0;
         k = here ? j : k;
@@ -540,9 +538,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void sparse_gemv_batch_multi_kernel(
         Y = here ? ma.Y[j] : Y;
         bound = here ? ma.bound[j] : bound;
     }
-    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial + partial_off,
-                                  tile_counter(counters, gtile, tiles), Y, m, n, ks, gtile - first, s,
-                                  tile_cols, splits, survivor_report(counters, k, splits));
+    batch_block<NB, WAVES, PARTS>(W, X, batch, bound, partial + partial_off, meet, gtile, Y, m, n, ks,
+                                  gtile - first, s, tile_cols, splits, survivor_report(meet.counters, k, splits));
 }
 
 constexpr int kBatchWaves = 8;
@@ -736,6 +733,7 @@ hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, 
     const int lanes = batch_tile(batch, sh).lanes_per_row;
     const size_t lds = batch_lds(g.ks);
     const double bound = (double)batch * (double)t;
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits, true);
     const __half *X = static_cast<const __half *>(X_f16);
 #define TEAL_LAUNCH_B(NB, PARTS)                                                                        \
     do {                                                                                         \
@@ -743,7 +741,7 @@ hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, 
             return hipErrorInvalidValue;                                                         \
         hipLaunchKernelGGL((sparse_gemv_batch_kernel<NB, kBatchWaves, PARTS>), dim3(g.tiles, g.splits), \
                            dim3(kBatchWaves * 64), lds, stream, Wt, X, batch, bound, partial,    \
-                           counters, Y, m, n, g.ks, g.tiles, g.tile_cols, g.splits);             \
+                           meet, Y, m, n, g.ks, g.tile_cols, g.splits);                          \
     } while (0)
     if (batch > 4) TEAL_LAUNCH_B(8, 1);
     else if (batch > 2) TEAL_LAUNCH_B(4, 1);
@@ -777,6 +775,7 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits, true);
     const __half *X = static_cast<const __half *>(X_f16);
 #define TEAL_LAUNCH_BM(NB, PARTS)                                                                       \
     do {                                                                                         \
@@ -784,7 +783,7 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
             return hipErrorInvalidValue;                                                         \
         hipLaunchKernelGGL((sparse_gemv_batch_multi_kernel<NB, kBatchWaves, PARTS>),                    \
                            dim3(tiles, g.splits), dim3(kBatchWaves * 64), lds, stream, ma, X,   \
-                           batch, partial, counters, m, g.ks, g.tile_cols, g.splits);            \
+                           batch, partial, meet, m, g.ks, g.tile_cols, g.splits);                \
     } while (0)
     if (batch > 4) TEAL_LAUNCH_BM(8, 1);
     else if (batch > 2) TEAL_LAUNCH_BM(4, 1);

@@ -8,6 +8,7 @@ namespace teal {
 struct FmtBF16 {
     static constexpr int kElemsPerLane = 8;   // 16 bytes = 8 bf16
     static constexpr int kBitsPerElem = 16;
+    static constexpr int kGridUnit = 40;      // sums of slices up to 2048, in steps of 1e-12
     struct Args {
         const void *W;
         int ld = 0;             // elements from one row of W to the next; 0 = n
@@ -51,14 +52,15 @@ hipError_t launch_gemv_bf16(const void *Wt, const void *x_f16, float t, float *y
 {
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtBF16::kElemsPerLane, 64, kMaxLongSlice);
     FmtBF16::Args a{Wt};
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
     do {                                                                                       \
         if (!allow_large_lds(sparse_gemv_kernel<F, LPR, WAVES, U>, g.lds))                     \
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits),   \
-                           dim3(WAVES * 64), g.lds, stream, a, x, t, partial, counters, y, m,  \
-                           n, g.ks, g.tiles, g.tile_cols, g.splits);                           \
+                           dim3(WAVES * 64), g.lds, stream, a, x, t, partial, meet, y, m, n,  \
+                           g.ks, g.tile_cols, g.splits);                                       \
     } while (0)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtBF16, sh);
 #undef TEAL_LAUNCH
@@ -71,10 +73,11 @@ hipError_t launch_gemv_bf16_swiglu(const void *Wt, const float *gate, const floa
 {
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtBF16::kElemsPerLane, 64);
     FmtBF16::Args a{Wt};
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
     hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits), \
-                       dim3(WAVES * 64), g.lds, stream, a, gate, up, t, partial, counters, y,  \
-                       m, n, g.ks, g.tiles, g.tile_cols, g.splits)
+                       dim3(WAVES * 64), g.lds, stream, a, gate, up, t, partial, meet, y,  \
+                       m, n, g.ks, g.tile_cols, g.splits)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtBF16, sh);
 #undef TEAL_LAUNCH
     return hipGetLastError();
@@ -102,6 +105,7 @@ hipError_t launch_gemv_bf16_multi(int count, const void *const *Wt, const int *r
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
     do {                                                                                       \
@@ -109,7 +113,7 @@ hipError_t launch_gemv_bf16_multi(int count, const void *const *Wt, const int *r
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_multi_kernel<F, LPR, WAVES, U>),                       \
                            dim3(tiles, g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
-                           partial, counters, m, g.ks, g.tile_cols, g.splits);                 \
+                           partial, meet, m, g.ks, g.tile_cols, g.splits);                     \
     } while (0)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtBF16, sh);
 #undef TEAL_LAUNCH
@@ -154,13 +158,14 @@ hipError_t launch_gemv_bf16_rmsnorm_multi(int count, const void *const *Wt, cons
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
 #define TEAL_LAUNCH_N(LPR)                                                                     \
     do {                                                                                       \
         if (!allow_large_lds(sparse_gemv_rmsnorm_multi_kernel<FmtBF16, LPR, 4>, g.lds))        \
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtBF16, LPR, 4>),                \
                            dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma,   \
-                           h, gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits);  \
+                           h, gamma, eps, 1.0 / m, partial, meet, m, g.ks, g.tile_cols, g.splits);  \
     } while (0)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_N(32);

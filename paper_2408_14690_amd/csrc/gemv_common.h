@@ -119,29 +119,63 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
 // workspace: the realised sparsity of a call (Section 4.2 fixes a target p per matrix
 // and a threshold estimated offline, so the two can drift apart).  The blocks of a
 // matrix's first output tile each know the count of their K-slice; they travel like
-// the partial rows (write-through store, then the arrival counter), and the block that
-// finishes that tile last adds them.  The report area follows the arrival counters:
-// int total[kMaxMatrices] (padded to kReportHeaderInts), then one row of `splits`
+// their sums, and the block that arrives last adds them.  The report area follows the arrival
+// counters: int total[kMaxMatrices] (padded to kReportHeaderInts), then one row of `splits`
 // slice counts per matrix.
 struct SurvivorReport {
     int *total;        // this matrix's slot
     int *per_split;    // this matrix's row of slice counts
+    int matrix;
 };
+
+// Column words: bits 0-3 count the arrivals, bits 4-7 those that left a part of their sum apart, bits 8-63
+// are the sum.  All arrivals but the last find at most 15 in either count.
+constexpr int kWordSplits = 16;
+constexpr unsigned kWordApart = 1u << 4;
+constexpr int kWordSumShift = 8;
+// The words, a flag word per column and one line per matrix for the survivors' count share the area of the
+// arrival counters, the part of a workspace that is zero between calls: 87338 columns.  Launches of more
+// columns or splits, and those that need to know when a tile is finished (by_tile), use the counters.
+constexpr int kReportWordBytes = kMaxMatrices * 128;
+constexpr int kWordColumns = (kCounterBytes - kReportWordBytes) / (sizeof(unsigned long long) + sizeof(unsigned));
+
+// How the K-slices of the tiles of a launch meet; see block_finish.  A tile's words begin on a 128-byte line,
+// and so does an arrival counter wherever the area has room for that (8192 tiles): atomics on one line
+// are executed one after the other, about 10 ns each, and with 16 counters to a line the 256 arrivals of
+// a launch queued up for 2.6 us (2048 x 2048: last ticket 6.0 us after the first block's start,
+// 3.6 us with a line per counter).  Worked out on the host: on the device it is on the way to the first load.
+struct Meeting {
+    int *counters;
+    int counter_step;      // ints from one tile's arrival counter to the next one's
+    int word_step;         // words from one tile's to the next one's; 0: arrival counters
+    int words;             // of all tiles; the flags follow them
+};
+inline Meeting meeting_of(int *counters, int tiles, int tile_cols, int splits, bool by_tile = false)
+{
+    Meeting m;
+    m.counters = counters;
+    m.counter_step = tiles <= kMaxSpacedTiles ? kCounterLineInts : 1;
+    const long long step = (tile_cols + 15) / 16 * 16;
+    const bool words = !by_tile && splits > 1 && splits <= kWordSplits && tiles * step <= kWordColumns;
+    m.word_step = words ? (int)step : 0;
+    m.words = words ? (int)(tiles * step) : 0;
+    return m;
+}
 
 __device__ __forceinline__ SurvivorReport survivor_report(int *counters_base, int matrix, int splits)
 {
     int *area = counters_base + kCounterBytes / sizeof(int);
-    return SurvivorReport{area + matrix, area + kReportHeaderInts + matrix * splits};
+    return SurvivorReport{area + matrix, area + kReportHeaderInts + matrix * splits, matrix};
 }
 
 // Called by one thread of a block of tile 0 before the block's arrival (or instead of it
-// when there is one split).
+// when there is one split).  Where there are column words the counts have one too, see block_finish.
 __device__ __forceinline__ void report_slice(const SurvivorReport &r, int s, int splits, int cnt)
 {
     store_coherent(splits == 1 ? r.total : r.per_split + s, cnt);
 }
 
-// Called by one wavefront of the block that arrived last at tile 0.
+// With arrival counters, by one wavefront of the block that arrived last at tile 0.
 __device__ __forceinline__ void report_total(const SurvivorReport &r, int splits)
 {
     const int lane = threadIdx.x & 63;
@@ -151,15 +185,48 @@ __device__ __forceinline__ void report_total(const SurvivorReport &r, int splits
     if (lane == 0) store_coherent(r.total, sum);
 }
 
-// The arrival counter of output tile `tile` of a launch with `tiles` tiles (over all its
-// matrices).  A counter has a 128-byte line of its own wherever the area has room for that
-// (8192 tiles; every shape the library picks has far fewer): atomics on one line are executed
-// one after the other, about 10 ns each, and with 16 counters to a line the 256 arrivals of
-// a launch queued up for 2.6 us (2048 x 2048: last ticket 6.0 us after the first block's
-// start, 3.6 us with a line per counter).
-__device__ __forceinline__ int *tile_counter(int *counters, int tile, int tiles)
+// The sums of up to kWordSplits slices are added as whole multiples of 2^-UNIT: whole numbers add up to the
+// same in any order, so the arrivals need no order, and their sum is rounded to fp32 once.
+// A slice's sum is within the grid, |sum| < 2^(51 - UNIT), and loses no more than what its wavefronts' sums
+// were rounded by: where the largest of those is below 2^(22 - UNIT) and the grid does not hold
+// the sum exactly, what the grid leaves is kept apart, and a sum beyond the grid (an infinity, a NaN) is kept
+// apart whole.  What is kept apart is added in fp64, in the order of the slices.
+struct GridSum {
+    long long whole;     // multiples of 2^-UNIT
+    float apart;         // what is left, zero unless `split`
+    bool split;
+};
+constexpr double kGridMagic = 0x1.8p52;         // x + kGridMagic rounds x to a whole number, in the low bits of the sum
+// takes the magic's own bits off the word again and counts one arrival
+constexpr unsigned long long kGridOnce =
+    1u - (__builtin_bit_cast(unsigned long long, kGridMagic) << kWordSumShift);
+template <int UNIT>
+__device__ __forceinline__ GridSum grid_sum(float sum, float largest)
 {
-    return counters + (size_t)tile * (tiles <= kMaxSpacedTiles ? kCounterLineInts : 1);
+#pragma clang fp contract(off)
+    constexpr double kScale = (double)(1ull << UNIT);
+    const double x = (double)sum * kScale;
+    const double shifted = x + kGridMagic;
+    const double left = x - (shifted - kGridMagic);
+    const bool inside = fabsf(sum) < (float)(1ull << 51) / (float)kScale;
+    GridSum g;
+    g.whole = inside ? __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic) : 0;
+    g.split = !inside || (left != 0.0 && largest < (float)(1u << 22) / (float)kScale);
+    g.apart = !inside ? sum : g.split ? (float)(left * (1.0 / kScale)) : 0.f;      // exact
+    return g;
+}
+// Whether a sum needs none of that (to spare the wavefronts the rest of grid_sum).
+template <int UNIT>
+__device__ __forceinline__ bool grid_plain(float sum, float largest)
+{
+    constexpr float kUnit = 1.f / (float)(1ull << UNIT);
+    return (fabsf(sum) < (float)(1ull << 51) * kUnit) & (largest >= (float)(1u << 22) * kUnit);
+}
+template <int UNIT>
+__device__ __forceinline__ float grid_value(long long whole, double apart)
+{
+#pragma clang fp contract(off)
+    return (float)((double)whole * (1.0 / (double)(1ull << UNIT)) + apart);
 }
 
 // Part of a vector as a buffer: a load past its `bytes` reads zero instead of memory, so the lanes
@@ -775,25 +842,30 @@ __device__ __forceinline__ void store_wave_sums(const float (&acc)[N], float *ds
     }
 }
 
-// Sums the wavefronts' accumulators through LDS.  With one split the sums are
-// the outputs.  Otherwise the block writes its fp32 partial row, and the block
-// that arrives last at the tile's counter adds the partial rows of all splits
-// in a fixed order (results do not depend on which block is last) and writes
-// y.  The split-K combine of Section 4.4, without atomics on y and without a
-// second launch.  The tile is columns [col0, col0 + cols) of y, cols <= TN.
-// Returns (block-uniform) whether this block wrote the tile's outputs.
+// Sums the wavefronts' accumulators through LDS.  With one split the sums are the outputs.  Otherwise the
+// slices of the tile meet (the split-K combine of Section 4.4, without a second launch), in one of two ways
+// with the same result, which does not depend on the order in which they arrive:
+//   column words: a slice adds its sum, as a whole number, to the word of each column, and whoever finds
+//     all others there has the column's sum in hand and writes y;
+//   partial rows: a slice writes its sums to a row of its own, and the block that arrives last at the tile's
+//     counter adds the rows and writes y.
+// The first takes one trip to memory behind the last sum, the second three (the stores' acknowledgement,
+// the counter, the rows), 0.4 to 0.5 us each while other blocks still stream (us per call, rows /
+// words: 2048 x 2048 4.45 / 3.95, 4096 x 4096 6.47 / 5.78, Llama-3-8B q + k + v 8.56 / 7.9).
+// The tile is columns [col0, col0 + cols) of y, cols <= TN.  Returns (block-uniform) whether this block wrote
+// the tile's outputs; false with column words, whose columns may be written by different blocks.
 // The combine buffer has SUMS rows of combine_row floats, a row per wavefront unless a format
 // says otherwise.
 template <class F, int LPR, int WAVES, int SUMS = WAVES>
-__device__ __forceinline__ bool block_finish(float *red,
-                                             float *partial, int *counter, float *y, int tile,
-                                             int col0, int cols, int s, int splits, int n,
-                                             const typename F::Args &a, const SurvivorReport &report)
+__device__ __forceinline__ bool block_finish(float *red, float *partial, const Meeting &meet, int gtile,
+                                             float *y, int tile, int col0, int cols, int s, int splits, int n,
+                                             const typename F::Args &a, const SurvivorReport &report, int cnt)
 {
     constexpr int EPL = F::kElemsPerLane;
     constexpr int TN = LPR * EPL;
     constexpr int THREADS = WAVES * 64;
     constexpr int OWN = (TN + THREADS - 1) / THREADS;     // columns c = thread + k * THREADS
+    constexpr int UNIT = F::kGridUnit;
     __shared__ int last_flag;
     const int w = threadIdx.x >> 6;
     if (cols > n - col0) cols = n - col0;
@@ -820,19 +892,105 @@ __device__ __forceinline__ bool block_finish(float *red,
         return true;
     }
 
+    // The sum of column c over this block's wavefronts and the largest of its terms.
+    const auto sum_of = [&](int c, float &largest) {
+        float sum = 0.f;
+        largest = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < SUMS; ++ww) {
+            const float v = red[ww * ROW + combine_index<EPL, LPR>(c)];
+            sum += v;
+            largest = fmaxf(largest, fabsf(v));
+        }
+        return sum;
+    };
+    const Buffer row = buffer_of(partial + (size_t)s * n + col0, 4u * (unsigned)cols);
+    if (meet.word_step) {
+        unsigned long long *const first = reinterpret_cast<unsigned long long *>(meet.counters);
+        unsigned long long *const word = first + gtile * meet.word_step;
+        unsigned *const apart_in = reinterpret_cast<unsigned *>(first + meet.words) + gtile * meet.word_step;
+        unsigned long long mine[OWN], found[OWN];
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int c = k * THREADS + (int)threadIdx.x;
+            if (c < cols) {
+                float largest;
+                const float sum = sum_of(c, largest);
+                const double shifted = (double)sum * (double)(1ull << UNIT) + kGridMagic;
+                mine[k] = (__builtin_bit_cast(unsigned long long, shifted) << kWordSumShift) + kGridOnce;
+                if (__builtin_expect(!grid_plain<UNIT>(sum, largest), 0)) {
+                    const GridSum g = grid_sum<UNIT>(sum, largest);
+                    mine[k] = ((unsigned long long)g.whole << kWordSumShift) + 1u;
+                    if (g.split) {             // flag and value are there before the word tells of them
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g.apart), row, 4 * c, 0, kAgentScope);
+                        __hip_atomic_fetch_or(apart_in + c, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        wait_vector_memory();
+                        mine[k] += kWordApart;
+                    }
+                }
+                found[k] = __hip_atomic_fetch_add(word + c, mine[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        // The survivors' count travels beside the sums: ahead of the row stream the loads behind it would
+        // wait for it.
+        unsigned long long *count_word =
+            reinterpret_cast<unsigned long long *>(meet.counters + kCounterBytes / sizeof(int)) -
+            (kMaxMatrices - report.matrix) * 16;
+        const bool reports = tile == 0 && threadIdx.x == (WAVES - 1) * 64;
+        unsigned long long counted = 0;
+        asm volatile("" : "+v"(count_word));       // (known to be one address, it would be added up over lanes first)
+        if (reports)
+            counted = __hip_atomic_fetch_add(count_word, ((unsigned long long)cnt << kWordSumShift) + 1u,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        trace_mark(4);
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int c = k * THREADS + (int)threadIdx.x;
+            if (c < cols && (found[k] & (kWordApart - 1u)) == (unsigned)splits - 1u) {
+                double apart = 0.0;
+                if (__builtin_expect(((found[k] | mine[k]) & (15u * kWordApart)) != 0, 0)) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    const unsigned from = __hip_atomic_load(apart_in + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const Buffer part = buffer_of(partial + col0, 4u * ((unsigned)(splits - 1) * n + cols));
+                    float v[kWordSplits];
+#pragma unroll
+                    for (int u = 0; u < kWordSplits; ++u)
+                        v[u] = __uint_as_float(
+                            __builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
+#pragma unroll
+                    for (int u = 0; u < kWordSplits; ++u) apart += from >> u & 1u ? (double)v[u] : 0.0;
+                    __hip_atomic_store(apart_in + c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                // ready for the next call
+                __hip_atomic_store(word + c, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const long long whole = ((long long)found[k] >> kWordSumShift) + ((long long)mine[k] >> kWordSumShift);
+                store_coherent(y + col0 + c, F::finish(grid_value<UNIT>(whole, apart), scale[k]));
+            }
+        }
+        if (reports && (counted & 255u) == (unsigned)splits - 1u) {
+            store_coherent(report.total, cnt + (int)(counted >> kWordSumShift));
+            __hip_atomic_store(count_word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        trace_mark(5);
+        return false;
+    }
+
     // The 8 XCDs have separate L2s.  A device-wide fence would write back and
     // invalidate a whole L2 per block; instead the partial rows themselves move
     // with device-coherent accesses (write-through stores, cache-bypassing
     // loads), ordered by the arrival counter: every thread waits for its stores
     // to complete, the block synchronises, then one thread takes the ticket.
-    const Buffer row = buffer_of(partial + (size_t)s * n + col0, 4u * (unsigned)cols);
+    const bool grid = splits <= kWordSplits;
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
         const int c = k * THREADS + (int)threadIdx.x;
         if (c < cols) {
-            float sum = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
+            float largest;
+            float sum = sum_of(c, largest);
+            if (grid) {                        // as the column words take it
+                const GridSum g = grid_sum<UNIT>(sum, largest);
+                if (!g.split) sum = grid_value<UNIT>(g.whole, 0.0);
+            }
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), row, 4 * c, 0, kAgentScope);
         }
     }
@@ -845,7 +1003,8 @@ __device__ __forceinline__ bool block_finish(float *red,
     // acquire invalidates it; measured +1.0 .. +5 us and +0.5 .. +0.9 us per call.  The data
     // this ticket orders never sits in an L2: see kAgentScope.)
     if (threadIdx.x == 0)
-        last_flag = atomicInc(reinterpret_cast<unsigned *>(counter), (unsigned)splits - 1u) ==
+        last_flag = atomicInc(reinterpret_cast<unsigned *>(meet.counters + (size_t)gtile * meet.counter_step),
+                              (unsigned)splits - 1u) ==
                     (unsigned)splits - 1u;
     __syncthreads();
     trace_mark(5);
@@ -862,6 +1021,7 @@ __device__ __forceinline__ bool block_finish(float *red,
     // address or a branch each (from the ticket to the end of 2048 x 2048 0.76 -> 0.60 us, 4.70 -> 4.53 us
     // per call).
     constexpr int MAXLD = 16;
+    static_assert(MAXLD == kWordSplits, "sums on the grid are added in one round of loads");
     float sum[OWN];
 #pragma unroll
     for (int k = 0; k < OWN; ++k) sum[k] = 0.f;
@@ -877,8 +1037,20 @@ __device__ __forceinline__ bool block_finish(float *red,
                 for (int u = 0; u < MAXLD; ++u)
                     v[u] = __uint_as_float(
                         __builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
+                if (grid) {
+                    long long whole = 0;
+                    double apart = 0.0;
 #pragma unroll
-                for (int u = 0; u < MAXLD; ++u) sum[k] += v[u];
+                    for (int u = 0; u < MAXLD; ++u) {
+                        const GridSum g = grid_sum<UNIT>(v[u], 0.f);
+                        whole += g.whole;
+                        apart += (double)g.apart;
+                    }
+                    sum[k] = grid_value<UNIT>(whole, apart);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < MAXLD; ++u) sum[k] += v[u];
+                }
             }
         }
     }
@@ -909,8 +1081,8 @@ __device__ __forceinline__ int lane_column(int col0, int cols, int n, int l)
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <class F, int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &x,
-                                           float t, float *partial, int *counter, float *y, int m,
-                                           int n, int ks, int tile, int s, int tile_cols,
+                                           float t, float *partial, const Meeting &meet, int gtile,
+                                           float *y, int m, int n, int ks, int tile, int s, int tile_cols,
                                            int splits, const SurvivorReport &report)
 {
     constexpr int EPL = F::kElemsPerLane;
@@ -921,7 +1093,7 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
 
     // Every argument is read now: left to the compiler, the weights' address was fetched between the
     // compaction and the first row, the outputs' behind the last one, a scalar load's latency each.
-    asm volatile("" ::"s"(a.W), "s"(a.ld), "s"(partial), "s"(counter), "s"(y));
+    asm volatile("" ::"s"(a.W), "s"(a.ld), "s"(partial), "s"(meet.counters), "s"(y));
     const int k0 = s * ks;
     const int k1 = min(m, k0 + ks);
     int cnt = 0;
@@ -945,7 +1117,7 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     }
 
     trace_mark(2);
-    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
+    if (tile == 0 && !meet.word_step && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int start, mine;
@@ -964,8 +1136,8 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
-    return block_finish<F, LPR, WAVES>(red, partial, counter, y, tile, col0, tile_cols, s, splits,
-                                       n, a, report);
+    return block_finish<F, LPR, WAVES>(red, partial, meet, gtile, y, tile, col0, tile_cols, s, splits, n, a,
+                                       report, cnt);
 }
 
 // One matrix per launch.  Grid: tiles x splits blocks (two dimensions: a division of the block index
@@ -975,14 +1147,13 @@ __device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &
 // of EPL, <= LPR * EPL) is the width of an output tile.
 template <class F, int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_kernel(
-    typename F::Args a, const __half *__restrict__ x, float t, float *partial, int *counters,
-    float *y, int m, int n, int ks, int tiles, int tile_cols, int splits)
+    typename F::Args a, const __half *__restrict__ x, float t, float *partial, Meeting meet,
+    float *y, int m, int n, int ks, int tile_cols, int splits)
 {
     trace_mark(0);
     const int tile = blockIdx.x;
-    gemv_block<F, LPR, WAVES, U>(a, HalfSource{x}, t, partial, tile_counter(counters, tile, tiles),
-                                 y, m, n, ks, tile, blockIdx.y, tile_cols, splits,
-                                 survivor_report(counters, 0, splits));
+    gemv_block<F, LPR, WAVES, U>(a, HalfSource{x}, t, partial, meet, tile, y, m, n, ks, tile, blockIdx.y,
+                                 tile_cols, splits, survivor_report(meet.counters, 0, splits));
     trace_mark(6);
 }
 
@@ -992,15 +1163,12 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_kernel(
 template <class F, int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_swiglu_kernel(
     typename F::Args a, const float *__restrict__ gate, const float *__restrict__ up, float t,
-    float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
-    int splits)
+    float *partial, Meeting meet, float *y, int m, int n, int ks, int tile_cols, int splits)
 {
     trace_mark(0);
     const int tile = blockIdx.x;
-    gemv_block<F, LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
-                                 tile_counter(counters, tile, tiles), y, m, n, ks, tile,
-                                 blockIdx.y, tile_cols, splits,
-                                 survivor_report(counters, 0, splits));
+    gemv_block<F, LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial, meet, tile, y, m, n, ks, tile,
+                                 blockIdx.y, tile_cols, splits, survivor_report(meet.counters, 0, splits));
     trace_mark(6);
 }
 
@@ -1023,13 +1191,13 @@ struct MultiArgs {
 
 template <class F, int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x, float *partial,
-                                            int *counters, int m, int ks, int tile_cols, int splits,
+                                            const Meeting &meet, int m, int ks, int tile_cols, int splits,
                                             int gtile, int s)
 {
     trace_mark(0);
     // All matrices' arguments are read at once and one is selected: looked up by the index found, they
     // would be a second scalar load behind the first, 0.4 us of every grouped call.
-    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];
+    int k = 0, first = 0, n = ma.n[0];
     size_t partial_off = 0;            // each matrix owns splits * n floats of partial rows
     typename F::Args a = ma.a[0];
     float *y = ma.y[0];
@@ -1037,11 +1205,10 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
     asm volatile("" ::"s"(ma.y[0]), "s"(ma.y[1]), "s"(ma.y[2]), "s"(ma.y[3]), "s"(ma.n[0]), "s"(ma.n[1]),
                  "s"(ma.n[2]), "s"(ma.n[3]), "s"(ma.t[0]), "s"(ma.t[1]), "s"(ma.t[2]), "s"(ma.t[3]),
                  "s"(ma.a[0].W), "s"(ma.a[1].W), "s"(ma.a[2].W), "s"(ma.a[3].W), "s"(ma.tile_begin[4]),
-                 "s"(partial), "s"(counters), "s"(splits), "s"(ks), "s"(tile_cols), "s"(m));
+                 "s"(partial), "s"(meet.counters), "s"(splits), "s"(ks), "s"(tile_cols), "s"(m));
     F::read_now(ma.a);
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count) tiles = ma.tile_begin[j + 1];
         const bool here = j < ma.count && gtile >= ma.tile_begin[j];
         partial_off += here ? (size_t)splits * ma.n[j - 1] : 0;
         k = here ? j : k;
@@ -1051,19 +1218,18 @@ __device__ __forceinline__ void multi_block(const MultiArgs<F> &ma, const XS &x,
         t = here ? ma.t[j] : t;
         F::select(a, ma.a[j], here);
     }
-    gemv_block<F, LPR, WAVES, U>(a, x, t, partial + partial_off, tile_counter(counters, gtile, tiles), y, m,
-                                 n, ks, gtile - first, s, tile_cols, splits,
-                                 survivor_report(counters, k, splits));
+    gemv_block<F, LPR, WAVES, U>(a, x, t, partial + partial_off, meet, gtile, y, m, n, ks, gtile - first, s,
+                                 tile_cols, splits, survivor_report(meet.counters, k, splits));
     trace_mark(6);
 }
 
 template <class F, int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_multi_kernel(
-    MultiArgs<F> ma, const __half *__restrict__ x, float *partial, int *counters, int m, int ks,
+    MultiArgs<F> ma, const __half *__restrict__ x, float *partial, Meeting meet, int m, int ks,
     int tile_cols, int splits)
 {
     asm volatile("" ::"s"(x));                 // as in multi_block
-    multi_block<F, LPR, WAVES, U>(ma, HalfSource{x}, partial, counters, m, ks, tile_cols, splits,
+    multi_block<F, LPR, WAVES, U>(ma, HalfSource{x}, partial, meet, m, ks, tile_cols, splits,
                                   (int)blockIdx.x, (int)blockIdx.y);
 }
 
@@ -1075,12 +1241,12 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_multi_kernel(
 template <class F, int LPR, int U>
 __global__ __launch_bounds__(kNormWaves * 64) void sparse_gemv_rmsnorm_multi_kernel(
     MultiArgs<F> ma, const float *__restrict__ h, const float *__restrict__ gamma, float eps,
-    double inv_m, float *partial, int *counters, int m, int ks, int tile_cols, int splits)
+    double inv_m, float *partial, Meeting meet, int m, int ks, int tile_cols, int splits)
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
     asm volatile("" ::"s"(h), "s"(gamma), "s"(eps), "s"(inv_m));      // as in multi_block
     multi_block<F, LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, inv_m, eps, wave_sums}, partial,
-                                       counters, m, ks, tile_cols, splits, (int)blockIdx.x,
+                                       meet, m, ks, tile_cols, splits, (int)blockIdx.x,
                                        (int)blockIdx.y);
 }
 
@@ -1098,7 +1264,7 @@ struct StackGroup {
     MultiArgs<F> ma;
     const __half *x;
     float *partial;
-    int *counters;
+    Meeting meet;
     int m, ks, tile_cols, splits;
     int lanes_per_row;               // 16, 32 or 64
 };
@@ -1135,16 +1301,16 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_stack_kernel(StackArgs
     const HalfSource x{sg.x};
     const int tiles = sg.ma.tile_begin[sg.ma.count], gtile = block % tiles, s = block / tiles;
     if (sg.lanes_per_row == 64)
-        multi_block<F, 64, WAVES, U>(sg.ma, x, sg.partial, sg.counters, sg.m, sg.ks, sg.tile_cols,
+        multi_block<F, 64, WAVES, U>(sg.ma, x, sg.partial, sg.meet, sg.m, sg.ks, sg.tile_cols,
                                      sg.splits, gtile, s);
     else if (sg.lanes_per_row == 32)
-        multi_block<F, 32, WAVES, U>(sg.ma, x, sg.partial, sg.counters, sg.m, sg.ks, sg.tile_cols,
+        multi_block<F, 32, WAVES, U>(sg.ma, x, sg.partial, sg.meet, sg.m, sg.ks, sg.tile_cols,
                                      sg.splits, gtile, s);
     else if (!LANES8 || sg.lanes_per_row == 16)
-        multi_block<F, 16, WAVES, U>(sg.ma, x, sg.partial, sg.counters, sg.m, sg.ks, sg.tile_cols,
+        multi_block<F, 16, WAVES, U>(sg.ma, x, sg.partial, sg.meet, sg.m, sg.ks, sg.tile_cols,
                                      sg.splits, gtile, s);
     else if constexpr (LANES8)
-        multi_block<F, 8, WAVES, U>(sg.ma, x, sg.partial, sg.counters, sg.m, sg.ks, sg.tile_cols,
+        multi_block<F, 8, WAVES, U>(sg.ma, x, sg.partial, sg.meet, sg.m, sg.ks, sg.tile_cols,
                                     sg.splits, gtile, s);
 }
 
@@ -1255,7 +1421,7 @@ hipError_t fill_stack_args(StackArgs<F> &sa, size_t &lds, int groups, const Stac
         }
         sg.x = static_cast<const __half *>(dg.x_f16);
         sg.partial = dg.partial;
-        sg.counters = dg.counters;
+        sg.meet = meeting_of(dg.counters, sg.ma.tile_begin[dg.count], g.tile_cols, g.splits);
         sg.m = dg.m;
         sg.ks = g.ks;
         sg.tile_cols = g.tile_cols;

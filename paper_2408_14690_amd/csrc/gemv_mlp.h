@@ -61,7 +61,7 @@ struct MlpArgs {
     int m;                       // input channels of gate / up
     int ks_gu;
     float *partial_gu;           // [2][splits_gu][f]
-    int *counters_gu;            // region of the gate / up products: counters, survivor report
+    Meeting meet_gu;             // region of the gate / up products: counters, survivor report
     // down
     typename F::Args a_d;
     float *y_d;
@@ -69,7 +69,7 @@ struct MlpArgs {
     int n_d;                     // output channels of W_down
     int tile_cols_d;
     float *partial_d;
-    int *counters_d;             // region of the W_down product
+    Meeting meet_d;              // region of the W_down product
     int *control;
     unsigned spin_limit;
 };
@@ -80,11 +80,11 @@ struct GemvBody {
     typedef F Format;
     template <int LPR, class XS>
     static __device__ __forceinline__ bool run(const typename F::Args &a, const XS &x, float t,
-                                               float *partial, int *counter, float *y, int m,
+                                               float *partial, const Meeting &meet, int gtile, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)
     {
-        return gemv_block<F, LPR, 8, 4>(a, x, t, partial, counter, y, m, n, ks, tile, s,
+        return gemv_block<F, LPR, 8, 4>(a, x, t, partial, meet, gtile, y, m, n, ks, tile, s,
                                         tile_cols, splits, report);
     }
 };
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
     const MlpGrid &g = A.grid;
     // gate's and up's arguments at once, as in multi_block
     asm volatile("" ::"s"(A.a_gu[0].W), "s"(A.a_gu[1].W), "s"(A.y_gu[0]), "s"(A.y_gu[1]), "s"(A.t_gu[0]),
-                 "s"(A.t_gu[1]), "s"(A.x), "s"(A.m), "s"(A.ks_gu), "s"(A.partial_gu), "s"(A.counters_gu),
+                 "s"(A.t_gu[1]), "s"(A.x), "s"(A.m), "s"(A.ks_gu), "s"(A.partial_gu), "s"(A.meet_gu.counters),
                  "s"(g.f), "s"(g.tiles_gu), "s"(g.tile_cols_gu), "s"(g.splits_gu), "s"(g.phase_tiles));
     const MlpBlock blk = mlp_block(g, (int)blockIdx.x);
     trace_mark(0);
@@ -114,10 +114,9 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
         Body::Format::select(a, A.a_gu[1], k != 0);
         const bool wrote = Body::template run<LPR_GU>(
             a, HalfSource{A.x}, k ? A.t_gu[1] : A.t_gu[0],
-            A.partial_gu + (k ? (size_t)g.splits_gu * g.f : 0),
-            tile_counter(A.counters_gu, k * g.tiles_gu + blk.tile, 2 * g.tiles_gu),
+            A.partial_gu + (k ? (size_t)g.splits_gu * g.f : 0), A.meet_gu, k * g.tiles_gu + blk.tile,
             k ? A.y_gu[1] : A.y_gu[0], A.m, g.f, A.ks_gu, blk.tile, blk.split, g.tile_cols_gu, g.splits_gu,
-            survivor_report(A.counters_gu, k, g.splits_gu));
+            survivor_report(A.meet_gu.counters, k, g.splits_gu));
         trace_mark(6);
         if (!wrote) return;
         // The tile's columns of gate / up are written (write-through stores): once every
@@ -161,12 +160,10 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
     trace_mark(7);
     if (!inputs_ready) return;
 
-    const bool wrote = Body::template run<LPR_D>(
-        A.a_d, SwigluReadySource{A.y_gu[0], A.y_gu[1]}, A.t_d, A.partial_d,
-        tile_counter(A.counters_d, blk.tile, g.tiles_d), A.y_d, g.f, A.n_d, g.ks_d, blk.tile,
-        blk.split, A.tile_cols_d, g.splits_d, survivor_report(A.counters_d, 0, g.splits_d));
+    Body::template run<LPR_D>(A.a_d, SwigluReadySource{A.y_gu[0], A.y_gu[1]}, A.t_d, A.partial_d, A.meet_d,
+                              blk.tile, A.y_d, g.f, A.n_d, g.ks_d, blk.tile, blk.split, A.tile_cols_d, g.splits_d,
+                              survivor_report(A.meet_d.counters, 0, g.splits_d));
     trace_mark(6);
-    (void)wrote;
 }
 
 // Host side.  Geometry of the two products from their launch shapes, argument block.
@@ -208,13 +205,14 @@ bool fill_mlp_args(MlpArgs<F> &A, size_t &lds, const MlpHostArgs &h, const MlpLa
     A.m = h.m;
     A.ks_gu = ggu.ks;
     A.partial_gu = h.partial_gu;
-    A.counters_gu = h.counters_gu;
+    // by arrival counters: the readers of a tile are told when all of it is written
+    A.meet_gu = meeting_of(h.counters_gu, 2 * ggu.tiles, ggu.tile_cols, ggu.splits, true);
     A.y_d = h.y;
     A.t_d = h.t_down;
     A.n_d = h.d;
     A.tile_cols_d = gd.tile_cols;
     A.partial_d = h.partial_d;
-    A.counters_d = h.counters_d;
+    A.meet_d = meeting_of(h.counters_d, gd.tiles, gd.tile_cols, gd.splits);
     A.control = h.control;
     A.spin_limit = L.spin_limit;
     lds = (ggu.lds > gd.lds ? ggu.lds : gd.lds) + (size_t)(L.extra_lds > 0 ? L.extra_lds : 0);

@@ -14,6 +14,7 @@ namespace teal {
 struct FmtW8 {
     static constexpr int kElemsPerLane = 16;   // 16 bytes = 16 int8
     static constexpr int kBitsPerElem = 8;
+    static constexpr int kGridUnit = 28;      // sums before the scale: up to 8e6, in steps of 4e-9
     struct Args {
         const void *W;
         const __half *scale;
@@ -56,6 +57,7 @@ struct FmtW8 {
 struct FmtW4 {
     static constexpr int kElemsPerLane = 32;   // 16 bytes = 32 nibbles
     static constexpr int kBitsPerElem = 4;
+    static constexpr int kGridUnit = 40;      // as bf16: the groups' scales are in the sums
     struct Args {
         const void *W;
         const __half *scale;
@@ -165,7 +167,7 @@ struct W4Sums {
 // Returns (block-uniform) whether this block wrote the tile's outputs.
 template <int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
-                                         float t, float *partial, int *counter, float *y, int m,
+                                         float t, float *partial, const Meeting &meet, int gtile, float *y, int m,
                                          int n, int ks, int tile, int s, int tile_cols, int splits,
                                          const SurvivorReport &report)
 {
@@ -181,7 +183,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     float *red = reinterpret_cast<float *>(smem + (size_t)ks * sizeof(int2));
     __shared__ int counts[kCompactInts];
 
-    asm volatile("" ::"s"(a.W), "s"(a.scale), "s"(partial), "s"(counter), "s"(y));   // as in gemv_block
+    asm volatile("" ::"s"(a.W), "s"(a.scale), "s"(partial), "s"(meet.counters), "s"(y));   // as in gemv_block
     const int k0 = s * ks;                       // multiple of 128
     const int k1 = min(m, k0 + ks);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -202,7 +204,7 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
                                                     &magnitude);
 
     trace_mark(2);
-    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
+    if (tile == 0 && !meet.word_step && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int lane = threadIdx.x & 63;
     const int l = lane & 15, g = lane >> 4;
     const int col0 = tile * tile_cols;
@@ -369,20 +371,19 @@ __device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
     for (int r = 0; r < 4; ++r)
         *reinterpret_cast<float2 *>(row + EPL * (4 * g + r)) =
             make_float2(acc[0][r] * unit, acc[1][r] * unit);
-    return block_finish<F, LPR, WAVES, SHARES>(red, partial, counter, y, tile, col0, tile_cols, s,
-                                               splits, n, a, report);
+    return block_finish<F, LPR, WAVES, SHARES>(red, partial, meet, gtile, y, tile, col0, tile_cols, s,
+                                               splits, n, a, report, cnt);
 }
 
 template <int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_kernel(
-    FmtW4::Args a, const __half *__restrict__ x, float t, float *partial, int *counters, float *y,
-    int m, int n, int ks, int tiles, int tile_cols, int splits)
+    FmtW4::Args a, const __half *__restrict__ x, float t, float *partial, Meeting meet, float *y,
+    int m, int n, int ks, int tile_cols, int splits)
 {
     trace_mark(0);
     const int tile = blockIdx.x;
-    w4_block<LPR, WAVES, U>(a, HalfSource{x}, t, partial, tile_counter(counters, tile, tiles), y,
-                            m, n, ks, tile, blockIdx.y, tile_cols, splits,
-                            survivor_report(counters, 0, splits));
+    w4_block<LPR, WAVES, U>(a, HalfSource{x}, t, partial, meet, tile, y, m, n, ks, tile, blockIdx.y, tile_cols, splits,
+                            survivor_report(meet.counters, 0, splits));
     trace_mark(6);
 }
 
@@ -391,26 +392,24 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_kernel(
 template <int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_swiglu_kernel(
     FmtW4::Args a, const float *__restrict__ gate, const float *__restrict__ up, float t,
-    float *partial, int *counters, float *y, int m, int n, int ks, int tiles, int tile_cols,
+    float *partial, Meeting meet, float *y, int m, int n, int ks, int tile_cols,
     int splits)
 {
     trace_mark(0);
     const int tile = blockIdx.x;
-    w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial,
-                            tile_counter(counters, tile, tiles), y, m, n, ks, tile,
-                            blockIdx.y, tile_cols, splits,
-                            survivor_report(counters, 0, splits));
+    w4_block<LPR, WAVES, U>(a, SwigluSource{gate, up}, t, partial, meet, tile, y, m, n, ks, tile, blockIdx.y, tile_cols,
+                            splits, survivor_report(meet.counters, 0, splits));
 }
 
 // Several int4 matrices that read the same hidden state in one launch; the block finds its
 // matrix from its tile index as in sparse_gemv_multi_kernel.
 template <int LPR, int WAVES, int U, class XS>
 __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const XS &x,
-                                               float *partial, int *counters, int m, int ks,
+                                               float *partial, Meeting meet, int m, int ks,
                                                int tile_cols, int splits, int gtile, int s)
 {
     trace_mark(0);
-    int k = 0, tiles = ma.tile_begin[1], first = 0, n = ma.n[0];      // as in multi_block
+    int k = 0, first = 0, n = ma.n[0];      // as in multi_block
     size_t partial_off = 0;
     FmtW4::Args a = ma.a[0];
     float *y = ma.y[0];
@@ -418,11 +417,10 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
     asm volatile("" ::"s"(ma.y[0]), "s"(ma.y[1]), "s"(ma.y[2]), "s"(ma.y[3]), "s"(ma.n[0]), "s"(ma.n[1]),
                  "s"(ma.n[2]), "s"(ma.n[3]), "s"(ma.t[0]), "s"(ma.t[1]), "s"(ma.t[2]), "s"(ma.t[3]),
                  "s"(ma.a[0].W), "s"(ma.a[1].W), "s"(ma.a[2].W), "s"(ma.a[3].W), "s"(ma.tile_begin[4]),
-                 "s"(partial), "s"(counters), "s"(splits), "s"(ma.a[0].scale), "s"(ma.a[1].scale), "s"(ma.a[2].scale),
+                 "s"(partial), "s"(meet.counters), "s"(splits), "s"(ma.a[0].scale), "s"(ma.a[1].scale), "s"(ma.a[2].scale),
                  "s"(ma.a[3].scale));
 #pragma unroll
     for (int j = 1; j < kMaxMulti; ++j) {
-        if (j < ma.count) tiles = ma.tile_begin[j + 1];
         const bool here = j < ma.count && gtile >= ma.tile_begin[j];
         partial_off += here ? (size_t)splits * ma.n[j - 1] : 0;
         k = here ? j : k;
@@ -432,18 +430,18 @@ __device__ __forceinline__ void w4_multi_block(const MultiArgs<FmtW4> &ma, const
         t = here ? ma.t[j] : t;
         FmtW4::select(a, ma.a[j], here);
     }
-    w4_block<LPR, WAVES, U>(a, x, t, partial + partial_off, tile_counter(counters, gtile, tiles), y, m, n, ks,
-                            gtile - first, s, tile_cols, splits, survivor_report(counters, k, splits));
+    w4_block<LPR, WAVES, U>(a, x, t, partial + partial_off, meet, gtile, y, m, n, ks, gtile - first, s, tile_cols, splits,
+                            survivor_report(meet.counters, k, splits));
     trace_mark(6);
 }
 
 template <int LPR, int WAVES, int U>
 __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_multi_kernel(
-    MultiArgs<FmtW4> ma, const __half *__restrict__ x, float *partial, int *counters, int m,
+    MultiArgs<FmtW4> ma, const __half *__restrict__ x, float *partial, Meeting meet, int m,
     int ks, int tile_cols, int splits)
 {
     asm volatile("" ::"s"(x));                 // as in multi_block
-    w4_multi_block<LPR, WAVES, U>(ma, HalfSource{x}, partial, counters, m, ks, tile_cols, splits,
+    w4_multi_block<LPR, WAVES, U>(ma, HalfSource{x}, partial, meet, m, ks, tile_cols, splits,
                                   (int)blockIdx.x, (int)blockIdx.y);
 }
 
@@ -452,12 +450,12 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_multi_kernel(
 template <int LPR, int U>
 __global__ __launch_bounds__(kNormWaves * 64) void sparse_gemv_w4_rmsnorm_multi_kernel(
     MultiArgs<FmtW4> ma, const float *__restrict__ h, const float *__restrict__ gamma, float eps,
-    double inv_m, float *partial, int *counters, int m, int ks, int tile_cols, int splits)
+    double inv_m, float *partial, Meeting meet, int m, int ks, int tile_cols, int splits)
 {
     __shared__ double wave_sums[kMaxNormChunks * kNormWaves];
     asm volatile("" ::"s"(h), "s"(gamma), "s"(eps), "s"(inv_m));      // as in multi_block
     w4_multi_block<LPR, kNormWaves, U>(ma, RmsnormSource{h, gamma, m, inv_m, eps, wave_sums}, partial,
-                                       counters, m, ks, tile_cols, splits, (int)blockIdx.x, (int)blockIdx.y);
+                                       meet, m, ks, tile_cols, splits, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // Independent int4 groups in one launch (see sparse_gemv_stack_kernel).
@@ -468,10 +466,10 @@ __global__ __launch_bounds__(WAVES * 64) void sparse_gemv_w4_stack_kernel(StackA
     const StackGroup<FmtW4> &sg = sa.g[stack_group_of_block(sa, block)];
     const int tiles = sg.ma.tile_begin[sg.ma.count], gtile = block % tiles, s = block / tiles;
     if (sg.lanes_per_row == 32)
-        w4_multi_block<32, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.counters, sg.m, sg.ks,
+        w4_multi_block<32, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.meet, sg.m, sg.ks,
                                      sg.tile_cols, sg.splits, gtile, s);
     else
-        w4_multi_block<16, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.counters, sg.m, sg.ks,
+        w4_multi_block<16, WAVES, U>(sg.ma, HalfSource{sg.x}, sg.partial, sg.meet, sg.m, sg.ks,
                                      sg.tile_cols, sg.splits, gtile, s);
 }
 
@@ -510,12 +508,13 @@ hipError_t launch_gemv_w8(const int8_t *Wq, const void *scale_f16, const void *x
                           const GemvShape &sh, hipStream_t stream)
 {
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtW8::kElemsPerLane, 64);
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW8::Args a{Wq, static_cast<const __half *>(scale_f16)};
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
     hipLaunchKernelGGL((sparse_gemv_kernel<F, LPR, WAVES, U>), dim3(g.tiles, g.splits), \
-                       dim3(WAVES * 64), g.lds, stream, a, x, t, partial, counters, y, m, n,   \
-                       g.ks, g.tiles, g.tile_cols, g.splits)
+                       dim3(WAVES * 64), g.lds, stream, a, x, t, partial, meet, y, m, n,   \
+                       g.ks, g.tile_cols, g.splits)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtW8, sh);
 #undef TEAL_LAUNCH
     return hipGetLastError();
@@ -543,6 +542,7 @@ hipError_t launch_gemv_w8_multi(int count, const int8_t *const *Wq, const int *r
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH(F, LPR, WAVES, U)                                                          \
     do {                                                                                       \
@@ -550,7 +550,7 @@ hipError_t launch_gemv_w8_multi(int count, const int8_t *const *Wq, const int *r
             return hipErrorInvalidValue;                                                       \
         hipLaunchKernelGGL((sparse_gemv_multi_kernel<F, LPR, WAVES, U>),                       \
                            dim3(tiles, g.splits), dim3(WAVES * 64), g.lds, stream, ma, x,     \
-                           partial, counters, m, g.ks, g.tile_cols, g.splits);                 \
+                           partial, meet, m, g.ks, g.tile_cols, g.splits);                 \
     } while (0)
     TEAL_DISPATCH(TEAL_LAUNCH, FmtW8, sh);
 #undef TEAL_LAUNCH
@@ -573,11 +573,12 @@ hipError_t launch_gemv_w8_swiglu(const int8_t *Wq, const void *scale_f16, const 
 {
     if (sh.waves != 8 || sh.unroll != 4 || !w8_lanes_supported(sh)) return hipErrorInvalidValue;
     const GemvGeometry g = gemv_geometry(m, n, sh, FmtW8::kElemsPerLane, 64);
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW8::Args a{Wq, static_cast<const __half *>(scale_f16)};
 #define TEAL_LAUNCH_S(LPR)                                                                     \
     hipLaunchKernelGGL((sparse_gemv_swiglu_kernel<FmtW8, LPR, 8, 4>), dim3(g.tiles, g.splits), \
-                       dim3(8 * 64), g.lds, stream, a, gate, up, t, partial, counters, y, m, n, \
-                       g.ks, g.tiles, g.tile_cols, g.splits)
+                       dim3(8 * 64), g.lds, stream, a, gate, up, t, partial, meet, y, m, n, \
+                       g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_S(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_S(32);
     else if (sh.lanes_per_row == 16) TEAL_LAUNCH_S(16);
@@ -611,10 +612,11 @@ hipError_t launch_gemv_w8_rmsnorm_multi(int count, const int8_t *const *Wq, cons
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
 #define TEAL_LAUNCH_N(LPR)                                                                     \
     hipLaunchKernelGGL((sparse_gemv_rmsnorm_multi_kernel<FmtW8, LPR, 4>),                      \
                        dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
-                       gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits)
+                       gamma, eps, 1.0 / m, partial, meet, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 64) TEAL_LAUNCH_N(64);
     else if (sh.lanes_per_row == 32) TEAL_LAUNCH_N(32);
     else if (sh.lanes_per_row == 16) TEAL_LAUNCH_N(16);
@@ -630,12 +632,13 @@ hipError_t launch_gemv_w4(const uint8_t *Wq, const void *scale_f16, const void *
     GemvShape w4 = sh;
     w4.waves = kW4Waves;                          // the int4 kernel is built for 8 wavefronts
     const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup);
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW4::Args a{Wq, static_cast<const __half *>(scale_f16)};
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH_W4(LPR)                                                                    \
     hipLaunchKernelGGL((sparse_gemv_w4_kernel<LPR, kW4Waves, kW4Unroll>),                      \
                        dim3(g.tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, a, x, t,  \
-                       partial, counters, y, m, n, g.ks, g.tiles, g.tile_cols, g.splits)
+                       partial, meet, y, m, n, g.ks, g.tile_cols, g.splits)
     // A lane covers 32 columns: 16 lanes per row (tiles up to 512 columns) or 32 lanes
     // per row (up to 1024 columns).
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4(32);
@@ -651,11 +654,12 @@ hipError_t launch_gemv_w4_swiglu(const uint8_t *Wq, const void *scale_f16, const
     GemvShape w4 = sh;
     w4.waves = kW4Waves;
     const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup);
+    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW4::Args a{Wq, static_cast<const __half *>(scale_f16)};
 #define TEAL_LAUNCH_W4S(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_swiglu_kernel<LPR, kW4Waves, kW4Unroll>),               \
                        dim3(g.tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, a, gate,  \
-                       up, t, partial, counters, y, m, n, g.ks, g.tiles, g.tile_cols, g.splits)
+                       up, t, partial, meet, y, m, n, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4S(32);
     else TEAL_LAUNCH_W4S(16);
 #undef TEAL_LAUNCH_W4S
@@ -687,10 +691,11 @@ hipError_t launch_gemv_w4_rmsnorm_multi(int count, const uint8_t *const *Wq,
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
 #define TEAL_LAUNCH_W4N(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_rmsnorm_multi_kernel<LPR, kW4Unroll>),                  \
                        dim3(tiles, g.splits), dim3(kNormWaves * 64), g.lds, stream, ma, h,    \
-                       gamma, eps, 1.0 / m, partial, counters, m, g.ks, g.tile_cols, g.splits)
+                       gamma, eps, 1.0 / m, partial, meet, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4N(32);
     else TEAL_LAUNCH_W4N(16);
 #undef TEAL_LAUNCH_W4N
@@ -719,11 +724,12 @@ hipError_t launch_gemv_w4_multi(int count, const uint8_t *const *Wq, const void 
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
+    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits);
     const __half *x = static_cast<const __half *>(x_f16);
 #define TEAL_LAUNCH_W4M(LPR)                                                                   \
     hipLaunchKernelGGL((sparse_gemv_w4_multi_kernel<LPR, kW4Waves, kW4Unroll>),                \
                        dim3(tiles, g.splits), dim3(kW4Waves * 64), g.lds, stream, ma, x,      \
-                       partial, counters, m, g.ks, g.tile_cols, g.splits)
+                       partial, meet, m, g.ks, g.tile_cols, g.splits)
     if (sh.lanes_per_row == 32) TEAL_LAUNCH_W4M(32);
     else TEAL_LAUNCH_W4M(16);
 #undef TEAL_LAUNCH_W4M
@@ -735,12 +741,12 @@ struct W4Body {
     typedef FmtW4 Format;
     template <int LPR, class XS>
     static __device__ __forceinline__ bool run(const FmtW4::Args &a, const XS &x, float t,
-                                               float *partial, int *counter, float *y, int m,
+                                               float *partial, const Meeting &meet, int gtile, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)
     {
         static_assert(LPR == 16 || LPR == 32, "a lane covers 32 int4 columns");
-        return w4_block<LPR, kW4Waves, kW4Unroll>(a, x, t, partial, counter, y, m, n, ks, tile,
+        return w4_block<LPR, kW4Waves, kW4Unroll>(a, x, t, partial, meet, gtile, y, m, n, ks, tile,
                                                   s, tile_cols, splits, report);
     }
 };
