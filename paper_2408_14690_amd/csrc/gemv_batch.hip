@@ -303,6 +303,9 @@ __device__ __forceinline__ void stream_rows_batch(BatchAcc &acc, const int *list
     }
 }
 
+constexpr int kBatchGridUnit = 40;                     // as for one vector
+constexpr int kBatchWordRows = 2;                      // most rows of a batch that meet in column words
+
 // One activation column of the combine buffer, padded so that the 16 columns a row of lanes
 // holds are written to different LDS banks.
 constexpr int kBatchRedRow = kBatchTile + 8;
@@ -337,22 +340,22 @@ __device__ __forceinline__ float2 load_coherent2(const float *p)        // 8-byt
                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// block_finish for a batch.  red[] (WAVES x kBatchRedWave floats) lies over the list,
-// which is dead once every wavefront has left the row stream.  Wavefront w holds sums of part
-// w % PARTS of the tile's columns.  A thread owns two neighbouring columns of one batch row.  Partial rows are laid out [split][batch row][n]; the block that
-// arrives last at the tile's counter adds them in split order and writes Y.
+// block_finish for a batch, with a word (or a place in the partial rows, [split][batch row][n]) per batch row
+// and column.  red[] (WAVES x kBatchRedWave floats) lies over the list, which is dead once every
+// wavefront has left the row stream.  Wavefront w holds sums of part w % PARTS of the tile's columns.  A
+// thread owns two neighbouring columns of one batch row.
 template <int NB, int WAVES, int PARTS>
 __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *red,
                                                    float *partial, const Meeting &meet, int gtile, float *Y,
-                                                   int tile, int col0, int cols, int s, int splits,
+                                                   int tile, int col0, int tile_cols, int s, int splits,
                                                    int n, int batch, int w,
-                                                   const SurvivorReport &report)
+                                                   const SurvivorReport &report, int cnt)
 {
     constexpr int PAIRS = PARTS * kBatchTile / 2;
     static_assert(NB * PAIRS <= WAVES * 64, "one pair of columns per thread");
     __shared__ int last_flag;
     const int thread = w * 64 + lanes_below(~0ull);
-    if (cols > n - col0) cols = n - col0;
+    const int cols = min(tile_cols, n - col0);
     __syncthreads();                   // every wavefront is done with the list
     batch_sums_to_lds(acc, red, w);
     __syncthreads();
@@ -360,7 +363,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     const int bb = thread / PAIRS;
     const int c = 2 * (thread % PAIRS);
     const bool owner = bb < batch && c < cols;          // cols is a multiple of 8
-    float2 sum = make_float2(0.f, 0.f);
+    float2 sum = make_float2(0.f, 0.f), largest = sum;
     if (owner) {
         // The high parts of all wavefronts, then the low ones.  Where the high sum is not
         // finite it is the result: an infinite weight or activation makes it infinite or a NaN,
@@ -374,6 +377,8 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             const float2 b = *reinterpret_cast<const float2 *>(lo + q * kBatchRedWave);
             h.x += a.x; h.y += a.y;
             l.x += b.x; l.y += b.y;
+            largest.x = fmaxf(largest.x, fabsf(a.x));
+            largest.y = fmaxf(largest.y, fabsf(a.y));
         }
         sum.x = fabsf(h.x) < INFINITY ? h.x + l.x : h.x;
         sum.y = fabsf(h.y) < INFINITY ? h.y + l.y : h.y;
@@ -386,8 +391,39 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
         }
         return;
     }
-    const size_t split_stride = (size_t)batch * n;
     float *p = partial + (size_t)bb * n + col0 + c;
+    const size_t split_stride = (size_t)batch * n;
+    // Words for one or two rows.  With more, the atomics themselves take longer than the trips they save (8 rows,
+    // Llama-3-8B block: 56.4 us by partial rows, 59.8 by words; 4 rows 52.1 and 52.3; 2 rows 53.2 and 52.0).
+    constexpr bool kWords = NB <= kBatchWordRows;
+    if constexpr (kWords) {
+        if (meet.word_step) {
+            const ColumnWords words = column_words(meet, gtile, partial + col0, (unsigned)batch * n,
+                                                   ((unsigned)splits * batch - 1u) * n + cols);
+            const int at = bb * tile_cols + c, place = bb * n + c;
+            unsigned long long mine_x = 0, mine_y = 0, found_x = 0, found_y = 0;
+            if (owner) {
+                mine_x = word_addend<kBatchGridUnit>(words, sum.x, largest.x, at, place, s, splits);
+                mine_y = word_addend<kBatchGridUnit>(words, sum.y, largest.y, at + 1, place + 1, s, splits);
+                found_x = word_add(words.word + at, mine_x);
+                found_y = word_add(words.word + at + 1, mine_y);
+            }
+            unsigned long long *const counts = count_word(meet, report.matrix);
+            const bool reports = tile == 0 && thread == (WAVES - 1) * 64;
+            unsigned long long counted = 0;
+            if (reports) counted = count_slice(counts, cnt);
+            trace_mark(4);
+            if (owner && word_complete(found_x, splits))
+                store_coherent(y, word_value<kBatchGridUnit>(words, mine_x, found_x, at, place, splits));
+            if (owner && word_complete(found_y, splits))
+                store_coherent(y + 1, word_value<kBatchGridUnit>(words, mine_y, found_y, at + 1, place + 1, splits));
+            if (reports) count_total(report, counts, cnt, splits, counted);
+            trace_mark(5);
+            return;
+        }
+    }
+    const bool grid = kWords && splits <= kWordSplits;
+    if (grid) sum = make_float2(grid_row<kBatchGridUnit>(sum.x, largest.x), grid_row<kBatchGridUnit>(sum.y, largest.y));
     if (owner) store_coherent2(p + s * split_stride, sum);
     wait_vector_memory();
     __syncthreads();
@@ -405,7 +441,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     // Second pass, up to 16 loads in flight; every output is summed in split order, so the
     // result does not depend on which block is last.
     if (!owner) return;
-    constexpr int MAXLD = 16;
+    constexpr int MAXLD = kWordSplits;
     sum = make_float2(0.f, 0.f);
     for (int j = 0; j < splits; j += MAXLD) {
         float2 v[MAXLD];
@@ -417,6 +453,12 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
         for (int u = 0; u < MAXLD; ++u) {
             sum.x += v[u].x;
             sum.y += v[u].y;
+        }
+        if (grid) {
+            float vx[MAXLD], vy[MAXLD];
+#pragma unroll
+            for (int u = 0; u < MAXLD; ++u) vx[u] = v[u].x, vy[u] = v[u].y;
+            sum = make_float2(grid_rows_sum<kBatchGridUnit>(vx, splits), grid_rows_sum<kBatchGridUnit>(vy, splits));
         }
     }
     store_coherent(y, sum.x);
@@ -464,7 +506,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
 #undef TEAL_COMPACT
 
     trace_mark(2);
-    if (tile == 0 && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
+    if (tile == 0 && !meet.word_step && threadIdx.x == (WAVES - 1) * 64) report_slice(report, s, splits, cnt);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int share = batch_share_rows<WAVES / PARTS>(cnt);
     const int start = w / PARTS * share;
@@ -483,7 +525,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, meet, gtile, Y, tile, col0, tile_cols, s, splits,
-                                  n, batch, w, report);
+                                  n, batch, w, report, cnt);
     trace_mark(6);
 }
 
@@ -723,6 +765,13 @@ static size_t batch_lds(int ks)
     return list > red ? list : red;
 }
 
+static Meeting batch_meeting(int *counters, int tiles, int batch, const GemvGeometry &g)
+{
+    Meeting m = meeting_of(counters, tiles, batch * g.tile_cols, g.splits);
+    if (batch > kBatchWordRows) m.word_step = 0;
+    return m;
+}
+
 hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, float t, float *Y,
                                   int m, int n, float *partial, int *counters,
                                   const GemvShape &sh, hipStream_t stream)
@@ -733,7 +782,7 @@ hipError_t launch_gemv_bf16_batch(const void *Wt, const void *X_f16, int batch, 
     const int lanes = batch_tile(batch, sh).lanes_per_row;
     const size_t lds = batch_lds(g.ks);
     const double bound = (double)batch * (double)t;
-    const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits, true);
+    const Meeting meet = batch_meeting(counters, g.tiles, batch, g);
     const __half *X = static_cast<const __half *>(X_f16);
 #define TEAL_LAUNCH_B(NB, PARTS)                                                                        \
     do {                                                                                         \
@@ -775,7 +824,7 @@ hipError_t launch_gemv_bf16_batch_multi(int count, const void *const *Wt, const 
         ma.tile_begin[k + 1] = ma.tile_begin[k] + (n[k] + g.tile_cols - 1) / g.tile_cols;
     }
     const int tiles = ma.tile_begin[count];
-    const Meeting meet = meeting_of(counters, tiles, g.tile_cols, g.splits, true);
+    const Meeting meet = batch_meeting(counters, tiles, batch, g);
     const __half *X = static_cast<const __half *>(X_f16);
 #define TEAL_LAUNCH_BM(NB, PARTS)                                                                       \
     do {                                                                                         \

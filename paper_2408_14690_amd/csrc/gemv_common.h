@@ -128,16 +128,16 @@ struct SurvivorReport {
     int matrix;
 };
 
-// Column words: bits 0-3 count the arrivals, bits 4-7 those that left a part of their sum apart, bits 8-63
-// are the sum.  All arrivals but the last find at most 15 in either count.
-constexpr int kWordSplits = 16;
+// Column words: bits 0-3 count the arrivals; bits 4-7 tell which of up to four slices left a part of their
+// sum apart, of more slices how many (a flag word then tells which); bits 8-63 are the sum.  All arrivals
+// but the last find at most 15 in a count.
+constexpr int kWordSplits = 16, kWordFlagged = 4;
 constexpr unsigned kWordApart = 1u << 4;
 constexpr int kWordSumShift = 8;
-// The words, a flag word per column and one line per matrix for the survivors' count share the area of the
-// arrival counters, the part of a workspace that is zero between calls: 87338 columns.  Launches of more
-// columns or splits, and those that need to know when a tile is finished (by_tile), use the counters.
+// The words, a flag word per column where there are any and one line per matrix for the survivors' count
+// share the area of the arrival counters, the part of a workspace that is zero between calls: 131008
+// columns, or 87338 with flags.  Launches of more columns or splits use the counters.
 constexpr int kReportWordBytes = kMaxMatrices * 128;
-constexpr int kWordColumns = (kCounterBytes - kReportWordBytes) / (sizeof(unsigned long long) + sizeof(unsigned));
 
 // How the K-slices of the tiles of a launch meet; see block_finish.  A tile's words begin on a 128-byte line,
 // and so does an arrival counter wherever the area has room for that (8192 tiles): atomics on one line
@@ -150,13 +150,16 @@ struct Meeting {
     int word_step;         // words from one tile's to the next one's; 0: arrival counters
     int words;             // of all tiles; the flags follow them
 };
-inline Meeting meeting_of(int *counters, int tiles, int tile_cols, int splits, bool by_tile = false)
+// `columns`: sums of a tile, its width times the rows of a batch.
+inline Meeting meeting_of(int *counters, int tiles, int columns, int splits)
 {
     Meeting m;
     m.counters = counters;
     m.counter_step = tiles <= kMaxSpacedTiles ? kCounterLineInts : 1;
-    const long long step = (tile_cols + 15) / 16 * 16;
-    const bool words = !by_tile && splits > 1 && splits <= kWordSplits && tiles * step <= kWordColumns;
+    const long long step = (columns + 15) / 16 * 16;
+    const long long each = sizeof(unsigned long long) + (splits > kWordFlagged ? sizeof(unsigned) : 0);
+    const bool words = splits > 1 && splits <= kWordSplits &&
+                       tiles * step * each <= (long long)kCounterBytes - kReportWordBytes;
     m.word_step = words ? (int)step : 0;
     m.words = words ? (int)(tiles * step) : 0;
     return m;
@@ -185,6 +188,19 @@ __device__ __forceinline__ void report_total(const SurvivorReport &r, int splits
     if (lane == 0) store_coherent(r.total, sum);
 }
 
+// Part of a vector as a buffer: a load past its `bytes` reads zero instead of memory, so the lanes
+// past the end of a slice need no clamped position and no test.  `first` is block-uniform.
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer_of(const void *first, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(first), 0, (int)bytes, 0x00027000);
+}
+// Cache policy (sc1) of a buffer access to data that crosses XCDs within a launch: write-through, and loads not
+// served from the local L2, as in store_coherent / load_coherent.  Unlike those the accesses are no atomics: what
+// keeps a store before the ticket or signal is wait_vector_memory(), and a load behind the ticket or the
+// readiness poll the fences of the __syncthreads() in between.  Never one without the other.
+constexpr int kAgentScope = 16;
+
 // The sums of up to kWordSplits slices are added as whole multiples of 2^-UNIT: whole numbers add up to the
 // same in any order, so the arrivals need no order, and their sum is rounded to fp32 once.
 // A slice's sum is within the grid, |sum| < 2^(51 - UNIT), and loses no more than what its wavefronts' sums
@@ -200,6 +216,7 @@ constexpr double kGridMagic = 0x1.8p52;         // x + kGridMagic rounds x to a 
 // takes the magic's own bits off the word again and counts one arrival
 constexpr unsigned long long kGridOnce =
     1u - (__builtin_bit_cast(unsigned long long, kGridMagic) << kWordSumShift);
+template <int UNIT> constexpr float grid_limit = (float)(1ull << 51) / (float)(1ull << UNIT);
 template <int UNIT>
 __device__ __forceinline__ GridSum grid_sum(float sum, float largest)
 {
@@ -208,7 +225,7 @@ __device__ __forceinline__ GridSum grid_sum(float sum, float largest)
     const double x = (double)sum * kScale;
     const double shifted = x + kGridMagic;
     const double left = x - (shifted - kGridMagic);
-    const bool inside = fabsf(sum) < (float)(1ull << 51) / (float)kScale;
+    const bool inside = fabsf(sum) < grid_limit<UNIT>;
     GridSum g;
     g.whole = inside ? __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic) : 0;
     g.split = !inside || (left != 0.0 && largest < (float)(1u << 22) / (float)kScale);
@@ -219,8 +236,7 @@ __device__ __forceinline__ GridSum grid_sum(float sum, float largest)
 template <int UNIT>
 __device__ __forceinline__ bool grid_plain(float sum, float largest)
 {
-    constexpr float kUnit = 1.f / (float)(1ull << UNIT);
-    return (fabsf(sum) < (float)(1ull << 51) * kUnit) & (largest >= (float)(1u << 22) * kUnit);
+    return (fabsf(sum) < grid_limit<UNIT>) & (largest >= (float)(1u << 22) / (float)(1ull << UNIT));
 }
 template <int UNIT>
 __device__ __forceinline__ float grid_value(long long whole, double apart)
@@ -229,18 +245,135 @@ __device__ __forceinline__ float grid_value(long long whole, double apart)
     return (float)((double)whole * (1.0 / (double)(1ull << UNIT)) + apart);
 }
 
-// Part of a vector as a buffer: a load past its `bytes` reads zero instead of memory, so the lanes
-// past the end of a slice need no clamped position and no test.  `first` is block-uniform.
-typedef __amdgpu_buffer_rsrc_t Buffer;
-__device__ __forceinline__ Buffer buffer_of(const void *first, unsigned bytes)
+// The same by partial rows: what a slice writes for its sum, and the sum of the slices (v[u]: row u; rows past
+// the last are zeros).
+template <int UNIT>
+__device__ __forceinline__ float grid_row(float sum, float largest)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(first), 0, (int)bytes, 0x00027000);
+    const GridSum g = grid_sum<UNIT>(sum, largest);
+    return g.split ? sum : grid_value<UNIT>(g.whole, 0.0);
 }
-// Cache policy (sc1) of a buffer access to data that crosses XCDs within a launch: write-through, and loads not
-// served from the local L2, as in store_coherent / load_coherent.  Unlike those the accesses are no atomics: what
-// keeps a store before the ticket or signal is wait_vector_memory(), and a load behind the ticket or the
-// readiness poll the fences of the __syncthreads() in between.  Never one without the other.
-constexpr int kAgentScope = 16;
+template <int UNIT>
+__device__ __forceinline__ float grid_rows_sum(const float (&v)[kWordSplits], int rows)
+{
+#pragma clang fp contract(off)
+    long long whole = 0;
+    double apart = 0.0;
+    bool plain = true;
+#pragma unroll
+    for (int q = 0; q < kWordSplits; q += 4) {
+        if (q >= rows) break;                             // block-uniform
+#pragma unroll
+        for (int u = q; u < q + 4; ++u) {
+            const double x = (double)v[u] * (double)(1ull << UNIT);
+            const double shifted = x + kGridMagic;
+            whole += __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic);
+            plain &= (fabsf(v[u]) < grid_limit<UNIT>) & (shifted - kGridMagic == x);
+        }
+    }
+    if (__builtin_expect(!plain, 0)) {
+        whole = 0;
+#pragma unroll
+        for (int u = 0; u < kWordSplits; ++u) {
+            const GridSum g = grid_sum<UNIT>(v[u], 0.f);
+            whole += g.whole;
+            apart += (double)g.apart;
+        }
+    }
+    return grid_value<UNIT>(whole, apart);
+}
+
+// The words of a tile, and the tile's place in the partial rows (from the first slice's on, rows `row_stride`
+// floats apart, `row_end` of them to the end of the last one's).  Sum `at` of the tile is at `place` of a row.
+struct ColumnWords {
+    unsigned long long *word;
+    unsigned *flags;
+    float *rows;
+    unsigned row_stride, row_end;
+};
+__device__ __forceinline__ ColumnWords column_words(const Meeting &m, int gtile, float *rows, unsigned row_stride,
+                                                    unsigned row_end)
+{
+    unsigned long long *const first = reinterpret_cast<unsigned long long *>(m.counters);
+    return ColumnWords{first + gtile * m.word_step,
+                       reinterpret_cast<unsigned *>(first + m.words) + gtile * m.word_step, rows, row_stride, row_end};
+}
+
+// What slice s adds to the word for its sum, `largest` the largest of the sum's terms.
+template <int UNIT>
+__device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, float sum, float largest, int at,
+                                                          int place, int s, int splits)
+{
+    const double shifted = (double)sum * (double)(1ull << UNIT) + kGridMagic;
+    unsigned long long mine = (__builtin_bit_cast(unsigned long long, shifted) << kWordSumShift) + kGridOnce;
+    if (__builtin_expect(!grid_plain<UNIT>(sum, largest), 0)) {
+        const GridSum g = grid_sum<UNIT>(sum, largest);
+        mine = ((unsigned long long)g.whole << kWordSumShift) + 1u;
+        if (g.split) {                 // flag and value are there before the word tells of them
+            const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g.apart), rows,
+                                                  4 * (place + s * (int)t.row_stride), 0, kAgentScope);
+            if (splits > kWordFlagged)
+                __hip_atomic_fetch_or(t.flags + at, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_vector_memory();
+            mine += splits > kWordFlagged ? kWordApart : kWordApart << s;
+        }
+    }
+    return mine;
+}
+__device__ __forceinline__ unsigned long long word_add(unsigned long long *word, unsigned long long mine)
+{
+    return __hip_atomic_fetch_add(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool word_complete(unsigned long long found, int splits)
+{
+    return (found & (kWordApart - 1u)) == (unsigned)splits - 1u;
+}
+
+// The sum of all slices, for the one that found the others complete; the word is zero again for the next call.
+template <int UNIT>
+__device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long long mine, unsigned long long found,
+                                            int at, int place, int splits)
+{
+    double apart = 0.0;
+    if (__builtin_expect(((found | mine) & (15u * kWordApart)) != 0, 0)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        unsigned from = (unsigned)(found | mine) / kWordApart & 15u;
+        if (splits > kWordFlagged) from = __hip_atomic_load(t.flags + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
+        float v[kWordSplits];
+#pragma unroll
+        for (int u = 0; u < kWordSplits; ++u)                 // zeros past the last row
+            v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, 4 * (u * (int)t.row_stride + place), 0,
+                                                                        kAgentScope));
+#pragma unroll
+        for (int u = 0; u < kWordSplits; ++u) apart += from >> u & 1u ? (double)v[u] : 0.0;
+        if (splits > kWordFlagged) __hip_atomic_store(t.flags + at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __hip_atomic_store(t.word + at, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return grid_value<UNIT>(((long long)found >> kWordSumShift) + ((long long)mine >> kWordSumShift), apart);
+}
+
+// The survivors' count of a launch with column words has a word of its own.  By one thread of each block of
+// tile 0, beside the sums (ahead of the row stream the loads behind it would wait for it):
+// count_slice() with the sums' atomics, count_total() behind them.
+__device__ __forceinline__ unsigned long long *count_word(const Meeting &m, int matrix)
+{
+    int at = kCounterBytes / sizeof(unsigned long long) - (kMaxMatrices - matrix) * 16;
+    asm volatile("" : "+v"(at));       // (known to be one address for all lanes, it would be added up over them first)
+    return reinterpret_cast<unsigned long long *>(m.counters) + at;
+}
+__device__ __forceinline__ unsigned long long count_slice(unsigned long long *word, int cnt)
+{
+    return word_add(word, ((unsigned long long)cnt << kWordSumShift) + 1u);
+}
+__device__ __forceinline__ void count_total(const SurvivorReport &r, unsigned long long *word, int cnt, int splits,
+                                            unsigned long long found)
+{
+    if ((found & 255u) != (unsigned)splits - 1u) return;
+    store_coherent(r.total, cnt + (int)(found >> kWordSumShift));
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // E pairs (a[i], b[i]) of fp32 vectors 64 channels apart, from channel `at` of a slice of `len` that begins at
 // channel k0; zeros past its end.  CACHE: cache policy of the loads.
@@ -852,12 +985,12 @@ __device__ __forceinline__ void store_wave_sums(const float (&acc)[N], float *ds
 // The first takes one trip to memory behind the last sum, the second three (the stores' acknowledgement,
 // the counter, the rows), 0.4 to 0.5 us each while other blocks still stream (us per call, rows /
 // words: 2048 x 2048 4.45 / 3.95, 4096 x 4096 6.47 / 5.78, Llama-3-8B q + k + v 8.56 / 7.9).
-// The tile is columns [col0, col0 + cols) of y, cols <= TN.  Returns (block-uniform) whether this block wrote
-// the tile's outputs; false with column words, whose columns may be written by different blocks.
+// The tile is columns [col0, col0 + cols) of y, cols <= TN.  Returns how many of its outputs this thread
+// wrote (with column words a tile's columns may be written by different blocks).
 // The combine buffer has SUMS rows of combine_row floats, a row per wavefront unless a format
 // says otherwise.
 template <class F, int LPR, int WAVES, int SUMS = WAVES>
-__device__ __forceinline__ bool block_finish(float *red, float *partial, const Meeting &meet, int gtile,
+__device__ __forceinline__ int block_finish(float *red, float *partial, const Meeting &meet, int gtile,
                                              float *y, int tile, int col0, int cols, int s, int splits, int n,
                                              const typename F::Args &a, const SurvivorReport &report, int cnt)
 {
@@ -878,6 +1011,7 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
     __syncthreads();                   // every wavefront has left its sums in red[]
     trace_mark(7);
     constexpr int ROW = combine_row<EPL, LPR>;
+    int wrote = 0;
     if (splits == 1) {
 #pragma unroll
         for (int k = 0; k < OWN; ++k) {
@@ -887,9 +1021,10 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
 #pragma unroll
                 for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
                 store_coherent(y + col0 + c, F::finish(sum, scale[k]));
+                ++wrote;
             }
         }
-        return true;
+        return wrote;
     }
 
     // The sum of column c over this block's wavefronts and the largest of its terms.
@@ -904,75 +1039,36 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
         }
         return sum;
     };
-    const Buffer row = buffer_of(partial + (size_t)s * n + col0, 4u * (unsigned)cols);
     if (meet.word_step) {
-        unsigned long long *const first = reinterpret_cast<unsigned long long *>(meet.counters);
-        unsigned long long *const word = first + gtile * meet.word_step;
-        unsigned *const apart_in = reinterpret_cast<unsigned *>(first + meet.words) + gtile * meet.word_step;
         unsigned long long mine[OWN], found[OWN];
+        const ColumnWords words = column_words(meet, gtile, partial + col0, n, (unsigned)(splits - 1) * n + cols);
 #pragma unroll
         for (int k = 0; k < OWN; ++k) {
             const int c = k * THREADS + (int)threadIdx.x;
             if (c < cols) {
                 float largest;
                 const float sum = sum_of(c, largest);
-                const double shifted = (double)sum * (double)(1ull << UNIT) + kGridMagic;
-                mine[k] = (__builtin_bit_cast(unsigned long long, shifted) << kWordSumShift) + kGridOnce;
-                if (__builtin_expect(!grid_plain<UNIT>(sum, largest), 0)) {
-                    const GridSum g = grid_sum<UNIT>(sum, largest);
-                    mine[k] = ((unsigned long long)g.whole << kWordSumShift) + 1u;
-                    if (g.split) {             // flag and value are there before the word tells of them
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g.apart), row, 4 * c, 0, kAgentScope);
-                        __hip_atomic_fetch_or(apart_in + c, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        wait_vector_memory();
-                        mine[k] += kWordApart;
-                    }
-                }
-                found[k] = __hip_atomic_fetch_add(word + c, mine[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                mine[k] = word_addend<UNIT>(words, sum, largest, c, c, s, splits);
+                found[k] = word_add(words.word + c, mine[k]);
             }
         }
-        // The survivors' count travels beside the sums: ahead of the row stream the loads behind it would
-        // wait for it.
-        unsigned long long *count_word =
-            reinterpret_cast<unsigned long long *>(meet.counters + kCounterBytes / sizeof(int)) -
-            (kMaxMatrices - report.matrix) * 16;
+        unsigned long long *const counts = count_word(meet, report.matrix);
         const bool reports = tile == 0 && threadIdx.x == (WAVES - 1) * 64;
         unsigned long long counted = 0;
-        asm volatile("" : "+v"(count_word));       // (known to be one address, it would be added up over lanes first)
-        if (reports)
-            counted = __hip_atomic_fetch_add(count_word, ((unsigned long long)cnt << kWordSumShift) + 1u,
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (reports) counted = count_slice(counts, cnt);
         trace_mark(4);
 #pragma unroll
         for (int k = 0; k < OWN; ++k) {
             const int c = k * THREADS + (int)threadIdx.x;
-            if (c < cols && (found[k] & (kWordApart - 1u)) == (unsigned)splits - 1u) {
-                double apart = 0.0;
-                if (__builtin_expect(((found[k] | mine[k]) & (15u * kWordApart)) != 0, 0)) {
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                    const unsigned from = __hip_atomic_load(apart_in + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const Buffer part = buffer_of(partial + col0, 4u * ((unsigned)(splits - 1) * n + cols));
-                    float v[kWordSplits];
-#pragma unroll
-                    for (int u = 0; u < kWordSplits; ++u)
-                        v[u] = __uint_as_float(
-                            __builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
-#pragma unroll
-                    for (int u = 0; u < kWordSplits; ++u) apart += from >> u & 1u ? (double)v[u] : 0.0;
-                    __hip_atomic_store(apart_in + c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                // ready for the next call
-                __hip_atomic_store(word + c, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const long long whole = ((long long)found[k] >> kWordSumShift) + ((long long)mine[k] >> kWordSumShift);
-                store_coherent(y + col0 + c, F::finish(grid_value<UNIT>(whole, apart), scale[k]));
+            if (c < cols && word_complete(found[k], splits)) {
+                const float sum = word_value<UNIT>(words, mine[k], found[k], c, c, splits);
+                store_coherent(y + col0 + c, F::finish(sum, scale[k]));
+                ++wrote;
             }
         }
-        if (reports && (counted & 255u) == (unsigned)splits - 1u) {
-            store_coherent(report.total, cnt + (int)(counted >> kWordSumShift));
-            __hip_atomic_store(count_word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (reports) count_total(report, counts, cnt, splits, counted);
         trace_mark(5);
-        return false;
+        return wrote;
     }
 
     // The 8 XCDs have separate L2s.  A device-wide fence would write back and
@@ -980,6 +1076,7 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
     // with device-coherent accesses (write-through stores, cache-bypassing
     // loads), ordered by the arrival counter: every thread waits for its stores
     // to complete, the block synchronises, then one thread takes the ticket.
+    const Buffer row = buffer_of(partial + (size_t)s * n + col0, 4u * (unsigned)cols);
     const bool grid = splits <= kWordSplits;
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
@@ -987,10 +1084,7 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
         if (c < cols) {
             float largest;
             float sum = sum_of(c, largest);
-            if (grid) {                        // as the column words take it
-                const GridSum g = grid_sum<UNIT>(sum, largest);
-                if (!g.split) sum = grid_value<UNIT>(g.whole, 0.0);
-            }
+            if (grid) sum = grid_row<UNIT>(sum, largest);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), row, 4 * c, 0, kAgentScope);
         }
     }
@@ -1008,7 +1102,7 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
                     (unsigned)splits - 1u;
     __syncthreads();
     trace_mark(5);
-    if (!last_flag) return false;
+    if (!last_flag) return 0;
     // (by a wavefront that has no columns where there is one: ahead of the first wavefront's partial rows
     // its loads made tile 0 the last to end, 1.0 us after its ticket against 0.76 for the others)
     if (tile == 0 && w == WAVES - 1) report_total(report, splits);
@@ -1038,15 +1132,7 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
                     v[u] = __uint_as_float(
                         __builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
                 if (grid) {
-                    long long whole = 0;
-                    double apart = 0.0;
-#pragma unroll
-                    for (int u = 0; u < MAXLD; ++u) {
-                        const GridSum g = grid_sum<UNIT>(v[u], 0.f);
-                        whole += g.whole;
-                        apart += (double)g.apart;
-                    }
-                    sum[k] = grid_value<UNIT>(whole, apart);
+                    sum[k] = grid_rows_sum<UNIT>(v, rows);
                 } else {
 #pragma unroll
                     for (int u = 0; u < MAXLD; ++u) sum[k] += v[u];
@@ -1057,9 +1143,12 @@ __device__ __forceinline__ bool block_finish(float *red, float *partial, const M
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
         const int c = k * THREADS + (int)threadIdx.x;
-        if (c < cols) store_coherent(y + col0 + c, F::finish(sum[k], scale[k]));
+        if (c < cols) {
+            store_coherent(y + col0 + c, F::finish(sum[k], scale[k]));
+            ++wrote;
+        }
     }
-    return true;
+    return wrote;
 }
 
 // This lane's first column: lane l of a row group covers EPL columns starting at
@@ -1078,9 +1167,9 @@ __device__ __forceinline__ int lane_column(int col0, int cols, int n, int l)
 
 // Work of one block for formats with no per-group state (bf16, int8): output
 // tile `tile` (tile_cols columns) x K-slice `s` (ks channels) of one matrix.
-// Returns (block-uniform) whether this block wrote the tile's outputs.
+// Returns how many of the tile's outputs this thread wrote.
 template <class F, int LPR, int WAVES, int U, class XS>
-__device__ __forceinline__ bool gemv_block(const typename F::Args &a, const XS &x,
+__device__ __forceinline__ int gemv_block(const typename F::Args &a, const XS &x,
                                            float t, float *partial, const Meeting &meet, int gtile,
                                            float *y, int m, int n, int ks, int tile, int s, int tile_cols,
                                            int splits, const SurvivorReport &report)

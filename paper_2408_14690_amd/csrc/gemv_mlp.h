@@ -79,7 +79,7 @@ template <class F>
 struct GemvBody {
     typedef F Format;
     template <int LPR, class XS>
-    static __device__ __forceinline__ bool run(const typename F::Args &a, const XS &x, float t,
+    static __device__ __forceinline__ int run(const typename F::Args &a, const XS &x, float t,
                                                float *partial, const Meeting &meet, int gtile, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)
@@ -90,7 +90,7 @@ struct GemvBody {
 };
 
 // Body::run<LPR>(...) is the format's block body (gemv_block or w4_block) and returns
-// whether the block wrote its tile's outputs.
+// how many of its tile's outputs the thread wrote.
 template <class Body, int LPR_GU, int LPR_D>
 __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Body::Format> A)
 {
@@ -112,23 +112,30 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
         const int k = blk.kind;
         typename Body::Format::Args a = A.a_gu[0];
         Body::Format::select(a, A.a_gu[1], k != 0);
-        const bool wrote = Body::template run<LPR_GU>(
+        const int wrote = Body::template run<LPR_GU>(
             a, HalfSource{A.x}, k ? A.t_gu[1] : A.t_gu[0],
             A.partial_gu + (k ? (size_t)g.splits_gu * g.f : 0), A.meet_gu, k * g.tiles_gu + blk.tile,
             k ? A.y_gu[1] : A.y_gu[0], A.m, g.f, A.ks_gu, blk.tile, blk.split, g.tile_cols_gu, g.splits_gu,
             survivor_report(A.meet_gu.counters, k, g.splits_gu));
         trace_mark(6);
-        if (!wrote) return;
-        // The tile's columns of gate / up are written (write-through stores): once every
-        // thread's stores are acknowledged, tell the K-slices of W_down that read them.
+        // Columns of gate / up that this block has written (write-through stores), a tile's perhaps in
+        // several blocks: once every thread's stores are acknowledged, tell the K-slices of W_down
+        // that read the tile how many.
+        __shared__ int written[8];
         wait_vector_memory();
+        const int in_wave = __popcll(__ballot(wrote > 0)) + __popcll(__ballot(wrote > 1));    // at most two a thread
+        if ((threadIdx.x & 63) == 0) written[threadIdx.x >> 6] = in_wave;
         __syncthreads();
         if (threadIdx.x < 64) {
+            int columns = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) columns += written[w];
+            if (columns == 0) return;
             int lo, hi;
             mlp_signal_range(g, blk.tile, lo, hi);
             for (int s = lo; s <= hi; ++s)
                 for (int j = threadIdx.x; j < g.tiles_d; j += 64)
-                    __hip_atomic_fetch_add(A.control + mlp_ready_index(s * g.tiles_d + j), 1,
+                    __hip_atomic_fetch_add(A.control + mlp_ready_index(s * g.tiles_d + j), columns,
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         trace_mark(7);
@@ -137,7 +144,7 @@ __global__ __launch_bounds__(8 * 64) void sparse_mlp_kernel(MlpArgs<typename Bod
 
     __shared__ int inputs_ready;
     if (threadIdx.x == 0) {
-        const int expected = mlp_expected(g, blk.split);
+        const int expected = mlp_expected_columns(g, blk.split);
         int *ready = A.control + mlp_ready_index(blk.split * g.tiles_d + blk.tile);
         unsigned spins = 0;
         int ok = 0;
@@ -205,8 +212,7 @@ bool fill_mlp_args(MlpArgs<F> &A, size_t &lds, const MlpHostArgs &h, const MlpLa
     A.m = h.m;
     A.ks_gu = ggu.ks;
     A.partial_gu = h.partial_gu;
-    // by arrival counters: the readers of a tile are told when all of it is written
-    A.meet_gu = meeting_of(h.counters_gu, 2 * ggu.tiles, ggu.tile_cols, ggu.splits, true);
+    A.meet_gu = meeting_of(h.counters_gu, 2 * ggu.tiles, ggu.tile_cols, ggu.splits);
     A.y_d = h.y;
     A.t_d = h.t_down;
     A.n_d = h.d;

@@ -164,9 +164,9 @@ struct W4Sums {
 // group), and a wavefront's share crosses few group boundaries: the scales are applied once per
 // (wavefront, group it touches).  Batches never straddle a group, and two batches are in flight
 // per wavefront across group boundaries.
-// Returns (block-uniform) whether this block wrote the tile's outputs.
+// Returns how many of the tile's outputs this thread wrote.
 template <int LPR, int WAVES, int U, class XS>
-__device__ __forceinline__ bool w4_block(const FmtW4::Args &a, const XS &x,
+__device__ __forceinline__ int w4_block(const FmtW4::Args &a, const XS &x,
                                          float t, float *partial, const Meeting &meet, int gtile, float *y, int m,
                                          int n, int ks, int tile, int s, int tile_cols, int splits,
                                          const SurvivorReport &report)
@@ -740,7 +740,7 @@ hipError_t launch_gemv_w4_multi(int count, const uint8_t *const *Wq, const void 
 struct W4Body {
     typedef FmtW4 Format;
     template <int LPR, class XS>
-    static __device__ __forceinline__ bool run(const FmtW4::Args &a, const XS &x, float t,
+    static __device__ __forceinline__ int run(const FmtW4::Args &a, const XS &x, float t,
                                                float *partial, const Meeting &meet, int gtile, float *y, int m,
                                                int n, int ks, int tile, int s, int tile_cols,
                                                int splits, const SurvivorReport &report)

@@ -11,11 +11,12 @@
 // the blocks that need the first columns of gate / up come first.  A consumer never
 // precedes, in block order, a producer it waits for.
 //
-// Readiness.  A gate / up tile is finished when the block that combines its K-slices has
-// written its columns of y; that block then adds one to the readiness counter of every
-// block of W_down whose K-slice reads any of those columns (one counter per W_down block:
-// a counter polled by one block only).  A block of W_down with K-slice s waits until its
-// counter equals mlp_expected(s) = the number of gate and up tiles that overlap the slice.
+// Readiness.  A gate / up tile is finished when the blocks that complete the sums of its
+// columns have written them; each such block then adds the number of columns it wrote to the
+// readiness counter of every block of W_down whose K-slice reads any of the tile's columns (one
+// counter per W_down block: a counter polled by one block only).  A block of W_down with
+// K-slice s waits for the mlp_expected(s) gate and up tiles that overlap the slice: until
+// its counter equals mlp_expected_columns(s), the columns of those tiles.
 #pragma once
 
 #if defined(__HIPCC__)
@@ -90,6 +91,17 @@ TEAL_HD inline int mlp_expected(const MlpGrid &g, int s)
     int k1 = k0 + g.ks_d;
     if (k1 > g.f) k1 = g.f;
     return 2 * ((k1 - 1) / g.tile_cols_gu - k0 / g.tile_cols_gu + 1);
+}
+
+// Their columns.
+TEAL_HD inline int mlp_expected_columns(const MlpGrid &g, int s)
+{
+    const int k0 = s * g.ks_d;
+    int k1 = k0 + g.ks_d;
+    if (k1 > g.f) k1 = g.f;
+    int end = ((k1 - 1) / g.tile_cols_gu + 1) * g.tile_cols_gu;
+    if (end > g.f) end = g.f;
+    return 2 * (end - k0 / g.tile_cols_gu * g.tile_cols_gu);
 }
 
 }  // namespace teal

@@ -101,10 +101,11 @@ def test_infinities_and_nans_stay_in_their_columns(T):   # noqa: F811
         assert not bool(ws[:T.teal_survivors_offset()].any())
 
 
-@pytest.mark.parametrize("m,splits", [(300, 2), (2048, 16)])
-def test_words_and_counters_give_the_same_bits(T, m, splits):   # noqa: F811
-    """682 tiles of 128 columns have words, 683 use the counters: the same columns, the same bits."""
-    n = 682 * 128
+@pytest.mark.parametrize("m,splits,tiles", [(300, 2, 1023), (700, 5, 682), (2048, 16, 682)])
+def test_words_and_counters_give_the_same_bits(T, m, splits, tiles):   # noqa: F811
+    """The most tiles of 128 columns that have words (fewer with more than four slices, which need flag
+    words), and one tile more, which uses the counters: the same columns, the same bits."""
+    n = tiles * 128
     wide = matrix(m, n + 8, 91)
     narrow, x = wide[:, :n].contiguous(), state(m, 92)
     t = 0.5
@@ -117,6 +118,82 @@ def test_words_and_counters_give_the_same_bits(T, m, splits):   # noqa: F811
     again = run(T, wide, x, t, ws, **shape)
     assert torch.equal(again, a) and survivors(T, ws) == [kept]
     assert not bool(ws[:T.teal_survivors_offset()].any())
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3])
+@pytest.mark.parametrize("m,n,splits", [(2048, 1040, 4), (2050, 520, 16)])
+def test_batches(T, batch, m, n, splits):   # noqa: F811
+    """One and two rows meet in words, three by counters."""
+    wt = matrix(m, n, 11 + m)
+    X = torch.stack([state(m, 20 + b) for b in range(batch)])
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, n, batch), dtype=torch.uint8, device="cuda")
+    got = []
+    for _ in range(2):
+        Y = torch.full((batch, n), float("nan"), dtype=torch.float32, device="cuda")
+        T.check(T.teal_sparse_gemv_bf16_batch_ex(wt, X, batch, 0.5, Y, m, n, ws, splits=splits))
+        torch.cuda.synchronize()
+        assert not bool(ws[:T.teal_survivors_offset()].any())
+        got.append(Y)
+    assert torch.equal(got[0], got[1])
+    kept = X.double().abs().sum(0) > batch * 0.5
+    assert survivors(T, ws) == [int(kept.sum())]
+    xk = torch.where(kept, X.double(), 0.0)
+    want, mag = xk @ wt.double(), xk.abs() @ wt.double().abs()
+    # as for one vector, twice: high and low parts of the activations are summed on their own
+    bound = 2 * (2 * int(kept.sum()) + 16 + 4 * splits) * 2.0 ** -24 * mag + 2.0 ** -148
+    err = (Y.double() - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("scale", [1e-7, 1.0, 1e5])
+@pytest.mark.parametrize("fmt", ["bf16", "w8", "w4"])
+def test_one_launch_mlp_waits_for_every_column(T, fmt, scale):   # noqa: F811
+    """gate and up in several slices, whose columns may be written by different blocks: as the calls one
+    by one, and the same bits every time, also where sums are kept apart."""
+    m, f = 1024, 2816
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn(m, generator=g, device="cuda").half()
+    dims = [(m, f), (m, f), (f, m)]
+    if fmt == "bf16":
+        W = [(torch.randn(d, generator=g, device="cuda") * 0.02 * s).to(torch.bfloat16)
+             for d, s in zip(dims, (scale, 1 / scale, 1.0))]
+        sc = []
+    else:
+        rows = {"w8": lambda a: 1, "w4": lambda a: a // 128}[fmt]
+        width = {"w8": lambda b: b, "w4": lambda b: b // 2}[fmt]
+        W = [torch.randint(-127, 128, (a, width(b)), generator=g, device="cuda", dtype=torch.int8) for a, b in dims]
+        sc = [(torch.rand((rows(a), b), generator=g, device="cuda") * 1e-3 * min(max(s, 1e-3), 10.0)).half()
+              for (a, b), s in zip(dims, (scale, 1 / scale, 1.0))]
+    st, shape = T.teal_mlp_plan({"bf16": 16, "w8": 8, "w4": 4}[fmt], m, f, m)
+    assert st == T.TEAL_OK and shape.gu_splits > 1
+    ws = torch.zeros(T.teal_workspace_bytes_mlp(m, f, m), dtype=torch.uint8, device="cuda")
+    ws1 = torch.zeros(T.teal_workspace_bytes(f, 2 * f), dtype=torch.uint8, device="cuda")
+
+    def outs():
+        return [torch.full((k,), float("nan"), dtype=torch.float32, device="cuda") for k in (f, f, m)]
+    ts = (0.5, 0.25, 1e-3)
+    mlp = {"bf16": T.teal_sparse_mlp_bf16, "w8": T.teal_sparse_mlp_w8, "w4": T.teal_sparse_mlp_w4}[fmt]
+    group = [128] if fmt == "w4" else []
+    first = None
+    for _ in range(8):
+        o = outs()
+        T.check(mlp(*W, *sc, *group, x, *ts, *o, m, f, m, ws, shape=shape))
+        torch.cuda.synchronize()
+        assert first is None or all(torch.equal(a, b) for a, b in zip(o, first))
+        first = o
+    assert not any(bool(a.isnan().any()) for a in first)
+    r = outs()
+    multi = {"bf16": T.teal_sparse_gemv_bf16_multi, "w8": T.teal_sparse_gemv_w8_multi,
+             "w4": T.teal_sparse_gemv_w4_multi}[fmt]
+    down = {"bf16": T.teal_sparse_gemv_bf16_swiglu, "w8": T.teal_sparse_gemv_w8_swiglu,
+            "w4": T.teal_sparse_gemv_w4_swiglu}[fmt]
+    T.check(multi(W[:2], *([sc[:2]] if sc else []), *group, ts[:2], r[:2], [f, f], x, m, ws1))
+    T.check(down(W[2], *sc[2:], *group, first[0], first[1], ts[2], r[2], f, m, ws1))
+    torch.cuda.synchronize()
+    for a, b in zip(first, r):
+        tol = 3e-7 * float(b.norm())          # (the calls one by one may have other launch shapes)
+        assert float((a - b).norm()) <= tol
 
 
 @pytest.mark.parametrize("scale", [1e-6, 1.0, 1000.0])
