@@ -423,7 +423,8 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
         }
     }
     const bool grid = kWords && splits <= kWordSplits;
-    if (grid) sum = make_float2(grid_row<kBatchGridUnit>(sum.x, largest.x), grid_row<kBatchGridUnit>(sum.y, largest.y));
+    if (grid) sum = make_float2(grid_row<kBatchGridUnit>(sum.x, largest.x, splits),
+                                grid_row<kBatchGridUnit>(sum.y, largest.y, splits));
     if (owner) store_coherent2(p + s * split_stride, sum);
     wait_vector_memory();
     __syncthreads();
@@ -441,8 +442,9 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     // Second pass, up to 16 loads in flight; every output is summed in split order, so the
     // result does not depend on which block is last.
     if (!owner) return;
-    constexpr int MAXLD = kWordSplits;
+    constexpr int MAXLD = kWords ? kGridRows : 16;
     sum = make_float2(0.f, 0.f);
+    GridTotal total_x, total_y;
     for (int j = 0; j < splits; j += MAXLD) {
         float2 v[MAXLD];
 #pragma unroll
@@ -454,13 +456,19 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             sum.x += v[u].x;
             sum.y += v[u].y;
         }
-        if (grid) {
-            float vx[MAXLD], vy[MAXLD];
+        if constexpr (kWords) {
+            if (grid) {
+                float vx[MAXLD], vy[MAXLD];
 #pragma unroll
-            for (int u = 0; u < MAXLD; ++u) vx[u] = v[u].x, vy[u] = v[u].y;
-            sum = make_float2(grid_rows_sum<kBatchGridUnit>(vx, splits), grid_rows_sum<kBatchGridUnit>(vy, splits));
+                for (int u = 0; u < MAXLD; ++u) vx[u] = v[u].x, vy[u] = v[u].y;
+                grid_add_rows<kBatchGridUnit>(total_x, vx, splits - j, splits);
+                grid_add_rows<kBatchGridUnit>(total_y, vy, splits - j, splits);
+            }
         }
     }
+    if (grid)
+        sum = make_float2(grid_value<kBatchGridUnit>(total_x.whole, total_x.apart),
+                          grid_value<kBatchGridUnit>(total_y.whole, total_y.apart));
     store_coherent(y, sum.x);
     store_coherent(y + 1, sum.y);
 }

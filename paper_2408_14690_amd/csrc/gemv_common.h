@@ -128,12 +128,11 @@ struct SurvivorReport {
     int matrix;
 };
 
-// Column words: bits 0-3 count the arrivals; bits 4-7 tell which of up to four slices left a part of their
-// sum apart, of more slices how many (a flag word then tells which); bits 8-63 are the sum.  All arrivals
-// but the last find at most 15 in a count.
-constexpr int kWordSplits = 16, kWordFlagged = 4;
-constexpr unsigned kWordApart = 1u << 4;
-constexpr int kWordSumShift = 8;
+// Column words: the lowest bits, 4 for up to 16 slices and 5 for up to 32, count the arrivals; as many above
+// them tell which of up to four slices left a part of their sum apart, of more slices how many (a flag word
+// then tells which); the other bits are the sum.  All arrivals but the last find counts that fit.
+constexpr int kWordSplits = 32, kWordFlagged = 4;
+__device__ __forceinline__ int word_count_bits(int splits) { return splits <= 16 ? 4 : 5; }
 // The words, a flag word per column where there are any and one line per matrix for the survivors' count
 // share the area of the arrival counters, the part of a workspace that is zero between calls: 131008
 // columns, or 87338 with flags.  Launches of more columns or splits use the counters.
@@ -203,7 +202,8 @@ constexpr int kAgentScope = 16;
 
 // The sums of up to kWordSplits slices are added as whole multiples of 2^-UNIT: whole numbers add up to the
 // same in any order, so the arrivals need no order, and their sum is rounded to fp32 once.
-// A slice's sum is within the grid, |sum| < 2^(51 - UNIT), and loses no more than what its wavefronts' sums
+// A slice's sum is within the grid, |sum| < 2^(51 - UNIT) (with more than 16 slices, whose sum has two bits less
+// to be in and may need one more, 2^(48 - UNIT)), and loses no more than what its wavefronts' sums
 // were rounded by: where the largest of those is below 2^(22 - UNIT) and the grid does not hold
 // the sum exactly, what the grid leaves is kept apart, and a sum beyond the grid (an infinity, a NaN) is kept
 // apart whole.  What is kept apart is added in fp64, in the order of the slices.
@@ -213,19 +213,21 @@ struct GridSum {
     bool split;
 };
 constexpr double kGridMagic = 0x1.8p52;         // x + kGridMagic rounds x to a whole number, in the low bits of the sum
-// takes the magic's own bits off the word again and counts one arrival
-constexpr unsigned long long kGridOnce =
-    1u - (__builtin_bit_cast(unsigned long long, kGridMagic) << kWordSumShift);
-template <int UNIT> constexpr float grid_limit = (float)(1ull << 51) / (float)(1ull << UNIT);
 template <int UNIT>
-__device__ __forceinline__ GridSum grid_sum(float sum, float largest)
+__device__ __forceinline__ float grid_limit(int splits)
+{
+    constexpr float kScale = (float)(1ull << UNIT);
+    return splits <= 16 ? (float)(1ull << 51) / kScale : (float)(1ull << 48) / kScale;
+}
+template <int UNIT>
+__device__ __forceinline__ GridSum grid_sum(float sum, float largest, float limit)
 {
 #pragma clang fp contract(off)
     constexpr double kScale = (double)(1ull << UNIT);
     const double x = (double)sum * kScale;
     const double shifted = x + kGridMagic;
     const double left = x - (shifted - kGridMagic);
-    const bool inside = fabsf(sum) < grid_limit<UNIT>;
+    const bool inside = fabsf(sum) < limit;
     GridSum g;
     g.whole = inside ? __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic) : 0;
     g.split = !inside || (left != 0.0 && largest < (float)(1u << 22) / (float)kScale);
@@ -234,9 +236,9 @@ __device__ __forceinline__ GridSum grid_sum(float sum, float largest)
 }
 // Whether a sum needs none of that (to spare the wavefronts the rest of grid_sum).
 template <int UNIT>
-__device__ __forceinline__ bool grid_plain(float sum, float largest)
+__device__ __forceinline__ bool grid_plain(float sum, float largest, float limit)
 {
-    return (fabsf(sum) < grid_limit<UNIT>) & (largest >= (float)(1u << 22) / (float)(1ull << UNIT));
+    return (fabsf(sum) < limit) & (largest >= (float)(1u << 22) / (float)(1ull << UNIT));
 }
 template <int UNIT>
 __device__ __forceinline__ float grid_value(long long whole, double apart)
@@ -245,42 +247,47 @@ __device__ __forceinline__ float grid_value(long long whole, double apart)
     return (float)((double)whole * (1.0 / (double)(1ull << UNIT)) + apart);
 }
 
-// The same by partial rows: what a slice writes for its sum, and the sum of the slices (v[u]: row u; rows past
-// the last are zeros).
+// The same by partial rows: what a slice writes for its sum, and the sum of the slices, of up to kGridRows at a
+// time (v[u]: row u; rows past the last are zeros).
+constexpr int kGridRows = 8;          // (16 cost the stack kernel a block per unit)
+struct GridTotal {
+    long long whole = 0;
+    double apart = 0.0;
+};
 template <int UNIT>
-__device__ __forceinline__ float grid_row(float sum, float largest)
+__device__ __forceinline__ float grid_row(float sum, float largest, int splits)
 {
-    const GridSum g = grid_sum<UNIT>(sum, largest);
+    const GridSum g = grid_sum<UNIT>(sum, largest, grid_limit<UNIT>(splits));
     return g.split ? sum : grid_value<UNIT>(g.whole, 0.0);
 }
 template <int UNIT>
-__device__ __forceinline__ float grid_rows_sum(const float (&v)[kWordSplits], int rows)
+__device__ __forceinline__ void grid_add_rows(GridTotal &total, const float (&v)[kGridRows], int rows, int splits)
 {
 #pragma clang fp contract(off)
+    const float limit = grid_limit<UNIT>(splits);
     long long whole = 0;
-    double apart = 0.0;
     bool plain = true;
 #pragma unroll
-    for (int q = 0; q < kWordSplits; q += 4) {
+    for (int q = 0; q < kGridRows; q += 4) {
         if (q >= rows) break;                             // block-uniform
 #pragma unroll
         for (int u = q; u < q + 4; ++u) {
             const double x = (double)v[u] * (double)(1ull << UNIT);
             const double shifted = x + kGridMagic;
             whole += __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic);
-            plain &= (fabsf(v[u]) < grid_limit<UNIT>) & (shifted - kGridMagic == x);
+            plain &= (fabsf(v[u]) < limit) & (shifted - kGridMagic == x);
         }
     }
     if (__builtin_expect(!plain, 0)) {
         whole = 0;
 #pragma unroll
-        for (int u = 0; u < kWordSplits; ++u) {
-            const GridSum g = grid_sum<UNIT>(v[u], 0.f);
+        for (int u = 0; u < kGridRows; ++u) {
+            const GridSum g = grid_sum<UNIT>(v[u], 0.f, limit);
             whole += g.whole;
-            apart += (double)g.apart;
+            total.apart += (double)g.apart;
         }
     }
-    return grid_value<UNIT>(whole, apart);
+    total.whole += whole;
 }
 
 // The words of a tile, and the tile's place in the partial rows (from the first slice's on, rows `row_stride`
@@ -304,11 +311,15 @@ template <int UNIT>
 __device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, float sum, float largest, int at,
                                                           int place, int s, int splits)
 {
+    const int bits = word_count_bits(splits);
+    const float limit = grid_limit<UNIT>(splits);
     const double shifted = (double)sum * (double)(1ull << UNIT) + kGridMagic;
-    unsigned long long mine = (__builtin_bit_cast(unsigned long long, shifted) << kWordSumShift) + kGridOnce;
-    if (__builtin_expect(!grid_plain<UNIT>(sum, largest), 0)) {
-        const GridSum g = grid_sum<UNIT>(sum, largest);
-        mine = ((unsigned long long)g.whole << kWordSumShift) + 1u;
+    // the magic's own bits are taken off again as one arrival is counted
+    const unsigned long long once = 1u - (__builtin_bit_cast(unsigned long long, kGridMagic) << 2 * bits);
+    unsigned long long mine = (__builtin_bit_cast(unsigned long long, shifted) << 2 * bits) + once;
+    if (__builtin_expect(!grid_plain<UNIT>(sum, largest, limit), 0)) {
+        const GridSum g = grid_sum<UNIT>(sum, largest, limit);
+        mine = ((unsigned long long)g.whole << 2 * bits) + 1u;
         if (g.split) {                 // flag and value are there before the word tells of them
             const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g.apart), rows,
@@ -316,7 +327,7 @@ __device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, 
             if (splits > kWordFlagged)
                 __hip_atomic_fetch_or(t.flags + at, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wait_vector_memory();
-            mine += splits > kWordFlagged ? kWordApart : kWordApart << s;
+            mine += 1u << bits << (splits > kWordFlagged ? 0 : s);
         }
     }
     return mine;
@@ -327,7 +338,7 @@ __device__ __forceinline__ unsigned long long word_add(unsigned long long *word,
 }
 __device__ __forceinline__ bool word_complete(unsigned long long found, int splits)
 {
-    return (found & (kWordApart - 1u)) == (unsigned)splits - 1u;
+    return ((unsigned)found & ((1u << word_count_bits(splits)) - 1u)) == (unsigned)splits - 1u;
 }
 
 // The sum of all slices, for the one that found the others complete; the word is zero again for the next call.
@@ -335,28 +346,36 @@ template <int UNIT>
 __device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long long mine, unsigned long long found,
                                             int at, int place, int splits)
 {
+    const int bits = word_count_bits(splits);
+    const unsigned told = (unsigned)(found | mine) >> bits & ((1u << bits) - 1u);
     double apart = 0.0;
-    if (__builtin_expect(((found | mine) & (15u * kWordApart)) != 0, 0)) {
+    if (__builtin_expect(told != 0, 0)) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        unsigned from = (unsigned)(found | mine) / kWordApart & 15u;
-        if (splits > kWordFlagged) from = __hip_atomic_load(t.flags + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned from = splits <= kWordFlagged
+                                  ? told : __hip_atomic_load(t.flags + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
-        float v[kWordSplits];
+        int stride = (int)t.row_stride;
+        asm volatile("" : "+v"(stride));       // (16 places in scalar registers would be spilled)
+#pragma unroll 1
+        for (int j = 0; j < splits; j += kGridRows) {
+            float v[kGridRows];
 #pragma unroll
-        for (int u = 0; u < kWordSplits; ++u)                 // zeros past the last row
-            v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, 4 * (u * (int)t.row_stride + place), 0,
-                                                                        kAgentScope));
+            for (int u = 0; u < kGridRows; ++u)               // zeros past the last row
+                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, 4 * ((j + u) * stride + place), 0,
+                                                                            kAgentScope));
 #pragma unroll
-        for (int u = 0; u < kWordSplits; ++u) apart += from >> u & 1u ? (double)v[u] : 0.0;
+            for (int u = 0; u < kGridRows; ++u) apart += from >> (j + u) & 1u ? (double)v[u] : 0.0;
+        }
         if (splits > kWordFlagged) __hip_atomic_store(t.flags + at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(t.word + at, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return grid_value<UNIT>(((long long)found >> kWordSumShift) + ((long long)mine >> kWordSumShift), apart);
+    return grid_value<UNIT>(((long long)found >> 2 * bits) + ((long long)mine >> 2 * bits), apart);
 }
 
 // The survivors' count of a launch with column words has a word of its own.  By one thread of each block of
 // tile 0, beside the sums (ahead of the row stream the loads behind it would wait for it):
 // count_slice() with the sums' atomics, count_total() behind them.
+constexpr int kCountShift = 8;          // arrivals below, the count above
 __device__ __forceinline__ unsigned long long *count_word(const Meeting &m, int matrix)
 {
     int at = kCounterBytes / sizeof(unsigned long long) - (kMaxMatrices - matrix) * 16;
@@ -365,13 +384,13 @@ __device__ __forceinline__ unsigned long long *count_word(const Meeting &m, int 
 }
 __device__ __forceinline__ unsigned long long count_slice(unsigned long long *word, int cnt)
 {
-    return word_add(word, ((unsigned long long)cnt << kWordSumShift) + 1u);
+    return word_add(word, ((unsigned long long)cnt << kCountShift) + 1u);
 }
 __device__ __forceinline__ void count_total(const SurvivorReport &r, unsigned long long *word, int cnt, int splits,
                                             unsigned long long found)
 {
-    if ((found & 255u) != (unsigned)splits - 1u) return;
-    store_coherent(r.total, cnt + (int)(found >> kWordSumShift));
+    if ((found & ((1u << kCountShift) - 1u)) != (unsigned)splits - 1u) return;
+    store_coherent(r.total, cnt + (int)(found >> kCountShift));
     __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1084,7 +1103,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         if (c < cols) {
             float largest;
             float sum = sum_of(c, largest);
-            if (grid) sum = grid_row<UNIT>(sum, largest);
+            if (grid) sum = grid_row<UNIT>(sum, largest, splits);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), row, 4 * c, 0, kAgentScope);
         }
     }
@@ -1108,32 +1127,50 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
     if (tile == 0 && w == WAVES - 1) report_total(report, splits);
 
     // Second pass.  A thread owns a column and adds its partial rows in split order (a fixed
-    // order, whichever block happens to be last), up to 16 loads in flight at once.  (Spreading
+    // order, whichever block happens to be last), 8 or 16 loads in flight at once.  (Spreading
     // the splits of a column over several threads and adding their sums through LDS costs two
     // more barriers and was measured slower by 0.3 us per Llama-2-7B block.)  The rows are read through a
-    // descriptor that ends with the last of them, so that 16 loads follow each other without a 64-bit
+    // descriptor that ends with the last of them, so that the loads follow each other without a 64-bit
     // address or a branch each (from the ticket to the end of 2048 x 2048 0.76 -> 0.60 us, 4.70 -> 4.53 us
     // per call).
-    constexpr int MAXLD = 16;
-    static_assert(MAXLD == kWordSplits, "sums on the grid are added in one round of loads");
     float sum[OWN];
 #pragma unroll
     for (int k = 0; k < OWN; ++k) sum[k] = 0.f;
-    for (int j = 0; j < splits; j += MAXLD) {
-        const int rows = min(MAXLD, splits - j);
+    // rows j .. j + ROWS - 1 (zeros past the last), loaded for column c
+    const auto load_rows = [&](auto &v, int j, int c) {
+        constexpr int ROWS = sizeof(v) / sizeof(v[0]);
+        const int rows = min(ROWS, splits - j);
         const Buffer part = buffer_of(partial + (size_t)j * n + col0, 4u * ((unsigned)(rows - 1) * n + cols));
 #pragma unroll
-        for (int k = 0; k < OWN; ++k) {
-            const int c = k * THREADS + (int)threadIdx.x;
-            if (c < cols) {
-                float v[MAXLD];
+        for (int u = 0; u < ROWS; ++u)
+            v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
+        return rows;
+    };
+    if (grid) {
+        GridTotal total[OWN];
+#pragma unroll 1
+        for (int j = 0; j < splits; j += kGridRows) {
 #pragma unroll
-                for (int u = 0; u < MAXLD; ++u)
-                    v[u] = __uint_as_float(
-                        __builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
-                if (grid) {
-                    sum[k] = grid_rows_sum<UNIT>(v, rows);
-                } else {
+            for (int k = 0; k < OWN; ++k) {
+                const int c = k * THREADS + (int)threadIdx.x;
+                if (c < cols) {
+                    float v[kGridRows];
+                    const int rows = load_rows(v, j, c);
+                    grid_add_rows<UNIT>(total[k], v, rows, splits);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) sum[k] = grid_value<UNIT>(total[k].whole, total[k].apart);
+    } else {
+        constexpr int MAXLD = 16;
+        for (int j = 0; j < splits; j += MAXLD) {
+#pragma unroll
+            for (int k = 0; k < OWN; ++k) {
+                const int c = k * THREADS + (int)threadIdx.x;
+                if (c < cols) {
+                    float v[MAXLD];
+                    load_rows(v, j, c);
 #pragma unroll
                     for (int u = 0; u < MAXLD; ++u) sum[k] += v[u];
                 }

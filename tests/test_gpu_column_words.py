@@ -57,9 +57,11 @@ def check(y, wt, x, t, splits):
 
 
 @pytest.mark.parametrize("m,n,splits,p", [(128, 8, 2, 0.5), (130, 520, 2, 0.0), (1000, 264, 7, 0.5), (2048, 1048, 16, 0.5),
-                                          (2048, 2048, 16, 0.99), (2176, 1048, 17, 0.5), (4096, 4096, 8, 0.5)])
+                                          (2048, 2048, 16, 0.99), (2176, 1048, 17, 0.5), (4096, 4096, 8, 0.5),
+                                          (4096, 520, 32, 0.5), (2112, 520, 33, 0.5)])
 def test_columns_of_all_magnitudes(T, m, n, splits, p):   # noqa: F811
-    """16 splits are the most that column words take; 17 use the counters.  Two calls, the second on a
+    """Counts of 4 bits up to 16 splits and of 5 bits up to 32, which are the most that column words take; 33 use
+    the counters.  Two calls, the second on a
     workspace whose rows hold the first one's: same bits, and the counters' area is zero again."""
     wt, x = matrix(m, n, m + n), state(m, 3 * m + n)
     t = float(torch.quantile(x.float().abs(), p)) if p else 0.0
@@ -101,7 +103,7 @@ def test_infinities_and_nans_stay_in_their_columns(T):   # noqa: F811
         assert not bool(ws[:T.teal_survivors_offset()].any())
 
 
-@pytest.mark.parametrize("m,splits,tiles", [(300, 2, 1023), (700, 5, 682), (2048, 16, 682)])
+@pytest.mark.parametrize("m,splits,tiles", [(300, 2, 1023), (700, 5, 682), (2048, 16, 682), (2048, 32, 682)])
 def test_words_and_counters_give_the_same_bits(T, m, splits, tiles):   # noqa: F811
     """The most tiles of 128 columns that have words (fewer with more than four slices, which need flag
     words), and one tile more, which uses the counters: the same columns, the same bits."""
