@@ -65,6 +65,12 @@ GemvShape shape_for(int m, int n, int elems_per_lane, int min_lanes, int max_lan
     tc = (tc + unit - 1) / unit * unit;
     if (tc < tc_min) tc = tc_min;
     if (wide && tc < 4 * unit) tc = 4 * unit;
+    // bf16 matrices of 8193 to 10240 columns: a KiB of a row with 12 to 15 splits instead of five lines with 8.  A
+    // quarter of the 256-byte pieces of memory is slower, and every KiB has one (us at 50 %, 640 bytes / a
+    // KiB: 5120 -> 9216 11.1 / 10.4, 8192 -> 8704 15.5 / 14.7, 14336 -> 10240 25.7 / 25.2; over 0 to 95 % and
+    // 5120 to 14336 channels 0.99 to 1.21 times as fast; with fewer channels up to 5 % slower from 80 % on.
+    // Three lines as four, 4097 to 6144 columns, and the int8 widths: 0.93 to 1.12, not done).
+    if (elems_per_lane == 8 && m >= 5120 && tc == 5 * unit && tc_max >= 8 * unit) tc = 8 * unit;
     if (tc > tc_max) tc = tc_max;
     const int tiles = (n + tc - 1) / tc;
     int splits = 8;
