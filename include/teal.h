@@ -27,9 +27,10 @@
  *     (only entries equal to zero are skipped).
  *   - y is fp32, fully overwritten (all zeros when nothing survives).
  *     Products are formed and summed in fp32, or exactly and rounded to fp32
- *     once (int4: a 128-channel group's integer sums, before its scale), in a
- *     fixed order: results are bitwise reproducible from run to run for a
- *     given shape.
+ *     once (int4: a 128-channel group's integer sums, before its scale; the
+ *     sums of up to 32 K-slices), in a fixed order or in whole numbers, which
+ *     add up to the same in any order: results are bitwise reproducible from
+ *     run to run for a given shape.
  *   - All argument checks happen on the host before any GPU work and return
  *     a status; nothing aborts, throws or prints.
  *   - `workspace` is caller-provided device scratch of at least
@@ -106,8 +107,10 @@ teal_status teal_sparsify(const void *x_f16, int m, float t,
  * y = s_t(x) W^T (Section 4.2), computed as in Section 4.4: the mask is built
  * inside the kernel from x and t, only rows Wt[i][:] with |x_i| > t are read,
  * the input dimension is split across thread blocks, and the per-split
- * partial sums (fp32) are combined in a fixed order by the block that
- * finishes a tile last (one kernel launch per call).
+ * partial sums (fp32) are added in whole multiples of a small unit (2^-40;
+ * int8, before the scale, 2^-28; sums that those do not hold are added in
+ * fp64, in the order of the splits), so that it does not matter which block
+ * is last (one kernel launch per call).
  *   Wt_bf16 [m][n] bfloat16, input-channel-major, 16-byte aligned.
  *   x_f16   [m] fp16, 2-byte aligned.
  *   y       [n] fp32, 4-byte aligned.
@@ -644,7 +647,10 @@ teal_status teal_sparse_gemv_bf16_batch_multi(int count, const void *const *Wt_b
  * these dimensions (weight_bits = 16, 8 or 4), in the terms of
  * teal_sparse_gemv_bf16_ex.  Host-only; every output pointer is HOST memory
  * and may be NULL.  Split-K (Section 4.4) is `splits` blocks along the input
- * dimension; the grid is ceil(n / tile_cols) * splits blocks.
+ * dimension; the grid is ceil(n / tile_cols) * splits blocks.  (int4, one
+ * matrix: where that grid has at most 160 blocks, teal_sparse_gemv_w4 and
+ * _w4_swiglu and W_down of the one-launch MLP cut the slices finer, to at
+ * most 256 blocks, 32 slices and at least 128 channels each.)
  */
 teal_status teal_gemv_plan(int weight_bits, int m, int n, int *lanes_per_row, int *tile_cols,
                            int *splits, int *waves, int *unroll);

@@ -182,3 +182,41 @@ def test_w4_fused_calls_with_large_activations_are_the_plain_calls(T, m):   # no
     torch.cuda.synchronize()
     assert xd.view(torch.float16).abs().max().item() > 2000
     assert torch.equal(ys[0][0], ys[1][0])
+
+
+@pytest.mark.parametrize("m,n,slices", [(2048, 2048, 16), (2176, 2048, 17), (4096, 1024, 32), (3584, 3072, 28), (4096, 4096, 32),
+                                        (8192, 5120, 22), (8192, 5664, 16), (128, 32, 1)])
+def test_w4_slices_cut_finer_for_one_matrix(T, m, n, slices):   # noqa: F811
+    """Up to 160 planned blocks a single int4 matrix runs in finer slices (22 of 384 channels where 25 would
+    take 328), a group of one as planned: both within the bound, the same survivors, reproducible."""
+    rng = np.random.default_rng(m + n)
+    q, scale, w = w4_case(n, m, 9950 + m + n)
+    x = rng.standard_normal(m).astype(np.float16)
+    t = 0.4
+    kept = np.abs(x.astype(np.float32)) > np.float32(t)
+    xk = np.where(kept, x.astype(np.float64), 0.0)
+    bound = w4_bound(m, xk, w) + 32 * 2.0 ** -24 * (np.abs(xk)[:, None] * np.abs(w)).sum(0)
+    want = xk @ w
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    got = []
+    for one in (True, True, False):
+        y = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+        if one:
+            T.check(T.teal_sparse_gemv_w4(q, scale, 128, dev(x), t, y, m, n, ws))
+        else:
+            T.check(T.teal_sparse_gemv_w4_multi([q], [scale], 128, [t], [y], [n], dev(x), m, ws))
+        torch.cuda.synchronize()
+        assert survivors(T, ws) == [int(kept.sum())]
+        got.append(y.cpu().numpy())
+        assert np.all(np.abs(got[-1] - want) <= bound)
+    assert np.array_equal(got[0], got[1])
+    st, plan = T.teal_gemv_plan(4, m, n)
+    tiles = -(-n // plan["tile_cols"])
+    if tiles * plan["splits"] > 160 or slices == plan["splits"]:
+        assert np.array_equal(got[0], got[2])
+    f = T.teal_mlp_plan(4, 128, m, n)[1]                     # the same rule, as the MLP's description of its blocks
+    f.down_lanes_per_row, f.down_tile_cols, f.down_splits = plan["lanes_per_row"], plan["tile_cols"], plan["splits"]
+    st, info = T.teal_mlp_block_info(4, 128, m, n, f, -1)
+    assert st == T.TEAL_OK
+    st, last = T.teal_mlp_block_info(4, 128, m, n, f, info[0] - 1)
+    assert (last[2] + 1, last[3] + 1) == (tiles, slices)
