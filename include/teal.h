@@ -448,7 +448,9 @@ teal_status teal_sparse_gemv_w4_multi(int count, const uint8_t *const *Wq,
  *           (teal_mlp_plan).  For tuning and tests: lanes per row, tile width
  *           and split count of the gate / up products and of the W_down
  *           product as for teal_sparse_gemv_bf16_ex (8 wavefronts, 4 loads per
- *           batch); gu_phase_tiles > 0 orders the gate / up blocks in phases
+ *           batch; int4: down_splits is the planned count, which up to 160
+ *           blocks of W_down is cut finer as in teal_sparse_gemv_w4_swiglu,
+ *           see teal_gemv_plan); gu_phase_tiles > 0 orders the gate / up blocks in phases
  *           of that many output tiles of each matrix, so that the first
  *           columns of gate and up are finished first (0 = one phase);
  *           extra_lds_bytes (0..49152) of unused shared memory per block lower
