@@ -401,7 +401,7 @@ const char *teal_status_string(teal_status s)
     return "unknown status";
 }
 
-int teal_version(void) { return 416; }
+int teal_version(void) { return 417; }
 
 size_t teal_survivors_offset(void) { return teal::kCounterBytes; }
 
