@@ -124,8 +124,8 @@ teal_status teal_sparse_gemv_bf16(const void *Wt_bf16, const void *x_f16, float 
 /*
  * teal_sparse_gemv_bf16 for callers that cannot allocate device memory and so
  * have no workspace to hand over: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  The split-K scratch (arrival
- * counters, survivor report, fp32 partial rows) lives in an array of the
+ * loops, harnesses that forbid hipMalloc.  The split-K scratch (column
+ * words or arrival counters, survivor report, fp32 partial rows) lives in an array of the
  * library's own, a file-scope device array of about 5.3 MB that every GPU the
  * library is used on holds until the process ends; the call itself calls no
  * hipMalloc, hipFree or other allocating routine, and no memset.  The device
@@ -142,7 +142,7 @@ teal_status teal_sparse_gemv_bf16(const void *Wt_bf16, const void *x_f16, float 
  *   time on one GPU (different streams, different host threads) race on it and
  *   are NOT allowed; calls on one stream run in order and are fine.  The array
  *   keeps the last call's contents; what must be zero at the start of a call
- *   (one arrival counter per output tile) is left at zero by the call before
+ *   (the column words and arrival counters) is left at zero by the call before
  *   it, and nothing else is read before it is written.  The survivor count of
  *   the call is not available to the caller.
  */

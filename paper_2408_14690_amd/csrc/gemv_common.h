@@ -5,9 +5,9 @@
 // mask creation) and compacts the survivors into an LDS list with wavefront
 // ballots and an LDS prefix sum, (2) streams only the surviving rows of the
 // input-channel-major weights with 16-byte non-temporal loads and fp32 FMAs,
-// (3) sums its wavefronts' accumulators through LDS and writes one fp32
-// partial row; the last block to finish a tile adds that tile's partial rows
-// in split order and writes y (second pass, same launch).
+// (3) sums its wavefronts' accumulators through LDS and adds its sum of each
+// column to that column's word; whoever finds the other slices there writes y
+// (same launch; see block_finish).
 #pragma once
 
 #include <hip/hip_fp16.h>

@@ -308,7 +308,7 @@ teal_status check_gemv(const GemvArgs &a, int n_multiple)
     return TEAL_OK;
 }
 
-// The head of the workspace holds one arrival counter per output tile.  The shapes the
+// The head of the workspace has room for one arrival counter per output tile.  The shapes the
 // library picks itself have tiles of at least kMinTile columns, which always fit; a
 // caller-chosen tile width may not.
 bool tiles_fit_counters(int n, const GemvShape &sh)
@@ -320,7 +320,7 @@ bool tiles_fit_counters(int n, const GemvShape &sh)
 
 teal_status from_hip(hipError_t e) { return e == hipSuccess ? TEAL_OK : TEAL_ERR_HIP; }
 
-// Workspace layout: [arrival counters, kCounterBytes][survivor report, report_bytes(m)]
+// Workspace layout: [column words or arrival counters, kCounterBytes][survivor report, report_bytes(m)]
 // [partial rows, splits x n fp32].  The report holds one total per matrix of the call and,
 // per matrix, one count per split; its size allows for the most splits any call with this
 // m can run with.
@@ -341,10 +341,10 @@ float *ws_partials(void *workspace, int m)
 // ---- the library's own scratch, for teal_sparse_gemv_bf16_static ----
 //
 // One array per GPU the library runs on, held until the process ends, laid out like a
-// caller's workspace for the largest call the entry point takes: [arrival counters]
+// caller's workspace for the largest call the entry point takes: [words or counters]
 // [survivor report][kStaticRows partial rows of kStaticMaxDim floats].  Zero at load; every
-// call leaves the counters at zero again (the block that finishes a tile last resets the
-// tile's counter), and the report and the partial rows are written before they are read, so
+// call leaves the words and counters at zero again (whoever completes one resets it), and the
+// report and the partial rows are written before they are read, so
 // the contents a call finds from the call before it never reach a result.
 constexpr int kStaticMaxDim = 65536;           // largest m and n of a static-scratch call
 constexpr int kStaticRows = 16;                // most splits the library picks for m <= kStaticMaxDim

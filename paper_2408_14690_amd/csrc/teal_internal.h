@@ -21,7 +21,7 @@ constexpr int kMaxNormInput = 16384; // longest hidden state the fused normalisa
 constexpr int kMaxBatch = 8;        // rows of a small batch (Section 5.4.4)
 constexpr int kMaxSliceBatch = 2048;  // most input channels one block compacts for a batch
 constexpr int kMaxLongSliceBatch = 4096;   // the same where that runs without split-K in one round of blocks
-// Head of the workspace: one arrival counter per output tile (zero between calls).
+// Head of the workspace: the column words of a launch, or one arrival counter per output tile (zero between calls).
 constexpr size_t kCounterBytes = (size_t)(kMaxDim / kMinTile) * sizeof(int);
 constexpr int kCounterLineInts = 32;    // counters 128 bytes apart while the area has room
 constexpr int kMaxSpacedTiles = (int)(kCounterBytes / (kCounterLineInts * sizeof(int)));
