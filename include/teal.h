@@ -27,10 +27,13 @@
  *     (only entries equal to zero are skipped).
  *   - y is fp32, fully overwritten (all zeros when nothing survives).
  *     Products are formed and summed in fp32, or exactly and rounded to fp32
- *     once (int4: a 128-channel group's integer sums, before its scale; the
- *     sums of up to 32 K-slices), in a fixed order or in whole numbers, which
- *     add up to the same in any order: results are bitwise reproducible from
- *     run to run for a given shape.
+ *     once (int4: a 128-channel group's integer sums, before its scale), in a
+ *     fixed order.  The fp32 sums of 2 to 32 K-slices are added without
+ *     rounding where they lie within a wide range (below), in fp64 otherwise,
+ *     and their total is rounded to fp32; those of more slices, and of the
+ *     batched calls from three rows on, are added in fp32 in the order of the
+ *     slices.  Results are bitwise reproducible from run to run for a given
+ *     shape.
  *   - All argument checks happen on the host before any GPU work and return
  *     a status; nothing aborts, throws or prints.
  *   - `workspace` is caller-provided device scratch of at least
@@ -107,10 +110,11 @@ teal_status teal_sparsify(const void *x_f16, int m, float t,
  * y = s_t(x) W^T (Section 4.2), computed as in Section 4.4: the mask is built
  * inside the kernel from x and t, only rows Wt[i][:] with |x_i| > t are read,
  * the input dimension is split across thread blocks, and the per-split
- * partial sums (fp32) are added in whole multiples of a small unit (2^-40;
- * int8, before the scale, 2^-28; sums that those do not hold are added in
- * fp64, in the order of the splits), so that it does not matter which block
- * is last (one kernel launch per call).
+ * partial sums (fp32) of up to 32 splits are added as whole multiples of a
+ * small unit (2^-40; int8, before the scale, 2^-28), so that it does not matter
+ * which block is last (one kernel launch per call).  A partial sum that is no
+ * such multiple or not below 2^51 units (2^48 with more than 16 splits) is
+ * added to their total in fp64, in the order of the splits.
  *   Wt_bf16 [m][n] bfloat16, input-channel-major, 16-byte aligned.
  *   x_f16   [m] fp16, 2-byte aligned.
  *   y       [n] fp32, 4-byte aligned.

@@ -363,7 +363,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     const int bb = thread / PAIRS;
     const int c = 2 * (thread % PAIRS);
     const bool owner = bb < batch && c < cols;          // cols is a multiple of 8
-    float2 sum = make_float2(0.f, 0.f), largest = sum;
+    float2 sum = make_float2(0.f, 0.f);
     if (owner) {
         // The high parts of all wavefronts, then the low ones.  Where the high sum is not
         // finite it is the result: an infinite weight or activation makes it infinite or a NaN,
@@ -377,8 +377,6 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             const float2 b = *reinterpret_cast<const float2 *>(lo + q * kBatchRedWave);
             h.x += a.x; h.y += a.y;
             l.x += b.x; l.y += b.y;
-            largest.x = fmaxf(largest.x, fabsf(a.x));
-            largest.y = fmaxf(largest.y, fabsf(a.y));
         }
         sum.x = fabsf(h.x) < INFINITY ? h.x + l.x : h.x;
         sum.y = fabsf(h.y) < INFINITY ? h.y + l.y : h.y;
@@ -403,8 +401,8 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             const int at = bb * tile_cols + c, place = bb * n + c;
             unsigned long long mine_x = 0, mine_y = 0, found_x = 0, found_y = 0;
             if (owner) {
-                mine_x = word_addend<kBatchGridUnit>(words, sum.x, largest.x, at, place, s, splits);
-                mine_y = word_addend<kBatchGridUnit>(words, sum.y, largest.y, at + 1, place + 1, s, splits);
+                mine_x = word_addend<kBatchGridUnit>(words, sum.x, at, place, s, splits);
+                mine_y = word_addend<kBatchGridUnit>(words, sum.y, at + 1, place + 1, s, splits);
                 found_x = word_add(words.word + at, mine_x);
                 found_y = word_add(words.word + at + 1, mine_y);
             }
@@ -423,8 +421,6 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
         }
     }
     const bool grid = kWords && splits <= kWordSplits;
-    if (grid) sum = make_float2(grid_row<kBatchGridUnit>(sum.x, largest.x, splits),
-                                grid_row<kBatchGridUnit>(sum.y, largest.y, splits));
     if (owner) store_coherent2(p + s * split_stride, sum);
     wait_vector_memory();
     __syncthreads();

@@ -13,6 +13,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include "grid_sum.h"
 #include "teal_internal.h"
 #include <map>
 #include <mutex>
@@ -128,11 +129,6 @@ struct SurvivorReport {
     int matrix;
 };
 
-// Column words: the lowest bits, 4 for up to 16 slices and 5 for up to 32, count the arrivals; as many above
-// them tell which of up to four slices left a part of their sum apart, of more slices how many (a flag word
-// then tells which); the other bits are the sum.  All arrivals but the last find counts that fit.
-constexpr int kWordSplits = 32, kWordFlagged = 4;
-__device__ __forceinline__ int word_count_bits(int splits) { return splits <= 16 ? 4 : 5; }
 // The words, a flag word per column where there are any and one line per matrix for the survivors' count
 // share the area of the arrival counters, the part of a workspace that is zero between calls: 131008
 // columns, or 87338 with flags.  Launches of more columns or splits use the counters.
@@ -200,96 +196,6 @@ __device__ __forceinline__ Buffer buffer_of(const void *first, unsigned bytes)
 // readiness poll the fences of the __syncthreads() in between.  Never one without the other.
 constexpr int kAgentScope = 16;
 
-// The sums of up to kWordSplits slices are added as whole multiples of 2^-UNIT: whole numbers add up to the
-// same in any order, so the arrivals need no order, and their sum is rounded to fp32 once.
-// A slice's sum is within the grid, |sum| < 2^(51 - UNIT) (with more than 16 slices, whose sum has two bits less
-// to be in and may need one more, 2^(48 - UNIT)), and loses no more than what its wavefronts' sums
-// were rounded by: where the largest of those is below 2^(22 - UNIT) and the grid does not hold
-// the sum exactly, what the grid leaves is kept apart, and a sum beyond the grid (an infinity, a NaN) is kept
-// apart whole.  What is kept apart is added in fp64, in the order of the slices.
-struct GridSum {
-    long long whole;     // multiples of 2^-UNIT
-    float apart;         // what is left, zero unless `split`
-    bool split;
-};
-constexpr double kGridMagic = 0x1.8p52;         // x + kGridMagic rounds x to a whole number, in the low bits of the sum
-template <int UNIT>
-__device__ __forceinline__ float grid_limit(int splits)
-{
-    constexpr float kScale = (float)(1ull << UNIT);
-    return splits <= 16 ? (float)(1ull << 51) / kScale : (float)(1ull << 48) / kScale;
-}
-template <int UNIT>
-__device__ __forceinline__ GridSum grid_sum(float sum, float largest, float limit)
-{
-#pragma clang fp contract(off)
-    constexpr double kScale = (double)(1ull << UNIT);
-    const double x = (double)sum * kScale;
-    const double shifted = x + kGridMagic;
-    const double left = x - (shifted - kGridMagic);
-    const bool inside = fabsf(sum) < limit;
-    GridSum g;
-    g.whole = inside ? __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic) : 0;
-    g.split = !inside || (left != 0.0 && largest < (float)(1u << 22) / (float)kScale);
-    g.apart = !inside ? sum : g.split ? (float)(left * (1.0 / kScale)) : 0.f;      // exact
-    return g;
-}
-// Whether a sum needs none of that (to spare the wavefronts the rest of grid_sum).
-template <int UNIT>
-__device__ __forceinline__ bool grid_plain(float sum, float largest, float limit)
-{
-    return (fabsf(sum) < limit) & (largest >= (float)(1u << 22) / (float)(1ull << UNIT));
-}
-template <int UNIT>
-__device__ __forceinline__ float grid_value(long long whole, double apart)
-{
-#pragma clang fp contract(off)
-    return (float)((double)whole * (1.0 / (double)(1ull << UNIT)) + apart);
-}
-
-// The same by partial rows: what a slice writes for its sum, and the sum of the slices, of up to kGridRows at a
-// time (v[u]: row u; rows past the last are zeros).
-constexpr int kGridRows = 8;          // (16 cost the stack kernel a block per unit)
-struct GridTotal {
-    long long whole = 0;
-    double apart = 0.0;
-};
-template <int UNIT>
-__device__ __forceinline__ float grid_row(float sum, float largest, int splits)
-{
-    const GridSum g = grid_sum<UNIT>(sum, largest, grid_limit<UNIT>(splits));
-    return g.split ? sum : grid_value<UNIT>(g.whole, 0.0);
-}
-template <int UNIT>
-__device__ __forceinline__ void grid_add_rows(GridTotal &total, const float (&v)[kGridRows], int rows, int splits)
-{
-#pragma clang fp contract(off)
-    const float limit = grid_limit<UNIT>(splits);
-    long long whole = 0;
-    bool plain = true;
-#pragma unroll
-    for (int q = 0; q < kGridRows; q += 4) {
-        if (q >= rows) break;                             // block-uniform
-#pragma unroll
-        for (int u = q; u < q + 4; ++u) {
-            const double x = (double)v[u] * (double)(1ull << UNIT);
-            const double shifted = x + kGridMagic;
-            whole += __builtin_bit_cast(long long, shifted) - __builtin_bit_cast(long long, kGridMagic);
-            plain &= (fabsf(v[u]) < limit) & (shifted - kGridMagic == x);
-        }
-    }
-    if (__builtin_expect(!plain, 0)) {
-        whole = 0;
-#pragma unroll
-        for (int u = 0; u < kGridRows; ++u) {
-            const GridSum g = grid_sum<UNIT>(v[u], 0.f, limit);
-            whole += g.whole;
-            total.apart += (double)g.apart;
-        }
-    }
-    total.whole += whole;
-}
-
 // The words of a tile, and the tile's place in the partial rows (from the first slice's on, rows `row_stride`
 // floats apart, `row_end` of them to the end of the last one's).  Sum `at` of the tile is at `place` of a row.
 struct ColumnWords {
@@ -306,29 +212,21 @@ __device__ __forceinline__ ColumnWords column_words(const Meeting &m, int gtile,
                        reinterpret_cast<unsigned *>(first + m.words) + gtile * m.word_step, rows, row_stride, row_end};
 }
 
-// What slice s adds to the word for its sum, `largest` the largest of the sum's terms.
+// What slice s adds to the word for its sum (grid_sum.h).
 template <int UNIT>
-__device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, float sum, float largest, int at,
-                                                          int place, int s, int splits)
+__device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, float sum, int at, int place, int s,
+                                                          int splits)
 {
-    const int bits = word_count_bits(splits);
-    const float limit = grid_limit<UNIT>(splits);
-    const double shifted = (double)sum * (double)(1ull << UNIT) + kGridMagic;
-    // the magic's own bits are taken off again as one arrival is counted
-    const unsigned long long once = 1u - (__builtin_bit_cast(unsigned long long, kGridMagic) << 2 * bits);
-    unsigned long long mine = (__builtin_bit_cast(unsigned long long, shifted) << 2 * bits) + once;
-    if (__builtin_expect(!grid_plain<UNIT>(sum, largest, limit), 0)) {
-        const GridSum g = grid_sum<UNIT>(sum, largest, limit);
-        mine = ((unsigned long long)g.whole << 2 * bits) + 1u;
-        if (g.split) {                 // flag and value are there before the word tells of them
-            const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g.apart), rows,
-                                                  4 * (place + s * (int)t.row_stride), 0, kAgentScope);
-            if (splits > kWordFlagged)
-                __hip_atomic_fetch_or(t.flags + at, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wait_vector_memory();
-            mine += 1u << bits << (splits > kWordFlagged ? 0 : s);
-        }
+    const GridSum g = grid_sum<UNIT>(sum, grid_limit<UNIT>(splits));
+    unsigned long long mine = word_addend_on(g, splits);
+    if (__builtin_expect(g.apart, 0)) {        // flag and value are there before the word tells of them
+        const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), rows, 4 * (place + s * (int)t.row_stride), 0,
+                                              kAgentScope);
+        if (splits > kWordFlagged)
+            __hip_atomic_fetch_or(t.flags + at, 1u << s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_vector_memory();
+        mine = word_addend_apart(s, splits);
     }
     return mine;
 }
@@ -336,18 +234,13 @@ __device__ __forceinline__ unsigned long long word_add(unsigned long long *word,
 {
     return __hip_atomic_fetch_add(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ bool word_complete(unsigned long long found, int splits)
-{
-    return ((unsigned)found & ((1u << word_count_bits(splits)) - 1u)) == (unsigned)splits - 1u;
-}
 
 // The sum of all slices, for the one that found the others complete; the word is zero again for the next call.
 template <int UNIT>
 __device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long long mine, unsigned long long found,
                                             int at, int place, int splits)
 {
-    const int bits = word_count_bits(splits);
-    const unsigned told = (unsigned)(found | mine) >> bits & ((1u << bits) - 1u);
+    const unsigned told = word_told(mine, found, splits);
     double apart = 0.0;
     if (__builtin_expect(told != 0, 0)) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -369,7 +262,7 @@ __device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long 
         if (splits > kWordFlagged) __hip_atomic_store(t.flags + at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(t.word + at, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return grid_value<UNIT>(((long long)found >> 2 * bits) + ((long long)mine >> 2 * bits), apart);
+    return grid_value<UNIT>(word_whole(mine, found, splits), apart);
 }
 
 // The survivors' count of a launch with column words has a word of its own.  By one thread of each block of
@@ -1046,16 +939,11 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         return wrote;
     }
 
-    // The sum of column c over this block's wavefronts and the largest of its terms.
-    const auto sum_of = [&](int c, float &largest) {
+    // The sum of column c over this block's wavefronts.
+    const auto sum_of = [&](int c) {
         float sum = 0.f;
-        largest = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < SUMS; ++ww) {
-            const float v = red[ww * ROW + combine_index<EPL, LPR>(c)];
-            sum += v;
-            largest = fmaxf(largest, fabsf(v));
-        }
+        for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
         return sum;
     };
     if (meet.word_step) {
@@ -1065,9 +953,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         for (int k = 0; k < OWN; ++k) {
             const int c = k * THREADS + (int)threadIdx.x;
             if (c < cols) {
-                float largest;
-                const float sum = sum_of(c, largest);
-                mine[k] = word_addend<UNIT>(words, sum, largest, c, c, s, splits);
+                mine[k] = word_addend<UNIT>(words, sum_of(c), c, c, s, splits);
                 found[k] = word_add(words.word + c, mine[k]);
             }
         }
@@ -1096,16 +982,11 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
     // loads), ordered by the arrival counter: every thread waits for its stores
     // to complete, the block synchronises, then one thread takes the ticket.
     const Buffer row = buffer_of(partial + (size_t)s * n + col0, 4u * (unsigned)cols);
-    const bool grid = splits <= kWordSplits;
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
         const int c = k * THREADS + (int)threadIdx.x;
-        if (c < cols) {
-            float largest;
-            float sum = sum_of(c, largest);
-            if (grid) sum = grid_row<UNIT>(sum, largest, splits);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), row, 4 * c, 0, kAgentScope);
-        }
+        if (c < cols)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum_of(c)), row, 4 * c, 0, kAgentScope);
     }
     wait_vector_memory();   // this thread's write-through stores have completed
     __syncthreads();
@@ -1146,7 +1027,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
             v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part, 4 * (u * n + c), 0, kAgentScope));
         return rows;
     };
-    if (grid) {
+    if (splits <= kWordSplits) {
         GridTotal total[OWN];
 #pragma unroll 1
         for (int j = 0; j < splits; j += kGridRows) {

@@ -14,7 +14,7 @@ namespace teal {
 struct FmtW8 {
     static constexpr int kElemsPerLane = 16;   // 16 bytes = 16 int8
     static constexpr int kBitsPerElem = 8;
-    static constexpr int kGridUnit = 28;      // sums before the scale: up to 8e6, in steps of 4e-9
+    static constexpr int kGridUnit = 28;      // sums before the scale: below 2^23 (more than 16 slices: 2^20), all whole multiples of 2^-24 as fp16 is
     struct Args {
         const void *W;
         const __half *scale;

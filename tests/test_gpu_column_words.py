@@ -39,8 +39,10 @@ def run(T, wt, x, t, ws, **shape):
 
 
 def check(y, wt, x, t, splits):
-    """32-bit sums of exact products in any order: (kept + wavefronts) * 2^-24 of the sum of magnitudes;
-    the grid's rounding is below 2^-22 of the largest of a slice's eight terms."""
+    """32-bit sums of exact products in any order: (kept + wavefronts) * 2^-24 of the sum of magnitudes for
+    every column.  And the columns of a magnitude together: a lane adds at most a chain of `chain` products of random
+    sign, whose roundings add up to 2^-24 * sqrt(chain / 6) of the norm, the sums of the lanes and of eight
+    wavefronts to less than 2 units more, and the meeting adds half a unit; bounded by twice that."""
     kept = x.float().abs() > t
     xk = torch.where(kept, x.double(), 0.0)
     w = wt.double()
@@ -53,6 +55,13 @@ def check(y, wt, x, t, splits):
     err = (y.double() - want).abs()[fin]
     bound = (2 * int(kept.sum()) + 16 + 4 * splits) * 2.0 ** -24 * mag[fin] + 2.0 ** -149
     assert bool((err <= bound).all()), float((err / (bound + 1e-300)).max())
+    chain = -(-int(kept.sum()) // (8 * splits)) + 1
+    for k in range(len(SCALES)):
+        cols = torch.arange(len(y), device=y.device) % len(SCALES) == k
+        cols &= fin & (want.abs() > 2.0 ** -120)                # (below, sums have fewer bits)
+        if int(cols.sum()) >= 8:
+            rel = float((y.double() - want)[cols].norm() / want[cols].norm())
+            assert rel <= 2 * 2.0 ** -24 * (2.5 + (chain / 6) ** 0.5), (SCALES[k], rel)
     return int(kept.sum())
 
 
@@ -74,6 +83,60 @@ def test_columns_of_all_magnitudes(T, m, n, splits, p):   # noqa: F811
     assert not bool(ws[:head].any())
     assert torch.equal(run(T, wt, x, t, ws, splits=splits), first)
     assert not bool(ws[:head].any())
+
+
+# Exponents of the columns' unit below, from far below the grid's step to beyond its end.
+EXPONENTS = list(range(-75, 6))
+
+
+def whole_sums(m, n, splits, seed):
+    """[m][n] weights and an input whose products are whole multiples of 2^EXPONENTS[column] with less than 2^24
+    units in all, so that 32-bit sums in any order are exact.  In the second half of the columns the first and the
+    last channel of a slice (its first and last wavefront's) add 2^23 units and take them off again."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    units = torch.randint(-(1 << 22) // m, (1 << 22) // m + 1, (m, n), generator=g, device="cuda").double()
+    units = units.clamp(-256, 256)
+    units[:, n // 2:] = units[:, n // 2:].abs() * (torch.rand((m, n - n // 2), generator=g, device="cuda") < 0.05)
+    ks = (-(-m // splits) + 63) // 64 * 64
+    first = m // ks // 2 * ks
+    last = min(m, first + ks) - 1
+    units[first, n // 2:], units[last, n // 2:] = 2.0 ** 23, -(2.0 ** 23)
+    unit = torch.tensor([2.0 ** e for e in EXPONENTS], device="cuda", dtype=torch.float64).repeat(-(-n // len(EXPONENTS)))[:n]
+    wt = (units * unit).to(torch.bfloat16)
+    assert torch.equal(wt.double(), units * unit)
+    x = torch.randint(0, 2, (m,), generator=g, device="cuda").half()
+    x[first] = x[last] = 1.0
+    return wt, x, (x.double() @ units) * unit
+
+
+@pytest.mark.parametrize("m,n,splits", [(1000, 1304, 2), (2048, 1304, 4), (2048, 1304, 5), (4096, 2048, 16), (4096, 1304, 32),
+                                        (700, 682 * 128, 5), (700, 682 * 128 + 8, 5)])
+def test_no_bit_of_a_slice_is_lost(T, m, n, splits):   # noqa: F811
+    """Sums that are exact in every slice come out exactly, also those that cancel to less than the grid's
+    step: words with and without flag words, and counters (the last)."""
+    wt, x, want = whole_sums(m, n, splits, m + splits)
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    shape = dict(lanes_per_row=16, tile_cols=128, splits=splits)
+    for _ in range(2):
+        y = run(T, wt, x, 0.5, ws, **shape)
+        bad = (y.double() != want).nonzero()[:, 0]
+        assert bad.numel() == 0, (sorted({EXPONENTS[int(c) % len(EXPONENTS)] for c in bad}), len(bad))
+        assert not bool(ws[:T.teal_survivors_offset()].any())
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3])
+@pytest.mark.parametrize("splits", [4, 16])
+def test_no_bit_of_a_batch_is_lost(T, batch, splits):   # noqa: F811
+    m, n = 2048, 1304
+    wt, x, want = whole_sums(m, n, splits, 5 * splits)
+    X = torch.stack([x * (1 if b % 2 == 0 else -1) for b in range(batch)])
+    ws = torch.zeros(T.teal_workspace_bytes_batch(m, n, batch), dtype=torch.uint8, device="cuda")
+    Y = torch.full((batch, n), float("nan"), dtype=torch.float32, device="cuda")
+    T.check(T.teal_sparse_gemv_bf16_batch_ex(wt, X, batch, 0.5, Y, m, n, ws, splits=splits))
+    torch.cuda.synchronize()
+    for b in range(batch):
+        assert torch.equal(Y[b].double(), want if b % 2 == 0 else -want), b
 
 
 @pytest.mark.parametrize("kept", [1, 3, 40])
