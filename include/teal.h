@@ -111,10 +111,10 @@ teal_status teal_sparsify(const void *x_f16, int m, float t,
  * inside the kernel from x and t, only rows Wt[i][:] with |x_i| > t are read,
  * the input dimension is split across thread blocks, and the per-split
  * partial sums (fp32) of up to 32 splits are added as whole multiples of a
- * small unit (2^-40; int8, before the scale, 2^-28), so that it does not matter
- * which block is last (one kernel launch per call).  A partial sum that is no
- * such multiple or not below 2^51 units (2^48 with more than 16 splits) is
- * added to their total in fp64, in the order of the splits.
+ * small unit that follows t, so that it does not matter which block is last
+ * (one kernel launch per call).  A partial sum that is no such multiple or not
+ * below 2^51 units (2^48 with more than 16 splits) is added to their total in
+ * fp64, in the order of the splits.
  *   Wt_bf16 [m][n] bfloat16, input-channel-major, 16-byte aligned.
  *   x_f16   [m] fp16, 2-byte aligned.
  *   y       [n] fp32, 4-byte aligned.

@@ -303,7 +303,6 @@ __device__ __forceinline__ void stream_rows_batch(BatchAcc &acc, const int *list
     }
 }
 
-constexpr int kBatchGridUnit = 40;                     // as for one vector
 constexpr int kBatchWordRows = 2;                      // most rows of a batch that meet in column words
 
 // One activation column of the combine buffer, padded so that the 16 columns a row of lanes
@@ -349,7 +348,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
                                                    float *partial, const Meeting &meet, int gtile, float *Y,
                                                    int tile, int col0, int tile_cols, int s, int splits,
                                                    int n, int batch, int w,
-                                                   const SurvivorReport &report, int cnt)
+                                                   const SurvivorReport &report, int cnt, double bound)
 {
     constexpr int PAIRS = PARTS * kBatchTile / 2;
     static_assert(NB * PAIRS <= WAVES * 64, "one pair of columns per thread");
@@ -394,6 +393,7 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
     // Words for one or two rows.  With more, the atomics themselves take longer than the trips they save (8 rows,
     // Llama-3-8B block: 56.4 us by partial rows, 59.8 by words; 4 rows 52.1 and 52.3; 2 rows 53.2 and 52.0).
     constexpr bool kWords = NB <= kBatchWordRows;
+    const Grid grid{grid_unit_bf16((float)bound), splits};
     if constexpr (kWords) {
         if (meet.word_step) {
             const ColumnWords words = column_words(meet, gtile, partial + col0, (unsigned)batch * n,
@@ -401,8 +401,8 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             const int at = bb * tile_cols + c, place = bb * n + c;
             unsigned long long mine_x = 0, mine_y = 0, found_x = 0, found_y = 0;
             if (owner) {
-                mine_x = word_addend<kBatchGridUnit>(words, sum.x, at, place, s, splits);
-                mine_y = word_addend<kBatchGridUnit>(words, sum.y, at + 1, place + 1, s, splits);
+                mine_x = word_addend(words, grid, sum.x, at, place, s, splits);
+                mine_y = word_addend(words, grid, sum.y, at + 1, place + 1, s, splits);
                 found_x = word_add(words.word + at, mine_x);
                 found_y = word_add(words.word + at + 1, mine_y);
             }
@@ -412,15 +412,15 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             if (reports) counted = count_slice(counts, cnt);
             trace_mark(4);
             if (owner && word_complete(found_x, splits))
-                store_coherent(y, word_value<kBatchGridUnit>(words, mine_x, found_x, at, place, splits));
+                store_coherent(y, word_value(words, grid, mine_x, found_x, at, place, splits));
             if (owner && word_complete(found_y, splits))
-                store_coherent(y + 1, word_value<kBatchGridUnit>(words, mine_y, found_y, at + 1, place + 1, splits));
+                store_coherent(y + 1, word_value(words, grid, mine_y, found_y, at + 1, place + 1, splits));
             if (reports) count_total(report, counts, cnt, splits, counted);
             trace_mark(5);
             return;
         }
     }
-    const bool grid = kWords && splits <= kWordSplits;
+    const bool on_grid = kWords && splits <= kWordSplits;
     if (owner) store_coherent2(p + s * split_stride, sum);
     wait_vector_memory();
     __syncthreads();
@@ -453,18 +453,18 @@ __device__ __forceinline__ void block_finish_batch(const BatchAcc &acc, float *r
             sum.y += v[u].y;
         }
         if constexpr (kWords) {
-            if (grid) {
+            if (on_grid) {
                 float vx[MAXLD], vy[MAXLD];
 #pragma unroll
                 for (int u = 0; u < MAXLD; ++u) vx[u] = v[u].x, vy[u] = v[u].y;
-                grid_add_rows<kBatchGridUnit>(total_x, vx, splits - j, splits);
-                grid_add_rows<kBatchGridUnit>(total_y, vy, splits - j, splits);
+                grid_add_rows(total_x, vx, splits - j, grid);
+                grid_add_rows(total_y, vy, splits - j, grid);
             }
         }
     }
-    if (grid)
-        sum = make_float2(grid_value<kBatchGridUnit>(total_x.whole, total_x.apart),
-                          grid_value<kBatchGridUnit>(total_y.whole, total_y.apart));
+    if (on_grid)
+        sum = make_float2(grid_value(total_x.whole, total_x.apart, grid),
+                          grid_value(total_y.whole, total_y.apart, grid));
     store_coherent(y, sum.x);
     store_coherent(y + 1, sum.y);
 }
@@ -529,7 +529,7 @@ __device__ __forceinline__ void batch_block(const void *__restrict__ W,
     trace_mark(3);
     trace_mark_thread(1, (WAVES - 1) * 64);
     block_finish_batch<NB, WAVES, PARTS>(acc, red, partial, meet, gtile, Y, tile, col0, tile_cols, s, splits,
-                                  n, batch, w, report, cnt);
+                                  n, batch, w, report, cnt, bound);
     trace_mark(6);
 }
 

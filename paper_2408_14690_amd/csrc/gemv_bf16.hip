@@ -8,7 +8,7 @@ namespace teal {
 struct FmtBF16 {
     static constexpr int kElemsPerLane = 8;   // 16 bytes = 8 bf16
     static constexpr int kBitsPerElem = 16;
-    static constexpr int kGridUnit = 40;      // sums of slices below 2^11 (more than 16 slices: 2^8), in steps of 2^-40
+    static __device__ __forceinline__ int grid_unit(float t) { return grid_unit_bf16(t); }
     struct Args {
         const void *W;
         int ld = 0;             // elements from one row of W to the next; 0 = n

@@ -213,11 +213,10 @@ __device__ __forceinline__ ColumnWords column_words(const Meeting &m, int gtile,
 }
 
 // What slice s adds to the word for its sum (grid_sum.h).
-template <int UNIT>
-__device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, float sum, int at, int place, int s,
-                                                          int splits)
+__device__ __forceinline__ unsigned long long word_addend(const ColumnWords &t, const Grid &grid, float sum, int at,
+                                                          int place, int s, int splits)
 {
-    const GridSum g = grid_sum<UNIT>(sum, grid_limit<UNIT>(splits));
+    const GridSum g = grid_sum(sum, grid);
     unsigned long long mine = word_addend_on(g, splits);
     if (__builtin_expect(g.apart, 0)) {        // flag and value are there before the word tells of them
         const Buffer rows = buffer_of(t.rows, 4u * t.row_end);
@@ -236,9 +235,8 @@ __device__ __forceinline__ unsigned long long word_add(unsigned long long *word,
 }
 
 // The sum of all slices, for the one that found the others complete; the word is zero again for the next call.
-template <int UNIT>
-__device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long long mine, unsigned long long found,
-                                            int at, int place, int splits)
+__device__ __forceinline__ float word_value(const ColumnWords &t, const Grid &grid, unsigned long long mine,
+                                            unsigned long long found, int at, int place, int splits)
 {
     const unsigned told = word_told(mine, found, splits);
     double apart = 0.0;
@@ -262,7 +260,7 @@ __device__ __forceinline__ float word_value(const ColumnWords &t, unsigned long 
         if (splits > kWordFlagged) __hip_atomic_store(t.flags + at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(t.word + at, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return grid_value<UNIT>(word_whole(mine, found, splits), apart);
+    return grid_value(word_whole(mine, found, splits), apart, grid);
 }
 
 // The survivors' count of a launch with column words has a word of its own.  By one thread of each block of
@@ -904,13 +902,13 @@ __device__ __forceinline__ void store_wave_sums(const float (&acc)[N], float *ds
 template <class F, int LPR, int WAVES, int SUMS = WAVES>
 __device__ __forceinline__ int block_finish(float *red, float *partial, const Meeting &meet, int gtile,
                                              float *y, int tile, int col0, int cols, int s, int splits, int n,
-                                             const typename F::Args &a, const SurvivorReport &report, int cnt)
+                                             const typename F::Args &a, const SurvivorReport &report, int cnt,
+                                             float t)
 {
     constexpr int EPL = F::kElemsPerLane;
     constexpr int TN = LPR * EPL;
     constexpr int THREADS = WAVES * 64;
     constexpr int OWN = (TN + THREADS - 1) / THREADS;     // columns c = thread + k * THREADS
-    constexpr int UNIT = F::kGridUnit;
     __shared__ int last_flag;
     const int w = threadIdx.x >> 6;
     if (cols > n - col0) cols = n - col0;
@@ -946,6 +944,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         for (int ww = 0; ww < SUMS; ++ww) sum += red[ww * ROW + combine_index<EPL, LPR>(c)];
         return sum;
     };
+    const Grid grid{F::grid_unit(t), splits};
     if (meet.word_step) {
         unsigned long long mine[OWN], found[OWN];
         const ColumnWords words = column_words(meet, gtile, partial + col0, n, (unsigned)(splits - 1) * n + cols);
@@ -953,7 +952,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         for (int k = 0; k < OWN; ++k) {
             const int c = k * THREADS + (int)threadIdx.x;
             if (c < cols) {
-                mine[k] = word_addend<UNIT>(words, sum_of(c), c, c, s, splits);
+                mine[k] = word_addend(words, grid, sum_of(c), c, c, s, splits);
                 found[k] = word_add(words.word + c, mine[k]);
             }
         }
@@ -966,7 +965,7 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
         for (int k = 0; k < OWN; ++k) {
             const int c = k * THREADS + (int)threadIdx.x;
             if (c < cols && word_complete(found[k], splits)) {
-                const float sum = word_value<UNIT>(words, mine[k], found[k], c, c, splits);
+                const float sum = word_value(words, grid, mine[k], found[k], c, c, splits);
                 store_coherent(y + col0 + c, F::finish(sum, scale[k]));
                 ++wrote;
             }
@@ -1037,12 +1036,12 @@ __device__ __forceinline__ int block_finish(float *red, float *partial, const Me
                 if (c < cols) {
                     float v[kGridRows];
                     const int rows = load_rows(v, j, c);
-                    grid_add_rows<UNIT>(total[k], v, rows, splits);
+                    grid_add_rows(total[k], v, rows, grid);
                 }
             }
         }
 #pragma unroll
-        for (int k = 0; k < OWN; ++k) sum[k] = grid_value<UNIT>(total[k].whole, total[k].apart);
+        for (int k = 0; k < OWN; ++k) sum[k] = grid_value(total[k].whole, total[k].apart, grid);
     } else {
         constexpr int MAXLD = 16;
         for (int j = 0; j < splits; j += MAXLD) {
@@ -1144,7 +1143,7 @@ __device__ __forceinline__ int gemv_block(const typename F::Args &a, const XS &x
     trace_mark_thread(1, (WAVES - 1) * 64);
     store_wave_sums<LPR>(acc, red + (threadIdx.x >> 6) * combine_row<EPL, LPR>);
     return block_finish<F, LPR, WAVES>(red, partial, meet, gtile, y, tile, col0, tile_cols, s, splits, n, a,
-                                       report, cnt);
+                                       report, cnt, t);
 }
 
 // One matrix per launch.  Grid: tiles x splits blocks (two dimensions: a division of the block index

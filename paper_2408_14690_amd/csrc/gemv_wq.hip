@@ -14,7 +14,7 @@ namespace teal {
 struct FmtW8 {
     static constexpr int kElemsPerLane = 16;   // 16 bytes = 16 int8
     static constexpr int kBitsPerElem = 8;
-    static constexpr int kGridUnit = 28;      // sums before the scale: below 2^23 (more than 16 slices: 2^20), all whole multiples of 2^-24 as fp16 is
+    static __device__ __forceinline__ int grid_unit(float t) { return grid_unit_w8(t); }
     struct Args {
         const void *W;
         const __half *scale;
@@ -57,7 +57,7 @@ struct FmtW8 {
 struct FmtW4 {
     static constexpr int kElemsPerLane = 32;   // 16 bytes = 32 nibbles
     static constexpr int kBitsPerElem = 4;
-    static constexpr int kGridUnit = 40;      // as bf16: the groups' scales are in the sums
+    static __device__ __forceinline__ int grid_unit(float t) { return grid_unit_w4(t); }
     struct Args {
         const void *W;
         const __half *scale;
@@ -372,7 +372,7 @@ __device__ __forceinline__ int w4_block(const FmtW4::Args &a, const XS &x,
         *reinterpret_cast<float2 *>(row + EPL * (4 * g + r)) =
             make_float2(acc[0][r] * unit, acc[1][r] * unit);
     return block_finish<F, LPR, WAVES, SHARES>(red, partial, meet, gtile, y, tile, col0, tile_cols, s,
-                                               splits, n, a, report, cnt);
+                                               splits, n, a, report, cnt, t);
 }
 
 template <int LPR, int WAVES, int U>

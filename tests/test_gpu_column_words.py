@@ -139,6 +139,40 @@ def test_no_bit_of_a_batch_is_lost(T, batch, splits):   # noqa: F811
         assert torch.equal(Y[b].double(), want if b % 2 == 0 else -want), b
 
 
+@pytest.mark.parametrize("e", [-13, -8, 0, 6, 11])
+@pytest.mark.parametrize("fmt", ["bf16", "w8", "w4", "batch"])
+def test_ordinary_sums_take_the_short_way_whatever_the_size_of_the_inputs(T, fmt, e):   # noqa: F811
+    """Inputs of size 2^e at 50 %: the step follows the threshold, so next to none of the slices' sums is kept
+    apart (int8 and int4: none, they are whole multiples of it).  A sum kept apart is written to its slice's row."""
+    m = n = 2048
+    g = torch.Generator(device="cuda")
+    g.manual_seed(e + 100)
+    x = (torch.randn(m, generator=g, device="cuda") * 2.0 ** e).half()
+    t = 0.6744898 * 2.0 ** e
+    size = T.teal_workspace_bytes(m, n)
+    ws = torch.zeros(max(size, T.teal_workspace_bytes_batch(m, n, 2)), dtype=torch.uint8, device="cuda")
+    rows = ws[size - 4 * 128 * n:].view(torch.int32)      # 128 rows behind the head and the report
+    rows.fill_(0x5A5A5A5A)
+    y = torch.full((2, n), float("nan"), dtype=torch.float32, device="cuda")
+    if fmt in ("bf16", "batch"):
+        w = (torch.randn((m, n), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+        if fmt == "bf16":
+            T.check(T.teal_sparse_gemv_bf16(w, x, t, y[0], m, n, ws))
+        else:
+            T.check(T.teal_sparse_gemv_bf16_batch(w, torch.stack([x, -x]), 2, t, y, m, n, ws))
+    elif fmt == "w8":
+        q = torch.randint(-127, 128, (m, n), generator=g, device="cuda", dtype=torch.int8)
+        T.check(T.teal_sparse_gemv_w8(q, torch.full((n,), 2e-4, device="cuda").half(), x, t, y[0], m, n, ws))
+    else:
+        q = torch.randint(0, 256, (m, n // 2), generator=g, device="cuda", dtype=torch.uint8)
+        sc = (torch.rand((m // 128, n), generator=g, device="cuda") * 0.005).half()
+        T.check(T.teal_sparse_gemv_w4(q, sc, 128, x, t, y[0], m, n, ws))
+    torch.cuda.synchronize()
+    apart = int((rows != 0x5A5A5A5A).sum())
+    assert apart <= (0 if fmt in ("w8", "w4") else 16 * n // 1000), apart
+    assert bool(torch.isfinite(y[0]).all()) and not bool(ws[:T.teal_survivors_offset()].any())
+
+
 @pytest.mark.parametrize("kept", [1, 3, 40])
 def test_few_survivors(T, kept):   # noqa: F811
     """Slices without a survivor and slices whose sum is one product: exact where the column has one."""

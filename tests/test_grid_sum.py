@@ -18,14 +18,15 @@ DRIVER = r"""
 using namespace teal;
 // One column: slice order[i] arrives i-th at a word that was left at zero.  Returns what the one that finds the
 // others complete writes; -1 arrivals if none or several did.
-template <int UNIT> static int words(const float *sums, const int *order, int splits, float *y)
+extern "C" int meet_words(int unit, const float *sums, const int *order, int splits, float *y)
 {
+    const Grid grid{unit, splits};
     unsigned long long word = 0;
     unsigned flags = 0;
     int wrote = 0;
     for (int i = 0; i < splits; ++i) {
         const int s = order[i];
-        const GridSum g = grid_sum<UNIT>(sums[s], grid_limit<UNIT>(splits));
+        const GridSum g = grid_sum(sums[s], grid);
         const unsigned long long mine = g.apart ? word_addend_apart(s, splits) : word_addend_on(g, splits);
         if (g.apart) flags |= 1u << s;
         const unsigned long long found = word;
@@ -37,28 +38,26 @@ template <int UNIT> static int words(const float *sums, const int *order, int sp
         double apart = 0.0;
         if (told)
             for (int j = 0; j < splits; ++j) apart += from >> j & 1u ? (double)sums[j] : 0.0;
-        *y = grid_value<UNIT>(word_whole(mine, found, splits), apart);
+        *y = grid_value(word_whole(mine, found, splits), apart, grid);
     }
     return wrote;
 }
-template <int UNIT> static float rows(const float *sums, int splits)
+extern "C" float meet_rows(int unit, const float *sums, int splits)
 {
+    const Grid grid{unit, splits};
     GridTotal total;
     for (int j = 0; j < splits; j += kGridRows) {
         float v[kGridRows] = {};
         const int n = splits - j < kGridRows ? splits - j : kGridRows;
         std::memcpy(v, sums + j, n * sizeof(float));
-        grid_add_rows<UNIT>(total, v, n, splits);
+        grid_add_rows(total, v, n, grid);
     }
-    return grid_value<UNIT>(total.whole, total.apart);
+    return grid_value(total.whole, total.apart, grid);
 }
-extern "C" int meet_words(int unit, const float *sums, const int *order, int splits, float *y)
+extern "C" int off_grid(int unit, int splits, float sum) { return grid_sum(sum, Grid{unit, splits}).apart; }
+extern "C" int unit_of(int bits, float t)
 {
-    return unit == 40 ? words<40>(sums, order, splits, y) : words<28>(sums, order, splits, y);
-}
-extern "C" float meet_rows(int unit, const float *sums, int splits)
-{
-    return unit == 40 ? rows<40>(sums, splits) : rows<28>(sums, splits);
+    return bits == 16 ? grid_unit_bf16(t) : bits == 8 ? grid_unit_w8(t) : grid_unit_w4(t);
 }
 """
 
@@ -74,6 +73,8 @@ def host(tmp_path_factory):
                     "-o", str(d / "driver.so")], check=True)
     lib = ctypes.CDLL(str(d / "driver.so"))
     lib.meet_rows.restype = ctypes.c_float
+    lib.unit_of.argtypes = [ctypes.c_int, ctypes.c_float]
+    lib.off_grid.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_float]
     return lib
 
 
@@ -94,7 +95,7 @@ def meet(host, sums, unit, rng):
 SPLITS = [2, 3, 4, 5, 8, 15, 16, 17, 22, 31, 32]
 
 
-@pytest.mark.parametrize("unit", [40, 28])
+@pytest.mark.parametrize("unit", [49, 40, 24, -5])
 @pytest.mark.parametrize("splits", SPLITS)
 def test_no_bit_of_a_slice_is_lost(host, unit, splits):
     """Sums that are small whole multiples of one power of two, from far below the grid's step to far above its
@@ -102,7 +103,7 @@ def test_no_bit_of_a_slice_is_lost(host, unit, splits):
     a last bit below the step, one that cancels to less than the step, and both ends of the grid."""
     rng = random.Random(splits)
     u = 2.0 ** -unit
-    for e in list(range(-unit - 70, -unit + 60)):
+    for e in range(max(-149, -unit - 70), -unit + 60):
         for _ in range(3):
             k = [rng.randint(-(2 ** 18), 2 ** 18) for _ in range(splits)]
             if rng.random() < 0.5:
@@ -120,7 +121,7 @@ def test_no_bit_of_a_slice_is_lost(host, unit, splits):
     assert meet(host, [-top * (1 - 2.0 ** -24)] * splits, unit, rng) == np.float32(-splits * top * (1 - 2.0 ** -24))
 
 
-@pytest.mark.parametrize("unit", [40, 28])
+@pytest.mark.parametrize("unit", [49, 40, 24, -5])
 @pytest.mark.parametrize("splits", SPLITS)
 def test_sums_of_any_size(host, unit, splits):
     """Random fp32 sums with a spread of 2^40 and more: within the rounding to fp32 once, and of fp64 sums of
@@ -143,3 +144,38 @@ def test_infinities_and_nans(host, splits):
     assert meet(host, [inf] + rest, 40, rng) == inf and meet(host, rest + [-inf], 40, rng) == -inf
     assert np.isnan(meet(host, [float("nan")] + rest, 40, rng))
     assert np.isnan(meet(host, [inf] + rest[1:] + [-inf], 40, rng))
+
+
+THRESHOLDS = [0.0, 1e-30, 2.0 ** -24, 3e-7, 1e-5, 2.0 ** -15, 1e-4, 1e-3, 0.02, 0.03125, 0.3, 0.6744898, 1.0, 1.999, 2.0, 5.0, 100.0, 1000.0,
+              32768.0, 65503.0]
+
+
+@pytest.mark.parametrize("t", THRESHOLDS)
+def test_sums_of_quantised_weights_are_on_the_grid(host, t):
+    """Whatever the surviving inputs: int8 products, and int4 products with their group's scale (for thresholds that
+    are not far below the inputs), are whole multiples of the step; long sums stay below the limit."""
+    rng = np.random.default_rng(int(t) + 7)
+    u8, u4 = host.unit_of(8, t), host.unit_of(4, t)
+    x = np.abs(rng.integers(0, 0x7C00, 4000, dtype=np.uint16).view(np.float16).astype(np.float64))
+    x = np.append(x, float(np.float16(min(t * (1 + 2.0 ** -8), 65504))))
+    x = x[x > t]
+    assert np.all(np.ldexp(x, u8) % 1 == 0)
+    scale = rng.integers(0, 0x7C00, len(x), dtype=np.uint16).view(np.float16).astype(np.float64)
+    if t == 0 or t >= 2.0 ** -14:
+        low = 2.0 ** -24 if t else 2.0 ** -16                # (dense: scales of 2^-16 and more)
+        assert np.all(np.ldexp(x * np.maximum(np.round(scale / low) * low, low), u4) % 1 == 0)
+    ordinary = max(t, 2.0 ** -9)
+    for bits, gain in ((8, 127 * 64), (4, 0.05 * 7 * 64), (16, 0.05 * 64)):
+        for splits in (16, 32):
+            assert not host.off_grid(host.unit_of(bits, t), splits, gain * ordinary), (bits, splits)
+
+
+@pytest.mark.parametrize("e", range(-14, 12))
+def test_unit_follows_the_inputs(host, e):
+    """Inputs of size 2^e with half of them dropped: sums of bf16 weights of 0.02 over 64 to 2048 channels, whose
+    sizes are some 0.05 to 1 times the inputs', are on the grid from 2^-7 of that on to 16 times it."""
+    unit = host.unit_of(16, 0.67 * 2.0 ** e)
+    for s in (0.05 * 2.0 ** -6, 0.05, 1.0, 16.0):
+        v = np.float32(s * 2.0 ** e)
+        assert not host.off_grid(unit, 16, np.nextafter(v, np.float32(np.inf))), s
+    assert host.unit_of(16, 0.0) == 40 and host.unit_of(4, 0.0) == 40 and host.unit_of(8, 0.0) == 24
