@@ -495,10 +495,11 @@ teal_status teal_sparse_gemv_w4_multi(int count, const uint8_t *const *Wq,
  * HOST array of 8 ints: [0] blocks in the grid (always set; the rest is -1 when
  * `block` is out of range), [1] 0 = gate, 1 = up, 2 = down, [2] output tile,
  * [3] K-slice; for a gate / up block [4], [5] = the columns [c0, c1) of its
- * tile and [6], [7] = the first and last K-slice of W_down told when the tile
- * is finished; for a block of W_down [4], [5] = the input channels [k0, k1) of
- * its slice, [6] = its K-slice and [7] = the number of gate and up tiles it
- * waits for.
+ * tile and [6], [7] = the first and last K-slice of W_down told of the columns
+ * of the tile that the block has finished; for a block of W_down [4], [5] = the
+ * input channels [k0, k1) of its slice, [6] = its K-slice and [7] = the number
+ * of gate and up columns it waits for: those of every tile that holds one of
+ * its channels.
  */
 typedef struct teal_mlp_shape {
     int gu_lanes_per_row, gu_tile_cols, gu_splits, gu_phase_tiles;

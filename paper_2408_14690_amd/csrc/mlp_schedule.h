@@ -15,8 +15,8 @@
 // columns have written them; each such block then adds the number of columns it wrote to the
 // readiness counter of every block of W_down whose K-slice reads any of the tile's columns (one
 // counter per W_down block: a counter polled by one block only).  A block of W_down with
-// K-slice s waits for the mlp_expected(s) gate and up tiles that overlap the slice: until
-// its counter equals mlp_expected_columns(s), the columns of those tiles.
+// K-slice s waits for the gate and up tiles that overlap the slice: until its counter equals
+// mlp_expected_columns(s), the columns of those tiles.
 #pragma once
 
 #if defined(__HIPCC__)
@@ -84,16 +84,7 @@ TEAL_HD inline void mlp_signal_range(const MlpGrid &g, int tile, int &lo, int &h
     hi = (c1 - 1) / g.ks_d;
 }
 
-// Number of gate and up tiles a block of W_down with K-slice s waits for.
-TEAL_HD inline int mlp_expected(const MlpGrid &g, int s)
-{
-    const int k0 = s * g.ks_d;
-    int k1 = k0 + g.ks_d;
-    if (k1 > g.f) k1 = g.f;
-    return 2 * ((k1 - 1) / g.tile_cols_gu - k0 / g.tile_cols_gu + 1);
-}
-
-// Their columns.
+// Columns of the gate and up tiles that a block of W_down with K-slice s waits for: of all that overlap the slice.
 TEAL_HD inline int mlp_expected_columns(const MlpGrid &g, int s)
 {
     const int k0 = s * g.ks_d;

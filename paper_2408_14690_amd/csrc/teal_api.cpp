@@ -1412,7 +1412,7 @@ teal_status teal_mlp_block_info(int weight_bits, int m, int f, int d, const teal
         info[4] = k0;
         info[5] = k0 + g.ks_d < f ? k0 + g.ks_d : f;
         info[6] = b.split;
-        info[7] = teal::mlp_expected(g, b.split);
+        info[7] = teal::mlp_expected_columns(g, b.split);
     } else {
         const int c0 = b.tile * g.tile_cols_gu;
         info[4] = c0;

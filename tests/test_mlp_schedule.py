@@ -2,9 +2,10 @@
 describes every thread block of a launch through teal_mlp_block_info (the same integer
 arithmetic the kernel runs), and a small model of a GPU's block dispatcher -- blocks start in
 index order as slots free up, running blocks finish in any order, a block of W_down cannot
-finish before the gate / up tiles it waits for -- checks that the work is covered exactly
+finish before the gate / up columns it waits for -- checks that the work is covered exactly
 once, that every wait is for exactly the tiles that hold the waiting block's inputs, and that
-no order of completion and no number of slots can leave a block waiting for ever."""
+no order of completion, no number of slots and no way in which the K-slices of a tile share
+out its columns can leave a block waiting for ever."""
 import os
 import random
 
@@ -44,11 +45,13 @@ def shape_of(bits, m, f, d, **over):
 
 def simulate(blocks, slots, rng, order=None):
     """In-order dispatch into `slots` slots; running blocks complete in random order, a
-    consumer only once its slice's counter has reached the value it waits for.  Returns the
+    consumer only once its slice's counter has reached the value it waits for.  A column of a gate / up
+    tile is finished by whichever K-slice's block adds its sum last, so a block that completes has finished
+    any share of the columns that are left, the tile's last one all of them, and tells as many.  Returns the
     completion order, or None if a state is reached in which nothing can complete."""
     order = list(range(len(blocks))) if order is None else order
     splits_gu = 1 + max(b["split"] for b in blocks if b["kind"] != DOWN)
-    arrived, ready = {}, {}
+    arrived, left, ready = {}, {}, {}
     running, nxt, done = [], 0, []
     while len(done) < len(blocks):
         while nxt < len(order) and len(running) < slots:
@@ -65,9 +68,13 @@ def simulate(blocks, slots, rng, order=None):
         if blk["kind"] != DOWN:
             key = (blk["kind"], blk["tile"])
             arrived[key] = arrived.get(key, 0) + 1
-            if arrived[key] == splits_gu:                 # the block that combines the K-slices
-                for s in range(blk["a"], blk["b"] + 1):
-                    ready[s] = ready.get(s, 0) + 1
+            columns = left.get(key, blk["hi"] - blk["lo"])
+            if arrived[key] < splits_gu:
+                columns = rng.choice([0, 0, rng.randint(0, columns)])
+            left[key] = left.get(key, blk["hi"] - blk["lo"]) - columns
+            for s in range(blk["a"], blk["b"] + 1):
+                ready[s] = ready.get(s, 0) + columns
+                assert all(ready[s] <= b["b"] for b in blocks if b["kind"] == DOWN and b["split"] == s)
     return done
 
 
@@ -82,6 +89,10 @@ SHAPES = [
                               down_lanes_per_row=16, down_tile_cols=72, down_splits=5)),
     (8, 4096, 14336, 4096, dict(gu_phase_tiles=2)),
     (4, 4096, 14336, 4096, dict(gu_phase_tiles=5)),
+    # the last gate / up tile is narrower, slices of W_down begin and end inside tiles
+    (16, 1024, 2808, 1024, dict(gu_lanes_per_row=32, gu_tile_cols=200, gu_splits=7, down_lanes_per_row=16,
+                                down_tile_cols=128, down_splits=11)),
+    (4, 512, 1408, 512, dict(gu_lanes_per_row=32, gu_tile_cols=992, gu_splits=4, down_splits=5)),
 ]
 
 
@@ -110,15 +121,18 @@ def test_every_tile_and_slice_is_covered_exactly_once(bits, m, f, d, over):
     slices = sorted({(b["split"], b["lo"], b["hi"]) for b in dn})
     assert slices[0][1] == 0 and slices[-1][2] == f
     assert all(a[2] == b[1] for a, b in zip(slices, slices[1:]))
-    # a slice waits for exactly the gate and up tiles that hold one of its channels, and
+    # a slice waits for the columns of exactly the gate and up tiles that hold one of its channels, and
     # exactly those tiles tell it
     for s, k0, k1 in slices:
+        columns = 0
         for kind in (GATE, UP):
             overlapping = {b["tile"] for b in gu if b["kind"] == kind and b["lo"] < k1 and b["hi"] > k0}
             telling = {b["tile"] for b in gu if b["kind"] == kind and b["a"] <= s <= b["b"]}
             assert overlapping == telling
+            columns += sum(hi - lo for tile, lo, hi in {(b["tile"], b["lo"], b["hi"]) for b in gu if b["kind"] == kind}
+                           if tile in overlapping)
         expected = {b["b"] for b in dn if b["split"] == s}
-        assert expected == {2 * len(overlapping)}
+        assert expected == {columns}
 
 
 @pytest.mark.parametrize("bits,m,f,d,over", SHAPES)
@@ -139,7 +153,7 @@ def test_phases_finish_the_first_columns_first(bits, m, f, d, over):
     assert [b["lo"] for b in dn] == sorted(b["lo"] for b in dn)
 
 
-@pytest.mark.parametrize("bits,m,f,d,over", SHAPES[:6])
+@pytest.mark.parametrize("bits,m,f,d,over", SHAPES[:6] + SHAPES[8:])
 @pytest.mark.parametrize("slots", [1, 2, 7, 256, 768, 100000])
 def test_no_wait_lasts_for_ever_whatever_finishes_first(bits, m, f, d, over, slots):
     sh = shape_of(bits, m, f, d, **over)
