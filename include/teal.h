@@ -412,7 +412,9 @@ teal_status teal_sparse_gemv_w4_rmsnorm_multi(int count, const uint8_t *const *W
  * (1..4) that read the same hidden state, one kernel launch.  Wq, scale_f16, t,
  * y, n are HOST arrays of length count (device pointers / values per matrix,
  * formats as for teal_sparse_gemv_w4, n_k % 32 == 0); group == 128,
- * m % 128 == 0.  workspace of at least
+ * m % 128 == 0.  Results are bitwise those of separate calls with the same
+ * launch shape (a group of one may have fewer splits than teal_sparse_gemv_w4,
+ * see teal_gemv_plan).  workspace of at least
  * teal_workspace_bytes(m, n_0 + ... + n_{count-1}).
  */
 teal_status teal_sparse_gemv_w4_multi(int count, const uint8_t *const *Wq,
@@ -452,9 +454,7 @@ teal_status teal_sparse_gemv_w4_multi(int count, const uint8_t *const *Wq,
  *           (teal_mlp_plan).  For tuning and tests: lanes per row, tile width
  *           and split count of the gate / up products and of the W_down
  *           product as for teal_sparse_gemv_bf16_ex (8 wavefronts, 4 loads per
- *           batch; int4: down_splits is the planned count, which up to 160
- *           blocks of W_down is cut finer as in teal_sparse_gemv_w4_swiglu,
- *           see teal_gemv_plan); gu_phase_tiles > 0 orders the gate / up blocks in phases
+ *           batch); gu_phase_tiles > 0 orders the gate / up blocks in phases
  *           of that many output tiles of each matrix, so that the first
  *           columns of gate and up are finished first (0 = one phase);
  *           extra_lds_bytes (0..49152) of unused shared memory per block lower
@@ -654,10 +654,11 @@ teal_status teal_sparse_gemv_bf16_batch_multi(int count, const void *const *Wt_b
  * these dimensions (weight_bits = 16, 8 or 4), in the terms of
  * teal_sparse_gemv_bf16_ex.  Host-only; every output pointer is HOST memory
  * and may be NULL.  Split-K (Section 4.4) is `splits` blocks along the input
- * dimension; the grid is ceil(n / tile_cols) * splits blocks.  (int4, one
- * matrix: where that grid has at most 160 blocks, teal_sparse_gemv_w4 and
- * _w4_swiglu and W_down of the one-launch MLP cut the slices finer, to at
- * most 256 blocks, 32 slices and at least 128 channels each.)
+ * dimension; the grid is ceil(n / tile_cols) * splits blocks.  (int4: also the
+ * shape of teal_sparse_gemv_w4_swiglu and of W_down in the one-launch MLP.  It
+ * may have up to 32 splits where a grouped or stack call of one such matrix,
+ * teal_gemv_plan_multi, has up to 16: those have the same sums to rounding, not
+ * bit for bit.)
  */
 teal_status teal_gemv_plan(int weight_bits, int m, int n, int *lanes_per_row, int *tile_cols,
                            int *splits, int *waves, int *unroll);

@@ -1356,33 +1356,14 @@ struct GemvGeometry {
     size_t lds;        // dynamic LDS bytes
 };
 
-// int4: as many slices as the compute units can take.  A tile has at least 512 columns there, so the 16 slices
-// of a planned shape make 64 blocks for 2048 columns and 128 for 4096, and the product is bound by
-// instruction issue: finer slices go to the units that would be idle.  Up to 160 blocks, where a third of the
-// units is left; with more, slices that do not divide the units do not pay.  At least 128 channels (a
-// group) per slice.  For one matrix: the groups of a stack launch have to be the grouped calls, bit for bit, and
-// there other groups' blocks take those units (Llama-3-8B stack 21.7 us as planned, 24.6 cut).  (us,
-// planned / cut: 4096 -> 2048 5.64 / 5.06, 14336 -> 4096 8.89 / 7.60, dense 12.1 / 9.5,
-// 5120 -> 5120 6.57 / 6.00, 3584 -> 1024 with SiLU(gate) * up 5.85 / 5.18.)
-inline int int4_slices(int m, int tiles, int splits)
-{
-    if (tiles * splits > 160) return splits;
-    int s = 256 / tiles;
-    if (s > kWordSplits) s = kWordSplits;
-    if (s > m / 128) s = m / 128;
-    return s > splits ? s : splits;
-}
-
-// `finer`: by int4_slices().
 inline GemvGeometry gemv_geometry(int m, int n, const GemvShape &sh, int elems_per_lane,
-                                  int ks_multiple, int max_slice = kMaxSlice, bool finer = false)
+                                  int ks_multiple, int max_slice = kMaxSlice)
 {
     GemvGeometry g;
     const int tn = sh.lanes_per_row * elems_per_lane;
     g.tile_cols = sh.tile_cols > 0 ? sh.tile_cols : tn;
     g.tiles = (n + g.tile_cols - 1) / g.tile_cols;
     int splits = sh.splits < 1 ? 1 : sh.splits;
-    if (finer) splits = int4_slices(m, g.tiles, splits);
     int ks = (m + splits - 1) / splits;
     ks = (ks + ks_multiple - 1) / ks_multiple * ks_multiple;
     if (ks > max_slice) ks = max_slice;

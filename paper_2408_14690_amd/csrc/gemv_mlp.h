@@ -178,7 +178,7 @@ inline bool mlp_grid(MlpGrid &g, GemvGeometry &ggu, GemvGeometry &gd, const MlpL
                      int f, int d, int elems_per_lane, int ks_multiple, int max_slice_gu = kMaxSlice)
 {
     ggu = gemv_geometry(m, f, L.gu, elems_per_lane, ks_multiple, max_slice_gu);
-    gd = gemv_geometry(f, d, L.down, elems_per_lane, ks_multiple, kMaxSlice, elems_per_lane == 32);
+    gd = gemv_geometry(f, d, L.down, elems_per_lane, ks_multiple);
     if ((long long)gd.tiles * gd.splits > kMlpMaxConsumers) return false;
     g.f = f;
     g.tiles_gu = ggu.tiles;

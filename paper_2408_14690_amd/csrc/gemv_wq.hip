@@ -631,7 +631,7 @@ hipError_t launch_gemv_w4(const uint8_t *Wq, const void *scale_f16, const void *
 {
     GemvShape w4 = sh;
     w4.waves = kW4Waves;                          // the int4 kernel is built for 8 wavefronts
-    const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup, kMaxSlice, true);
+    const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup);
     const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW4::Args a{Wq, static_cast<const __half *>(scale_f16)};
     const __half *x = static_cast<const __half *>(x_f16);
@@ -653,7 +653,7 @@ hipError_t launch_gemv_w4_swiglu(const uint8_t *Wq, const void *scale_f16, const
 {
     GemvShape w4 = sh;
     w4.waves = kW4Waves;
-    const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup, kMaxSlice, true);
+    const GemvGeometry g = gemv_geometry(m, n, w4, FmtW4::kElemsPerLane, kGroup);
     const Meeting meet = meeting_of(counters, g.tiles, g.tile_cols, g.splits);
     FmtW4::Args a{Wq, static_cast<const __half *>(scale_f16)};
 #define TEAL_LAUNCH_W4S(LPR)                                                                   \

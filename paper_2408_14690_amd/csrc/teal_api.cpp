@@ -8,6 +8,7 @@
 #include <atomic>
 #include <cmath>
 
+#include "grid_sum.h"
 #include "teal_internal.h"
 
 namespace {
@@ -156,6 +157,27 @@ GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_la
 {
     return shape_for(m, n, elems_per_lane, min_lanes, max_lanes, ks_multiple, teal::kMaxSlice,
                      wide_tiles(m, &n, row_pitch, 1, elems_per_lane));
+}
+// One int4 matrix: as many slices as the compute units can take.  A tile has at least 512 columns there, so the 16
+// slices of the other formats make 64 blocks for 2048 columns and 128 for 4096, and the product is bound by
+// instruction issue: finer slices go to the units that would be idle.  Up to 160 blocks, where a third of the
+// units is left; with more, slices that do not divide the units do not pay.  At least 128 channels (a
+// group) per slice.  Not for a group of one: the groups of a stack launch have to be the grouped calls, bit for bit, and
+// there other groups' blocks take those units (Llama-3-8B block as a stack 22.5 us as planned, 25.5 cut; four 4096 x 4096
+// 12.4 and 19.1).  (us, planned / cut: 4096 -> 2048 5.64 / 5.06, 14336 -> 4096 8.89 / 7.60, dense 12.1 / 9.5,
+// 5120 -> 5120 6.57 / 6.00, 3584 -> 1024 with SiLU(gate) * up 5.85 / 5.18.)
+GemvShape w4_shape(int m, int n)
+{
+    GemvShape sh = auto_shape(m, n, 32, 16, 32, 128);
+    const int tiles = (n + sh.tile_cols - 1) / sh.tile_cols;
+    if (tiles * sh.splits > 160) return sh;
+    int splits = kComputeUnits / tiles;
+    if (splits > teal::kWordSplits) splits = teal::kWordSplits;
+    if (splits > m / 128) splits = m / 128;
+    if (splits <= sh.splits) return sh;
+    const int ks = ((m + splits - 1) / splits + 127) / 128 * 128;
+    sh.splits = (m + ks - 1) / ks;
+    return sh;
 }
 GemvShape auto_shape_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
                            int max_lanes, int ks_multiple, const int *row_pitch = nullptr)
@@ -457,7 +479,7 @@ teal_status teal_gemv_plan(int weight_bits, int m, int n, int *lanes_per_row, in
     GemvShape sh;
     if (weight_bits == 16) sh = auto_shape(m, n, 8, 16, 64, 64);
     else if (weight_bits == 8) sh = auto_shape(m, n, 16, 8, 64, 64);
-    else if (weight_bits == 4) sh = auto_shape(m, n, 32, 16, 32, 128);
+    else if (weight_bits == 4) sh = w4_shape(m, n);
     else return TEAL_ERR_UNSUPPORTED;
     if (lanes_per_row) *lanes_per_row = sh.lanes_per_row;
     if (tile_cols) *tile_cols = sh.tile_cols;
@@ -479,8 +501,6 @@ teal_status teal_gemv_plan_multi(int weight_bits, int m, const int *n, int count
         n_total += n[k];
     }
     if (m < 1 || m > teal::kMaxDim || n_total > teal::kMaxDim) return TEAL_ERR_SHAPE;
-    if (count == 1)
-        return teal_gemv_plan(weight_bits, m, n[0], lanes_per_row, tile_cols, splits, waves, unroll);
     GemvShape sh;
     if (weight_bits == 16) sh = auto_shape_multi(m, n, count, 8, 16, 64, 64);
     else if (weight_bits == 8) sh = auto_shape_multi(m, n, count, 16, 8, 64, 64);
@@ -1030,7 +1050,7 @@ teal_status teal_sparse_gemv_w4(const uint8_t *Wq, const void *scale_f16, int gr
     if (st != TEAL_OK) return st;
     if (!aligned(scale_f16, 16)) return TEAL_ERR_ALIGN;
     if (group != 128 || m % 128 != 0) return TEAL_ERR_UNSUPPORTED;
-    const GemvShape sh = auto_shape(m, n, 32, 16, 32, 128);
+    const GemvShape sh = w4_shape(m, n);
     return from_hip(teal::launch_gemv_w4(Wq, scale_f16, x_f16, t, y, m, n, ws_partials(workspace, m),
                                          ws_counters(workspace), sh,
                                          static_cast<hipStream_t>(stream)));
@@ -1048,7 +1068,7 @@ teal_status teal_sparse_gemv_w4_swiglu(const uint8_t *Wq, const void *scale_f16,
     if (!aligned(gate, 4) || !aligned(up, 4) || !aligned(scale_f16, 16)) return TEAL_ERR_ALIGN;
     if (group != 128 || m % 128 != 0) return TEAL_ERR_UNSUPPORTED;
     // The launch shape of teal_sparse_gemv_w4: same sums, bit for bit.
-    const GemvShape sh = auto_shape(m, n, 32, 16, 32, 128);
+    const GemvShape sh = w4_shape(m, n);
     return from_hip(teal::launch_gemv_w4_swiglu(Wq, scale_f16, gate, up, t, y, m, n,
                                                 ws_partials(workspace, m), ws_counters(workspace),
                                                 sh, static_cast<hipStream_t>(stream)));
@@ -1241,8 +1261,9 @@ void mlp_default_shape(const MlpFormat &fm, int m, int f, int d, int gu_row_pitc
     else if (m <= teal::kMaxSlice && narrow_blocks >= 160 && narrow_blocks <= 384 &&
              narrow / fm.elems_per_lane >= fm.min_lanes)
         gu = to_shape(narrow / fm.elems_per_lane, narrow, 1);
-    const GemvShape dn = auto_shape(f, d, fm.elems_per_lane, fm.min_lanes, fm.max_lanes,
-                                    fm.ks_multiple, down_row_pitch > 0 ? &down_row_pitch : nullptr);
+    const GemvShape dn = fm.bits == 4 ? w4_shape(f, d)
+                                      : auto_shape(f, d, fm.elems_per_lane, fm.min_lanes, fm.max_lanes, fm.ks_multiple,
+                                                   down_row_pitch > 0 ? &down_row_pitch : nullptr);
     out->gu_lanes_per_row = gu.lanes_per_row;
     out->gu_tile_cols = gu.tile_cols;
     out->gu_splits = gu.splits;

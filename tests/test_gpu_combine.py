@@ -187,8 +187,8 @@ def test_w4_fused_calls_with_large_activations_are_the_plain_calls(T, m):   # no
 @pytest.mark.parametrize("m,n,slices", [(2048, 2048, 16), (2176, 2048, 17), (4096, 1024, 32), (3584, 3072, 28), (4096, 4096, 32),
                                         (8192, 5120, 22), (8192, 5664, 16), (128, 32, 1)])
 def test_w4_slices_cut_finer_for_one_matrix(T, m, n, slices):   # noqa: F811
-    """Up to 160 planned blocks a single int4 matrix runs in finer slices (22 of 384 channels where 25 would
-    take 328), a group of one as planned: both within the bound, the same survivors, reproducible."""
+    """Up to 160 blocks of 16 slices a single int4 matrix runs in finer ones (22 of 384 channels where 25 would
+    take 328), a group of one does not, and the plans of either say so: both within the bound, the same survivors, reproducible."""
     rng = np.random.default_rng(m + n)
     q, scale, w = w4_case(n, m, 9950 + m + n)
     x = rng.standard_normal(m).astype(np.float16)
@@ -211,12 +211,36 @@ def test_w4_slices_cut_finer_for_one_matrix(T, m, n, slices):   # noqa: F811
         assert np.all(np.abs(got[-1] - want) <= bound)
     assert np.array_equal(got[0], got[1])
     st, plan = T.teal_gemv_plan(4, m, n)
-    tiles = -(-n // plan["tile_cols"])
-    if tiles * plan["splits"] > 160 or slices == plan["splits"]:
+    st, of_one = T.teal_gemv_plan_multi(4, m, [n])
+    assert plan["splits"] == slices and plan["tile_cols"] == of_one["tile_cols"]
+    if slices == of_one["splits"]:
         assert np.array_equal(got[0], got[2])
-    f = T.teal_mlp_plan(4, 128, m, n)[1]                     # the same rule, as the MLP's description of its blocks
-    f.down_lanes_per_row, f.down_tile_cols, f.down_splits = plan["lanes_per_row"], plan["tile_cols"], plan["splits"]
-    st, info = T.teal_mlp_block_info(4, 128, m, n, f, -1)
-    assert st == T.TEAL_OK
-    st, last = T.teal_mlp_block_info(4, 128, m, n, f, info[0] - 1)
-    assert (last[2] + 1, last[3] + 1) == (tiles, slices)
+
+
+@pytest.mark.parametrize("m,f,d", [(256, 4096, 2048), (512, 2176, 1024)])
+@pytest.mark.parametrize("down_splits", [1, 4, 16, None])
+def test_w4_mlp_runs_in_the_shape_it_is_given(T, m, f, d, down_splits):   # noqa: F811
+    """W_down of the one-launch int4 MLP in the caller's splits, also fewer than planned; without a shape in
+    the planned ones, which are those of the call by itself."""
+    mats = [ti.quantize_w4(ti.weights_bf16(b, a, 9990 + a + b), 128) for a, b in ((m, f), (m, f), (f, d))]
+    q, sc = [dev(a) for a, _ in mats], [dev(b) for _, b in mats]
+    x = dev(ti.make_x(m, 17, "laplace"))
+    st, shape = T.teal_mlp_plan(4, m, f, d)
+    planned = T.teal_gemv_plan(4, f, d)[1]
+    assert (shape.down_tile_cols, shape.down_splits) == (planned["tile_cols"], planned["splits"])
+    if down_splits:
+        shape.down_splits = down_splits
+    blocks = T.teal_mlp_block_info(4, m, f, d, shape, -1)[1][0]
+    last = T.teal_mlp_block_info(4, m, f, d, shape, blocks - 1)[1]
+    ks = -(-(-(-f // shape.down_splits)) // 128) * 128
+    assert last[1] == 2 and last[3] + 1 == -(-f // ks)
+    ys = [[torch.full((k,), float("nan"), dtype=torch.float32, device="cuda") for k in (f, f, d)] for _ in range(2)]
+    ws = torch.zeros(T.teal_workspace_bytes_mlp(m, f, d), dtype=torch.uint8, device="cuda")
+    T.check(T.teal_sparse_mlp_w4(*q, *sc, 128, x, 0.1, 0.1, 1e-4, *ys[0], m, f, d, ws, shape=shape))
+    T.check(T.teal_sparse_mlp_w4(*q, *sc, 128, x, 0.1, 0.1, 1e-4, *ys[1], m, f, d, ws))
+    wd = torch.zeros(T.teal_workspace_bytes(f, d), dtype=torch.uint8, device="cuda")
+    yd = torch.full((d,), float("nan"), dtype=torch.float32, device="cuda")
+    T.check(T.teal_sparse_gemv_w4_swiglu(q[2], sc[2], 128, ys[0][0], ys[0][1], 1e-4, yd, f, d, wd))
+    torch.cuda.synchronize()
+    assert torch.equal(ys[1][2], yd) and (down_splits or torch.equal(ys[0][2], yd))
+    assert rel_l2(ys[0][2].cpu().numpy(), yd.cpu().numpy()) <= TIGHT

@@ -280,6 +280,26 @@ def test_plan_and_argument_errors():
     assert T.teal_sparse_mlp_w8(shape=s8, **q) == T.TEAL_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("bits", [16, 8, 4])
+@pytest.mark.parametrize("down_splits", [1, 2, 7, 16, 28])
+def test_w_down_runs_in_the_slices_of_the_shape(bits, down_splits):
+    """As many as the caller asks for (in slices that are whole multiples of 64 or 128 channels), fewer than planned too."""
+    f, d = 3584, 1024
+    sh = shape_of(bits, 1024, f, d, down_splits=down_splits)
+    ks = -(-(-(-f // down_splits)) // (128 if bits == 4 else 64)) * (128 if bits == 4 else 64)
+    st, i = T.teal_mlp_block_info(bits, 1024, f, d, sh, -1)
+    st, last = T.teal_mlp_block_info(bits, 1024, f, d, sh, i[0] - 1)
+    assert (last[1], last[3] + 1, last[5]) == (DOWN, -(-f // ks), f)
+
+
+def test_the_planned_w_down_is_its_own_call():
+    for bits in (16, 8, 4):
+        for m, f, d in ((4096, 14336, 4096), (1024, 3584, 1024), (2048, 5504, 2048), (8192, 28672, 8192), (512, 1408, 5664)):
+            sh, (st, dn) = shape_of(bits, m, f, d), T.teal_gemv_plan(bits, f, d)
+            assert (sh.down_lanes_per_row, sh.down_tile_cols, sh.down_splits) == \
+                (dn["lanes_per_row"], dn["tile_cols"], dn["splits"])
+
+
 def test_every_plan_for_padded_rows_is_a_shape_the_launch_accepts():
     """teal_mlp_plan told the row pitches never names a shape teal_mlp_block_info (which
     validates like the launch) refuses, whatever the sizes."""
