@@ -139,6 +139,37 @@ def test_no_bit_of_a_batch_is_lost(T, batch, splits):   # noqa: F811
         assert torch.equal(Y[b].double(), want if b % 2 == 0 else -want), b
 
 
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("e", [-24, -12, 0, 15])
+@pytest.mark.parametrize("fmt,m,n", [("w8", 2048, 2048), ("w8", 4096, 16384), ("w4", 2048, 2048), ("w4", 4096, 1024)])
+def test_no_bit_of_a_quantised_slice_is_lost(T, fmt, m, n, e, dense):   # noqa: F811
+    """Sums of less than 2^24 units of 2^e, or of 2^e times the group's scale: exact in every slice and in all, in
+    words (16, 4 and 32 slices) and, in the dense calls on large inputs, kept apart."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n + e)
+    x = (torch.randint(-1, 2, (m,), generator=g, device="cuda").float() * 2.0 ** e).half()
+    t = 0.0 if dense else 0.75 * 2.0 ** e
+    ws = torch.zeros(T.teal_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
+    y = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+    if fmt == "w8":
+        q = torch.randint(-127, 128, (m, n), generator=g, device="cuda", dtype=torch.int8)
+        sc = (2.0 ** -torch.arange(n, device="cuda").remainder(8).float()).half()
+        want = (x.double() @ q.double()) * sc.double()
+    else:
+        q = torch.randint(0, 256, (m, n // 2), generator=g, device="cuda", dtype=torch.uint8)
+        sc = (2.0 ** -torch.arange(n, device="cuda").remainder(8).float()).half().expand(m // 128, n).contiguous()
+        b = q.view(torch.int8)
+        want = (x.double() @ torch.stack([(b << 4) >> 4, b >> 4], 2).reshape(m, n).double()) * sc[0].double()
+    call = (lambda: T.teal_sparse_gemv_w8(q, sc, x, t, y, m, n, ws)) if fmt == "w8" else \
+        (lambda: T.teal_sparse_gemv_w4(q, sc, 128, x, t, y, m, n, ws))
+    for _ in range(2):
+        y.fill_(float("nan"))
+        T.check(call())
+        torch.cuda.synchronize()
+        assert torch.equal(y.double(), want)
+        assert not bool(ws[:T.teal_survivors_offset()].any())
+
+
 @pytest.mark.parametrize("e", [-13, -8, 0, 6, 11])
 @pytest.mark.parametrize("fmt", ["bf16", "w8", "w4", "batch"])
 def test_ordinary_sums_take_the_short_way_whatever_the_size_of_the_inputs(T, fmt, e):   # noqa: F811
