@@ -1295,7 +1295,7 @@ __device__ __forceinline__ int stack_group_of_block(const StackArgs<F> &sa, int 
 }
 
 // The group is found by an index, so its matrices' arguments lie behind another load; reading all of them at once
-// (multi_block) is still the better form although it spills 8 to 18 scalar registers here: looked up one by one,
+// (multi_block) is still the better form although it spills scalar registers here (int8 and int4 12): looked up one by one,
 // without spills, int8 stacks took 0.99 to 1.06 times as long, bf16 0.99 to 1.02, int4 0.99 to 1.00 (decoder
 // blocks of four sizes from 2048 to 5120 channels, dense to 95 %).
 // LANES8: the format's launch shapes include 8 lanes per row (int8 weights).

@@ -51,8 +51,10 @@ bool wide_tiles(int m, const int *n, const int *row_pitch, int count, int elems_
 
 // Launch shape for one GEMV, from sweeps on MI355X.  A call costs a fixed latency
 // chain (load x, compact, first weight rows), the row stream, and with split-K
-// (Section 4.4) the publish / ticket / second-pass chain, which grows with the
-// number of splits.  Measured times are flat over a wide range of shapes as long
+// (Section 4.4) the meeting of the slices.  The sweeps are of launches whose slices
+// met by partial row, ticket and second pass, which grows with the number of splits;
+// column words have put one trip in its place, and only the two rules that say so
+// were fitted to them.  Measured times are flat over a wide range of shapes as long
 // as (a) there is about one block of 8 wavefronts per compute unit and never a
 // nearly empty second round, (b) the split-K depth is about 8, at most 16, and
 // (c) a block's row segment is 256 B .. 1 KiB and starts on a 128-byte boundary
@@ -66,7 +68,7 @@ GemvShape shape_for(int m, int n, int elems_per_lane, int min_lanes, int max_lan
     tc = (tc + unit - 1) / unit * unit;
     if (tc < tc_min) tc = tc_min;
     if (wide && tc < 4 * unit) tc = 4 * unit;
-    // bf16 matrices of 8193 to 10240 columns: a KiB of a row with 12 to 15 splits instead of five lines with 8.  A
+    // Fitted to column words: bf16 matrices of 8193 to 10240 columns, a KiB of a row with 12 to 15 splits instead of five lines with 8.  A
     // quarter of the 256-byte pieces of memory is slower, and every KiB has one (us at 50 %, 640 bytes / a
     // KiB: 5120 -> 9216 11.1 / 10.4, 8192 -> 8704 15.5 / 14.7, 14336 -> 10240 25.7 / 25.2; over 0 to 95 % and
     // 5120 to 14336 channels 0.99 to 1.21 times as fast; with fewer channels up to 5 % slower from 80 % on.
@@ -103,9 +105,9 @@ GemvShape shape_for(int m, int n, int elems_per_lane, int min_lanes, int max_lan
 // counts, and a width that divides the matrices unevenly leaves ragged tiles.  Every
 // candidate (tile width in steps of 128 bytes of a row, 1..16 splits) that fits one block
 // per compute unit is scored by how evenly it spreads the work: total work over 256 times
-// the largest block's work, with a small penalty per split beyond 8 (longer combine chain)
-// and a slight preference for wider row segments.  For one matrix this reproduces the
-// choices of shape_for above.
+// the largest block's work, with a small penalty per split beyond 8 (fitted, like shape_for,
+// to the second pass over partial rows; not fitted again to column words) and a slight
+// preference for wider row segments.  One matrix has shape_for's shape, also in a grouped call.
 GemvShape shape_for_multi(int m, const int *n, int count, int elems_per_lane, int min_lanes,
                           int max_lanes, int ks_multiple, int max_slice, bool wide)
 {
@@ -158,7 +160,7 @@ GemvShape auto_shape(int m, int n, int elems_per_lane, int min_lanes, int max_la
     return shape_for(m, n, elems_per_lane, min_lanes, max_lanes, ks_multiple, teal::kMaxSlice,
                      wide_tiles(m, &n, row_pitch, 1, elems_per_lane));
 }
-// One int4 matrix: as many slices as the compute units can take.  A tile has at least 512 columns there, so the 16
+// Fitted to column words: one int4 matrix in as many slices as the compute units can take.  A tile has at least 512 columns there, so the 16
 // slices of the other formats make 64 blocks for 2048 columns and 128 for 4096, and the product is bound by
 // instruction issue: finer slices go to the units that would be idle.  Up to 160 blocks, where a third of the
 // units is left; with more, slices that do not divide the units do not pay.  At least 128 channels (a
@@ -423,7 +425,7 @@ const char *teal_status_string(teal_status s)
     return "unknown status";
 }
 
-int teal_version(void) { return 417; }
+int teal_version(void) { return 418; }
 
 size_t teal_survivors_offset(void) { return teal::kCounterBytes; }
 
@@ -1235,9 +1237,9 @@ GemvShape to_shape(int lanes, int tile_cols, int splits)
 
 // The library's choice.  W_down: the launch shape of its own call.  Gate / up: no split-K with
 // tiles of 256 bytes of a row when that alone gives about one block per compute unit (the
-// tile is then finished by the block that streamed it, and its consumers are told without the
-// publish / ticket / second-pass chain in between: measured 1.3-1.6 us per call on
-// Llama-2-7B- and Llama-3-8B-sized layers); else the launch shape of the grouped gate + up
+// tile is then finished by the block that streamed it, and its consumers are told without a
+// meeting of slices in between: measured 1.3-1.6 us per call on Llama-2-7B- and Llama-3-8B-sized
+// layers against slices that met by partial rows); else the launch shape of the grouped gate + up
 // call.
 // On rows that rotate over the address quarters (gu_row_pitch an odd multiple of 256 bytes;
 // bf16 and int8) the rule of the grouped call on padded rows applies to gate / up: narrow
