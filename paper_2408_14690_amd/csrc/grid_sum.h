@@ -39,6 +39,13 @@ struct Grid {
 // 4096 at 2^12 6.69, 6.53, now 5.86; int4 4096 x 4096 5.58 / 5.66 / 7.77, 6.75, now 5.57 / 5.58 / 5.57.  What is
 // left are weights of an unusual size (bf16 2048 x 2048 of 2^-10 or 2^14 times 0.02: 4.85 and 5.37) and inputs of one in
 // dense calls (t = 0; about 2^-12 or 2^12: 5.69 and 5.78, by rows 5.18).
+// A low threshold belongs to small inputs or to ordinary ones of which hardly any are dropped.  So the step stops
+// getting finer (`finest`) where both still take the short way.  With 48, whose sums end at 8 (more than 16 slices: at 1),
+// the latter went the long way.  us, by rows / 48 / as below: int4 4096 x 4096, inputs about 1, t = 1e-4 6.61 / 7.47 / 5.88;
+// bf16 2048 x 2048, t = 1e-4, inputs about 64 4.95 / 5.73 / 4.58, about 1 with some of 300 4.99 / 5.51 / 4.60; the other end,
+// inputs about 2^-15 at 50 %: bf16 4.50 / 4.19 / 4.56, int4 4096 x 4096 with scales about 2^-8 6.72 / 5.50 / 5.50.  Left on the
+// long way: int4 in more than 16 slices for inputs about 64 with t below 2^-8 (by rows 7.10, 7.93), or about 2^-12 and less with scales
+// about 2^-9 (6.77, 7.18).
 // floor(log2 t); kNoExponent and less for a t that keeps every input but zeros.
 constexpr int kNoExponent = -25;
 TEAL_HD_INLINE int threshold_exponent(float t) { return (int)(__builtin_bit_cast(unsigned, t) >> 23 & 255u) - 127; }
@@ -51,12 +58,12 @@ TEAL_HD_INLINE int grid_unit(float t, int at_one, int finest, int dense)
 // every one is of 2^-24, so all sums are multiples of the step.  The 8192 products a slice may have stay below the
 // limit for inputs up to 2^21 times the threshold (t = 0: up to 2^7).
 TEAL_HD_INLINE int grid_unit_w8(float t) { return grid_unit(t, 10, 24, 24); }
-// int4: fp16 scales are multiples of 2^-24, so the sums are of 2^(e - 34).  Not finer than 2^-48, for a threshold that is
-// far below the inputs (as t = 0 says nothing of them).
-TEAL_HD_INLINE int grid_unit_w4(float t) { return grid_unit(t, 34, 48, 40); }
+// int4: fp16 scales are multiples of 2^-24, so the sums are of 2^(e - 34); and of 2^-43, whatever the inputs, where the scales are
+// 2^-9 or more.
+TEAL_HD_INLINE int grid_unit_w4(float t) { return grid_unit(t, 34, 43, 40); }
 // bf16 weights have any exponent: the sums of a slice of ordinary weights (about 0.02) are some 2^-2 of the inputs'
-// size, in the middle of the 28 powers of two between 2^(23 - unit) and the limit.  Not finer than 2^-48 either.
-TEAL_HD_INLINE int grid_unit_bf16(float t) { return grid_unit(t, 38, 48, 40); }
+// size, in the middle of the 28 powers of two between 2^(23 - unit) and the limit.
+TEAL_HD_INLINE int grid_unit_bf16(float t) { return grid_unit(t, 38, 44, 40); }
 
 struct GridSum {
     unsigned long long shifted;     // the bits of sum * 2^unit + kGridMagic

@@ -174,7 +174,9 @@ def test_no_bit_of_a_quantised_slice_is_lost(T, fmt, m, n, e, dense):   # noqa: 
 @pytest.mark.parametrize("fmt", ["bf16", "w8", "w4", "batch"])
 def test_ordinary_sums_take_the_short_way_whatever_the_size_of_the_inputs(T, fmt, e):   # noqa: F811
     """Inputs of size 2^e at 50 %: the step follows the threshold, so next to none of the slices' sums is kept
-    apart (int8 and int4: none, they are whole multiples of it).  A sum kept apart is written to its slice's row."""
+    apart (int8 and int4: none, they are whole multiples of it).  A sum kept apart is written to its slice's row.
+    The step gets no finer than 2^-44 (int4: 2^-43), and an fp32 sum below 2^-21 (2^-20) may have a bit below it: of sums about
+    0.2 * 2^e (0.1 * 2^e) a share of 4 * 2^(-21 - e) (8 * 2^(-20 - e), at e = -13 alone: above, all products are multiples)."""
     m = n = 2048
     g = torch.Generator(device="cuda")
     g.manual_seed(e + 100)
@@ -200,7 +202,42 @@ def test_ordinary_sums_take_the_short_way_whatever_the_size_of_the_inputs(T, fmt
         T.check(T.teal_sparse_gemv_w4(q, sc, 128, x, t, y[0], m, n, ws))
     torch.cuda.synchronize()
     apart = int((rows != 0x5A5A5A5A).sum())
-    assert apart <= (0 if fmt in ("w8", "w4") else 16 * n // 1000), apart
+    share = 0.0 if fmt == "w8" else 0.001 + 2 * 4 * 2.0 ** (-21 - e)
+    if fmt == "w4":
+        share = 8 * 2.0 ** (-20 - e) if e == -13 else 0.0
+    assert apart <= 16 * n * share, apart
+    assert bool(torch.isfinite(y[0]).all()) and not bool(ws[:T.teal_survivors_offset()].any())
+
+
+@pytest.mark.parametrize("t", [1e-6, 1e-4, 1e-3])
+@pytest.mark.parametrize("size", [1.0, 8.0])
+@pytest.mark.parametrize("fmt", ["bf16", "w4", "batch"])
+def test_low_thresholds_take_the_short_way_too(T, fmt, size, t):   # noqa: F811
+    """A threshold that drops next to nothing says as little of the inputs' size as none: sums of ordinary inputs
+    stay within the grid (int4 here in 32 slices, whose end is nearer).  Off it are bf16 sums near zero: below 2^-21 of
+    about 0.2, and int4's of scales with bits below 2^-18."""
+    m = n = 4096 if fmt == "w4" else 2048
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(size))
+    x = (torch.randn(m, generator=g, device="cuda") * size).half()
+    bytes_ = T.teal_workspace_bytes(m, n)
+    ws = torch.zeros(max(bytes_, T.teal_workspace_bytes_batch(m, n, 2)), dtype=torch.uint8, device="cuda")
+    rows = ws[bytes_ - 4 * 128 * n:].view(torch.int32)
+    rows.fill_(0x5A5A5A5A)
+    y = torch.full((2, n), float("nan"), dtype=torch.float32, device="cuda")
+    if fmt == "w4":
+        q = torch.randint(0, 256, (m, n // 2), generator=g, device="cuda", dtype=torch.uint8)
+        sc = (torch.rand((m // 128, n), generator=g, device="cuda") * 0.005).half()
+        T.check(T.teal_sparse_gemv_w4(q, sc, 128, x, t, y[0], m, n, ws))
+    else:
+        w = (torch.randn((m, n), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+        if fmt == "bf16":
+            T.check(T.teal_sparse_gemv_bf16(w, x, t, y[0], m, n, ws))
+        else:
+            T.check(T.teal_sparse_gemv_bf16_batch(w, torch.stack([x, -x]), 2, t, y, m, n, ws))
+    torch.cuda.synchronize()
+    apart = int((rows != 0x5A5A5A5A).sum())
+    assert apart <= 32 * n // 1000, apart
     assert bool(torch.isfinite(y[0]).all()) and not bool(ws[:T.teal_survivors_offset()].any())
 
 

@@ -162,7 +162,9 @@ def test_sums_of_quantised_weights_are_on_the_grid(host, t):
     assert np.all(np.ldexp(x, u8) % 1 == 0)
     scale = rng.integers(0, 0x7C00, len(x), dtype=np.uint16).view(np.float16).astype(np.float64)
     if t == 0 or t >= 2.0 ** -14:
-        low = 2.0 ** -24 if t else 2.0 ** -16                # (dense: scales of 2^-16 and more)
+        # inputs above t are multiples of 2^(e - 10), which with scales of 2^-24 gives the step down to its finest,
+        # 2^-43; below that, and dense, scales of that much more
+        low = max(2.0 ** -24, 2.0 ** (-33 - np.floor(np.log2(t)))) if t else 2.0 ** -16
         assert np.all(np.ldexp(x * np.maximum(np.round(scale / low) * low, low), u4) % 1 == 0)
     ordinary = max(t, 2.0 ** -9)
     for bits, gain in ((8, 127 * 64), (4, 0.05 * 7 * 64), (16, 0.05 * 64)):
@@ -173,9 +175,23 @@ def test_sums_of_quantised_weights_are_on_the_grid(host, t):
 @pytest.mark.parametrize("e", range(-14, 12))
 def test_unit_follows_the_inputs(host, e):
     """Inputs of size 2^e with half of them dropped: sums of bf16 weights of 0.02 over 64 to 2048 channels, whose
-    sizes are some 0.05 to 1 times the inputs', are on the grid from 2^-7 of that on to 16 times it."""
+    sizes are some 0.05 to 1 times the inputs', are on the grid from 2^-7 of that on to 16 times it (for the smallest
+    inputs from 2^-21 on: an odd last bit of less is below the finest step of 2^-44)."""
     unit = host.unit_of(16, 0.67 * 2.0 ** e)
     for s in (0.05 * 2.0 ** -6, 0.05, 1.0, 16.0):
-        v = np.float32(s * 2.0 ** e)
+        v = np.float32(max(s * 2.0 ** e, 2.0 ** -21))
         assert not host.off_grid(unit, 16, np.nextafter(v, np.float32(np.inf))), s
     assert host.unit_of(16, 0.0) == 40 and host.unit_of(4, 0.0) == 40 and host.unit_of(8, 0.0) == 24
+
+
+@pytest.mark.parametrize("t", [1e-9, 2.0 ** -24, 1e-6, 1e-5, 1e-4, 4e-4, 1e-3])
+def test_low_thresholds_on_ordinary_inputs(host, t):
+    """Thresholds that drop next to nothing of inputs about 1 to 8: the sums of 1024 such inputs with weights of 0.02
+    (0.64 to 5.1) are on the grid up to six times that."""
+    for bits in (16, 4):
+        for splits in (2, 16, 32):
+            if (bits, splits) == (16, 32):          # (by a caller's own shape only: they end at 16)
+                continue
+            for v in (0.64, 5.1, 6 * 5.1):
+                for v32 in (np.float32(v), -np.nextafter(np.float32(v), np.float32(0))):
+                    assert not host.off_grid(host.unit_of(bits, t), splits, v32), (bits, splits, v)
